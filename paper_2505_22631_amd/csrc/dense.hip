@@ -23,10 +23,10 @@
 
 #include <cmath>
 
+#include "dense_pairs.hpp"
 #include "internal.hpp"
 #include "noise.hpp"
 #include "phase.hpp"
-#include "tree.hpp"
 
 namespace oim {
 
@@ -596,61 +596,70 @@ __global__ __launch_bounds__(256) void dense_split_kernel(const float* J, unsign
     }
 }
 
-// Thresholded energy per replica from the phase words (in-run readout):
-// one workgroup per replica, H = Eq. 1 (q = 2) or Eq. 2 (q >= 3) in the
-// library's fixed FP64 order: thread t owns row 256 b + t of block b and
-// sums its terms over j > i in column order; a block's rows are folded by
-// the pairwise tree (lanes by the xor butterfly, partner distance 1, ..., 32,
-// then the four waves), and the blocks by the same tree, in order, in
-// thread 0.
-__global__ __launch_bounds__(256) void dense_readout_kernel(const float* J, const uint32_t* U,
-                                                            int n, int np, int q, double* Hout) {
-    __shared__ double red[4];
-    __shared__ double stack[TreeAcc::kLevels];
-    const int r = blockIdx.x;
-    const uint32_t* ur = U + (size_t)r * np;
-    TreeAcc tree(stack);
-    for (int i0 = 0; i0 < n; i0 += 256) {
-        const int i = i0 + (int)threadIdx.x;
-        double part = 0.0;
-        if (i < n) {
-            const int ci = nearest_state(ur[i], q);
-            const float* row = J + (size_t)i * n;
-            for (int j = i + 1; j < n; ++j) {
-                const int cj = nearest_state(ur[j], q);
-                const double w = (double)row[j];
-                part += (q == 2) ? (ci == cj ? w : -w) : (ci == cj ? w : 0.0);
+// In-run readout: the thresholded energy of NR replicas from their phase
+// words, H = Eq. 1 (ISING, q = 2) or Eq. 2 (q >= 3) in the library's fixed
+// FP64 order (dense_pairs.hpp), then the trace, the best-so-far and the
+// colours of a new best, all by the workgroup that holds the replica's
+// colours in LDS (a second kernel with a thread per replica copying n
+// colours took 404 us more).  A readout of n = 2000, 128 replicas: 3061 ->
+// 164 us; n = 777, 24 replicas: 346 -> 34 us; dense_pairs.hpp says what
+// bounds it.
+struct ReadArgs {
+    const float* J;
+    const uint32_t* U;
+    int n, np, R, q, kread, first;
+    int32_t gstep;
+    double* trace;       // [readouts][R] or null
+    double* best;        // running best (workspace)
+    int32_t* best_step;  // running best step (workspace)
+    int8_t* best_colour; // [R][n] or null
+};
+
+template <int NR, bool ISING>
+__global__ __launch_bounds__(dpair::kTB) void dense_readout_kernel(ReadArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int improved[NR];
+    const int n = a.n, ld = dpair::code_stride(n), nblk = dpair::row_blocks(n);
+    double* bs = reinterpret_cast<double*>(smem + (size_t)NR * ld);
+    const int r0 = blockIdx.x * NR;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const uint32_t* ur = a.U + (size_t)(r0 + r < a.R ? r0 + r : a.R - 1) * a.np;
+        for (int j = threadIdx.x; j < ld; j += dpair::kTB)  // ld <= np
+            smem[r * ld + j] = (unsigned char)nearest_state(ur[j], a.q);
+    }
+    __syncthreads();
+    dpair::block_sums<NR, ISING ? dpair::kIsing : dpair::kSame, false, false>(a.J, n, smem, bs,
+                                                                              nullptr);
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int r = r0 + wave;
+    if (wave < NR) {
+        const double H = -dpair::fold_blocks(bs + wave * nblk, nblk);
+        if (lane == 0) {
+            improved[wave] = 0;
+            if (r < a.R) {
+                if (a.trace) a.trace[(size_t)a.kread * a.R + r] = H;
+                if (a.first || H < a.best[r]) {
+                    a.best[r] = H;
+                    a.best_step[r] = a.gstep;
+                    improved[wave] = 1;
+                }
             }
         }
-        for (int o = 1; o < 64; o <<= 1) part += __shfl_xor(part, o, 64);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
-        __syncthreads();
-        if (threadIdx.x == 0) tree.push((red[0] + red[1]) + (red[2] + red[3]));
-        __syncthreads();
     }
-    if (threadIdx.x == 0) Hout[r] = -tree.finish();
-}
-
-// Trace / best-so-far bookkeeping after a readout (one thread per replica).
-__global__ void dense_best_kernel(const double* H, int R, int kread, int32_t gstep, double* trace,
-                                  double* best_h, int32_t* best_step, double* best_tmp,
-                                  int32_t* best_tmp_step, int8_t* best_colour,
-                                  const uint32_t* U, int n, int np, int q, int first) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    const double h = H[r];
-    if (trace) trace[(size_t)kread * R + r] = h;
-    if (first || h < best_tmp[r]) {
-        best_tmp[r] = h;
-        best_tmp_step[r] = gstep;
-        if (best_colour)
-            for (int i = 0; i < n; ++i) best_colour[(size_t)r * n + i] = (int8_t)nearest_state(U[(size_t)r * np + i], q);
+    __syncthreads();
+    if (a.best_colour) {
+#pragma unroll
+        for (int x = 0; x < NR; ++x)
+            if (improved[x])
+                for (int i = threadIdx.x; i < n; i += dpair::kTB)
+                    a.best_colour[(size_t)(r0 + x) * n + i] = (int8_t)smem[x * ld + i];
     }
-    (void)best_h;
-    (void)best_step;
 }
 
 using StepFn = void (*)(DenseArgs);
+using ReadFn = void (*)(ReadArgs);
 
 int alloc_or_fail(void** p, size_t bytes, const char* what) {
     const hipError_t e = hipMalloc(p, bytes);
@@ -758,6 +767,19 @@ int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* K
     a.sqrt_dt = std::sqrt(cfg->dt);
     hipError_t e = hipSuccess;
     dim3 grid((np / kTM) * (Rp / kTR));
+    const int nr = dpair::replicas_per_group(n, R, false);
+    const size_t read_lds = dpair::lds_bytes(n, nr, false);
+    const bool ising = cfg->q == 2;
+    const ReadFn read_fn = nr == 4   ? (ising ? dense_readout_kernel<4, true> : dense_readout_kernel<4, false>)
+                           : nr == 2 ? (ising ? dense_readout_kernel<2, true> : dense_readout_kernel<2, false>)
+                                     : (ising ? dense_readout_kernel<1, true> : dense_readout_kernel<1, false>);
+    if (M > 0 && read_lds > 64 * 1024) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(read_fn),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)read_lds);
+        if (e != hipSuccess) return hip_error(e, "dense readout LDS");
+    }
+    ReadArgs ra{p->d_Jdense, U, n, np, R, cfg->q, 0, 0, 0, ro ? ro->trace : nullptr, btmp, bstep,
+                ro ? ro->best_colour : nullptr};
     for (int s = 0; s < cfg->steps; ++s) {
         a.Xin = (s & 1) ? X1 : X0;
         a.Xout = (s & 1) ? X0 : X1;
@@ -766,15 +788,11 @@ int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* K
         hipLaunchKernelGGL(fn, grid, dim3(kTB), 0, stream, a);
         if ((st = check_launch("dense_step_kernel"))) return st;
         if (M > 0 && ((s + 1) % M == 0 || s + 1 == cfg->steps)) {
-            const int kread = (s + M) / M - 1;
-            hipLaunchKernelGGL(dense_readout_kernel, dim3(R), dim3(256), 0, stream, p->d_Jdense, U,
-                               n, np, cfg->q, H);
+            ra.kread = (s + M) / M - 1;
+            ra.gstep = (int32_t)(step0 + s + 1);
+            ra.first = ra.kread == 0 ? 1 : 0;
+            hipLaunchKernelGGL(read_fn, dim3((R + nr - 1) / nr), dim3(dpair::kTB), read_lds, stream, ra);
             if ((st = check_launch("dense_readout_kernel"))) return st;
-            hipLaunchKernelGGL(dense_best_kernel, dim3((R + 63) / 64), dim3(64), 0, stream, H, R,
-                               kread, (int32_t)(step0 + s + 1), ro ? ro->trace : nullptr, nullptr,
-                               nullptr, btmp, bstep, ro ? ro->best_colour : nullptr, U, n, np,
-                               cfg->q, kread == 0 ? 1 : 0);
-            if ((st = check_launch("dense_best_kernel"))) return st;
         }
     }
 

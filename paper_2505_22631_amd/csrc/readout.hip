@@ -7,17 +7,17 @@
 //   energy     Eq. 1 (q = 2) or Eq. 2 (q >= 3) at the colours, and Eq. 6 with
 //              w = -J at the continuous phases, FP64
 //
-// One workgroup per replica walks the upper triangle of the coupling (CSR
-// rows, or the dense matrix).  Every FP64 sum follows one fixed order, the
-// same in every readout of the library: each row i sums its terms over
-// j > i in ascending column order, from +0, and the row sums are combined by
-// the pairwise tree over rows (zero-padded to a power of two, adjacent pairs
-// first, the lower rows on the left).  Here a thread owns one row of a block
-// of 256; the block's tree runs over lanes (xor butterfly, partner distance
-// 1, 2, ..., 32) and then over the four waves; the blocks are combined by
-// the same tree, built incrementally in the order the blocks complete
-// (tree_push / tree_finish).  Integer weights are accumulated in int64 and
-// are exact.
+// Every FP64 sum follows one fixed order, the same in every readout of the
+// library: each row i sums its terms over j > i in ascending column order,
+// from +0, and the row sums are combined by the pairwise tree over rows
+// (zero-padded to a power of two, adjacent pairs first, the lower rows on the
+// left).  A lane owns one row of a block of 64; the block's tree runs over
+// lanes (xor butterfly, partner distance 1, 2, ..., 32), the blocks' sums meet
+// in LDS and one wave folds them by the same tree.  Results that are whole
+// numbers by definition (the int64 cut, the conflicts) are exact in any order.
+#include <type_traits>
+
+#include "dense_pairs.hpp"
 #include "internal.hpp"
 #include "phase.hpp"
 #include "tree.hpp"
@@ -28,22 +28,6 @@
 namespace oim {
 
 namespace {
-
-constexpr int kTB = 256;
-
-// Sum of a 256-thread block's values, one per row of the block, by the
-// pairwise tree over the rows (thread t = row t); valid in thread 0.
-template <typename T>
-__device__ T block_tree(T v, T* scratch) {
-    for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) scratch[wave] = v;
-    __syncthreads();
-    T tot = 0;
-    if (threadIdx.x == 0) tot = (scratch[0] + scratch[1]) + (scratch[2] + scratch[3]);
-    __syncthreads();
-    return tot;
-}
 
 __global__ __launch_bounds__(256) void round_kernel(int64_t count, const float* theta, int q,
                                                     float scale, int8_t* colour) {
@@ -76,93 +60,336 @@ __global__ __launch_bounds__(256) void phase_convert_kernel(int64_t count, const
     }
 }
 
-// mode 0: cut (int64 + f64), 1: conflicts, 2: energies.  Thread t of the
-// workgroup owns row 256 b + t of block b; the block sums are combined in
-// thread 0 by the pairwise tree over blocks.
-template <int MODE, bool DENSE>
-__global__ __launch_bounds__(kTB) void pair_sum_kernel(
+// ---- dense coupling (dense_pairs.hpp) ----
+
+// Cut (kDiffer), conflicts (kCount) or Eq. 1 / Eq. 2 (kIsing / kSame) of
+// colours [R][n] with the pair's weight -J; NR replicas per workgroup.
+template <int NR, int KIND, bool INTS>
+__global__ __launch_bounds__(dpair::kTB) void dense_pair_kernel(int n, int R, const float* J,
+                                                                const int8_t* colour,
+                                                                int64_t* out_i64, double* out_f64) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int ld = dpair::code_stride(n), nblk = dpair::row_blocks(n);
+    double* bs = reinterpret_cast<double*>(smem + (size_t)NR * ld);
+    int64_t* bi = reinterpret_cast<int64_t*>(bs + (size_t)NR * nblk);
+    const int r0 = blockIdx.x * NR;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int8_t* k = colour + (int64_t)(r0 + r < R ? r0 + r : R - 1) * n;
+        for (int j = threadIdx.x; j < ld; j += dpair::kTB)
+            smem[r * ld + j] = j < n ? (unsigned char)k[j] : 0;
+    }
+    __syncthreads();
+    dpair::block_sums<NR, KIND, true, INTS>(J, n, smem, bs, bi);
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (wave < NR && r0 + wave < R) {
+        const double v = dpair::fold_blocks(bs + wave * nblk, nblk);
+        if (lane == 0 && out_f64) out_f64[r0 + wave] = v;
+        if constexpr (INTS) {
+            const int64_t vi = dpair::fold_blocks_int(bi + wave * nblk, nblk);
+            if (lane == 0 && out_i64) out_i64[r0 + wave] = vi;
+        }
+    }
+}
+
+// Eq. 6 at the continuous phases [R][n]: the same walk with one FP64 cosine
+// per pair, which bounds it; one replica per workgroup.
+__global__ __launch_bounds__(dpair::kTB) void dense_cos_kernel(int n, const float* __restrict__ J,
+                                                               const float* __restrict__ theta,
+                                                               double* out) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* bs = reinterpret_cast<double*>(smem);
+    const int nblk = dpair::row_blocks(n);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float* th = theta + (int64_t)blockIdx.x * n;
+    for (int t = 0; t * dpair::kWaves < nblk; ++t) {
+        const int blk = t * dpair::kWaves + ((t & 1) ? dpair::kWaves - 1 - wave : wave);
+        if (blk >= nblk) continue;
+        const int i = blk * 64 + lane, ic = i < n ? i : n - 1;
+        const double ti = (double)th[ic];
+        double acc = 0.0;
+        for (int j = blk * 64 + 1; j < n; ++j) {
+            const double c = cos(ti - (double)th[j]);
+            const double term = -(double)J[(size_t)j * n + ic] * c;
+            acc += j > i ? term : 0.0;
+        }
+        double v = i < n ? acc : 0.0;
+        for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+        if (lane == 0) bs[blk] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const double v = dpair::fold_blocks(bs, nblk);
+        if (threadIdx.x == 0) out[blockIdx.x] = v;
+    }
+}
+
+// ---- sparse coupling ----
+
+// Upper-triangle entries of row i, four at a time so that their columns and
+// weights, then what the caller gathers at those columns, are in flight
+// together: fn(valid, gathered, w) for each, in column order.  With LPR lanes
+// per row (whole-number sums only), lane `sub` of them takes every LPR-th
+// group of four.
+template <int LPR, class Gather, class Fn>
+__device__ __forceinline__ void upper_entries(const int64_t* __restrict__ row_ptr,
+                                              const int32_t* __restrict__ col,
+                                              const float* __restrict__ J, int i, int sub,
+                                              Gather gather, Fn fn) {
+    const int64_t e1 = row_ptr[i + 1];
+    for (int64_t e = row_ptr[i] + 4 * sub; e < e1; e += 4 * LPR) {
+        int j[4];
+        float w[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int64_t ee = e + x < e1 ? e + x : e1 - 1;
+            j[x] = col[ee];
+            w[x] = J[ee];
+        }
+        decltype(gather(0)) g[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) g[x] = gather(j[x]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) fn(e + x < e1 && j[x] > i, g[x], w[x]);
+    }
+}
+
+// Whole-number results alone: the cut of integer weights (CUT) or the
+// conflicts.  LPR lanes share a row, and the rows of a replica are split over
+// gridDim.x workgroups whose sums meet in out (zeroed before, unless one
+// workgroup holds all rows) by integer atomics.  One workgroup per replica,
+// a lane per row, left the chip idle for few replicas of a large graph: the
+// conflicts of 256 colouring graphs (86 928 oscillators) x 8 replicas took
+// 1642 us, now 42; the cut of a 200 x 300 torus x 64 replicas 549, now 38; of
+// G(800, 0.06) x 1 replica 79, now 5 (and 5 for the zeroing).
+constexpr int kIntTB = 256;
+
+__global__ void zero_kernel(int R, int64_t* out) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < R) out[r] = 0;
+}
+
+template <bool CUT, int LPR>
+__global__ __launch_bounds__(kIntTB) void sparse_int_kernel(
+    int n, int rows, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+    const float* __restrict__ J, const int8_t* __restrict__ colour, int64_t* out) {
+    __shared__ int64_t red[kIntTB / 64];
+    const int r = blockIdx.y;
+    const int8_t* k = colour + (int64_t)r * n;
+    int64_t acc = 0;
+    const int64_t i0 = (int64_t)blockIdx.x * rows;
+    const int64_t i1 = i0 + rows < n ? i0 + rows : n;
+    for (int64_t i = i0 + threadIdx.x / LPR; i < i1; i += kIntTB / LPR) {
+        const int ki = k[i];
+        upper_entries<LPR>(row_ptr, col, J, (int)i, threadIdx.x % LPR,
+                           [&](int j) { return (int)k[j]; },
+                           [&](bool on, int kj, float w) {
+                               if (CUT) acc += on && ki != kj ? (int64_t)(-w) : 0;
+                               else acc += on && w != 0.0f && ki == kj ? 1 : 0;
+                           });
+    }
+    for (int o = 1; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int64_t tot = (red[0] + red[1]) + (red[2] + red[3]);
+        if (gridDim.x == 1) out[r] = tot;
+        else atomicAdd(reinterpret_cast<unsigned long long*>(out + r), (unsigned long long)tot);
+    }
+}
+
+// FP64 results: one workgroup of 16 waves per replica.  A wave takes every
+// 16th block of 64 rows, one row per lane, without a barrier; the block sums
+// of a round of kRoundBlocks blocks meet in LDS, where a wave folds each
+// result's by the pairwise tree, and the rounds (a power of two of rows
+// each) are folded in order.  STAGE: the replica's colours and phases are
+// copied to LDS first, so a neighbour's value is an LDS read.  Bound by the
+// latency of the row bounds and entries (and, for Eq. 6, the FP64 cosines).
+// 100 x 100 torus, real weights, 64 replicas: cut 73 -> 25 us, both energies
+// 130 -> 42 us against four waves with two to four barriers per 256 rows.
+constexpr int kSumTB = 1024;
+constexpr int kSumWaves = kSumTB / 64;
+constexpr int kRoundBlocks = 1024;
+
+struct Gathered {
+    int k;
+    float th;
+};
+
+// MODE 0: cut (FP64 and, when out_i64, int64), 2: energies.
+template <int MODE, bool STAGE>
+__global__ __launch_bounds__(kSumTB) void sparse_sum_kernel(
     int n, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-    const float* __restrict__ J, const float* __restrict__ Jd, const int8_t* __restrict__ colour,
-    const float* __restrict__ theta, int q, int64_t* out_i64, double* out_f64a, double* out_f64b) {
-    __shared__ int64_t si[kTB / 64];
-    __shared__ double sd[kTB / 64];
+    const float* __restrict__ J, const int8_t* __restrict__ colour,
+    const float* __restrict__ theta, int q, int64_t* out_i64, double* out_a, double* out_b) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double bs[2][kRoundBlocks];
     __shared__ double stack[2][TreeAcc::kLevels];
     const int r = blockIdx.x;
     const int8_t* k = colour ? colour + (int64_t)r * n : nullptr;
     const float* th = theta ? theta + (int64_t)r * n : nullptr;
-    int64_t tot_i = 0;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool want_a = out_a != nullptr, want_b = MODE == 2 && out_b != nullptr;
+    const bool want_i = MODE == 0 && out_i64 != nullptr;
+    float* th_lds = reinterpret_cast<float*>(smem);
+    int8_t* k_lds = reinterpret_cast<int8_t*>(th_lds + (th ? n : 0));
+    if constexpr (STAGE) {
+        for (int i = threadIdx.x; i < n; i += kSumTB) {
+            if (th) th_lds[i] = th[i];
+            if (k) k_lds[i] = k[i];
+        }
+        __syncthreads();
+    }
+    auto gather = [&](int j) __attribute__((always_inline)) {
+        Gathered g{0, 0.f};
+        if constexpr (STAGE) {
+            if (k) g.k = k_lds[j];
+            if (th) g.th = th_lds[j];
+        } else {
+            if (k) g.k = k[j];
+            if (th) g.th = th[j];
+        }
+        return g;
+    };
+    const int nblk = (n + 63) / 64;
     TreeAcc tree_a(stack[0]), tree_b(stack[1]);
-    for (int i0 = 0; i0 < n; i0 += kTB) {
-        const int i = i0 + (int)threadIdx.x;
-        int64_t acc_i = 0;
-        double acc_a = 0.0, acc_b = 0.0;
-        if (i < n) {
-            const int ki = k ? k[i] : 0;
-            const double ti = th ? (double)th[i] : 0.0;
-            auto visit = [&](int j, float w) {
-                if (MODE == 0) {
-                    if (ki != k[j]) {
-                        acc_i += (int64_t)(-w);
-                        acc_a += -(double)w;
+    int64_t tot_i = 0;
+    for (int b0 = 0; b0 < nblk; b0 += kRoundBlocks) {
+        const int nb = nblk - b0 < kRoundBlocks ? nblk - b0 : kRoundBlocks;
+        for (int b = wave; b < nb; b += kSumWaves) {
+            const int i = (b0 + b) * 64 + lane;
+            int64_t acc_i = 0;
+            double acc_a = 0.0, acc_b = 0.0;
+            if (i < n) {
+                const Gathered own = gather(i);
+                const double ti = (double)own.th;
+                upper_entries<1>(row_ptr, col, J, i, 0, gather, [&](bool on, Gathered g, float w) {
+                    if (!on) return;
+                    if (MODE == 0) {
+                        if (own.k != g.k) {
+                            acc_i += (int64_t)(-w);
+                            acc_a += -(double)w;
+                        }
+                    } else {
+                        if (k) {
+                            if (q == 2) acc_a += (own.k == g.k) ? -(double)w : (double)w;
+                            else if (own.k == g.k) acc_a += -(double)w;
+                        }
+                        if (th) {
+                            const double c = cos(ti - (double)g.th);
+                            const double term = -(double)w * c;
+                            acc_b += term;
+                        }
                     }
-                } else if (MODE == 1) {
-                    if (w != 0.0f && ki == k[j]) acc_i += 1;
-                } else {
-                    if (k) {
-                        if (q == 2) acc_a += (ki == k[j]) ? -(double)w : (double)w;
-                        else if (ki == k[j]) acc_a += -(double)w;
-                    }
-                    if (th) {
-                        const double c = cos(ti - (double)th[j]);
-                        const double term = -(double)w * c;
-                        acc_b += term;
-                    }
-                }
-            };
-            if (DENSE) {
-                const float* rowJ = Jd + (int64_t)i * n;
-                for (int j = i + 1; j < n; ++j) visit(j, rowJ[j]);
-            } else {
-                for (int64_t e = row_ptr[i]; e < row_ptr[i + 1]; ++e) {
-                    const int j = col[e];
-                    if (j > i) visit(j, J[e]);
-                }
+                });
+            }
+            if (MODE == 0 && want_i) {
+                for (int o = 1; o < 64; o <<= 1) acc_i += __shfl_xor(acc_i, o, 64);
+                tot_i += acc_i;
+            }
+            if (want_a) {
+                for (int o = 1; o < 64; o <<= 1) acc_a += __shfl_xor(acc_a, o, 64);
+                if (lane == 0) bs[0][b] = acc_a;
+            }
+            if (want_b) {
+                for (int o = 1; o < 64; o <<= 1) acc_b += __shfl_xor(acc_b, o, 64);
+                if (lane == 0) bs[1][b] = acc_b;
             }
         }
-        if (MODE == 0 || MODE == 1) {
-            const int64_t bi = block_tree<int64_t>(acc_i, si);
-            if (threadIdx.x == 0) tot_i += bi;
+        __syncthreads();
+        if (wave == 0 && want_a) {
+            const double v = dpair::fold_blocks(bs[0], nb);
+            if (lane == 0) tree_a.push(v);
         }
-        if (MODE == 0 || MODE == 2) {
-            const double ba = block_tree<double>(acc_a, sd);
-            if (threadIdx.x == 0) tree_a.push(ba);
+        if (wave == 1 && want_b) {
+            const double v = dpair::fold_blocks(bs[1], nb);
+            if (lane == 0) tree_b.push(v);
         }
-        if (MODE == 2) {
-            const double bb = block_tree<double>(acc_b, sd);
-            if (threadIdx.x == 0) tree_b.push(bb);
-        }
+        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        if ((MODE == 0 || MODE == 1) && out_i64) out_i64[r] = tot_i;
-        if ((MODE == 0 || MODE == 2) && out_f64a) out_f64a[r] = tree_a.finish();
-        if (MODE == 2 && out_f64b) out_f64b[r] = tree_b.finish();
+    if (wave == 0 && lane == 0 && want_a) out_a[r] = tree_a.finish();
+    if (wave == 1 && lane == 0 && want_b) out_b[r] = tree_b.finish();
+    if (MODE == 0 && want_i) {
+        int64_t* ti = reinterpret_cast<int64_t*>(bs[0]);
+        if (lane == 0) ti[wave] = tot_i;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int64_t t = 0;
+            for (int w = 0; w < kSumWaves; ++w) t += ti[w];
+            out_i64[r] = t;
+        }
     }
 }
 
-template <int MODE>
-int launch_pairs(const Problem* p, int R, const int8_t* colour, const float* theta, int q,
-                 int64_t* oi, double* oa, double* ob, hipStream_t s) {
-    if (R < 1) return set_error(OIM_E_ARG, "R must be >= 1");
-    if (p->dense)
-        hipLaunchKernelGGL((pair_sum_kernel<MODE, true>), dim3(R), dim3(kTB), 0, s, p->n,
-                           nullptr, nullptr, nullptr, p->d_Jdense, colour, theta, q, oi, oa, ob);
-    else
-        hipLaunchKernelGGL((pair_sum_kernel<MODE, false>), dim3(R), dim3(kTB), 0, s, p->n,
-                           p->d_row_ptr, p->d_col, p->d_J, nullptr, colour, theta, q, oi, oa,
-                           ob);
+int launched(const char* what) {
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_error(e, "readout launch");
-    return OIM_OK;
+    return e == hipSuccess ? OIM_OK : hip_error(e, what);
+}
+
+// More than 64 KiB of dynamic LDS has to be asked for.
+int allow_lds(const void* fn, size_t bytes) {
+    if (bytes <= 64 * 1024) return OIM_OK;
+    const hipError_t e =
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    return e == hipSuccess ? OIM_OK : hip_error(e, "hipFuncSetAttribute");
+}
+
+template <int KIND, bool INTS>
+int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* oi, double* of,
+                       hipStream_t s) {
+    const int nr = dpair::replicas_per_group(p->n, R, INTS);
+    const size_t lds = dpair::lds_bytes(p->n, nr, INTS);
+    auto fn = nr == 4   ? dense_pair_kernel<4, KIND, INTS>
+              : nr == 2 ? dense_pair_kernel<2, KIND, INTS>
+                        : dense_pair_kernel<1, KIND, INTS>;
+    if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
+    hipLaunchKernelGGL(fn, dim3((R + nr - 1) / nr), dim3(dpair::kTB), lds, s, p->n, R, p->d_Jdense,
+                       colour, oi, of);
+    return launched("readout launch");
+}
+
+template <bool CUT>
+int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* out, hipStream_t s) {
+    // lanes per row: about one group of four entries each at the mean degree
+    const int64_t deg = p->nnz / p->n;
+    const int lpr = deg > 32 ? 16 : deg > 8 ? 4 : 1;
+    auto fn = lpr == 16  ? sparse_int_kernel<CUT, 16>
+              : lpr == 4 ? sparse_int_kernel<CUT, 4>
+                         : sparse_int_kernel<CUT, 1>;
+    // rows per workgroup: one pass of its 256 threads while that gives at
+    // most 2048 workgroups (eight per CU), more passes beyond; a replica of
+    // at most two passes stays in one workgroup, which saves the zeroing
+    const int64_t per_pass = kIntTB / lpr;
+    const int64_t passes = (p->n + per_pass - 1) / per_pass;
+    int64_t per_group = passes * R / 2048;
+    if (per_group < 1) per_group = passes <= 2 ? passes : 1;
+    const int chunks = (int)((passes + per_group - 1) / per_group);
+    const int rows = (int)(per_group * per_pass < p->n ? per_group * per_pass : p->n);
+    for (int r0 = 0; r0 < R; r0 += 65535) {  // grid.y limit
+        const int nr = R - r0 < 65535 ? R - r0 : 65535;
+        if (chunks > 1)
+            hipLaunchKernelGGL(zero_kernel, dim3((nr + 255) / 256), dim3(256), 0, s, nr, out + r0);
+        hipLaunchKernelGGL(fn, dim3(chunks, nr), dim3(kIntTB), 0, s, p->n, rows, p->d_row_ptr,
+                           p->d_col, p->d_J, colour + (int64_t)r0 * p->n, out + r0);
+    }
+    return launched("readout launch");
+}
+
+template <int MODE>
+int launch_sparse_sum(const Problem* p, int R, const int8_t* colour, const float* theta, int q,
+                      int64_t* oi, double* oa, double* ob, hipStream_t s) {
+    // the staged copies next to the static arrays (16.5 KiB), where they fit
+    size_t lds = (size_t)p->n * ((theta ? 4 : 0) + (colour ? 1 : 0));
+    const bool stage = lds + 20 * 1024 <= dpair::kLdsLimit;
+    if (!stage) lds = 0;
+    auto fn = stage ? sparse_sum_kernel<MODE, true> : sparse_sum_kernel<MODE, false>;
+    if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds + 20 * 1024)) return st;
+    hipLaunchKernelGGL(fn, dim3(R), dim3(kSumTB), lds, s, p->n, p->d_row_ptr, p->d_col, p->d_J,
+                       colour, theta, q, oi, oa, ob);
+    return launched("readout launch");
 }
 
 }  // namespace
@@ -193,18 +420,36 @@ int launch_phase_convert(int64_t count, const float* theta_in, uint32_t* phase_o
 
 int launch_cut(const Problem* p, int32_t R, const int8_t* colour, int64_t* cut_i64,
                double* cut_f64, hipStream_t s) {
-    return launch_pairs<0>(p, R, colour, nullptr, 2, cut_i64, cut_f64, nullptr, s);
+    if (p->dense)
+        return cut_i64 ? launch_dense_pairs<dpair::kDiffer, true>(p, R, colour, cut_i64, cut_f64, s)
+                       : launch_dense_pairs<dpair::kDiffer, false>(p, R, colour, nullptr, cut_f64, s);
+    if (!cut_f64) return launch_sparse_int<true>(p, R, colour, cut_i64, s);
+    return launch_sparse_sum<0>(p, R, colour, nullptr, 2, cut_i64, cut_f64, nullptr, s);
 }
 
 int launch_conflicts(const Problem* p, int32_t R, const int8_t* colour, int64_t* conflicts,
                      hipStream_t s) {
-    return launch_pairs<1>(p, R, colour, nullptr, 2, conflicts, nullptr, nullptr, s);
+    if (p->dense) return launch_dense_pairs<dpair::kCount, true>(p, R, colour, conflicts, nullptr, s);
+    return launch_sparse_int<false>(p, R, colour, conflicts, s);
 }
 
 int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
                   const int8_t* colour, double* h_model, double* h_eq6, hipStream_t s) {
-    return launch_pairs<2>(p, R, h_model ? colour : nullptr, h_eq6 ? theta : nullptr, q, nullptr,
-                           h_model, h_eq6, s);
+    if (!p->dense)
+        return launch_sparse_sum<2>(p, R, h_model ? colour : nullptr, h_eq6 ? theta : nullptr, q,
+                                    nullptr, h_model, h_eq6, s);
+    if (h_model) {
+        const int st = q == 2
+                           ? launch_dense_pairs<dpair::kIsing, false>(p, R, colour, nullptr, h_model, s)
+                           : launch_dense_pairs<dpair::kSame, false>(p, R, colour, nullptr, h_model, s);
+        if (st) return st;
+    }
+    if (h_eq6) {
+        hipLaunchKernelGGL(dense_cos_kernel, dim3(R), dim3(dpair::kTB),
+                           sizeof(double) * dpair::row_blocks(p->n), s, p->n, p->d_Jdense, theta, h_eq6);
+        return launched("readout launch");
+    }
+    return OIM_OK;
 }
 
 }  // namespace oim
