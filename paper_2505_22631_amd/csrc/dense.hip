@@ -15,7 +15,8 @@
 //
 // One kernel per Euler-Maruyama step: workgroup tile = 128 rows x 64
 // replicas (S and C columns of the same replicas), 4 waves of 64 rows x 32
-// replicas, K in stages of 32 moved into a ring of 4 LDS buffers.  The
+// replicas, K in stages of 32 moved into a ring of 4 LDS buffers; smaller
+// tiles (dense_tile_kernel) where those leave CUs idle.  The
 // epilogue owns, per lane, quads of 4 consecutive rows of one replica -- the
 // MFMA accumulator layout -- so it draws one Philox call per quad, advances
 // the phase words and writes the next step's split [S | C] (ping-pong).
@@ -131,6 +132,74 @@ __device__ __forceinline__ void block_tiles(int ntr, int& ti, int& tr) {
     tr = f - ti * ntr;
 }
 
+constexpr int kRow32 = kTK * 4;  // bytes per FP32 row
+
+__device__ __forceinline__ int swz32(int row, int seg) {
+    return row * kRow32 + ((seg ^ ((row >> 1) & 7)) << 4);
+}
+// byte offset of (row rr, K index kk) inside a block region
+__device__ __forceinline__ int tile_off32(int rr, int kk) {
+    const int pos = (kk & 3) * 8 + (kk >> 2);
+    return swz32(rr, pos >> 2) + (pos & 3) * 4;
+}
+
+// Epilogue of a step for one quad (rows i .. i + 3) of replica r, from its
+// coupling sums J S and J C: SHIL, noise, Euler-Maruyama update, and the next
+// step's [S | C] in the image layout of the precision.  The multiply-adds are
+// written out, so every tile shape rounds alike.
+template <int QM, bool F32>
+__device__ __forceinline__ void step_quad(const DenseArgs& a, int r, int i, uint4 uq, uint64_t seed,
+                                          float K, float Ks, float sg, const f32x4& js,
+                                          const f32x4& jc) {
+#pragma clang fp contract(off)
+    if (r >= a.R || i >= a.n) return;
+    // step coefficients in 2^-32-turn units
+    const float kcoef = -a.dt * K * kTurnScale;
+    const float kscoef = -a.dt * Ks * kTurnScale;
+    const float nscoef = sg * a.sqrt_dt * kTurnScale;
+    uint32_t u[4] = {uq.x, uq.y, uq.z, uq.w};
+    float z[4];
+    normals4((uint32_t)(i >> 2), a.t, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), z);
+    float s1[4], c1[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const float s0 = sin_turn(u[x]), c0 = cos_turn(u[x]);
+        const float coup = __builtin_fmaf(s0, jc[x], -(c0 * js[x]));
+        const float sq = QM == 3 ? s0 * __builtin_fmaf(-4.0f * s0, s0, 3.0f)
+                                 : sin_q<QM>(s0, c0, u[x], a.q);
+        const float drift = __builtin_fmaf(kscoef, sq, kcoef * coup);
+        if (i + x < a.n) u[x] = advance(u[x], __builtin_fmaf(nscoef, z[x], drift));
+        s1[x] = i + x < a.n ? sin_turn(u[x]) : 0.f;
+        c1[x] = i + x < a.n ? cos_turn(u[x]) : 0.f;
+    }
+    *reinterpret_cast<uint4*>(a.U + (size_t)r * a.np + i) = uint4{u[0], u[1], u[2], u[3]};
+    unsigned char* xo = a.Xout + ((size_t)(r >> 6) * a.nk + (i >> 5)) * kBlock;
+    if constexpr (F32) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int off = tile_off32(r & 63, (i & 31) + x);
+            *reinterpret_cast<float*>(xo + off) = s1[x];
+            *reinterpret_cast<float*>(xo + kTR * kRow32 + off) = c1[x];
+        }
+    } else {
+        uint16_t shi[4], slo[4], chi[4], clo[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            split_bf16(s1[x], shi[x], slo[x]);
+            split_bf16(c1[x], chi[x], clo[x]);
+        }
+        xo += tile_off(r & 63, i & 31);
+        *reinterpret_cast<uint2*>(xo + 0 * kB) =
+            uint2{shi[0] | ((uint32_t)shi[1] << 16), shi[2] | ((uint32_t)shi[3] << 16)};
+        *reinterpret_cast<uint2*>(xo + 1 * kB) =
+            uint2{slo[0] | ((uint32_t)slo[1] << 16), slo[2] | ((uint32_t)slo[3] << 16)};
+        *reinterpret_cast<uint2*>(xo + 2 * kB) =
+            uint2{chi[0] | ((uint32_t)chi[1] << 16), chi[2] | ((uint32_t)chi[3] << 16)};
+        *reinterpret_cast<uint2*>(xo + 3 * kB) =
+            uint2{clo[0] | ((uint32_t)clo[1] << 16), clo[2] | ((uint32_t)clo[3] << 16)};
+    }
+}
+
 // One 256-thread workgroup per CU (one wave per SIMD).  Stages move from
 // global memory to LDS with direct DMA loads (global_load_lds_dwordx4: lane
 // l of a wave writes bytes 16l..16l+15 of a 1 KiB LDS chunk), so no staging
@@ -147,8 +216,7 @@ void dense_step_kernel(DenseArgs a) {
     int ti, tr;
     block_tiles(a.Rp / kTR, ti, tr);
     const int i0 = ti * kTM, r0 = tr * kTR;
-    const int np = a.np, Rp = a.Rp;
-    const size_t plane = (size_t)Rp * np;
+    const int np = a.np;
 
     // Chunk c of a stage (1 KiB) sits at LDS bytes 1024c: chunks 0-15 are the
     // J block of the stage, 16-31 the X block.  Wave w moves chunks
@@ -276,48 +344,12 @@ void dense_step_kernel(DenseArgs a) {
     // the refills issued by the last stages land before the LDS is released
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
-    // ---- epilogue: SHIL, noise, Euler-Maruyama update, next split X ----
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        const int r = r0 + wn * 32 + cb * 16 + (lane & 15);
-        const bool rvalid = r < a.R;
-        // step coefficients in 2^-32-turn units
-        const float kcoef = -a.dt * sK[cb] * kTurnScale;
-        const float kscoef = -a.dt * sKs[cb] * kTurnScale;
-        const float nscoef = sS[cb] * a.sqrt_dt * kTurnScale;
-        const uint32_t k0 = (uint32_t)seedv[cb], k1 = (uint32_t)(seedv[cb] >> 32);
+    for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int i = qi0 + b * 16;  // first row of the quad
-            if (!rvalid || i >= a.n) continue;
-            uint32_t u[4] = {uq[cb][b].x, uq[cb][b].y, uq[cb][b].z, uq[cb][b].w};
-            float z[4];
-            normals4((uint32_t)(i >> 2), a.t, 0u, k0, k1, z);
-            uint16_t shi[4], slo[4], chi[4], clo[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float s0 = sin_turn(u[x]), c0 = cos_turn(u[x]);
-                const float coup = s0 * acc[b][cb][1][x] - c0 * acc[b][cb][0][x];
-                const float drift = kcoef * coup + kscoef * sin_q<QM>(s0, c0, u[x], a.q);
-                if (i + x < a.n) u[x] = advance(u[x], __builtin_fmaf(nscoef, z[x], drift));
-                const float s1 = i + x < a.n ? sin_turn(u[x]) : 0.f;
-                const float c1 = i + x < a.n ? cos_turn(u[x]) : 0.f;
-                split_bf16(s1, shi[x], slo[x]);
-                split_bf16(c1, chi[x], clo[x]);
-            }
-            *reinterpret_cast<uint4*>(a.U + (size_t)r * np + i) = uint4{u[0], u[1], u[2], u[3]};
-            unsigned char* xo = a.Xout + ((size_t)(r >> 6) * a.nk + (i >> 5)) * kBlock +
-                                tile_off(r & 63, i & 31);
-            *reinterpret_cast<uint2*>(xo + 0 * kB) =
-                uint2{shi[0] | ((uint32_t)shi[1] << 16), shi[2] | ((uint32_t)shi[3] << 16)};
-            *reinterpret_cast<uint2*>(xo + 1 * kB) =
-                uint2{slo[0] | ((uint32_t)slo[1] << 16), slo[2] | ((uint32_t)slo[3] << 16)};
-            *reinterpret_cast<uint2*>(xo + 2 * kB) =
-                uint2{chi[0] | ((uint32_t)chi[1] << 16), chi[2] | ((uint32_t)chi[3] << 16)};
-            *reinterpret_cast<uint2*>(xo + 3 * kB) =
-                uint2{clo[0] | ((uint32_t)clo[1] << 16), clo[2] | ((uint32_t)clo[3] << 16)};
-        }
-    }
+        for (int b = 0; b < 4; ++b)
+            step_quad<QM, false>(a, r0 + wn * 32 + cb * 16 + (lane & 15), qi0 + b * 16, uq[cb][b],
+                                 seedv[cb], sK[cb], sKs[cb], sS[cb], acc[b][cb][0], acc[b][cb][1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -337,17 +369,6 @@ void dense_step_kernel(DenseArgs a) {
 //   J: block (row tile ti, stage kc) at (ti * nk + kc) * 16 KiB, 128 rows;
 //   X: block (replica tile tr, stage kc) at (tr * nk + kc) * 16 KiB, S rows
 //      (64) then C rows (64).
-constexpr int kRow32 = kTK * 4;  // bytes per FP32 row
-
-__device__ __forceinline__ int swz32(int row, int seg) {
-    return row * kRow32 + ((seg ^ ((row >> 1) & 7)) << 4);
-}
-// byte offset of (row rr, K index kk) inside a block region
-__device__ __forceinline__ int tile_off32(int rr, int kk) {
-    const int pos = (kk & 3) * 8 + (kk >> 2);
-    return swz32(rr, pos >> 2) + (pos & 3) * 4;
-}
-
 template <int QM>
 __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void dense_step32_kernel(DenseArgs a) {
@@ -454,41 +475,185 @@ void dense_step32_kernel(DenseArgs a) {
     mfmas(F1);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
-    // ---- epilogue: SHIL, noise, Euler-Maruyama update, next [S | C] ----
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        const int r = r0 + wn * 32 + cb * 16 + (lane & 15);
-        const bool rvalid = r < a.R;
-        const float kcoef = -a.dt * sK[cb] * kTurnScale;
-        const float kscoef = -a.dt * sKs[cb] * kTurnScale;
-        const float nscoef = sS[cb] * a.sqrt_dt * kTurnScale;
-        const uint32_t k0 = (uint32_t)seedv[cb], k1 = (uint32_t)(seedv[cb] >> 32);
+    for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int i = qi0 + b * 16;
-            if (!rvalid || i >= a.n) continue;
-            uint32_t u[4] = {uq[cb][b].x, uq[cb][b].y, uq[cb][b].z, uq[cb][b].w};
-            float z[4];
-            normals4((uint32_t)(i >> 2), a.t, 0u, k0, k1, z);
-            float s1[4], c1[4];
+        for (int b = 0; b < 4; ++b)
+            step_quad<QM, true>(a, r0 + wn * 32 + cb * 16 + (lane & 15), qi0 + b * 16, uq[cb][b],
+                                seedv[cb], sK[cb], sKs[cb], sS[cb], acc[b][cb][0], acc[b][cb][1]);
+}
+
+// ---------------------------------------------------------------------------
+// The same step in smaller workgroup tiles, for shapes whose 128 x 64 tiles
+// leave most CUs idle (choose_tile has the figures): WM x WN waves of RB x CB blocks of 16 rows x 16
+// replicas (S and C), both precisions (F32).  Bound by the chain of stages
+// (barrier, fragment reads, MFMAs) while a workgroup has a CU to itself, at
+// n = 4096 by the stream of J (67 MB per step).  Each accumulator still sums
+// its K values in the same order with the same MFMA, so the results are the
+// large tile's bit for bit.  Images, DMA ring and barriers as above; a ring
+// slot holds KS stages, so a barrier is paid once per KS stages.
+template <int RB, int CB, int WM, int WN, int KS, int DEPTH>
+struct TileShape {
+    static constexpr int kRows = 16 * RB * WM, kReps = 16 * CB * WN;
+    static constexpr int kWaves = WM * WN;
+    static constexpr int kBytes = kRows * 128 + kReps * 256;        // one stage in LDS
+    static constexpr int kChunks = kBytes / 1024 / kWaves;          // per wave and stage
+    static_assert(kBytes % (1024 * kWaves) == 0 && kTM % kRows == 0 && kTR % kReps == 0, "tile");
+};
+
+template <int QM, bool F32, int RB, int CB, int WM, int WN, int KS, int DEPTH>
+__global__ __launch_bounds__(64 * WM * WN) void dense_tile_kernel(DenseArgs a) {
+    using T = TileShape<RB, CB, WM, WN, KS, DEPTH>;
+    __shared__ __align__(1024) unsigned char lds[DEPTH][KS][T::kBytes];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    int ti, tr;
+    block_tiles((a.R + T::kReps - 1) / T::kReps, ti, tr);
+    const int i0 = ti * T::kRows, r0 = tr * T::kReps;
+    const int np = a.np, nss = a.nk / KS;  // nk is a multiple of 4
+
+    // Chunk c of a stage (1 KiB of LDS): first the tile's rows of the J block
+    // (BF16: hi then lo), then its replicas of each X component.
+    const unsigned char* src[T::kChunks];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float s0 = sin_turn(u[x]), c0 = cos_turn(u[x]);
-                const float coup = s0 * acc[b][cb][1][x] - c0 * acc[b][cb][0][x];
-                const float drift = kcoef * coup + kscoef * sin_q<QM>(s0, c0, u[x], a.q);
-                if (i + x < a.n) u[x] = advance(u[x], __builtin_fmaf(nscoef, z[x], drift));
-                s1[x] = i + x < a.n ? sin_turn(u[x]) : 0.f;
-                c1[x] = i + x < a.n ? cos_turn(u[x]) : 0.f;
-            }
-            *reinterpret_cast<uint4*>(a.U + (size_t)r * np + i) = uint4{u[0], u[1], u[2], u[3]};
-            unsigned char* xo = a.Xout + ((size_t)(r >> 6) * a.nk + (i >> 5)) * kBlock;
+    for (int x = 0; x < T::kChunks; ++x) {
+        const int b = (wave * T::kChunks + x) * 1024;
+        constexpr int jPart = F32 ? T::kRows * kRow32 : T::kRows * kRow;  // one J region
+        constexpr int xPart = F32 ? T::kReps * kRow32 : T::kReps * kRow;  // one X component
+        constexpr int jFull = F32 ? kTM * kRow32 : kA, xFull = F32 ? kTR * kRow32 : kB;
+        if (b < T::kRows * 128) {
+            const int part = b / jPart;
+            src[x] = a.Jt + (size_t)(i0 / kTM) * a.nk * kBlock + part * jFull +
+                     (i0 % kTM) / T::kRows * jPart + (b - part * jPart);
+        } else {
+            const int bx = b - T::kRows * 128, part = bx / xPart;
+            src[x] = a.Xin + (size_t)(r0 / kTR) * a.nk * kBlock + part * xFull +
+                     (r0 % kTR) / T::kReps * xPart + (bx - part * xPart);
+        }
+        src[x] += lane * 16;
+    }
+    auto issue = [&](int ss, int buf) __attribute__((always_inline)) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int off = tile_off32(r & 63, (i & 31) + x);
-                *reinterpret_cast<float*>(xo + off) = s1[x];
-                *reinterpret_cast<float*>(xo + kTR * kRow32 + off) = c1[x];
+        for (int k = 0; k < KS; ++k)
+#pragma unroll
+            for (int x = 0; x < T::kChunks; ++x)
+                __builtin_amdgcn_global_load_lds(
+                    (glb_void_t*)(src[x] + (size_t)(ss * KS + k) * kBlock),
+                    (lds_void_t*)(lds[buf][k] + (wave * T::kChunks + x) * 1024), 16, 0, 0);
+    };
+
+    f32x4 acc[RB][CB][2];
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) acc[b][c][0] = acc[b][c][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int frow = lane & 15, g = lane >> 4;
+    struct TileFrags {
+        f32x4 a[KS][RB][2];     // BF16: hi, lo; F32: the lane's 8 values
+        f32x4 b[KS][CB][2][2];  // [replica block][S, C], the same
+    };
+    auto read_frags = [&](int buf, TileFrags& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const unsigned char* base = lds[buf][k];
+            const unsigned char* bx = base + T::kRows * 128;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    const int row = (wn * CB + cb) * 16 + frow;
+#pragma unroll
+                    for (int sc = 0; sc < 2; ++sc)
+                        f.b[k][cb][sc][h] = *reinterpret_cast<const f32x4*>(
+                            F32 ? bx + sc * T::kReps * kRow32 + swz32(row, 2 * g + h)
+                                : bx + (2 * sc + h) * T::kReps * kRow + swz(row, g));
+                }
+#pragma unroll
+                for (int b = 0; b < RB; ++b) {
+                    const int row = (wm * RB + b) * 16 + frow;
+                    f.a[k][b][h] = *reinterpret_cast<const f32x4*>(
+                        F32 ? base + swz32(row, 2 * g + h) : base + h * T::kRows * kRow + swz(row, g));
+                }
             }
         }
+    };
+    auto mfmas = [&](const TileFrags& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+#pragma unroll
+            for (int p = 0; p < (F32 ? 8 : 3); ++p)
+#pragma unroll
+                for (int b = 0; b < RB; ++b)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int sc = 0; sc < 2; ++sc) {
+                            if constexpr (F32)
+                                acc[b][cb][sc] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                    f.a[k][b][p >> 2][p & 3], f.b[k][cb][sc][p >> 2][p & 3],
+                                    acc[b][cb][sc], 0, 0, 0);
+                            else
+                                acc[b][cb][sc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8, f.a[k][b][p == 2 ? 1 : 0]),
+                                    __builtin_bit_cast(bf16x8, f.b[k][cb][sc][p == 1 ? 1 : 0]),
+                                    acc[b][cb][sc], 0, 0, 0);
+                        }
+        }
+    };
+    constexpr int kInFlight = T::kChunks * KS;
+    auto stage = [&](int ss, int bufn, int bufi, TileFrags& cur, TileFrags& nxt)
+        __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((DEPTH - 3) * kInFlight));
+        lds_barrier();
+        read_frags(bufn, nxt);
+        issue(ss + DEPTH - 1 < nss ? ss + DEPTH - 1 : nss - 1, bufi);
+        mfmas(cur);
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH - 1; ++d) issue(d < nss ? d : nss - 1, d);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((DEPTH - 2) * kInFlight));
+    lds_barrier();
+    TileFrags F0, F1;
+    read_frags(0, F0);
+    int b1 = 1 % DEPTH, bi = DEPTH - 1;  // buffers of the next stage and of the refill
+    auto next = [&]() {
+        b1 = b1 + 1 == DEPTH ? 0 : b1 + 1;
+        bi = bi + 1 == DEPTH ? 0 : bi + 1;
+    };
+    for (int ss = 0; ss < nss - 2; ss += 2) {
+        stage(ss, b1, bi, F0, F1);
+        next();
+        stage(ss + 1, b1, bi, F1, F0);
+        next();
+    }
+    stage(nss - 2, b1, bi, F0, F1);
+    const int qi0 = i0 + wm * RB * 16 + 4 * g;
+    uint4 uq[CB][RB];
+    uint64_t seedv[CB];
+    float sK[CB], sKs[CB], sS[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int r = r0 + (wn * CB + cb) * 16 + frow;
+        seedv[cb] = r < a.R ? a.seeds[r] : 0ull;
+        const int64_t so = (int64_t)(r < a.R ? r : 0) * a.sched_stride + a.s;
+        sK[cb] = a.K[so];
+        sKs[cb] = a.Ks[so];
+        sS[cb] = a.sigma[so];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+            uq[cb][b] = *reinterpret_cast<const uint4*>(a.U + (size_t)r * np + qi0 + b * 16);
+    }
+    mfmas(F1);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the refills land before the LDS is released
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int r = r0 + (wn * CB + cb) * 16 + frow;
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+            step_quad<QM, F32>(a, r, qi0 + b * 16, uq[cb][b], seedv[cb], sK[cb], sKs[cb], sS[cb],
+                               acc[b][cb][0], acc[b][cb][1]);
     }
 }
 
@@ -716,6 +881,61 @@ size_t dense_need(int n, int R) {
     return plane * 4 + 2 * 4 * plane * 2 + (size_t)R * 8 * 2 + (size_t)R * 4 + 256;
 }
 
+struct TileChoice {
+    StepFn fn;
+    int rows, reps, threads;
+};
+
+template <bool F32, int RB, int CB, int WM, int WN, int KS, int DEPTH>
+TileChoice tile_of(int q) {
+    using T = TileShape<RB, CB, WM, WN, KS, DEPTH>;
+    return {q == 2   ? dense_tile_kernel<2, F32, RB, CB, WM, WN, KS, DEPTH>
+            : q == 3 ? dense_tile_kernel<3, F32, RB, CB, WM, WN, KS, DEPTH>
+                     : dense_tile_kernel<0, F32, RB, CB, WM, WN, KS, DEPTH>,
+            T::kRows, T::kReps, 64 * WM * WN};
+}
+
+// The tile of a shape, the one of least cost; of equal ones the largest.
+// Cost: rounds of workgroups over the 256 CUs times what one workgroup's
+// stage costs.  With BF16 products that is the bytes it moves (rows x 128 +
+// replicas x 256): 32 x 16 replaces the large tile's 18.7 us per step by 5.8
+// at n = 777, R = 24 (7 workgroups before, 50 now) and 54.3 by 16.2 at
+// n = 4096, R = 16; 64 x 16: 32.8 by 11.6 at n = 2000, R = 128; 64 x 32: 57.1
+// by 30.4 at n = 4096, R = 128; 128 x 32: 58.4 by 51.5 at n = 4096, R = 256;
+// at R = 512 the large tile fills the chip (78.7 against 103 for 128 x 32).
+// With FP32 products it is the matrix-core time (rows x replicas): 62.2 ->
+// 10.9 us (n = 777, R = 24), 134.7 -> 24.0 (2000, 128), 259 -> 38.7 (4096,
+// 16), 262 -> 74.5 (4096, 128), 263 -> 141 (4096, 256), 268 against 279
+// (4096, 512).
+template <bool F32>
+TileChoice choose_tile(int n, int R, int q) {
+    // FP32's 32 x 16 tile takes two stages per barrier (38.7 against 40.5 us
+    // at n = 4096, R = 16), BF16's one (16.2 against 18.2)
+    const TileChoice tiles[] = {
+        {q == 2   ? (F32 ? dense_step32_kernel<2> : dense_step_kernel<2>)
+         : q == 3 ? (F32 ? dense_step32_kernel<3> : dense_step_kernel<3>)
+                  : (F32 ? dense_step32_kernel<0> : dense_step_kernel<0>),
+         kTM, kTR, kTB},
+        tile_of<F32, 2, 2, 4, 1, 1, 4>(q),                     // 128 x 32
+        tile_of<F32, 2, 1, 2, 2, 2, 4>(q),                     // 64 x 32
+        tile_of<F32, 1, 1, 4, 1, 1, 6>(q),                     // 64 x 16
+        tile_of<F32, 1, 1, 2, 1, F32 ? 2 : 1, F32 ? 4 : 6>(q)  // 32 x 16
+    };
+    const TileChoice* best = nullptr;
+    int64_t best_cost = 0;
+    for (const TileChoice& t : tiles) {
+        const int64_t groups =
+            (int64_t)((n + t.rows - 1) / t.rows) * ((R + t.reps - 1) / t.reps);
+        const int64_t cost =
+            (groups + 255) / 256 * (F32 ? t.rows * t.reps : t.rows * 128 + t.reps * 256);
+        if (!best || cost < best_cost) {
+            best = &t;
+            best_cost = cost;
+        }
+    }
+    return *best;
+}
+
 int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* Ks,
               const float* sigma, const uint64_t* seeds, int64_t step0, float* theta,
               uint32_t* phase, const oim_readout* ro, hipStream_t stream, void* work) {
@@ -741,13 +961,8 @@ int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* K
                            X1, n, R, np, Rp);
     int st = check_launch("dense_init_kernel");
     if (st) return st;
-    StepFn fn;
-    if (fp32)
-        fn = cfg->q == 2 ? dense_step32_kernel<2> : cfg->q == 3 ? dense_step32_kernel<3>
-                                                                : dense_step32_kernel<0>;
-    else
-        fn = cfg->q == 2 ? dense_step_kernel<2> : cfg->q == 3 ? dense_step_kernel<3>
-                                                              : dense_step_kernel<0>;
+    const TileChoice tile = fp32 ? choose_tile<true>(n, R, cfg->q) : choose_tile<false>(n, R, cfg->q);
+    const StepFn fn = tile.fn;
     DenseArgs a{};
     a.Jt = fp32 ? p->d_Jtiled32 : p->d_Jtiled;
     a.nk = np / kTK;
@@ -766,7 +981,7 @@ int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* K
     a.dt = cfg->dt;
     a.sqrt_dt = std::sqrt(cfg->dt);
     hipError_t e = hipSuccess;
-    dim3 grid((np / kTM) * (Rp / kTR));
+    const dim3 grid(((n + tile.rows - 1) / tile.rows) * ((R + tile.reps - 1) / tile.reps));
     const int nr = dpair::replicas_per_group(n, R, false);
     const size_t read_lds = dpair::lds_bytes(n, nr, false);
     const bool ising = cfg->q == 2;
@@ -785,7 +1000,7 @@ int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* K
         a.Xout = (s & 1) ? X0 : X1;
         a.t = (uint32_t)(step0 + s);
         a.s = s;
-        hipLaunchKernelGGL(fn, grid, dim3(kTB), 0, stream, a);
+        hipLaunchKernelGGL(fn, grid, dim3(tile.threads), 0, stream, a);
         if ((st = check_launch("dense_step_kernel"))) return st;
         if (M > 0 && ((s + 1) % M == 0 || s + 1 == cfg->steps)) {
             ra.kread = (s + M) / M - 1;

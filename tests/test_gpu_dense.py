@@ -213,3 +213,28 @@ def test_dense_paper_scale_sampled_replica(oim, orc):
     assert np.all(np.isfinite(got)) and got.min() >= 0 and got.max() < 2 * np.pi
     _check_bf16x3(orc, got[pick], J, th0[pick], K, Ks, sg, sd[pick], 2, step0=7,
                   label=f"n={n} R={R} replica {pick}, {steps} steps")
+
+
+@pytest.mark.parametrize("prec,q", [("bf16x3", 2), ("bf16x3", 5), ("fp32", 2), ("fp32", 3)])
+def test_dense_tiles_same_bits(oim, prec, q):
+    # the workgroup tile follows from (n, R): 7 .. 1024 replicas of a coupling
+    # with a ragged last row tile run on every tile shape, and the replicas
+    # they share agree bit for bit (replica tiles are ragged too)
+    import torch
+    n, steps = 1100, 4
+    flags = oim.OIM_PREC_BF16X3 if prec == "bf16x3" else oim.OIM_PREC_FP32
+    J = synth.sk_dense(n, seed=6)
+    th0 = synth.theta0(1024, n, seed=3)
+    sd = synth.seeds(1024, 5)
+    with oim.Problem.from_dense(J) as prob:
+        K, Ks, sg = (torch.from_numpy(x).cuda() for x in
+                     (synth.ramp(0, 20, steps), synth.ramp(0, 5, steps), synth.const(0.1, steps)))
+        got = {}
+        for R in (1024, 512, 350, 200, 60, 7):
+            th = torch.from_numpy(th0[:R].copy()).cuda()
+            ph = oim.oim_phase_from_theta(th)
+            oim.run(prob, th, K, Ks, sg, torch.from_numpy(sd[:R].copy()).cuda(), q=q, dt=DT,
+                    flags=flags, phase=ph)
+            got[R] = ph.cpu().numpy()
+    for R, ph in got.items():
+        np.testing.assert_array_equal(ph, got[1024][:R], err_msg=f"R={R}")
