@@ -41,10 +41,19 @@ size_t lds_bytes(int plane, int tb, int rpl, int covered = 0) {
 
 constexpr uint64_t kMaxSellBytes = 0x7fffffffull;
 
-// Default choice without tuning: fewest waves that still cover every slice
-// with the registers of one variant, preferring 8 waves per workgroup, among
-// blocks of at least 256 threads.
-const Variant* pick_variant(int S, int tb_hint) {
+// The variant of `tb` threads and `rpl` rows per lane with the fewest slices
+// per wave group that covers S slices, or null.
+const Variant* covering(int tb, int rpl, int S) {
+    const Variant* best = nullptr;
+    for (const Variant& v : kVariants)
+        if (v.tb == tb && v.rpl == rpl && v.covers() >= S && (!best || v.ms < best->ms)) best = &v;
+    return best;
+}
+
+// The whole-quad variant with the fewest waves that cover S slices, preferring
+// 8 waves per workgroup, among blocks of at least 256 threads (tb_hint: of
+// that many).
+const Variant* fewest_waves(int S, int tb_hint) {
     const Variant* best = nullptr;
     for (const Variant& v : kVariants) {
         const int W = v.tb / 64;
@@ -58,6 +67,55 @@ const Variant* pick_variant(int S, int tb_hint) {
         if (cv < cb || (cv == cb && pv < pb)) best = &v;
     }
     return best;
+}
+
+// Default choice without tuning, from the slices of the largest instance (S),
+// the workgroups a CU holds at once and the rows' mean length: about sixteen
+// working waves per CU, four per SIMD.
+//  - A step's latency is shared by the waves of a workgroup, so while a CU has
+//    few workgroups the rows of a quad are split over waves until sixteen
+//    work: G(200, 0.05) unit weights 1.57 -> 1.03 us per step (256 x 1 with
+//    whole quads -> 1 row per lane), G(800, 0.06) 4.5 -> 3.1 (1024 x 1 x 1),
+//    n = 1500 of degree 10 2.2 -> 2.1 (1024 x 1 x 2), of degree 47 5.4 -> 4.8
+//    (1024 x 2 x 1: long rows take one more split).  A split repeats the quad's
+//    Philox call in each of its waves, so it ends there: with the general
+//    image two waves per slice lose from 7 slices on (n = 2000 of degree 10:
+//    3.2 against 3.5 us).
+//  - Instances of more slices take sixteen waves of whole quads: n = 3500 of
+//    degree 10 4.1 -> 3.6 us (1024 x 1), n = 10000 of degree 5 8.6 -> 6.0
+//    (1024 x 3); the general image, which holds more registers, twelve waves of
+//    four slices for 33 to 48 (10.8 -> 9.3, against 9.75 with sixteen).
+//  - Where a CU holds several workgroups each takes its share of the sixteen
+//    waves: 256 colouring graphs of up to 600 oscillators x 8 replicas 3.6 ->
+//    3.0 us (256 -> 128 threads), of up to 250 3.1 -> 1.8 (64); n = 2000, 600
+//    replicas 6.0 -> 5.6 (512 -> 256).  Beyond 16 slices the sixteen waves stay
+//    (n = 6000, 600 replicas: 11.8 us with 1024 x 2, 15.6 with 512 x 5).
+const Variant* default_variant(const Problem* p, int R) {
+    const int S = p->max_slices;
+    const int64_t fit = (int64_t)(kLdsLimit / lds_bytes(S * 64, 64, 4));
+    const int64_t per_cu = ((int64_t)R * p->n_inst + 255) / 256;
+    const int64_t g = S > 16 ? 1 : per_cu < fit ? per_cu : fit;
+    const int waves = g >= 16 ? 1 : (int)(16 / (g < 1 ? 1 : g));
+    const bool uw = p->d_sell_uw != nullptr;
+    const bool long_rows = p->nnz / p->n >= 24;
+    const Variant* v = nullptr;
+    if (4 * S <= waves) {
+        v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
+    } else if (2 * S <= waves && (uw || S <= 6)) {
+        v = long_rows && S > 4 ? covering(1024, 1, S) : covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
+    } else if (uw && long_rows && waves == 16 && S <= 16) {
+        v = covering(1024, 2, S);
+    } else if (!uw && waves == 16 && S > 32 && S <= 48) {
+        v = covering(768, 4, S);
+    } else {
+        int W = S;  // or the largest power of two within the share
+        if (S > waves)
+            for (W = 16; W > waves;) W /= 2;
+        for (int tb = W <= 1 ? 64 : W <= 2 ? 128 : W <= 4 ? 256 : W <= 8 ? 512 : 1024; !v && tb <= 1024;
+             tb *= 2)
+            v = covering(tb, 4, S);
+    }
+    return v && lds_bytes(S * 64, v->tb, v->rpl) <= kLdsLimit ? v : fewest_waves(S, 0);
 }
 
 int env_int(const char* name, int dflt) {
@@ -81,14 +139,15 @@ int q_class(int q) { return q == 2 ? 1 : q == 3 ? 2 : 0; }
 
 // The variant a run uses: the tuned one for this SHIL order if set, else an
 // OIM_PERSIST_TB block-size hint, else the default choice.
-const Variant* run_variant(const Problem* p, int q) {
+const Variant* run_variant(const Problem* p, int q, int R) {
     const int qc = q_class(q);
     if (p->tuned_tb[qc]) {
         const Variant* v = find_variant(p->tuned_tb[qc], p->tuned_ms[qc], p->tuned_rpl[qc]);
         if (v && variant_ok(p, *v)) return v;
     }
-    const Variant* v = pick_variant(p->max_slices, env_int("OIM_PERSIST_TB", 0));
-    return v ? v : pick_variant(p->max_slices, 0);
+    const int hint = env_int("OIM_PERSIST_TB", 0);
+    const Variant* v = hint ? fewest_waves(p->max_slices, hint) : nullptr;
+    return v ? v : default_variant(p, R);
 }
 
 }  // namespace
@@ -102,7 +161,7 @@ bool persistent_sparse_fits(const Problem* p) {
     if (p->dense || p->max_slices == 0) return false;
     if (lds_bytes(p->max_slices * 64, 1024, 4) > kLdsLimit) return false;
     if ((uint64_t)p->sell_entries * 8 > kMaxSellBytes) return false;
-    return pick_variant(p->max_slices, 0) != nullptr;
+    return fewest_waves(p->max_slices, 0) != nullptr;
 }
 
 namespace {
@@ -113,7 +172,7 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
                    uint32_t* phase, const oim_readout* ro, hipStream_t stream,
                    const Variant* forced, int32_t sched_stride) {
     const int S = p->max_slices;
-    const Variant* v = forced ? forced : run_variant(p, cfg->q);
+    const Variant* v = forced ? forced : run_variant(p, cfg->q, cfg->R);
     if (!v || !persistent_sparse_fits(p) || !variant_ok(p, *v))
         return set_error(OIM_E_UNSUPPORTED, "replica does not fit the LDS-resident kernel");
     PersistArgs a{};
