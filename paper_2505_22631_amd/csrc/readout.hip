@@ -164,24 +164,22 @@ __device__ __forceinline__ void upper_entries(const int64_t* __restrict__ row_pt
 // conflicts of 256 colouring graphs (86 928 oscillators) x 8 replicas took
 // 1642 us, now 42; the cut of a 200 x 300 torus x 64 replicas 549, now 38; of
 // G(800, 0.06) x 1 replica 79, now 5 (and 5 for the zeroing).
-constexpr int kIntTB = 256;
-
 __global__ void zero_kernel(int R, int64_t* out) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r < R) out[r] = 0;
 }
 
 template <bool CUT, int LPR>
-__global__ __launch_bounds__(kIntTB) void sparse_int_kernel(
+__global__ __launch_bounds__(1024) void sparse_int_kernel(
     int n, int rows, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
     const float* __restrict__ J, const int8_t* __restrict__ colour, int64_t* out) {
-    __shared__ int64_t red[kIntTB / 64];
+    __shared__ int64_t red[16];
     const int r = blockIdx.y;
     const int8_t* k = colour + (int64_t)r * n;
     int64_t acc = 0;
     const int64_t i0 = (int64_t)blockIdx.x * rows;
     const int64_t i1 = i0 + rows < n ? i0 + rows : n;
-    for (int64_t i = i0 + threadIdx.x / LPR; i < i1; i += kIntTB / LPR) {
+    for (int64_t i = i0 + threadIdx.x / LPR; i < i1; i += blockDim.x / LPR) {
         const int ki = k[i];
         upper_entries<LPR>(row_ptr, col, J, (int)i, threadIdx.x % LPR,
                            [&](int j) { return (int)k[j]; },
@@ -194,7 +192,8 @@ __global__ __launch_bounds__(kIntTB) void sparse_int_kernel(
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int64_t tot = (red[0] + red[1]) + (red[2] + red[3]);
+        int64_t tot = 0;
+        for (int w = 0; w < (int)blockDim.x / 64; ++w) tot += red[w];
         if (gridDim.x == 1) out[r] = tot;
         else atomicAdd(reinterpret_cast<unsigned long long*>(out + r), (unsigned long long)tot);
     }
@@ -359,20 +358,27 @@ int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* ou
     auto fn = lpr == 16  ? sparse_int_kernel<CUT, 16>
               : lpr == 4 ? sparse_int_kernel<CUT, 4>
                          : sparse_int_kernel<CUT, 1>;
-    // rows per workgroup: one pass of its 256 threads while that gives at
-    // most 2048 workgroups (eight per CU), more passes beyond; a replica of
-    // at most two passes stays in one workgroup, which saves the zeroing
-    const int64_t per_pass = kIntTB / lpr;
-    const int64_t passes = (p->n + per_pass - 1) / per_pass;
-    int64_t per_group = passes * R / 2048;
-    if (per_group < 1) per_group = passes <= 2 ? passes : 1;
-    const int chunks = (int)((passes + per_group - 1) / per_group);
-    const int rows = (int)(per_group * per_pass < p->n ? per_group * per_pass : p->n);
+    // A replica of at most 6 passes of 1024 threads stays in one workgroup,
+    // which saves the zeroing launch (about 5 us; a pass is latency, 1 to 2
+    // us).  Beyond, workgroups of 256 threads take one pass each while that
+    // gives at most 2048 of them (eight per CU), else more.
+    int tb = 1024, chunks = 1;
+    int64_t rows = p->n;
+    if ((int64_t)p->n * lpr > 6 * 1024) {
+        tb = 256;
+        const int64_t per_pass = tb / lpr;
+        const int64_t passes = (p->n + per_pass - 1) / per_pass;
+        const int64_t per_group = passes * R / 2048 > 1 ? passes * R / 2048 : 1;
+        chunks = (int)((passes + per_group - 1) / per_group);
+        rows = per_group * per_pass;
+    } else if ((int64_t)p->n * lpr <= 256) {
+        tb = 256;
+    }
     for (int r0 = 0; r0 < R; r0 += 65535) {  // grid.y limit
         const int nr = R - r0 < 65535 ? R - r0 : 65535;
         if (chunks > 1)
             hipLaunchKernelGGL(zero_kernel, dim3((nr + 255) / 256), dim3(256), 0, s, nr, out + r0);
-        hipLaunchKernelGGL(fn, dim3(chunks, nr), dim3(kIntTB), 0, s, p->n, rows, p->d_row_ptr,
+        hipLaunchKernelGGL(fn, dim3(chunks, nr), dim3(tb), 0, s, p->n, (int)rows, p->d_row_ptr,
                            p->d_col, p->d_J, colour + (int64_t)r0 * p->n, out + r0);
     }
     return launched("readout launch");
