@@ -31,14 +31,23 @@ __device__ __forceinline__ void philox_mulhilo(uint32_t m, uint32_t a, uint32_t&
     lo = (uint32_t)p;
 }
 
-// Ten Philox rounds on counter c with key (k0, k1).
+// a ^ b ^ c in one instruction (v_bitop3_b32, truth table of the 3-input xor).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// Ten Philox rounds on counter c with key (k0, k1).  The first two rounds'
+// xors have uniform operands (the step, the instance, the key), which the
+// scalar unit folds; from the third on two operands are the lane's, and the
+// compiler, left alone, spends two v_xor on each.
 __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         uint32_t hi0, lo0, hi1, lo1;
         philox_mulhilo(0xD2511F53u, c.x, hi0, lo0);
         philox_mulhilo(0xCD9E8D57u, c.z, hi1, lo1);
-        c = u32x4{hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0};
+        if (r < 2) c = u32x4{hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0};
+        else c = u32x4{xor3(hi1, c.y, k0), lo1, xor3(hi0, c.w, k1), lo0};
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
