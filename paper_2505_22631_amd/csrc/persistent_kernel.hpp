@@ -28,6 +28,8 @@
 #pragma once
 #include <float.h>
 
+#include <type_traits>
+
 #include "internal.hpp"
 #include "noise.hpp"
 #include "phase.hpp"
@@ -97,6 +99,48 @@ __device__ __forceinline__ float2 sc_at(const unsigned char*, int byte_off) {
     return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
 
+// The step's increment of one oscillator in 2^-32-turn units, from its own
+// (sin, cos), its sums A = sum J c_j and B = sum J s_j, its phase word and its
+// normal z.
+template <int QM>
+__device__ __forceinline__ float increment(float2 own, float A, float B, uint32_t u, int q, float kc,
+                                           float ks, float ns, float z) {
+    const float coup = __builtin_fmaf(own.x, A, -(own.y * B));
+    // sin(3 theta) = s (3 - 4 s^2) with its multiply-add fused
+    const float sq = QM == 3 ? own.x * __builtin_fmaf(-4.0f * own.x, own.x, 3.0f)
+                             : sin_q<QM>(own.x, own.y, u, q);
+    // the deterministic part of the increment; which of its two products is
+    // fused keeps the rounding this kernel has always had (the SHIL term for
+    // q = 2, the coupling term otherwise), so results are unchanged bit for bit
+    const float det = QM == 2 ? __builtin_fmaf(ks, sq, kc * coup) : __builtin_fmaf(kc, coup, ks * sq);
+    return __builtin_fmaf(ns, z, det);
+}
+
+// Shapes of one slice per wave group keep the first 8 / RPL groups of 16
+// bytes of every row's entries and their own (sin, cos) in registers and
+// read and write two tables in turn, one barrier per step.  Such instances are
+// small, so a step is a chain of latencies -- the entries' L2 round trip, two
+// barriers, an own-entry read -- rather than a stream of work; what is left
+// of the chain is LDS reads, Philox beside them, the sums and the update.  us
+// per step before and now, one replica: n = 200 of degree 10 unit weights
+// 1.03 -> 0.85, real weights 1.31 -> 0.93; n = 800 of degree 10 1.49 -> 1.24,
+// real 1.93 -> 1.37; n = 800 of degree 47, bound by its LDS reads, 3.13 ->
+// 3.05, real 4.72 -> 3.94; n = 2000 of degree 10 2.41 -> 2.19, real 3.00 ->
+// 2.46; n = 3500 of degree 10 3.56 -> 3.08, real 4.87 -> 4.36.  (Guarding the
+// groups one by one split the reads into blocks that each waited: slower than
+// before; now whole batches are read, padded where a row ends.)
+__host__ __device__ constexpr bool resident_rows(int ms) { return ms == 1; }
+// LDS byte offset of the second table of a shape of `groups` slices: past the
+// first table, the colours and the zero entry of its largest instance, a
+// constant so that a read's table is part of its instruction.
+__host__ __device__ constexpr int second_table(int groups) { return 36 * 64 * groups + 16; }
+
+// The same entry as one 64-bit word (sine below).
+__device__ __forceinline__ uint64_t sc_word(int byte_off) {
+    typedef __attribute__((address_space(3))) const uint64_t lds_u64;
+    return *reinterpret_cast<lds_u64*>((uint32_t)byte_off);
+}
+
 // Launch shape: TB threads (W = TB / 64 waves), MS slices per wave group,
 // RPL rows of every quad per lane.  RPL = 4: a lane owns whole quads (one
 // wave per slice).  RPL = 2 or 1 (rows split): G = 4 / RPL waves share a
@@ -106,7 +150,8 @@ __device__ __forceinline__ float2 sc_at(const unsigned char*, int byte_off) {
 // entry order, its Philox normal, its update -- is the same in all shapes,
 // so they give identical results.
 template <int TB, int MS, int QM, int RPL, bool UWT>
-__global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
+__global__ __launch_bounds__(TB, resident_rows(MS) ? 4 : (TB / 64 + 3) / 4)
+void persistent_sparse_kernel(PersistArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     // workgroup -> (instance, replica).  Consecutive workgroup ids go to the
     // 8 XCDs in turn, each with its own L2; the replicas of one instance are
@@ -137,11 +182,15 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
     constexpr int G = 4 / RPL;     // waves per slice
     constexpr int WS = W / G;      // wave groups (slices in flight)
     constexpr int U = 8 / RPL;     // 16-byte entry loads per row per iteration
+    constexpr bool RES = resident_rows(MS);
+    constexpr int T1 = RES ? second_table(WS) : 0;  // byte offset of the second table
+    constexpr int U4 = U / 2;      // 16-byte loads (4 edges) per row per iteration, unit weights
     float2* sc = reinterpret_cast<float2*>(smem);                   // [4 * plane]
     unsigned char* col8 = smem + (size_t)8 * 4 * plane;            // [4 * plane] (readout)
-    // (0, 0) at byte 36 * plane, what padding entries of the unit-weight image read
+    // (0, 0) at byte 36 * plane of each table, what padding entries of the
+    // unit-weight image read
     float2* zero_entry = reinterpret_cast<float2*>(col8 + 4 * plane);
-    double* red = reinterpret_cast<double*>(col8 + 4 * plane + 16);  // [W]
+    double* red = reinterpret_cast<double*>(col8 + 4 * plane + 16 + T1);  // [W]
     double* tstack = red + W;                                                   // tree levels
     // readout state of thread 0: [0] improved flag, [1] best step, [2..3] best H
     int* flag = reinterpret_cast<int*>(tstack + kSliceTreeLevels);
@@ -168,6 +217,13 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
     uint32_t ph[MS][RPL];
     float drift[MS][RPL];
     int sbase[MS], sdeg[MS];
+    // resident rows: the first groups of each row's entries and the lane's own
+    // (sin, cos), held in registers for the whole run
+    constexpr int G16 = 4 / RPL;            // 16-byte groups per row read together
+    constexpr int E = UWT ? 4 : 2;          // edges per group
+    constexpr int NV = RES ? 2 * G16 : 1;   // resident groups per row
+    int4 res[RPL][NV];
+    float2 own_sc[RPL];
 
 #pragma unroll
     for (int k = 0; k < MS; ++k) {
@@ -184,12 +240,32 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
             const uint32_t u = valid ? (pw ? pw[i] : phase_from_theta(th[i])) : 0u;
             ph[k][jj] = u;
             drift[k][jj] = 0.0f;
-            if (slice < S) sc[j * plane + m] = make_float2(sin_turn(u), cos_turn(u));
+            const float2 v = make_float2(sin_turn(u), cos_turn(u));
+            if (slice < S) sc[j * plane + m] = v;
+            if constexpr (RES) own_sc[jj] = v;
         }
+    }
+    const int D16 = UWT ? sdeg[0] >> 2 : sdeg[0] >> 1;  // resident rows: 16-byte groups per row
+    // group h of row jj of the wave's slice
+    auto load_group = [&](int jj, int h) __attribute__((always_inline)) {
+        const int base = UWT ? sbase[0] >> 1 : sbase[0];
+        return load_pair(UWT ? rsrc_uw : rsrc, voff, (base + (j0 + jj) * D16 + h) * 1024);
+    };
+    // what a group past the row's end holds: the zero entry, or with general
+    // weights the row itself at weight 0
+    auto pad_group = [&](int jj) __attribute__((always_inline)) {
+        const int off = UWT ? 36 * plane : 8 * ((j0 + jj) * plane + ws * 64 + lane);
+        return UWT ? make_int4(off, off, off, off) : make_int4(off, 0, off, 0);
+    };
+    if constexpr (RES) {
+#pragma unroll
+        for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+            for (int h = 0; h < NV; ++h) res[jj][h] = h < D16 ? load_group(jj, h) : pad_group(jj);
     }
     if (threadIdx.x == 0) {
         *best_lds = DBL_MAX;
-        *zero_entry = make_float2(0.f, 0.f);
+        zero_entry[0] = zero_entry[T1 / 8] = make_float2(0.f, 0.f);
         flag[1] = -1;
     }
     __syncthreads();
@@ -207,6 +283,122 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
     };
     float cK = sched(a.K, 0), cKs = sched(a.Ks, 0), cS = sched(a.sigma, 0);
     float nK = sched(a.K, 1), nKs = sched(a.Ks, 1), nS = sched(a.sigma, 1);
+
+    // One step of resident rows (see resident_rows): the first NV groups of
+    // every row's entries come from registers, their LDS reads go out at
+    // once, and the Philox noise is computed while they are in flight; the
+    // rest of a long row is streamed, its first loads issued before the
+    // resident groups are used.  Groups are read G16 at a time, those past a
+    // row's end being padding that adds +-0.  Sums, increment and update are
+    // those of the two-phase step below, operation for operation; step s
+    // reads table s % 2 and writes the other, so one barrier per step is
+    // enough.
+    auto resident_step = [&](auto odd, uint32_t t, float kc, float ks, float ns)
+        __attribute__((always_inline)) {
+        constexpr int rd = decltype(odd)::value ? T1 : 0, wr = decltype(odd)::value ? 0 : T1;
+        const int m = ws * 64 + lane;
+        float A[RPL], B[RPL], z[RPL];
+#pragma unroll
+        for (int jj = 0; jj < RPL; ++jj) A[jj] = B[jj] = 0.f;
+        int4 str[RPL][G16];
+        auto stream = [&](int h0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+                for (int h = 0; h < G16; ++h)
+                    str[jj][h] = h == 0 || h0 + h < D16 ? load_group(jj, h0 + h) : pad_group(jj);
+        };
+        uint64_t p[RPL][G16][E];
+        auto read = [&](int jj, int h, const int4& v) __attribute__((always_inline)) {
+            p[jj][h][0] = sc_word(v.x + rd);
+            if constexpr (UWT) {
+                p[jj][h][1] = sc_word(v.y + rd);
+                p[jj][h][2] = sc_word(v.z + rd);
+                p[jj][h][3] = sc_word(v.w + rd);
+            } else {
+                p[jj][h][1] = sc_word(v.z + rd);
+            }
+        };
+        // the reads' results arrive here, not before
+        auto arrive = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+                for (int h = 0; h < G16; ++h)
+#pragma unroll
+                    for (int x = 0; x < E; ++x) asm volatile("" : "+v"(p[jj][h][x]));
+        };
+        auto add = [&](int jj, int h, const int4& v) __attribute__((always_inline)) {
+#pragma unroll
+            for (int x = 0; x < E; ++x) {
+                const float ps = __uint_as_float((uint32_t)p[jj][h][x]);
+                const float pc = __uint_as_float((uint32_t)(p[jj][h][x] >> 32));
+                if constexpr (UWT) {
+                    A[jj] = A[jj] + pc;
+                    B[jj] = B[jj] + ps;
+                } else {
+                    const float w = __int_as_float(x == 0 ? v.y : v.w);
+                    A[jj] = __builtin_fmaf(w, pc, A[jj]);
+                    B[jj] = __builtin_fmaf(w, ps, B[jj]);
+                }
+            }
+        };
+        if (D16 > NV) stream(NV);
+#pragma unroll
+        for (int c = 0; c < NV; c += G16) {
+            if (c > 0 && c >= D16) break;
+#pragma unroll
+            for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+                for (int h = 0; h < G16; ++h) read(jj, h, res[jj][c + h]);
+            if (c == 0) {
+                // (re-materialised and pinned as in the two-phase step)
+                uint32_t mm = (uint32_t)m, kk0 = k0, kk1 = k1;
+                asm volatile("" : "+v"(mm), "+s"(kk0), "+s"(kk1));
+                float zz[4];
+                if constexpr (RPL == 4) normals4(mm, t, (uint32_t)inst_id, kk0, kk1, zz);
+                else normals2(mm, t, (uint32_t)inst_id, kk0, kk1, RPL == 2 ? g : g >> 1, zz);
+#pragma unroll
+                for (int jj = 0; jj < RPL; ++jj) {
+                    z[jj] = RPL > 1 ? zz[jj] : (g & 1) ? zz[1] : zz[0];
+                    asm volatile("" : "+v"(z[jj]));
+                }
+            }
+            arrive();
+#pragma unroll
+            for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+                for (int h = 0; h < G16; ++h) add(jj, h, res[jj][c + h]);
+        }
+        for (int h0 = NV; h0 < D16; h0 += G16) {
+            int4 cur[RPL][G16];
+#pragma unroll
+            for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+                for (int h = 0; h < G16; ++h) {
+                    cur[jj][h] = str[jj][h];
+                    read(jj, h, cur[jj][h]);
+                }
+            if (h0 + G16 < D16) stream(h0 + G16);
+            arrive();
+#pragma unroll
+            for (int jj = 0; jj < RPL; ++jj)
+#pragma unroll
+                for (int h = 0; h < G16; ++h) add(jj, h, cur[jj][h]);
+        }
+#pragma unroll
+        for (int jj = 0; jj < RPL; ++jj) {
+            if constexpr (UWT) {
+                A[jj] = a.w0 * A[jj];
+                B[jj] = a.w0 * B[jj];
+            }
+            const float inc = increment<QM>(own_sc[jj], A[jj], B[jj], ph[0][jj], q, kc, ks, ns, z[jj]);
+            const uint32_t u = advance(ph[0][jj], inc);
+            ph[0][jj] = u;
+            own_sc[jj] = make_float2(sin_turn(u), cos_turn(u));
+            sc[wr / 8 + (j0 + jj) * plane + m] = own_sc[jj];
+        }
+    };
 
     for (int s = 0; s < a.steps; ++s) {
         const uint32_t t = (uint32_t)(a.step0 + s);
@@ -227,6 +419,13 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
         const float ks = -a.dt * Kst * kTurnScale;
         const float ns = St * sqrt_dt * kTurnScale;
 
+        if constexpr (RES) {
+            if (ws < S) {
+                if (s & 1) resident_step(std::true_type{}, t, kc, ks, ns);
+                else resident_step(std::false_type{}, t, kc, ks, ns);
+            }
+            __syncthreads();
+        } else {
         // ---- phase A: noise, and coupling sums over the sliced-ELL rows ----
         // The first edge loads of a slice are issued, then its Philox noise
         // is computed while they are in flight (the noise depends only on
@@ -272,7 +471,6 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
                     // equals the chain of roundings of the negated terms, so
                     // the result is the multiply-add chain's up to the sign
                     // of a zero sum, which no phase update can tell apart.
-                    constexpr int U4 = U / 2;  // 16-byte loads (4 edges) per row per iteration
                     const int D4 = sdeg[k] >> 2;
                     int4 v[RPL][U4];
                     auto load_iter = [&](int e4) __attribute__((always_inline)) {
@@ -375,17 +573,8 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
 #pragma unroll
                 for (int jj = 0; jj < RPL; ++jj) {
                     const float2 own = sc[(j0 + jj) * plane + m];
-                    const float coup = __builtin_fmaf(own.x, A[jj], -(own.y * B[jj]));
-                    // sin(3 theta) = s (3 - 4 s^2) with its multiply-add fused
-                    const float sq = QM == 3 ? own.x * __builtin_fmaf(-4.0f * own.x, own.x, 3.0f)
-                                             : sin_q<QM>(own.x, own.y, ph[k][jj], q);
-                    // the deterministic part of the increment; which of its two
-                    // products is fused keeps the rounding this kernel has
-                    // always had (the SHIL term for q = 2, the coupling term
-                    // otherwise), so results are unchanged bit for bit
-                    const float det = QM == 2 ? __builtin_fmaf(ks, sq, kc * coup)
-                                              : __builtin_fmaf(kc, coup, ks * sq);
-                    drift[k][jj] = __builtin_fmaf(ns, drift[k][jj], det);
+                    drift[k][jj] = increment<QM>(own, A[jj], B[jj], ph[k][jj], q, kc, ks, ns,
+                                                 drift[k][jj]);
                 }
             }
         }
@@ -409,6 +598,7 @@ __global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
             }
         }
         __syncthreads();
+        }
 
         // ---- optional readout: threshold, Eq. 1 / Eq. 2, best-so-far ----
         if (a.M > 0 && ((s + 1) % a.M == 0 || s + 1 == a.steps)) {

@@ -30,8 +30,9 @@ constexpr size_t kLdsLimit = 160 * 1024;
 
 // LDS of a launch; with slice_sums, room for the readout's per-slice sums
 // (slices covered by the variant) too.
-size_t lds_bytes(int plane, int tb, int rpl, int covered = 0) {
+size_t lds_bytes(int plane, int tb, int ms, int rpl, int covered = 0) {
     size_t b = (size_t)8 * 4 * plane;                 // (sin, cos) table
+    if (resident_rows(ms)) b += second_table(tb / 64 * rpl / 4);  // and the second one
     b += (size_t)4 * plane + 16;                      // colours for readout, zero entry
     b += sizeof(double) * (tb / 64 + kSliceTreeLevels) + 32;  // reduction, tree levels, readout state
     if (rpl < 4) b += sizeof(double) * (size_t)tb;    // quads' partial row sums (readout)
@@ -74,25 +75,24 @@ const Variant* fewest_waves(int S, int tb_hint) {
 // working waves per CU, four per SIMD.
 //  - A step's latency is shared by the waves of a workgroup, so while a CU has
 //    few workgroups the rows of a quad are split over waves until sixteen
-//    work: G(200, 0.05) unit weights 1.57 -> 1.03 us per step (256 x 1 with
-//    whole quads -> 1 row per lane), G(800, 0.06) 4.5 -> 3.1 (1024 x 1 x 1),
-//    n = 1500 of degree 10 2.2 -> 2.1 (1024 x 1 x 2), of degree 47 5.4 -> 4.8
-//    (1024 x 2 x 1: long rows take one more split).  A split repeats the quad's
-//    Philox call in each of its waves, so it ends there: with the general
-//    image two waves per slice lose from 7 slices on (n = 2000 of degree 10:
-//    3.2 against 3.5 us).
+//    work: us per step with whole quads on 256 threads and now, one replica,
+//    G(200, 0.05) 1.57 -> 0.85 (256 x 1 with 1 row per lane), G(800, 0.06)
+//    4.5 -> 3.0 (1024 x 1 x 1), n = 2000 of degree 10 2.4 -> 2.2 (1024 x 1 x 2;
+//    real weights 3.0 -> 2.5), n = 1500 of degree 46 5.4 -> 4.7 (1024 x 2 x 1:
+//    long rows take one more split).  A split repeats the quad's Philox call in
+//    each of its waves, so it ends there.
 //  - Instances of more slices take sixteen waves of whole quads: n = 3500 of
-//    degree 10 4.1 -> 3.6 us (1024 x 1), n = 10000 of degree 5 8.6 -> 6.0
+//    degree 10 4.1 -> 3.1 us (1024 x 1), n = 10000 of degree 5 8.6 -> 6.0
 //    (1024 x 3); the general image, which holds more registers, twelve waves of
 //    four slices for 33 to 48 (10.8 -> 9.3, against 9.75 with sixteen).
 //  - Where a CU holds several workgroups each takes its share of the sixteen
 //    waves: 256 colouring graphs of up to 600 oscillators x 8 replicas 3.6 ->
-//    3.0 us (256 -> 128 threads), of up to 250 3.1 -> 1.8 (64); n = 2000, 600
-//    replicas 6.0 -> 5.6 (512 -> 256).  Beyond 16 slices the sixteen waves stay
+//    2.9 us (256 -> 128 threads), of up to 250 3.1 -> 1.8 (64); n = 2000, 600
+//    replicas 6.0 -> 5.4 (512 -> 256).  Beyond 16 slices the sixteen waves stay
 //    (n = 6000, 600 replicas: 11.8 us with 1024 x 2, 15.6 with 512 x 5).
 const Variant* default_variant(const Problem* p, int R) {
     const int S = p->max_slices;
-    const int64_t fit = (int64_t)(kLdsLimit / lds_bytes(S * 64, 64, 4));
+    const int64_t fit = (int64_t)(kLdsLimit / lds_bytes(S * 64, 64, 2, 4));
     const int64_t per_cu = ((int64_t)R * p->n_inst + 255) / 256;
     const int64_t g = S > 16 ? 1 : per_cu < fit ? per_cu : fit;
     const int waves = g >= 16 ? 1 : (int)(16 / (g < 1 ? 1 : g));
@@ -101,7 +101,7 @@ const Variant* default_variant(const Problem* p, int R) {
     const Variant* v = nullptr;
     if (4 * S <= waves) {
         v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
-    } else if (2 * S <= waves && (uw || S <= 6)) {
+    } else if (2 * S <= waves) {
         v = long_rows && S > 4 ? covering(1024, 1, S) : covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
     } else if (uw && long_rows && waves == 16 && S <= 16) {
         v = covering(1024, 2, S);
@@ -115,7 +115,7 @@ const Variant* default_variant(const Problem* p, int R) {
              tb *= 2)
             v = covering(tb, 4, S);
     }
-    return v && lds_bytes(S * 64, v->tb, v->rpl) <= kLdsLimit ? v : fewest_waves(S, 0);
+    return v && lds_bytes(S * 64, v->tb, v->ms, v->rpl) <= kLdsLimit ? v : fewest_waves(S, 0);
 }
 
 int env_int(const char* name, int dflt) {
@@ -132,7 +132,7 @@ const Variant* find_variant(int tb, int ms, int rpl) {
 // The variant covers every slice of the largest instance and its LDS fits.
 bool variant_ok(const Problem* p, const Variant& v) {
     return v.covers() >= p->max_slices &&
-           lds_bytes(p->max_slices * 64, v.tb, v.rpl) <= kLdsLimit;
+           lds_bytes(p->max_slices * 64, v.tb, v.ms, v.rpl) <= kLdsLimit;
 }
 
 int q_class(int q) { return q == 2 ? 1 : q == 3 ? 2 : 0; }
@@ -159,7 +159,7 @@ bool persistent_variant_fits(const Problem* p, int tb, int ms, int rpl) {
 
 bool persistent_sparse_fits(const Problem* p) {
     if (p->dense || p->max_slices == 0) return false;
-    if (lds_bytes(p->max_slices * 64, 1024, 4) > kLdsLimit) return false;
+    if (lds_bytes(p->max_slices * 64, 1024, 5, 4) > kLdsLimit) return false;
     if ((uint64_t)p->sell_entries * 8 > kMaxSellBytes) return false;
     return fewest_waves(p->max_slices, 0) != nullptr;
 }
@@ -211,9 +211,9 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
         fn = kUniformKernels[v - kVariants][qi];
     }
     // the readout keeps per-slice sums in LDS when there is room for them
-    const size_t lds_fast = lds_bytes(plane, v->tb, v->rpl, v->covers());
+    const size_t lds_fast = lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers());
     a.slice_sums = (a.M > 0 && lds_fast <= kLdsLimit) ? 1 : 0;
-    const size_t lds = a.slice_sums ? lds_fast : lds_bytes(plane, v->tb, v->rpl);
+    const size_t lds = a.slice_sums ? lds_fast : lds_bytes(plane, v->tb, v->ms, v->rpl);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, "hipFuncSetAttribute");
