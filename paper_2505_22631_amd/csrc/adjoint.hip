@@ -17,15 +17,26 @@
 // identities cos(a-b) = ca cb + sa sb and sin(a-b) = sa cb - ca sb every sum
 // above is a CSR gather of four per-node values (s, c, s lam, c lam).
 //
-// Forward kernel: one workgroup per (instance, replica), phases in registers
-// (one quad of 4 consecutive oscillators per thread slot), neighbour (s, c)
-// in an LDS ping-pong table; the phase words are checkpointed every C steps
-// into caller memory.  Backward kernel: per segment of C steps (last first) it
-// recomputes the states from the checkpoint (the Philox noise is a pure
-// function of (seed, oscillator, step, instance), so the recomputation is
-// exact), keeps them in device scratch, and runs the adjoint recurrence back
-// through the segment.  Per-step gradient partials are reduced over each wave
-// and summed over waves and workgroups in FP64 in a fixed order.
+// One workgroup per (instance, replica).  The rows of an instance are dealt to
+// the lanes by length, longest first (AdjRows in internal.hpp): the 64 rows a
+// wave walks together have nearly the same length, where consecutive rows are
+// padded to twice the mean (G(2000, 10/1999): mean 10, longest of 256 about
+// 20).  A group of 64 rows is walked two entries per 32-bit word; groups go to
+// the waves back and forth, so every wave has about the same work.  The
+// oscillator at sorted position p of its instance is "slot" p: tables and the
+// buffers between kernels are in slot order, caller arrays in oscillator
+// order.
+//
+// Forward kernel: phases and own (sin, cos) in registers, neighbour (s, c) in
+// an LDS ping-pong table, one barrier per step; the phase words are
+// checkpointed every C steps into caller memory.  The Philox normals of a quad
+// are drawn by one lane a step ahead and handed to the four rows' owners
+// through LDS.  Backward: per segment of C steps (last first) the states are
+// recomputed from the checkpoint (the noise is a pure function of (seed,
+// oscillator, step, instance), so the recomputation is exact) into device
+// scratch, and the adjoint recurrence runs back through them.  Per-step
+// gradient partials are reduced over each wave in FP32 and over waves and
+// workgroups in FP64 in a fixed order.
 #include <float.h>
 
 #include <cmath>
@@ -33,6 +44,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
+#include <vector>
 
 #include "internal.hpp"
 #include "noise.hpp"
@@ -46,20 +58,17 @@ namespace oim {
 
 namespace {
 
-constexpr int kAdjTB = 512;
-constexpr int kAdjWaves = kAdjTB / 64;
-constexpr int kAdjQPT = kAdjMaxN / 4 / kAdjTB;  // quads per thread at the size limit
-constexpr int kCsrGlobal = 0, kCsrLdsUnit = 1, kCsrLds = 2, kEllUnit = 3;
-constexpr int kEllSlices = kAdjMaxN / 4 / 64;  // slices of 64 quads at the size limit
+constexpr int kMaxTB = 1024;
+constexpr int kMaxWaves = kMaxTB / 64;
+constexpr int kMaxRounds = kAdjMaxN / kMaxTB;  // rows per lane at the size limit
 
 struct AdjArgs {
-    const int64_t* row_ptr;
-    const int32_t* col;
-    const float* J;
-    int tabN;              // table length in LDS (largest instance, rounded up to 4)
-    int64_t max_nnz;       // most stored entries of one instance
-    int64_t max_ell;       // most padded row-image entries of one instance (kEllUnit)
+    AdjRows rows;          // device arrays of the sorted rows (internal.hpp)
     const int4* inst;      // per instance: first slice, slices, first oscillator, size
+    int tabN;              // slots of the largest instance (its rows rounded up to 64)
+    int quads;             // quads of the largest instance
+    int noise2;            // 1: two noise buffers (segment kernel)
+    int img_words;         // LDS words of the largest instance's image (LDSI)
     int I, n_total, P;     // instances, oscillators, padded words per replica
     int R, q, steps, C, nseg;
     int64_t step0;
@@ -69,12 +78,12 @@ struct AdjArgs {
     const float* sigma;
     const uint64_t* seeds;
     const float* theta0;   // [R][n_total] radians
-    uint32_t* ckpt;        // [nseg][R][P] phase words
+    uint32_t* ckpt;        // [nseg][R][P] phase words, oscillator order
     float* thetaT;         // [R][n_total] or null
     double* loss;          // [R * I] or null
-    uint32_t* seg;         // [C + 1][R][P] states of one segment (backward)
-    float4* gpart;         // [steps][R * I][kAdjWaves] (backward)
-    float* lam;            // [R][P] adjoint state between segments (backward)
+    uint32_t* seg;         // [C + 1][R][P] states of one segment, slot order (backward)
+    double* gpart;         // [steps][3][R * I] (backward)
+    float* lam;            // [R][P] adjoint state between segments, slot order (backward)
     int cur_seg;           // segment of this launch (backward)
 };
 
@@ -89,10 +98,16 @@ __device__ __forceinline__ float cos_q(float s, float c, uint32_t u, int q) {
     }
 }
 
-// Per-workgroup view of its instance and replica.
+// Per-workgroup view of its instance and replica, and the rows of a lane:
+// round k holds slot slot[k] (group slot / 64), oscillator osc[k] of the
+// instance (nb: no row).
 struct Ctx {
-    int wg, b, r, off, nb, nq, base;
+    int wg, b, r, off, nb, nq, base, ng, rounds;
     uint32_t k0, k1;
+    int grp[kMaxRounds];   // wave-uniform; ng: none
+    int slot[kMaxRounds], osc[kMaxRounds];
+    int pairs[kMaxRounds]; // wave-uniform: 32-bit words per row of the group
+    int first[kMaxRounds]; // wave-uniform: the group's first word (in rows of 64) in the image
 };
 
 __device__ __forceinline__ Ctx make_ctx(const AdjArgs& a) {
@@ -105,432 +120,278 @@ __device__ __forceinline__ Ctx make_ctx(const AdjArgs& a) {
     x.nb = in.w;
     x.nq = (in.w + 3) / 4;
     x.base = in.x * (4 * kSliceQuads);
+    x.ng = (in.w + 63) / 64;
     const uint64_t seed = a.seeds[x.r];
     x.k0 = (uint32_t)seed;
     x.k1 = (uint32_t)(seed >> 32);
+    const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g0 = a.rows.group0[x.b];
+#pragma unroll
+    for (int k = 0; k < kMaxRounds; ++k) {
+        const int g = k * W + ((k & 1) ? W - 1 - wave : wave);
+        x.grp[k] = g < x.ng ? g : x.ng;
+        x.slot[k] = g * 64 + lane;
+        x.osc[k] = x.nb;
+        x.pairs[k] = x.first[k] = 0;
+        if (g < x.ng) {
+            const int2 gd = a.rows.group[g0 + g];
+            x.first[k] = __builtin_amdgcn_readfirstlane(gd.x);
+            x.pairs[k] = __builtin_amdgcn_readfirstlane(gd.y);
+            const int i = a.rows.osc[(g0 + g) * 64 + lane];
+            x.osc[k] = i >= 0 ? i : x.nb;
+        }
+    }
     return x;
 }
 
-// Offset of (slot, replica, local oscillator) in a [slots][R][P] phase array.
-__device__ __forceinline__ size_t slot_index(const AdjArgs& a, const Ctx& x, int slot, int i) {
-    return ((size_t)slot * a.R + x.r) * a.P + x.base + i;
+// Offset of (step slot, replica, local position) in a [steps][R][P] array.
+__device__ __forceinline__ size_t at(const AdjArgs& a, const Ctx& x, int step, int i) {
+    return ((size_t)step * a.R + x.r) * a.P + x.base + i;
 }
 
-// Where a workgroup reads its instance's CSR rows.  CSR_LDS: copies in LDS
-// made at kernel start (row offsets relative to the instance, 16-bit local
-// column indices, and either FP32 weights or, with UNIT, the sign of a
-// unit weight in the index's top bit); otherwise the global CSR through L2.
-// ELL_UNIT (unit weights, forward kernel): the step loop reads a padded row
-// image in LDS (gather_quad_ell); the whole-row sums of the loss use the
-// global CSR.
-template <int MODE>
-struct Rows {
-    static constexpr bool kGlobal = MODE == kCsrGlobal || MODE == kEllUnit;
-    // entry positions: 64-bit in the global CSR, 32-bit in the LDS copy (no
-    // 64-bit compares and adds in the gathers' loops)
-    using Idx = std::conditional_t<kGlobal, int64_t, int32_t>;
-    const AdjArgs* a;
-    int off;
-    const int32_t* rp;    // LDS row offsets [nb + 1]
-    const uint16_t* col;  // LDS column indices
-    const float* w;       // LDS weights (MODE == kCsrLds)
-    // ELL_UNIT: the row image and, per slice of the thread's quads, the
-    // padded row length and the slice's offset in the image (wave-uniform)
-    const uint16_t* ell;
-    int ellD[kAdjQPT], ellBase[kAdjQPT];
-    __device__ __forceinline__ Idx begin(int i) const {
-        if constexpr (kGlobal) return a->row_ptr[off + i];
-        else return rp[i];
-    }
-    __device__ __forceinline__ Idx end(int i) const {
-        if constexpr (kGlobal) return a->row_ptr[off + i + 1];
-        else return rp[i + 1];
-    }
-    __device__ __forceinline__ void edge(Idx e, int& j, float& wt) const {
-        if constexpr (kGlobal) {
-            j = a->col[e] - off;
-            wt = a->J[e];
-        } else if constexpr (MODE == kCsrLdsUnit) {
-            const uint32_t c = col[e];
-            j = (int)(c & 0x7fffu);
-            wt = (c & 0x8000u) ? -1.0f : 1.0f;
-        } else {
-            j = col[e];
-            wt = w[e];
+// Where the rows' entries are read.  An entry is 16 bits: the neighbour's slot
+// and, for unit weights, the sign of the weight in the top bit; two per word,
+// [pair][lane] within a group, padding pointing at the zero entry (slot tabN).
+//   UNIT  weights are +-1 (else FP32 weights are streamed from global memory,
+//         two per lane and pair)
+//   LDSI  the image sits in LDS, else it is streamed through L2
+// The forward kernels of UNIT && LDSI keep a negated copy of the table and
+// entries that point into either, so a term is an add and no sign is decoded.
+template <bool UNIT, bool LDSI>
+struct Image {
+    const uint32_t* idx;  // LDS or global
+    const float2* w;      // global, !UNIT
+    __device__ __forceinline__ uint32_t pair(int e) const { return idx[e * 64]; }
+    __device__ __forceinline__ float2 weight(int e) const { return w[e * 64]; }
+};
+
+__device__ __forceinline__ float sign_weight(uint32_t sign_bit) {
+    return __uint_as_float((sign_bit & 0x80000000u) | 0x3f800000u);
+}
+
+// Row sums over the table entries, `pairs` words of two entries: even entries
+// into one partial sum, odd ones into the other, in order (a padding entry
+// adds +-0 to a partial sum that is never -0), so every placement and
+// grouping gives the same bits.  TERMS = 2: A = sum J c_j, B = sum J s_j from
+// (s, c); TERMS = 4: also Cl, Dl from (s, c, s lam, c lam).  NEG: the table
+// has a negated copy and the entries their final position.
+template <int TERMS, bool NEG, bool UNIT, bool LDSI, class T>
+__device__ __forceinline__ void row_sums(const Image<UNIT, LDSI>& im, const T* tab, int first,
+                                         int pairs, float (&S)[4]) {
+    float s0[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
+    auto batch = [&](int e, auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        uint32_t v[N];
+        float2 w[N];
+        T p[2 * N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            v[k] = im.pair(first + e + k);
+            if constexpr (!UNIT) w[k] = im.weight(first + e + k);
         }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint32_t mask = UNIT && !NEG ? 0x7fffu : 0xffffu;
+            p[2 * k] = tab[v[k] & mask];
+            p[2 * k + 1] = tab[(v[k] >> 16) & mask];
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if constexpr (NEG) {
+                s0[0] = s0[0] + p[2 * k].y;
+                s0[1] = s0[1] + p[2 * k].x;
+                s1[0] = s1[0] + p[2 * k + 1].y;
+                s1[1] = s1[1] + p[2 * k + 1].x;
+            } else {
+                const float w0 = UNIT ? sign_weight(v[k] << 16) : w[k].x;
+                const float w1 = UNIT ? sign_weight(v[k]) : w[k].y;
+                s0[0] = __builtin_fmaf(w0, p[2 * k].y, s0[0]);
+                s0[1] = __builtin_fmaf(w0, p[2 * k].x, s0[1]);
+                s1[0] = __builtin_fmaf(w1, p[2 * k + 1].y, s1[0]);
+                s1[1] = __builtin_fmaf(w1, p[2 * k + 1].x, s1[1]);
+                if constexpr (TERMS == 4) {
+                    s0[2] = __builtin_fmaf(w0, p[2 * k].w, s0[2]);
+                    s0[3] = __builtin_fmaf(w0, p[2 * k].z, s0[3]);
+                    s1[2] = __builtin_fmaf(w1, p[2 * k + 1].w, s1[2]);
+                    s1[3] = __builtin_fmaf(w1, p[2 * k + 1].z, s1[3]);
+                }
+            }
+        }
+    };
+    int e = 0;
+    for (; e + 4 <= pairs; e += 4) batch(e, std::integral_constant<int, 4>{});
+    if (e + 2 <= pairs) {
+        batch(e, std::integral_constant<int, 2>{});
+        e += 2;
+    }
+    if (e < pairs) batch(e, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int t = 0; t < 4; ++t) S[t] = s0[t] + s1[t];
+}
+
+// Dynamic LDS: `tables` (2 tables of T, see the kernels), the noise buffers
+// [2 or 1][4 quads], the image (LDSI).  Copies the instance's image, turning
+// signs into positions in the negated copy of the table (NEG); the caller's
+// first barrier publishes it.
+template <bool UNIT, bool LDSI, bool NEG>
+__device__ __forceinline__ Image<UNIT, LDSI> setup_image(const AdjArgs& a, const Ctx& x,
+                                                         uint32_t* lds) {
+    const int lane = threadIdx.x & 63;
+    const int2 span = a.rows.span[x.b];  // first row of 64 words, rows
+    const uint32_t* src = a.rows.idx + (size_t)span.x * 64;
+    Image<UNIT, LDSI> im;
+    if constexpr (LDSI) {
+        for (int e = threadIdx.x; e < span.y * 64; e += blockDim.x) {
+            uint32_t v = src[e];
+            if constexpr (NEG) {
+                const uint32_t lo = v & 0xffffu, hi = v >> 16;
+                v = ((lo & 0x7fffu) + (lo >> 15) * (a.tabN + 1)) |
+                    (((hi & 0x7fffu) + (hi >> 15) * (a.tabN + 1)) << 16);
+            }
+            lds[e] = v;
+        }
+        im.idx = lds + lane;
+    } else {
+        im.idx = src + lane;
+    }
+    im.w = UNIT ? nullptr : a.rows.w + (size_t)span.x * 64 + lane;
+    return im;
+}
+
+// The normals of step t of every quad, four per quad in oscillator order.
+__device__ __forceinline__ void draw_noise(const AdjArgs& a, const Ctx& x, uint32_t t, float4* noise) {
+    for (int m = threadIdx.x; m < x.nq; m += blockDim.x) {
+        float z[4];
+        normals4((uint32_t)m, t, (uint32_t)x.b, x.k0, x.k1, z);
+        noise[m] = make_float4(z[0], z[1], z[2], z[3]);
+    }
+}
+
+// The schedules, 64 steps at a time in the lanes of every wave (backwards:
+// chunks of the same alignment), so that no step waits on a scalar load.
+struct Sched {
+    float K, Ks, sg;
+    int chunk;
+    __device__ __forceinline__ void load(const AdjArgs& a, int c) {
+        const int i = c * 64 + (int)(threadIdx.x & 63);
+        const bool in = i < a.steps;
+        K = in ? a.K[i] : 0.f;
+        Ks = in ? a.Ks[i] : 0.f;
+        sg = in ? a.sigma[i] : 0.f;
+        chunk = c;
+    }
+    __device__ __forceinline__ static float pick(float v, int s) {
+        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), s & 63));
     }
 };
 
-// Gather over the CSR row of local oscillator i from an LDS table of
-// (s, c, s lam, c lam): A = sum J c_j, B = sum J s_j and, if LAM,
-// Cl = sum J c_j lam_j, Dl = sum J s_j lam_j.
-template <bool LAM, int MODE>
-__device__ __forceinline__ void gather(const Rows<MODE>& g,
-                                       const std::conditional_t<LAM, float4, float2>* tab, int i,
-                                       float& A, float& B, float& Cl, float& Dl) {
-    using Idx = typename Rows<MODE>::Idx;
-    const Idx e0 = g.begin(i), e1 = g.end(i);
-    float A0 = 0.f, B0 = 0.f, C0 = 0.f, D0 = 0.f, A1 = 0.f, B1 = 0.f, C1 = 0.f, D1 = 0.f;
-    Idx e = e0;
-    // eight edges at a time: eight index reads, then eight table reads, in
-    // flight together; edges at even offsets from e0 go to the first partial
-    // sums and odd ones to the second, in order, exactly as in the pairwise
-    // loop below, so the sums do not depend on the unrolling
-    for (; e + 8 <= e1; e += 8) {
-        int jj[8];
-        float ww[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) g.edge(e + k, jj[k], ww[k]);
-        if constexpr (LAM) {
-            float4 pv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) pv[k] = tab[jj[k]];
-#pragma unroll
-            for (int k = 0; k < 8; k += 2) {
-                A0 = __builtin_fmaf(ww[k], pv[k].y, A0);
-                B0 = __builtin_fmaf(ww[k], pv[k].x, B0);
-                C0 = __builtin_fmaf(ww[k], pv[k].w, C0);
-                D0 = __builtin_fmaf(ww[k], pv[k].z, D0);
-                A1 = __builtin_fmaf(ww[k + 1], pv[k + 1].y, A1);
-                B1 = __builtin_fmaf(ww[k + 1], pv[k + 1].x, B1);
-                C1 = __builtin_fmaf(ww[k + 1], pv[k + 1].w, C1);
-                D1 = __builtin_fmaf(ww[k + 1], pv[k + 1].z, D1);
-            }
-        } else {
-            float2 pv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) pv[k] = tab[jj[k]];
-#pragma unroll
-            for (int k = 0; k < 8; k += 2) {
-                A0 = __builtin_fmaf(ww[k], pv[k].y, A0);
-                B0 = __builtin_fmaf(ww[k], pv[k].x, B0);
-                A1 = __builtin_fmaf(ww[k + 1], pv[k + 1].y, A1);
-                B1 = __builtin_fmaf(ww[k + 1], pv[k + 1].x, B1);
-            }
-        }
-    }
-    for (; e + 2 <= e1; e += 2) {
-        int j0, j1;
-        float w0, w1;
-        g.edge(e, j0, w0);
-        g.edge(e + 1, j1, w1);
-        if constexpr (LAM) {
-            const float4 p0 = tab[j0], p1 = tab[j1];
-            A0 = __builtin_fmaf(w0, p0.y, A0);
-            B0 = __builtin_fmaf(w0, p0.x, B0);
-            C0 = __builtin_fmaf(w0, p0.w, C0);
-            D0 = __builtin_fmaf(w0, p0.z, D0);
-            A1 = __builtin_fmaf(w1, p1.y, A1);
-            B1 = __builtin_fmaf(w1, p1.x, B1);
-            C1 = __builtin_fmaf(w1, p1.w, C1);
-            D1 = __builtin_fmaf(w1, p1.z, D1);
-        } else {
-            const float2 p0 = tab[j0];
-            const float2 p1 = tab[j1];
-            A0 = __builtin_fmaf(w0, p0.y, A0);
-            B0 = __builtin_fmaf(w0, p0.x, B0);
-            A1 = __builtin_fmaf(w1, p1.y, A1);
-            B1 = __builtin_fmaf(w1, p1.x, B1);
-        }
-    }
-    if (e < e1) {
-        int j0;
-        float w0;
-        g.edge(e, j0, w0);
-        if constexpr (LAM) {
-            const float4 p0 = tab[j0];
-            A0 = __builtin_fmaf(w0, p0.y, A0);
-            B0 = __builtin_fmaf(w0, p0.x, B0);
-            C0 = __builtin_fmaf(w0, p0.w, C0);
-            D0 = __builtin_fmaf(w0, p0.z, D0);
-        } else {
-            const float2 p0 = tab[j0];
-            A0 = __builtin_fmaf(w0, p0.y, A0);
-            B0 = __builtin_fmaf(w0, p0.x, B0);
-        }
-    }
-    A = A0 + A1;
-    B = B0 + B1;
-    Cl = C0 + C1;
-    Dl = D0 + D1;
-}
-
-// Forward sums (A, B of gather) for the four rows of quad k of the thread from
-// the ELL row image: the slice's rows are padded to one length D (a multiple
-// of 4; pads point at the tables' zero entry), entry e of row j of the lane's
-// quad at u16 offset base + ((j D/4 + e/4) 64 + lane) 4 + e % 4, so each
-// 8-byte read brings four consecutive entries of one row and the loop length
-// is the same for the whole wave.  Per row the partial sums take the even and
-// the odd entries in order, exactly as gather does, and a pad adds +-0 to a
-// partial sum that is never -0: the results are the same bits.
-__device__ __forceinline__ void gather_quad_ell(const Rows<kEllUnit>& g, const float2* tab, int k,
-                                                int lane, float (&A)[4], float (&B)[4]) {
-    const int D4 = g.ellD[k] >> 2;
-    const uint2* img = reinterpret_cast<const uint2*>(g.ell + g.ellBase[k]) + lane;
-    float a0[4], b0[4], a1[4], b1[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) a0[j] = b0[j] = a1[j] = b1[j] = 0.f;
-    for (int gi = 0; gi < D4; ++gi) {
-        uint2 v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = img[(j * D4 + gi) * 64];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t word = t < 2 ? v[j].x : v[j].y;
-                const uint32_t c = (t & 1) ? word >> 16 : word & 0xffffu;
-                const float wt = (c & 0x8000u) ? -1.0f : 1.0f;
-                const float2 p = tab[c & 0x7fffu];
-                if (t & 1) {
-                    a1[j] = __builtin_fmaf(wt, p.y, a1[j]);
-                    b1[j] = __builtin_fmaf(wt, p.x, b1[j]);
-                } else {
-                    a0[j] = __builtin_fmaf(wt, p.y, a0[j]);
-                    b0[j] = __builtin_fmaf(wt, p.x, b0[j]);
-                }
-            }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        A[j] = a0[j] + a1[j];
-        B[j] = b0[j] + b1[j];
-    }
-}
-
-// Writes (s, c) of the thread's oscillators into a table.
-__device__ __forceinline__ void put_sc(const Ctx& x, float2* tab, const uint32_t (&u)[kAdjQPT][4]) {
-#pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k) {
-        const int m = threadIdx.x + k * kAdjTB;
-        if (m >= x.nq) break;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            tab[4 * m + j] = make_float2(sin_turn(u[k][j]), cos_turn(u[k][j]));
-    }
-}
-
-// One synchronous Euler-Maruyama step of the thread's oscillators reading
-// neighbour (s, c) from tin and writing the new (s, c) into tout.
-template <int QM, int MODE>
-__device__ __forceinline__ void fwd_step(const AdjArgs& a, const Ctx& x, const Rows<MODE>& g, int s,
-                                         const float2* tin, float2* tout,
-                                         uint32_t (&u)[kAdjQPT][4]) {
+// The forward steps t0 .. t1 - 1 from the words u: body(s) sees the state
+// before step s, in registers and in tab(parity).  Leaves the state at t1 in
+// u, sc and tab(returned parity).
+template <int QM, bool UNIT, bool LDSI, class Body>
+__device__ __forceinline__ int forward_steps(const AdjArgs& a, const Ctx& x,
+                                             const Image<UNIT, LDSI>& im, float2* tabs, int stride,
+                                             float4* noise, int t0, int t1, uint32_t (&u)[kMaxRounds],
+                                             float2 (&sc)[kMaxRounds], Body body) {
+    constexpr bool NEG = UNIT && LDSI;
     const int q = QM ? QM : a.q;
-    const uint32_t t = (uint32_t)(a.step0 + s);
-    const float kc = -a.dt * a.K[s] * kTurnScale;
-    const float ks = -a.dt * a.Ks[s] * kTurnScale;
-    const float ns = a.sigma[s] * __builtin_sqrtf(a.dt) * kTurnScale;
+    const float sqrt_dt = __builtin_sqrtf(a.dt);
+    auto put = [&](int p, int k) __attribute__((always_inline)) {
+        float2* t = tabs + p * stride;
+        t[x.slot[k]] = sc[k];
+        if constexpr (NEG) t[x.slot[k] + a.tabN + 1] = make_float2(-sc[k].x, -sc[k].y);
+    };
 #pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k) {
-        const int m = threadIdx.x + k * kAdjTB;
-        if (m >= x.nq) break;
-        float z[4];
-        normals4((uint32_t)m, t, (uint32_t)x.b, x.k0, x.k1, z);
-        float Aq[4], Bq[4];
-        if constexpr (MODE == kEllUnit) gather_quad_ell(g, tin, k, threadIdx.x & 63, Aq, Bq);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = 4 * m + j;
-            if (i >= x.nb) break;
-            float A, B, Cl, Dl;
-            if constexpr (MODE == kEllUnit) {
-                A = Aq[j];
-                B = Bq[j];
-            } else {
-                gather<false>(g, tin, i, A, B, Cl, Dl);
-            }
-            const float si = sin_turn(u[k][j]), ci = cos_turn(u[k][j]);
-            const float coup = __builtin_fmaf(si, A, -(ci * B));
-            const float drift = __builtin_fmaf(kc, coup, ks * sin_q<QM>(si, ci, u[k][j], q));
-            u[k][j] = advance(u[k][j], __builtin_fmaf(ns, z[j], drift));
+    for (int k = 0; k < kMaxRounds; ++k)
+        if (x.grp[k] < x.ng) {
+            sc[k] = make_float2(sin_turn(u[k]), cos_turn(u[k]));
+            put(0, k);
         }
-    }
-    put_sc(x, tout, u);
-}
-
-__device__ __forceinline__ void load_words(const AdjArgs& a, const Ctx& x, const uint32_t* src,
-                                           int slot, uint32_t (&u)[kAdjQPT][4]) {
-#pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k) {
-        const int m = threadIdx.x + k * kAdjTB;
-        if (m >= x.nq) break;
-        const uint4 v = *reinterpret_cast<const uint4*>(src + slot_index(a, x, slot, 4 * m));
-        u[k][0] = v.x;
-        u[k][1] = v.y;
-        u[k][2] = v.z;
-        u[k][3] = v.w;
-    }
-}
-
-__device__ __forceinline__ void store_words(const AdjArgs& a, const Ctx& x, uint32_t* dst, int slot,
-                                            const uint32_t (&u)[kAdjQPT][4]) {
-#pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k) {
-        const int m = threadIdx.x + k * kAdjTB;
-        if (m >= x.nq) break;
-        *reinterpret_cast<uint4*>(dst + slot_index(a, x, slot, 4 * m)) =
-            uint4{u[k][0], u[k][1], u[k][2], u[k][3]};
-    }
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// The same two tables as (s, c) alone, 8 bytes per oscillator from the start
-// of each table's space: the forward steps read only (s, c), and at an
-// 8-byte stride a gather's random reads spread over all LDS banks (at the
-// 16-byte stride of the full entries, over half of them).  Entry tabN of
-// each stays zero (padding of the row image points there); the full entries
-// it overlaps are written before the backward reads them.
-__device__ __forceinline__ float2* tab2_of(unsigned char* smem, int tabN, int k) {
-    return reinterpret_cast<float2*>(smem) + (size_t)k * 2 * (tabN + 1);
-}
-
-// Dynamic LDS: two tables of tabN + 1 float4 (entry tabN of each stays zero),
-// then (CSR in LDS) the instance's row offsets, 16-bit column indices and FP32
-// weights, or (ELL_UNIT) per-slice lengths and the padded row image.  Fills
-// the row copy; the caller's first barrier publishes it.
-template <int MODE>
-__device__ __forceinline__ Rows<MODE> setup_rows(const AdjArgs& a, const Ctx& x, unsigned char* smem) {
-    Rows<MODE> g;
-    g.a = &a;
-    g.off = x.off;
-    float4* tabs = reinterpret_cast<float4*>(smem);
-    if (threadIdx.x < 2) {
-        tabs[(size_t)threadIdx.x * (a.tabN + 1) + a.tabN] = make_float4(0.f, 0.f, 0.f, 0.f);
-        tab2_of(smem, a.tabN, threadIdx.x)[a.tabN] = make_float2(0.f, 0.f);
-    }
-    unsigned char* p = smem + (size_t)32 * (a.tabN + 1);
-    if constexpr (MODE == kEllUnit) {
-        // slice s holds quads 64 s .. 64 s + 63, i.e. the quads of wave
-        // s % 8 for k = s / 8 (thread t owns quad t + k kAdjTB)
-        int* lenD = reinterpret_cast<int*>(p);
-        g.ell = reinterpret_cast<const uint16_t*>(p + 16 * kEllSlices);
-        uint16_t* img = reinterpret_cast<uint16_t*>(p + 16 * kEllSlices);
-        const int lane = threadIdx.x & 63;
-        int deg[kAdjQPT][4];
-        int64_t rb[kAdjQPT][4];
-#pragma unroll
-        for (int k = 0; k < kAdjQPT; ++k) {
-            const int m = threadIdx.x + k * kAdjTB;
-            int dmax = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = 4 * m + j;
-                rb[k][j] = i < x.nb ? a.row_ptr[x.off + i] : 0;
-                deg[k][j] = i < x.nb ? (int)(a.row_ptr[x.off + i + 1] - rb[k][j]) : 0;
-                dmax = deg[k][j] > dmax ? deg[k][j] : dmax;
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const int other = __shfl_xor(dmax, o, 64);
-                dmax = other > dmax ? other : dmax;
-            }
-            const int s = m >> 6;
-            if (lane == 0 && s < kEllSlices) lenD[s] = (dmax + 3) & ~3;
-        }
-        __syncthreads();
-        const int nsl = (x.nq + 63) >> 6;
-#pragma unroll
-        for (int k = 0; k < kAdjQPT; ++k) {
-            const int s = (int)((threadIdx.x + k * kAdjTB) >> 6);
-            int base = 0;
-            for (int s2 = 0; s2 < s && s2 < nsl; ++s2) base += 256 * lenD[s2];
-            const int D = s < nsl ? lenD[s] : 0;
-            g.ellD[k] = __builtin_amdgcn_readfirstlane(D);
-            g.ellBase[k] = __builtin_amdgcn_readfirstlane(base);
-            const int m = threadIdx.x + k * kAdjTB;
-            if (m >= x.nq) continue;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                for (int e = 0; e < D; ++e) {
-                    uint16_t v = (uint16_t)a.tabN;  // pad: the zero entry
-                    if (e < deg[k][j]) {
-                        const int64_t ge = rb[k][j] + e;
-                        const uint32_t c = (uint32_t)(a.col[ge] - x.off);
-                        v = (uint16_t)(c | (a.J[ge] < 0.0f ? 0x8000u : 0u));
-                    }
-                    img[base + ((j * (D >> 2) + (e >> 2)) * 64 + lane) * 4 + (e & 3)] = v;
-                }
-        }
-        return g;
-    }
-    g.rp = reinterpret_cast<const int32_t*>(p);
-    int32_t* rp = reinterpret_cast<int32_t*>(p);
-    p += ((size_t)4 * (a.tabN + 1) + 15) & ~(size_t)15;
-    uint16_t* col = reinterpret_cast<uint16_t*>(p);
-    g.col = col;
-    p += ((size_t)2 * a.max_nnz + 15) & ~(size_t)15;
-    float* w = reinterpret_cast<float*>(p);
-    g.w = w;
-    if constexpr (MODE != kCsrGlobal) {
-        const int64_t e0 = a.row_ptr[x.off];
-        const int64_t ne = a.row_ptr[x.off + x.nb] - e0;
-        for (int i = threadIdx.x; i <= x.nb; i += kAdjTB)
-            rp[i] = (int32_t)(a.row_ptr[x.off + i] - e0);
-        for (int64_t e = threadIdx.x; e < ne; e += kAdjTB) {
-            const uint32_t c = (uint32_t)(a.col[e0 + e] - x.off);
-            const float wt = a.J[e0 + e];
-            if constexpr (MODE == kCsrLdsUnit) {
-                col[e] = (uint16_t)(c | (wt < 0.0f ? 0x8000u : 0u));
-            } else {
-                col[e] = (uint16_t)c;
-                w[e] = wt;
-            }
-        }
-    }
-    return g;
-}
-
-template <int QM, int MODE>
-__global__ __launch_bounds__(kAdjTB) void adjoint_forward_kernel(AdjArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[kAdjWaves];
-    const Ctx x = make_ctx(a);
-    const Rows<MODE> g = setup_rows<MODE>(a, x, smem);
-    auto tab = [&](int k) { return tab2_of(smem, a.tabN, k); };
-    uint32_t u[kAdjQPT][4];
-#pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = 4 * (threadIdx.x + k * kAdjTB) + j;
-            u[k][j] = i < x.nb ? phase_from_theta(a.theta0[(size_t)x.r * a.n_total + x.off + i]) : 0u;
-        }
-    put_sc(x, tab(0), u);
+    if (t0 < t1) draw_noise(a, x, (uint32_t)(a.step0 + t0), noise);
+    Sched sch;
+    sch.load(a, t0 >> 6);
     __syncthreads();
-    for (int s = 0; s < a.steps; ++s) {
-        if (s % a.C == 0) store_words(a, x, a.ckpt, s / a.C, u);
-        fwd_step<QM>(a, x, g, s, tab(s & 1), tab((s + 1) & 1), u);
+    int p = 0;
+    for (int s = t0; s < t1; ++s) {
+        if ((s >> 6) != sch.chunk) sch.load(a, s >> 6);
+        body(s);
+        const float kc = -a.dt * Sched::pick(sch.K, s) * kTurnScale;
+        const float ks = -a.dt * Sched::pick(sch.Ks, s) * kTurnScale;
+        const float ns = Sched::pick(sch.sg, s) * sqrt_dt * kTurnScale;
+        const float* z = reinterpret_cast<const float*>(noise + p * a.quads);
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k) {
+            if (x.grp[k] >= x.ng) break;
+            const float zk = z[x.osc[k] < x.nb ? x.osc[k] : 0];
+            float S[4];
+            row_sums<2, NEG>(im, tabs + p * stride, x.first[k], x.pairs[k], S);
+            const float si = sc[k].x, ci = sc[k].y;
+            const float coup = __builtin_fmaf(si, S[0], -(ci * S[1]));
+            const float drift = __builtin_fmaf(kc, coup, ks * sin_q<QM>(si, ci, u[k], q));
+            u[k] = advance(u[k], __builtin_fmaf(ns, zk, drift));
+            sc[k] = make_float2(sin_turn(u[k]), cos_turn(u[k]));
+            put(p ^ 1, k);
+        }
+        if (s + 1 < t1) draw_noise(a, x, (uint32_t)(a.step0 + s + 1), noise + (p ^ 1) * a.quads);
+        p ^= 1;
         __syncthreads();
     }
+    return p;
+}
+
+// LDS of the forward kernels: the tables [2][stride] of (s, c), stride =
+// tabN + 1 entries, twice that with the negated copies; then noise, image.
+template <bool UNIT, bool LDSI>
+struct ForwardLds {
+    float2* tabs;
+    int stride;
+    float4* noise;
+    uint32_t* img;
+    __device__ __forceinline__ ForwardLds(const AdjArgs& a, unsigned char* smem) {
+        stride = (a.tabN + 1) * (UNIT && LDSI ? 2 : 1);
+        tabs = reinterpret_cast<float2*>(smem);
+        noise = reinterpret_cast<float4*>(smem + (((size_t)2 * stride * sizeof(float2) + 15) & ~(size_t)15));
+        img = reinterpret_cast<uint32_t*>(noise + 2 * a.quads);
+        if (threadIdx.x < 4 && (UNIT && LDSI || threadIdx.x < 2))  // the zero entries
+            tabs[(threadIdx.x & 1) * stride + (threadIdx.x >> 1) * (a.tabN + 1) + a.tabN] =
+                make_float2(0.f, 0.f);
+    }
+};
+
+template <int QM, bool UNIT, bool LDSI>
+__global__ __launch_bounds__(kMaxTB) void adjoint_forward_kernel(AdjArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[kMaxWaves];
+    const Ctx x = make_ctx(a);
+    const ForwardLds<UNIT, LDSI> l(a, smem);
+    const Image<UNIT, LDSI> im = setup_image<UNIT, LDSI, UNIT && LDSI>(a, x, l.img);
+    uint32_t u[kMaxRounds];
+    float2 sc[kMaxRounds];
+#pragma unroll
+    for (int k = 0; k < kMaxRounds; ++k)
+        u[k] = x.osc[k] < x.nb
+                   ? phase_from_theta(a.theta0[(size_t)x.r * a.n_total + x.off + x.osc[k]])
+                   : 0u;
+    const int p = forward_steps<QM>(a, x, im, l.tabs, l.stride, l.noise, 0, a.steps, u, sc, [&](int s) {
+        if (s % a.C) return;
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k)
+            if (x.osc[k] < x.nb) a.ckpt[at(a, x, s / a.C, x.osc[k])] = u[k];
+    });
     // relaxed cut of the final phases: sum_i (c_i A_i + s_i B_i - sum_j J_ij) / 4
-    const float2* fin = tab(a.steps & 1);
+    const float2* fin = l.tabs + p * l.stride;
     double part = 0.0;
 #pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k) {
-        const int m = threadIdx.x + k * kAdjTB;
-        if (m >= x.nq) break;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = 4 * m + j;
-            if (i >= x.nb) break;
-            float A, B, Cl, Dl;
-            gather<false>(g, fin, i, A, B, Cl, Dl);
-            double rs = 0.0;
-            for (int64_t e = g.begin(i); e < g.end(i); ++e) {
-                int j;
-                float wt;
-                g.edge(e, j, wt);
-                rs += (double)wt;
-            }
-            const float si = sin_turn(u[k][j]), ci = cos_turn(u[k][j]);
-            part += 0.25 * ((double)ci * A + (double)si * B - rs);
-            if (a.thetaT) a.thetaT[(size_t)x.r * a.n_total + x.off + i] = theta_from_phase(u[k][j]);
+    for (int k = 0; k < kMaxRounds; ++k) {
+        if (x.grp[k] >= x.ng) break;
+        float S[4];
+        row_sums<2, UNIT && LDSI>(im, fin, x.first[k], x.pairs[k], S);
+        if (x.osc[k] < x.nb) {
+            const double rs = a.rows.row_sum[x.off + x.osc[k]];
+            part += 0.25 * ((double)sc[k].y * S[0] + (double)sc[k].x * S[1] - rs);
+            if (a.thetaT)
+                a.thetaT[(size_t)x.r * a.n_total + x.off + x.osc[k]] = theta_from_phase(u[k]);
         }
     }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
@@ -538,7 +399,7 @@ __global__ __launch_bounds__(kAdjTB) void adjoint_forward_kernel(AdjArgs a) {
     __syncthreads();
     if (threadIdx.x == 0 && a.loss) {
         double tot = 0.0;
-        for (int w = 0; w < kAdjWaves; ++w) tot += red[w];
+        for (int w = 0; w < (int)blockDim.x / 64; ++w) tot += red[w];
         a.loss[x.wg] = tot;
     }
 }
@@ -548,249 +409,281 @@ __global__ __launch_bounds__(kAdjTB) void adjoint_forward_kernel(AdjArgs a) {
 // adjoint of the next (later) one, each kernel on its own half of the CUs.
 //
 // Recompute: the segment's states from its checkpoint, written to a.seg
-// (slot s - t0 holds the state at step s; the last segment also computes its
-// final step and stores the state at t1 in slot t1 - t0).  The Philox noise is
-// a pure function of (seed, oscillator, step, instance) and every placement
-// of the rows gives the same bits, so these are the forward pass's states.
-template <int QM, int MODE>
-__global__ __launch_bounds__(kAdjTB) void adjoint_recompute_kernel(AdjArgs a) {
+// (step slot s - t0 holds the state at step s; the last segment also computes
+// its final step and stores the state at t1 in step slot t1 - t0).  The
+// Philox noise is a pure function of (seed, oscillator, step, instance) and
+// every placement of the rows gives the same bits, so these are the forward
+// pass's states.
+template <int QM, bool UNIT, bool LDSI>
+__global__ __launch_bounds__(kMaxTB) void adjoint_recompute_kernel(AdjArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Ctx x = make_ctx(a);
-    const Rows<MODE> g = setup_rows<MODE>(a, x, smem);
-    auto tab = [&](int k) { return tab2_of(smem, a.tabN, k); };
+    const ForwardLds<UNIT, LDSI> l(a, smem);
+    const Image<UNIT, LDSI> im = setup_image<UNIT, LDSI, UNIT && LDSI>(a, x, l.img);
     const int sg = a.cur_seg;
     const int t0 = sg * a.C;
     const int t1 = t0 + a.C < a.steps ? t0 + a.C : a.steps;
     const bool last = sg == a.nseg - 1;
-    uint32_t u[kAdjQPT][4];
-    load_words(a, x, a.ckpt, sg, u);
-    put_sc(x, tab(0), u);
-    __syncthreads();
-    int p = 0;
-    for (int s = t0; s < t1; ++s) {
-        store_words(a, x, a.seg, s - t0, u);
-        if (s + 1 < t1 || last) {
-            fwd_step<QM>(a, x, g, s, tab(p), tab(p ^ 1), u);
-            p ^= 1;
-            __syncthreads();
-        }
-    }
-    if (last) store_words(a, x, a.seg, t1 - t0, u);
+    uint32_t u[kMaxRounds];
+    float2 sc[kMaxRounds];
+#pragma unroll
+    for (int k = 0; k < kMaxRounds; ++k)
+        u[k] = x.osc[k] < x.nb ? a.ckpt[at(a, x, sg, x.osc[k])] : 0u;
+    auto store = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k)
+            if (x.grp[k] < x.ng) a.seg[at(a, x, s - t0, x.slot[k])] = u[k];
+    };
+    // the state at t1 - 1 needs t1 - 1 steps, the last segment's end one more
+    forward_steps<QM>(a, x, im, l.tabs, l.stride, l.noise, t0, last ? t1 : t1 - 1, u, sc, store);
+    store(last ? t1 : t1 - 1);
+}
+
+// v plus the value a DPP move brings (0 where it brings none).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float add_dpp(float v) {
+    return v + __int_as_float(
+                   __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+
+// Sum over the wave by DPP adds (no LDS traffic); valid in lane 63.
+__device__ __forceinline__ float wave_sum63(float v) {
+    v = add_dpp<0x111, 0xf>(v);  // row_shr:1
+    v = add_dpp<0x112, 0xf>(v);  // row_shr:2
+    v = add_dpp<0x114, 0xf>(v);  // row_shr:4
+    v = add_dpp<0x118, 0xf>(v);  // row_shr:8
+    v = add_dpp<0x142, 0xa>(v);  // row_bcast:15
+    return add_dpp<0x143, 0xc>(v);  // row_bcast:31
 }
 
 // Adjoint: the recurrence back through the segment's stored states, from the
 // adjoint state left by the later segment in a.lam (or, for the last
 // segment, lam_T from the final phases); the adjoint state at t0 goes back
-// to a.lam.  Per-step gradient partials per wave go to a.gpart.
-template <int QM, int MODE>
-__global__ __launch_bounds__(kAdjTB) void adjoint_segment_kernel(AdjArgs a) {
+// to a.lam.  Per-step gradient partials of the workgroup go to a.gpart.
+template <int QM, bool UNIT, bool LDSI>
+__global__ __launch_bounds__(kMaxTB) void adjoint_segment_kernel(AdjArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ float red[2][3][kMaxWaves];
     const Ctx x = make_ctx(a);
-    const Rows<MODE> g = setup_rows<MODE>(a, x, smem);
     float4* const tabs = reinterpret_cast<float4*>(smem);
-    auto tab = [&](int k) { return tabs + (size_t)k * (a.tabN + 1); };
+    float4* const noise = tabs + 2 * (a.tabN + 1);
+    const Image<UNIT, LDSI> im = setup_image<UNIT, LDSI, false>(
+        a, x, reinterpret_cast<uint32_t*>(noise + (a.noise2 ? 2 : 1) * a.quads));
+    if (threadIdx.x < 2) tabs[threadIdx.x * (a.tabN + 1) + a.tabN] = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto tab = [&](int p) { return tabs + (size_t)p * (a.tabN + 1); };
     const int q = QM ? QM : a.q;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
     const int nwg = a.R * a.I;
     const float sqrt_dt = __builtin_sqrtf(a.dt);
     const int sg = a.cur_seg;
     const int t0 = sg * a.C;
     const int t1 = t0 + a.C < a.steps ? t0 + a.C : a.steps;
-    uint32_t u[kAdjQPT][4];
-    float lam[kAdjQPT][4];
+    uint32_t u[kMaxRounds], un[kMaxRounds];
+    float lam[kMaxRounds];
+    auto load_words = [&](int step) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k)
+            un[k] = x.grp[k] < x.ng ? a.seg[at(a, x, step, x.slot[k])] : 0u;
+    };
     int p = 0;  // table written next
     if (sg == a.nseg - 1) {
         // lam_T from the final phases
-        load_words(a, x, a.seg, t1 - t0, u);
-        put_sc(x, tab2_of(smem, a.tabN, p), u);
+        load_words(t1 - t0);
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k)
+            if (x.grp[k] < x.ng)
+                tab(0)[x.slot[k]] = make_float4(sin_turn(un[k]), cos_turn(un[k]), 0.f, 0.f);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kAdjQPT; ++k) {
-            const int m = threadIdx.x + k * kAdjTB;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = 4 * m + j;
-                lam[k][j] = 0.f;
-                if (m >= x.nq || i >= x.nb) continue;
-                float A, B, Cl, Dl;
-                gather<false>(g, tab2_of(smem, a.tabN, p), i, A, B, Cl, Dl);
-                const float si = sin_turn(u[k][j]), ci = cos_turn(u[k][j]);
-                lam[k][j] = -0.5f * (si * A - ci * B);
-            }
+        for (int k = 0; k < kMaxRounds; ++k) {
+            lam[k] = 0.f;
+            if (x.grp[k] >= x.ng) continue;
+            float S[4];
+            row_sums<4, false>(im, tab(0), x.first[k], x.pairs[k], S);
+            const float si = sin_turn(un[k]), ci = cos_turn(un[k]);
+            if (x.osc[k] < x.nb) lam[k] = -0.5f * (si * S[0] - ci * S[1]);
         }
-        p ^= 1;
+        p = 1;
     } else {
 #pragma unroll
-        for (int k = 0; k < kAdjQPT; ++k) {
-            const int m = threadIdx.x + k * kAdjTB;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) lam[k][j] = 0.f;
-            if (m >= x.nq) continue;
-            const float4 v = *reinterpret_cast<const float4*>(a.lam + slot_index(a, x, 0, 4 * m));
-            lam[k][0] = v.x;
-            lam[k][1] = v.y;
-            lam[k][2] = v.z;
-            lam[k][3] = v.w;
-        }
+        for (int k = 0; k < kMaxRounds; ++k)
+            lam[k] = x.grp[k] < x.ng ? a.lam[at(a, x, 0, x.slot[k])] : 0.f;
     }
+    load_words(t1 - 1 - t0);
+    Sched sch;
+    sch.load(a, (t1 - 1) >> 6);
     for (int s = t1 - 1; s >= t0; --s) {
-        load_words(a, x, a.seg, s - t0, u);
-        const uint32_t t = (uint32_t)(a.step0 + s);
+        if ((s >> 6) != sch.chunk) sch.load(a, s >> 6);
+        float2 sc[kMaxRounds];
 #pragma unroll
-        for (int k = 0; k < kAdjQPT; ++k) {
-            const int m = threadIdx.x + k * kAdjTB;
-            if (m >= x.nq) break;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float si = sin_turn(u[k][j]), ci = cos_turn(u[k][j]);
-                tab(p)[4 * m + j] = make_float4(si, ci, si * lam[k][j], ci * lam[k][j]);
-            }
+        for (int k = 0; k < kMaxRounds; ++k) {
+            u[k] = un[k];
+            if (x.grp[k] >= x.ng) continue;
+            sc[k] = make_float2(sin_turn(u[k]), cos_turn(u[k]));
+            tab(p)[x.slot[k]] = make_float4(sc[k].x, sc[k].y, sc[k].x * lam[k], sc[k].y * lam[k]);
         }
+        if (s > t0) load_words(s - 1 - t0);  // their latency under this step
+        float4* nz = noise + (a.noise2 ? p * a.quads : 0);
+        draw_noise(a, x, (uint32_t)(a.step0 + s), nz);
         __syncthreads();
-        const float Kt = a.K[s], Kst = a.Ks[s];
-        float gk = 0.f, gks = 0.f, gs = 0.f;
-#pragma unroll
-        for (int k = 0; k < kAdjQPT; ++k) {
-            const int m = threadIdx.x + k * kAdjTB;
-            if (m >= x.nq) break;
-            float z[4];
-            normals4((uint32_t)m, t, (uint32_t)x.b, x.k0, x.k1, z);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = 4 * m + j;
-                if (i >= x.nb) break;
-                float A, B, Cl, Dl;
-                gather<true>(g, tab(p), i, A, B, Cl, Dl);
-                const float si = sin_turn(u[k][j]), ci = cos_turn(u[k][j]);
-                const float l = lam[k][j];
-                const float csin = si * A - ci * B;
-                const float ccos = ci * Cl + si * Dl - l * (ci * A + si * B);
-                gk = __builtin_fmaf(l, csin, gk);
-                gks = __builtin_fmaf(l, sin_q<QM>(si, ci, u[k][j], q), gks);
-                gs = __builtin_fmaf(l, z[j], gs);
-                lam[k][j] = l + a.dt * (Kt * ccos - (float)q * Kst * cos_q<QM>(si, ci, u[k][j], q) * l);
+        // the previous step's wave partials: FP64, waves in order
+        auto flush = [&](int step, int buf) __attribute__((always_inline)) {
+            if (threadIdx.x < 3) {
+                double g = 0.0;
+                for (int w = 0; w < W; ++w) g += (double)red[buf][threadIdx.x][w];
+                a.gpart[((size_t)step * 3 + threadIdx.x) * nwg + x.wg] = g;
             }
+        };
+        if (s + 1 < t1) flush(s + 1, p ^ 1);
+        const float Kt = Sched::pick(sch.K, s), Kst = Sched::pick(sch.Ks, s);
+        float gk = 0.f, gks = 0.f, gs = 0.f;
+        const float* z = reinterpret_cast<const float*>(nz);
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k) {
+            if (x.grp[k] >= x.ng) break;
+            const float zk = z[x.osc[k] < x.nb ? x.osc[k] : 0];
+            float S[4];
+            row_sums<4, false>(im, tab(p), x.first[k], x.pairs[k], S);
+            const float si = sc[k].x, ci = sc[k].y;
+            const float l = lam[k];  // 0 past the instance's rows, and stays 0
+            const float csin = si * S[0] - ci * S[1];
+            const float ccos = ci * S[2] + si * S[3] - l * (ci * S[0] + si * S[1]);
+            gk = __builtin_fmaf(l, csin, gk);
+            gks = __builtin_fmaf(l, sin_q<QM>(si, ci, u[k], q), gks);
+            gs = __builtin_fmaf(l, zk, gs);
+            lam[k] = l + a.dt * (Kt * ccos - (float)q * Kst * cos_q<QM>(si, ci, u[k], q) * l);
         }
-        gk = wave_sum(gk);
-        gks = wave_sum(gks);
-        gs = wave_sum(gs);
-        if (lane == 0)
-            a.gpart[((size_t)s * nwg + x.wg) * kAdjWaves + wave] =
-                make_float4(-a.dt * gk, -a.dt * gks, sqrt_dt * gs, 0.f);
+        gk = wave_sum63(gk);
+        gks = wave_sum63(gks);
+        gs = wave_sum63(gs);
+        if (lane == 63) {
+            red[p][0][wave] = -a.dt * gk;
+            red[p][1][wave] = -a.dt * gks;
+            red[p][2][wave] = sqrt_dt * gs;
+        }
+        if (!a.noise2) __syncthreads();  // the one noise buffer is rewritten next
+        if (s == t0) {
+            __syncthreads();
+            flush(s, p);
+        }
         p ^= 1;
     }
 #pragma unroll
-    for (int k = 0; k < kAdjQPT; ++k) {
-        const int m = threadIdx.x + k * kAdjTB;
-        if (m >= x.nq) break;
-        *reinterpret_cast<float4*>(a.lam + slot_index(a, x, 0, 4 * m)) =
-            make_float4(lam[k][0], lam[k][1], lam[k][2], lam[k][3]);
+    for (int k = 0; k < kMaxRounds; ++k)
+        if (x.grp[k] < x.ng) a.lam[at(a, x, 0, x.slot[k])] = lam[k];
+}
+
+// gK[s] etc. = sum over the workgroups' partials, FP64, in a fixed order: one
+// workgroup per step, thread t takes partials t, t + 256, ..., then a tree.
+__global__ __launch_bounds__(256) void adjoint_reduce_kernel(const double* gpart, int nparts,
+                                                             double* gK, double* gKs, double* gS) {
+    __shared__ double red[3][4];
+    const int s = blockIdx.x;
+    for (int v = 0; v < 3; ++v) {
+        const double* p = gpart + ((size_t)s * 3 + v) * nparts;
+        double t = 0.0;
+        for (int k = threadIdx.x; k < nparts; k += 256) t += p[k];
+        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+        if ((threadIdx.x & 63) == 0) red[v][threadIdx.x >> 6] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const double t = (red[threadIdx.x][0] + red[threadIdx.x][1]) +
+                         (red[threadIdx.x][2] + red[threadIdx.x][3]);
+        (threadIdx.x == 0 ? gK : threadIdx.x == 1 ? gKs : gS)[s] = t;
     }
 }
 
-// gK[s] etc. = sum over workgroups and waves of the partials, FP64, fixed order.
-__global__ __launch_bounds__(256) void adjoint_reduce_kernel(const float4* gpart, int steps, int nparts,
-                                                             double* gK, double* gKs, double* gS) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= steps) return;
-    const float4* p = gpart + (size_t)s * nparts;
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int k = 0; k < nparts; ++k) {
-        const float4 v = p[k];
-        a += (double)v.x;
-        b += (double)v.y;
-        c += (double)v.z;
+// ---- the sorted rows, made with the problem ----
+
+// Words and weights of one group of 64 rows, a lane per row; row_sum[i] = sum
+// of the row's weights in entry order (the loss's constant).
+__global__ __launch_bounds__(64) void adjoint_rows_kernel(AdjRows rows, const int64_t* row_ptr,
+                                                          const int32_t* col, const float* J,
+                                                          const int4* inst, const int32_t* inst_of,
+                                                          const uint16_t* slot_of, uint32_t* idx,
+                                                          float2* w, double* row_sum, int tabN,
+                                                          int unit) {
+    const int g = blockIdx.x, lane = threadIdx.x;
+    const int b = inst_of[g];
+    const int off = inst[b].z;
+    const int2 gd = rows.group[g];
+    const int i = rows.osc[g * 64 + lane];
+    const int64_t r0 = i >= 0 ? row_ptr[off + i] : 0;
+    const int len = i >= 0 ? (int)(row_ptr[off + i + 1] - r0) : 0;
+    const size_t base = (size_t)(rows.span[b].x + gd.x) * 64 + lane;
+    double sum = 0.0;
+    for (int e = 0; e < gd.y; ++e) {
+        uint32_t v[2];
+        float wt[2];
+        for (int h = 0; h < 2; ++h) {
+            const int x = 2 * e + h;
+            v[h] = (uint32_t)tabN;
+            wt[h] = 0.f;
+            if (x < len) {
+                wt[h] = J[r0 + x];
+                v[h] = slot_of[col[r0 + x]] | (unit && wt[h] < 0.f ? 0x8000u : 0u);
+                sum += (double)wt[h];
+            }
+        }
+        idx[base + (size_t)e * 64] = v[0] | (v[1] << 16);
+        if (w) w[base + (size_t)e * 64] = make_float2(wt[0], wt[1]);
     }
-    gK[s] = a;
-    gKs[s] = b;
-    gS[s] = c;
+    if (i >= 0) row_sum[off + i] = sum;
 }
 
 using AdjFn = void (*)(AdjArgs);
 
-// LDS bytes of the two tables, and of the CSR copy in each mode.
-size_t tab_bytes(int tabN) { return (size_t)32 * (tabN + 1); }
-size_t ell_bytes(int64_t entries) { return 16 * kEllSlices + (((size_t)2 * entries + 15) & ~(size_t)15); }
-size_t csr_bytes(int tabN, int64_t nnz, bool weights) {
-    size_t b = ((size_t)4 * (tabN + 1) + 15) & ~(size_t)15;
-    b += ((size_t)2 * nnz + 15) & ~(size_t)15;
-    if (weights) b += (size_t)4 * nnz;
-    return b;
-}
-constexpr size_t kAdjLdsLimit = 160 * 1024 - 256;  // dynamic LDS next to the static reduction slots
+constexpr size_t kAdjLdsLimit = 160 * 1024 - 1024;  // dynamic LDS next to the static reduction slots
 
-// Row placement for a problem: the padded row image in LDS for unit weights
-// when it fits (forward kernel only), else the CSR in LDS (unit weights need
-// no weight array), else the global CSR.  The backward kernel keeps the CSR:
-// its adjoint gathers read 16-byte table entries, and the padded slots cost
-// more there than the shorter dependency chains save (measured).
-// OIM_ADJ_ROWS=csr or =global skips the earlier choices (a switch for
-// comparing the placements; all give the same bits).
-int csr_mode(const Problem* p, int tabN, size_t* lds, bool allow_ell) {
-    const size_t t = tab_bytes(tabN);
-    const bool small_idx = p->max_inst_n <= 0x7fff;
+// Placement of the rows' words and the LDS a kernel needs with it: in LDS
+// when they fit next to the tables and noise buffers, else streamed from
+// global memory (OIM_ADJ_ROWS=global streams them at any size; any other
+// value leaves the choice).  The segment kernel of instances near 4096
+// oscillators has room for one noise buffer only, at one more barrier per
+// step.
+struct Placement {
+    bool ldsi;
+    int noise2;
+    size_t lds;
+};
+
+Placement place(const Problem* p, const AdjArgs& a, bool segment) {
     const char* env = getenv("OIM_ADJ_ROWS");
-    const int skip = env && !strcmp(env, "global") ? 2 : env && !strcmp(env, "csr") ? 1 : 0;
-    if (skip >= 2) {
-        *lds = t;
-        return kCsrGlobal;
-    }
-    if (skip < 1 && allow_ell && small_idx && p->unit_weights && p->max_inst_ell > 0 &&
-        t + ell_bytes(p->max_inst_ell) <= kAdjLdsLimit) {
-        *lds = t + ell_bytes(p->max_inst_ell);
-        return kEllUnit;
-    }
-    if (small_idx && p->unit_weights && t + csr_bytes(tabN, p->max_inst_nnz, false) <= kAdjLdsLimit) {
-        *lds = t + csr_bytes(tabN, p->max_inst_nnz, false);
-        return kCsrLdsUnit;
-    }
-    if (small_idx && t + csr_bytes(tabN, p->max_inst_nnz, true) <= kAdjLdsLimit) {
-        *lds = t + csr_bytes(tabN, p->max_inst_nnz, true);
-        return kCsrLds;
-    }
-    *lds = t;
-    return kCsrGlobal;
+    const bool stream = env && !strcmp(env, "global");
+    const size_t noise = (size_t)a.quads * 16, img = (size_t)a.img_words * 4;
+    auto tables = [&](bool ldsi) -> size_t {
+        if (segment) return (size_t)2 * (a.tabN + 1) * 16;
+        return ((size_t)2 * (a.tabN + 1) * 8 * (p->unit_weights && ldsi ? 2 : 1) + 15) & ~(size_t)15;
+    };
+    if (!stream && tables(true) + 2 * noise + img <= kAdjLdsLimit)
+        return {true, 1, tables(true) + 2 * noise + img};
+    if (tables(false) + 2 * noise <= kAdjLdsLimit) return {false, 1, tables(false) + 2 * noise};
+    return {false, 0, tables(false) + noise};
 }
 
-AdjFn forward_fn(int q, int mode) {
-    const int qc = q == 2 ? 1 : q == 3 ? 2 : 0;
-    static const AdjFn f[3][4] = {
-        {adjoint_forward_kernel<0, 0>, adjoint_forward_kernel<0, 1>, adjoint_forward_kernel<0, 2>,
-         adjoint_forward_kernel<0, 3>},
-        {adjoint_forward_kernel<2, 0>, adjoint_forward_kernel<2, 1>, adjoint_forward_kernel<2, 2>,
-         adjoint_forward_kernel<2, 3>},
-        {adjoint_forward_kernel<3, 0>, adjoint_forward_kernel<3, 1>, adjoint_forward_kernel<3, 2>,
-         adjoint_forward_kernel<3, 3>}};
-    return f[qc][mode];
-}
+#define OIM_ADJ_FNS(NAME)                                                                   \
+    AdjFn NAME##_fn(int q, bool unit, bool ldsi) {                                          \
+        static const AdjFn f[3][2][2] = {                                                   \
+            {{adjoint_##NAME##_kernel<0, false, false>, adjoint_##NAME##_kernel<0, false, true>}, \
+             {adjoint_##NAME##_kernel<0, true, false>, adjoint_##NAME##_kernel<0, true, true>}},  \
+            {{adjoint_##NAME##_kernel<2, false, false>, adjoint_##NAME##_kernel<2, false, true>}, \
+             {adjoint_##NAME##_kernel<2, true, false>, adjoint_##NAME##_kernel<2, true, true>}},  \
+            {{adjoint_##NAME##_kernel<3, false, false>, adjoint_##NAME##_kernel<3, false, true>}, \
+             {adjoint_##NAME##_kernel<3, true, false>, adjoint_##NAME##_kernel<3, true, true>}}}; \
+        return f[q == 2 ? 1 : q == 3 ? 2 : 0][unit][ldsi];                                  \
+    }
+OIM_ADJ_FNS(forward)
+OIM_ADJ_FNS(recompute)
+OIM_ADJ_FNS(segment)
+#undef OIM_ADJ_FNS
 
-AdjFn recompute_fn(int q, int mode) {
-    const int qc = q == 2 ? 1 : q == 3 ? 2 : 0;
-    static const AdjFn f[3][4] = {
-        {adjoint_recompute_kernel<0, 0>, adjoint_recompute_kernel<0, 1>,
-         adjoint_recompute_kernel<0, 2>, adjoint_recompute_kernel<0, 3>},
-        {adjoint_recompute_kernel<2, 0>, adjoint_recompute_kernel<2, 1>,
-         adjoint_recompute_kernel<2, 2>, adjoint_recompute_kernel<2, 3>},
-        {adjoint_recompute_kernel<3, 0>, adjoint_recompute_kernel<3, 1>,
-         adjoint_recompute_kernel<3, 2>, adjoint_recompute_kernel<3, 3>}};
-    return f[qc][mode];
-}
-
-AdjFn segment_fn(int q, int mode) {
-    const int qc = q == 2 ? 1 : q == 3 ? 2 : 0;
-    static const AdjFn f[3][3] = {
-        {adjoint_segment_kernel<0, 0>, adjoint_segment_kernel<0, 1>, adjoint_segment_kernel<0, 2>},
-        {adjoint_segment_kernel<2, 0>, adjoint_segment_kernel<2, 1>, adjoint_segment_kernel<2, 2>},
-        {adjoint_segment_kernel<3, 0>, adjoint_segment_kernel<3, 1>, adjoint_segment_kernel<3, 2>}};
-    return f[qc][mode];
-}
-
-int launch_adj(AdjFn fn, size_t lds, int grid, hipStream_t stream, const AdjArgs& a,
+int launch_adj(AdjFn fn, size_t lds, int grid, int threads, hipStream_t stream, const AdjArgs& a,
                const char* what) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, what);
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kAdjTB), lds, stream, a);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), lds, stream, a);
     e = hipGetLastError();
     return e == hipSuccess ? OIM_OK : hip_error(e, what);
 }
@@ -803,9 +696,7 @@ int check_launch(const char* what) {
 AdjArgs base_args(const Problem* p, const oim_adjoint_cfg* cfg, const float* K, const float* Ks,
                   const float* sigma, const uint64_t* seeds, int64_t step0) {
     AdjArgs a{};
-    a.row_ptr = p->d_row_ptr;
-    a.col = p->d_col;
-    a.J = p->d_J;
+    a.rows = p->adj_rows;
     a.inst = p->d_inst;
     a.I = p->n_inst;
     a.n_total = p->n;
@@ -817,9 +708,9 @@ AdjArgs base_args(const Problem* p, const oim_adjoint_cfg* cfg, const float* K, 
     a.nseg = (cfg->steps + cfg->checkpoint_every - 1) / cfg->checkpoint_every;
     a.step0 = step0;
     a.dt = cfg->dt;
-    a.tabN = (p->max_inst_n + 3) & ~3;
-    a.max_nnz = p->max_inst_nnz;
-    a.max_ell = p->max_inst_ell;
+    a.tabN = (p->max_inst_n + 63) & ~63;
+    a.quads = (p->max_inst_n + 3) / 4;
+    a.img_words = p->adj_max_words;
     a.K = K;
     a.Ks = Ks;
     a.sigma = sigma;
@@ -827,7 +718,73 @@ AdjArgs base_args(const Problem* p, const oim_adjoint_cfg* cfg, const float* K, 
     return a;
 }
 
+// A wave per group of 64 rows of the largest instance, sixteen at most.
+int block_threads(const AdjArgs& a) { return a.tabN < kMaxTB ? a.tabN : kMaxTB; }
+
+template <typename T>
+int alloc_and_copy(T** dst, const T* src, size_t count, const char* what) {
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(dst), count * sizeof(T) + 16);
+    if (e != hipSuccess) {
+        *dst = nullptr;
+        return e == hipErrorOutOfMemory ? set_error(OIM_E_NOMEM, std::string(what) + ": out of device memory")
+                                        : hip_error(e, what);
+    }
+    if (src) e = hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice);
+    return e == hipSuccess ? OIM_OK : hip_error(e, what);
+}
+
 }  // namespace
+
+int adjoint_prepare(Problem* p, const AdjRowsHost& h) {
+    // one upload: group spans, groups, first groups, oscillators, slots, instances of groups
+    const size_t I = h.span.size(), G = h.group.size(), n = h.slot_of.size();
+    std::vector<unsigned char> blob;
+    auto append = [&](const void* src, size_t bytes) {
+        const size_t o = blob.size();
+        blob.resize(o + (bytes + 15) / 16 * 16);
+        if (bytes) std::memcpy(blob.data() + o, src, bytes);
+        return o;
+    };
+    const size_t o_span = append(h.span.data(), I * sizeof(int2));
+    const size_t o_group = append(h.group.data(), G * sizeof(int2));
+    const size_t o_group0 = append(h.group0.data(), I * sizeof(int32_t));
+    const size_t o_osc = append(h.osc.data(), G * 64 * sizeof(int16_t));
+    const size_t o_slot = append(h.slot_of.data(), n * sizeof(uint16_t));
+    const size_t o_inst = append(h.inst_of.data(), G * sizeof(int32_t));
+    unsigned char* d = nullptr;
+    int st = alloc_and_copy(&d, blob.data(), blob.size(), "adjoint rows");
+    p->d_adj_rows = d;
+    if (st) return st;
+    const size_t words = (size_t)h.rows64 * 64;
+    const size_t idx_bytes = (words * 4 + 255) / 256 * 256;
+    const size_t w_bytes = p->unit_weights ? 0 : (words * 8 + 255) / 256 * 256;
+    unsigned char* img = nullptr;
+    st = alloc_and_copy(&img, static_cast<const unsigned char*>(nullptr), idx_bytes + w_bytes + n * 8,
+                        "adjoint row image");
+    p->d_adj_img = img;
+    if (st) return st;
+    uint32_t* idx = reinterpret_cast<uint32_t*>(img);
+    float2* w = w_bytes ? reinterpret_cast<float2*>(img + idx_bytes) : nullptr;
+    double* row_sum = reinterpret_cast<double*>(img + idx_bytes + w_bytes);
+    AdjRows& r = p->adj_rows;
+    r.span = reinterpret_cast<const int2*>(d + o_span);
+    r.group = reinterpret_cast<const int2*>(d + o_group);
+    r.group0 = reinterpret_cast<const int32_t*>(d + o_group0);
+    r.osc = reinterpret_cast<const int16_t*>(d + o_osc);
+    r.idx = idx;
+    r.w = w;
+    r.row_sum = row_sum;
+    p->adj_max_words = h.max_words;
+    hipLaunchKernelGGL(adjoint_rows_kernel, dim3((unsigned)G), dim3(64), 0, 0, r, p->d_row_ptr, p->d_col,
+                       p->d_J, p->d_inst, reinterpret_cast<const int32_t*>(d + o_inst),
+                       reinterpret_cast<const uint16_t*>(d + o_slot), idx, w, row_sum,
+                       (p->max_inst_n + 63) & ~63, p->unit_weights ? 1 : 0);
+    st = check_launch("adjoint_rows_kernel");
+    if (st) return st;
+    // callers may run on any stream next
+    const hipError_t e = hipStreamSynchronize(0);
+    return e == hipSuccess ? OIM_OK : hip_error(e, "adjoint row image");
+}
 
 int64_t adjoint_checkpoint_words(const Problem* p, const oim_adjoint_cfg* cfg) {
     const int64_t nseg = (cfg->steps + cfg->checkpoint_every - 1) / cfg->checkpoint_every;
@@ -843,10 +800,9 @@ int launch_adjoint_forward(Problem* p, const oim_adjoint_cfg* cfg, const float* 
     a.ckpt = ckpt;
     a.thetaT = thetaT;
     a.loss = loss;
-    size_t lds = 0;
-    const int mode = csr_mode(p, a.tabN, &lds, true);
-    return launch_adj(forward_fn(cfg->q, mode), lds, cfg->R * p->n_inst, stream, a,
-                      "adjoint_forward_kernel");
+    const Placement pl = place(p, a, false);
+    return launch_adj(forward_fn(cfg->q, p->unit_weights, pl.ldsi), pl.lds, cfg->R * p->n_inst,
+                      block_threads(a), stream, a, "adjoint_forward_kernel");
 }
 
 namespace {
@@ -899,7 +855,7 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t seg_bytes = up((size_t)(cfg->checkpoint_every + 1) * cfg->R * a.P * sizeof(uint32_t));
     const size_t lam_bytes = up((size_t)cfg->R * a.P * sizeof(float));
-    const size_t part_bytes = (size_t)cfg->steps * nwg * kAdjWaves * sizeof(float4);
+    const size_t part_bytes = (size_t)cfg->steps * nwg * 3 * sizeof(double);
     const size_t need = 2 * seg_bytes + lam_bytes + part_bytes + 256;
     if (p->adj_bytes < need) {
         (void)hipFree(p->d_adj);
@@ -920,10 +876,12 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     uint32_t* segbuf[2] = {reinterpret_cast<uint32_t*>(w), reinterpret_cast<uint32_t*>(w + seg_bytes)};
     a.ckpt = const_cast<uint32_t*>(ckpt);
     a.lam = reinterpret_cast<float*>(w + 2 * seg_bytes);
-    a.gpart = reinterpret_cast<float4*>(w + 2 * seg_bytes + lam_bytes);
-    size_t lds_rec = 0, lds_adj = 0;
-    const AdjFn frec = recompute_fn(cfg->q, csr_mode(p, a.tabN, &lds_rec, true));
-    const AdjFn fadj = segment_fn(cfg->q, csr_mode(p, a.tabN, &lds_adj, false));
+    a.gpart = reinterpret_cast<double*>(w + 2 * seg_bytes + lam_bytes);
+    const Placement prec = place(p, a, false), padj = place(p, a, true);
+    const AdjFn frec = recompute_fn(cfg->q, p->unit_weights, prec.ldsi);
+    const AdjFn fadj = segment_fn(cfg->q, p->unit_weights, padj.ldsi);
+    a.noise2 = padj.noise2;
+    const int tb = block_threads(a);
     hipStream_t side = p->adj_stream;
     hipEvent_t* start = &p->adj_ev[0];
     hipEvent_t* rec = &p->adj_ev[1];   // [2]
@@ -937,17 +895,17 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
         a.seg = segbuf[buf];
         if (sg + 2 <= a.nseg - 1 && (e = hipStreamWaitEvent(side, adj[buf], 0)) != hipSuccess)
             return hip_error(e, "adjoint buffer wait");
-        if ((st = launch_adj(frec, lds_rec, nwg, side, a, "adjoint_recompute_kernel"))) break;
+        if ((st = launch_adj(frec, prec.lds, nwg, tb, side, a, "adjoint_recompute_kernel"))) break;
         if ((e = hipEventRecord(rec[buf], side)) != hipSuccess ||
             (e = hipStreamWaitEvent(stream, rec[buf], 0)) != hipSuccess)
             return hip_error(e, "adjoint segment order");
-        if ((st = launch_adj(fadj, lds_adj, nwg, stream, a, "adjoint_segment_kernel"))) break;
+        if ((st = launch_adj(fadj, padj.lds, nwg, tb, stream, a, "adjoint_segment_kernel"))) break;
         if ((e = hipEventRecord(adj[buf], stream)) != hipSuccess)
             return hip_error(e, "adjoint segment order");
     }
     if (st) return st;
-    hipLaunchKernelGGL(adjoint_reduce_kernel, dim3((cfg->steps + 255) / 256), dim3(256), 0, stream,
-                       a.gpart, cfg->steps, nwg * kAdjWaves, gK, gKs, gS);
+    hipLaunchKernelGGL(adjoint_reduce_kernel, dim3(cfg->steps), dim3(256), 0, stream, a.gpart, nwg, gK,
+                       gKs, gS);
     return check_launch("adjoint_reduce_kernel");
 }
 

@@ -54,6 +54,8 @@ void release(Problem* p) {
     hipFree(p->d_work);
     adjoint_release(p);
     hipFree(p->d_adj);
+    hipFree(p->d_adj_rows);
+    hipFree(p->d_adj_img);
     dense_release(p);
     unregister_problem(p);
     delete p;
@@ -132,31 +134,14 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
     p->nnz = nnz;
     p->n_inst = n_inst;
     p->max_inst_n = n;
-    p->max_inst_nnz = nnz;
     if (n_inst > 1) {
         p->max_inst_n = 0;
-        p->max_inst_nnz = 0;
-        for (int32_t b = 0; b < n_inst; ++b) {
+        for (int32_t b = 0; b < n_inst; ++b)
             p->max_inst_n = std::max(p->max_inst_n, inst_off[b + 1] - inst_off[b]);
-            p->max_inst_nnz = std::max<int64_t>(p->max_inst_nnz,
-                                                row_ptr[inst_off[b + 1]] - row_ptr[inst_off[b]]);
-        }
     }
     p->unit_weights = true;
     for (int64_t e = 0; e < nnz && p->unit_weights; ++e)
         if (std::fabs(J[e]) != 1.0f) p->unit_weights = false;
-    p->max_inst_ell = 0;
-    for (int32_t b = 0; b < n_inst; ++b) {
-        const int32_t r0 = n_inst > 1 ? inst_off[b] : 0, r1 = n_inst > 1 ? inst_off[b + 1] : n;
-        int64_t ell = 0;
-        for (int32_t s0 = r0; s0 < r1; s0 += 256) {
-            int64_t dmax = 0;
-            for (int32_t i = s0; i < std::min(r1, s0 + 256); ++i)
-                dmax = std::max<int64_t>(dmax, row_ptr[i + 1] - row_ptr[i]);
-            ell += 256 * ((dmax + 3) & ~int64_t(3));
-        }
-        p->max_inst_ell = std::max(p->max_inst_ell, ell);
-    }
     weight_stats(p, n, row_ptr, col_idx, J);
     SellImage img;
     // one weight of +1 or -1 on every entry: the kernel reads a half-size
@@ -201,6 +186,14 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
         p->ell_D = ell.D;
         if ((st = dev_upload(&p->d_ell_col, ell.col.data(), ell.col.size(), "upload ell col")) ||
             (st = dev_upload(&p->d_ell_J, ell.J.data(), ell.J.size(), "upload ell J"))) {
+            release(p);
+            return st;
+        }
+    }
+    if (p->max_inst_n <= kAdjMaxN) {
+        AdjRowsHost rows;
+        build_adj_rows(n, row_ptr, n_inst, n_inst > 1 ? inst_off : nullptr, rows);
+        if ((st = adjoint_prepare(p, rows))) {
             release(p);
             return st;
         }

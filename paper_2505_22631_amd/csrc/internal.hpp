@@ -50,6 +50,34 @@ struct SellImage {
 
 constexpr size_t kCsrPad = 4;
 
+// The rows of a sparse problem as the adjoint kernels walk them.  Within an
+// instance the oscillators are sorted by row length, longest first (equal
+// lengths by index); the one at position p is "slot" p.  64 consecutive
+// slots are a group: its rows are padded to the longest, rounded up to two
+// entries, and stored as 32-bit words of two 16-bit entries (the neighbour's
+// slot; unit weights: the sign in the top bit), word e of lane l at
+// (span.x + first + e) * 64 + l.  Padding points at slot tabN (the largest
+// instance's slots rounded up to 64), which the kernels keep at zero.
+struct AdjRows {
+    const int2* span = nullptr;       // [I] first row of 64 words, rows of 64 words
+    const int2* group = nullptr;      // [G] (first row of 64 words within the instance, words per row)
+    const int32_t* group0 = nullptr;  // [I] first group
+    const int16_t* osc = nullptr;     // [G][64] oscillator within the instance, or -1
+    const uint32_t* idx = nullptr;
+    const float2* w = nullptr;        // weights of a word's entries, or null (unit weights)
+    const double* row_sum = nullptr;  // [n] sum of a row's weights
+};
+
+// The host side of it (built without HIP calls, validate.cpp).
+struct AdjRowsHost {
+    std::vector<int2> span, group;
+    std::vector<int32_t> group0, inst_of;  // inst_of[G]
+    std::vector<int16_t> osc;
+    std::vector<uint16_t> slot_of;         // [n] slot of an oscillator
+    int64_t rows64 = 0;                    // rows of 64 words in all
+    int32_t max_words = 0;                 // words of the largest instance
+};
+
 struct Problem {
     uint64_t handle = 0;  // registry key, the value callers hold as oim_problem
     int device = 0;
@@ -79,9 +107,6 @@ struct Problem {
     // instances of a block-diagonal batch (1 for a single graph)
     int32_t n_inst = 1;
     int32_t max_inst_n = 0;  // largest instance (oscillators)
-    int64_t max_inst_nnz = 0;  // most stored entries of one instance
-    int64_t max_inst_ell = 0;  // most entries of one instance's padded row image (slices of
-                               // 256 rows, each padded to its longest row rounded up to 4)
     bool unit_weights = false; // every |J| is 1
     int4* d_inst = nullptr;
     int32_t* d_order = nullptr;
@@ -112,6 +137,12 @@ struct Problem {
     int16_t tuned_tb[3] = {0, 0, 0};
     int16_t tuned_ms[3] = {0, 0, 0};
     int16_t tuned_rpl[3] = {4, 4, 4};
+
+    // the adjoint's rows (instances of at most kAdjMaxN oscillators), else null
+    AdjRows adj_rows;
+    void* d_adj_rows = nullptr;
+    void* d_adj_img = nullptr;
+    int32_t adj_max_words = 0;
 
     // cached scratch of the adjoint backward pass, and its second stream and
     // events (start, recomputed[2], adjoint done[2])
@@ -168,6 +199,10 @@ bool ell_wanted(int32_t n, const int64_t* row_ptr, int mode);
 void build_ell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
                EllImage& out);
 
+// inst_off null: one instance.  Every instance has at most kAdjMaxN oscillators.
+void build_adj_rows(int32_t n, const int64_t* row_ptr, int32_t n_inst, const int32_t* inst_off,
+                    AdjRowsHost& out);
+
 // kernels' host launchers
 int launch_persistent_sparse(const Problem* p, const oim_run_cfg* cfg, const float* K,
                              const float* Ks, const float* sigma, const uint64_t* seeds,
@@ -205,6 +240,7 @@ int tune_persistent(Problem* p, const oim_run_cfg* cfg, const float* K, const fl
                     int32_t trial_steps, oim_tune_report* rep, hipStream_t stream);
 int validate_adjoint_cfg(const Problem* p, const oim_adjoint_cfg* cfg);
 int64_t adjoint_checkpoint_words(const Problem* p, const oim_adjoint_cfg* cfg);
+int adjoint_prepare(Problem* p, const AdjRowsHost& rows);
 constexpr int kAdjEvents = 5;
 void adjoint_release(Problem* p);
 int launch_adjoint_forward(Problem* p, const oim_adjoint_cfg* cfg, const float* K, const float* Ks,

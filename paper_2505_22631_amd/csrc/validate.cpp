@@ -291,4 +291,40 @@ void build_ell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const 
     }
 }
 
+void build_adj_rows(int32_t n, const int64_t* row_ptr, int32_t n_inst, const int32_t* inst_off,
+                    AdjRowsHost& out) {
+    out = AdjRowsHost{};
+    out.slot_of.resize((size_t)n);
+    std::vector<int32_t> count, order;
+    for (int32_t b = 0; b < n_inst; ++b) {
+        const int32_t o = inst_off ? inst_off[b] : 0;
+        const int32_t nb = inst_off ? inst_off[b + 1] - o : n;
+        // counting sort by row length, longest first, stable
+        int64_t dmax = 0;
+        auto len = [&](int32_t i) { return row_ptr[o + i + 1] - row_ptr[o + i]; };
+        for (int32_t i = 0; i < nb; ++i) dmax = std::max(dmax, len(i));
+        count.assign((size_t)dmax + 2, 0);
+        for (int32_t i = 0; i < nb; ++i) ++count[(size_t)(dmax - len(i)) + 1];
+        for (size_t d = 1; d < count.size(); ++d) count[d] += count[d - 1];
+        order.resize((size_t)nb);
+        for (int32_t i = 0; i < nb; ++i) order[(size_t)count[(size_t)(dmax - len(i))]++] = i;
+        out.group0.push_back((int32_t)out.group.size());
+        int64_t rows = 0;
+        for (int32_t s0 = 0; s0 < nb; s0 += 64) {
+            const int32_t words = (int32_t)((len(order[(size_t)s0]) + 1) / 2);
+            out.group.push_back(int2{(int32_t)rows, words});
+            out.inst_of.push_back(b);
+            for (int32_t l = 0; l < 64; ++l) {
+                const int32_t p = s0 + l;
+                out.osc.push_back(p < nb ? (int16_t)order[(size_t)p] : (int16_t)-1);
+                if (p < nb) out.slot_of[(size_t)(o + order[(size_t)p])] = (uint16_t)p;
+            }
+            rows += words;
+        }
+        out.span.push_back(int2{(int32_t)out.rows64, (int32_t)rows});
+        out.rows64 += rows;
+        out.max_words = std::max(out.max_words, (int32_t)(rows * 64));
+    }
+}
+
 }  // namespace oim
