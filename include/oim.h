@@ -359,7 +359,8 @@ int oim_adjoint_forward(oim_problem p, const oim_adjoint_cfg* cfg, const float* 
  * later segment on `stream`; the work forks from and joins back into
  * `stream`, so the call stays asynchronous and later work on `stream` sees
  * the gradients.  Uses a workspace cached in p (2 (C + 1) R slots words,
- * R slots floats, plus 128 bytes per step and workgroup); one stream at a
+ * R slots floats, 24 bytes per step, replica and instance, and 4 C R slots
+ * floats more while those are at most 8 GiB and can be had); one stream at a
  * time per problem.  Errors as the forward pass, plus OIM_E_NOMEM. */
 int oim_adjoint_backward(oim_problem p, const oim_adjoint_cfg* cfg, const float* K,
                          const float* Ks, const float* sigma, const uint64_t* seeds,

@@ -25,7 +25,10 @@
 // the waves back and forth, so every wave has about the same work.  The
 // oscillator at sorted position p of its instance is "slot" p: tables and the
 // buffers between kernels are in slot order, caller arrays in oscillator
-// order.
+// order.  128 x G(2000, 10/1999), us per step and workgroup, with consecutive
+// rows on eight waves and now: forward 3.9 -> 2.05, adjoint 6.7 -> 2.8; bound by
+// the LDS reads of the neighbours (8 bytes each at random slots), then by the
+// vector instructions beside them.
 //
 // Forward kernel: phases and own (sin, cos) in registers, neighbour (s, c) in
 // an LDS ping-pong table, one barrier per step; the phase words are
@@ -67,7 +70,7 @@ struct AdjArgs {
     const int4* inst;      // per instance: first slice, slices, first oscillator, size
     int tabN;              // slots of the largest instance (its rows rounded up to 64)
     int quads;             // quads of the largest instance
-    int noise2;            // 1: two noise buffers (segment kernel)
+    int noise2;            // 1: two noise buffers (0: one, wide segment kernel)
     int img_words;         // LDS words of the largest instance's image (LDSI)
     int I, n_total, P;     // instances, oscillators, padded words per replica
     int R, q, steps, C, nseg;
@@ -82,6 +85,7 @@ struct AdjArgs {
     float* thetaT;         // [R][n_total] or null
     double* loss;          // [R * I] or null
     uint32_t* seg;         // [C + 1][R][P] states of one segment, slot order (backward)
+    float2* sums;          // [C][R][P] (csin, ccos0) of one segment's steps, or null (backward)
     double* gpart;         // [steps][3][R * I] (backward)
     float* lam;            // [R][P] adjoint state between segments, slot order (backward)
     int cur_seg;           // segment of this launch (backward)
@@ -156,14 +160,27 @@ __device__ __forceinline__ size_t at(const AdjArgs& a, const Ctx& x, int step, i
 //   UNIT  weights are +-1 (else FP32 weights are streamed from global memory,
 //         two per lane and pair)
 //   LDSI  the image sits in LDS, else it is streamed through L2
-// The forward kernels of UNIT && LDSI keep a negated copy of the table and
-// entries that point into either, so a term is an add and no sign is decoded.
-template <bool UNIT, bool LDSI>
+//   WIDE  the table's entries are 16 bytes (s, c, s lam, c lam), else 8
+// In LDS the entries of an 8-byte table are byte offsets into it, and with
+// unit weights the table has a negated copy that the entries of negative ones
+// point into (NEG), so a term is an address, a read and two adds.
+template <bool UNIT, bool LDSI, bool WIDE>
 struct Image {
+    static constexpr bool NEG = UNIT && LDSI && !WIDE;
+    static constexpr bool BYTES = LDSI && !WIDE;
+    using T = std::conditional_t<WIDE, float4, float2>;
     const uint32_t* idx;  // LDS or global
     const float2* w;      // global, !UNIT
     __device__ __forceinline__ uint32_t pair(int e) const { return idx[e * 64]; }
     __device__ __forceinline__ float2 weight(int e) const { return w[e * 64]; }
+    // entry `half` of a word
+    __device__ __forceinline__ static T read(const T* tab, uint32_t v, int half) {
+        const uint32_t x = half ? v >> 16 : v & 0xffffu;
+        if constexpr (BYTES)
+            return *reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(tab) + x);
+        else
+            return tab[UNIT ? x & 0x7fffu : x];
+    }
 };
 
 __device__ __forceinline__ float sign_weight(uint32_t sign_bit) {
@@ -173,18 +190,19 @@ __device__ __forceinline__ float sign_weight(uint32_t sign_bit) {
 // Row sums over the table entries, `pairs` words of two entries: even entries
 // into one partial sum, odd ones into the other, in order (a padding entry
 // adds +-0 to a partial sum that is never -0), so every placement and
-// grouping gives the same bits.  TERMS = 2: A = sum J c_j, B = sum J s_j from
-// (s, c); TERMS = 4: also Cl, Dl from (s, c, s lam, c lam).  NEG: the table
-// has a negated copy and the entries their final position.
-template <int TERMS, bool NEG, bool UNIT, bool LDSI, class T>
-__device__ __forceinline__ void row_sums(const Image<UNIT, LDSI>& im, const T* tab, int first,
+// grouping gives the same bits.  S[0] = sum J y_j, S[1] = sum J x_j of the
+// table's (x, y); WIDE: S[2] = sum J w_j, S[3] = sum J z_j too.
+template <bool UNIT, bool LDSI, bool WIDE>
+__device__ __forceinline__ void row_sums(const Image<UNIT, LDSI, WIDE>& im,
+                                         const typename Image<UNIT, LDSI, WIDE>::T* tab, int first,
                                          int pairs, float (&S)[4]) {
+    using Im = Image<UNIT, LDSI, WIDE>;
     float s0[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
     auto batch = [&](int e, auto count) __attribute__((always_inline)) {
         constexpr int N = decltype(count)::value;
         uint32_t v[N];
         float2 w[N];
-        T p[2 * N];
+        typename Im::T p[2 * N];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             v[k] = im.pair(first + e + k);
@@ -192,13 +210,12 @@ __device__ __forceinline__ void row_sums(const Image<UNIT, LDSI>& im, const T* t
         }
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-            const uint32_t mask = UNIT && !NEG ? 0x7fffu : 0xffffu;
-            p[2 * k] = tab[v[k] & mask];
-            p[2 * k + 1] = tab[(v[k] >> 16) & mask];
+            p[2 * k] = Im::read(tab, v[k], 0);
+            p[2 * k + 1] = Im::read(tab, v[k], 1);
         }
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-            if constexpr (NEG) {
+            if constexpr (Im::NEG) {
                 s0[0] = s0[0] + p[2 * k].y;
                 s0[1] = s0[1] + p[2 * k].x;
                 s1[0] = s1[0] + p[2 * k + 1].y;
@@ -210,7 +227,7 @@ __device__ __forceinline__ void row_sums(const Image<UNIT, LDSI>& im, const T* t
                 s0[1] = __builtin_fmaf(w0, p[2 * k].x, s0[1]);
                 s1[0] = __builtin_fmaf(w1, p[2 * k + 1].y, s1[0]);
                 s1[1] = __builtin_fmaf(w1, p[2 * k + 1].x, s1[1]);
-                if constexpr (TERMS == 4) {
+                if constexpr (WIDE) {
                     s0[2] = __builtin_fmaf(w0, p[2 * k].w, s0[2]);
                     s0[3] = __builtin_fmaf(w0, p[2 * k].z, s0[3]);
                     s1[2] = __builtin_fmaf(w1, p[2 * k + 1].w, s1[2]);
@@ -230,34 +247,54 @@ __device__ __forceinline__ void row_sums(const Image<UNIT, LDSI>& im, const T* t
     for (int t = 0; t < 4; ++t) S[t] = s0[t] + s1[t];
 }
 
-// Dynamic LDS: `tables` (2 tables of T, see the kernels), the noise buffers
-// [2 or 1][4 quads], the image (LDSI).  Copies the instance's image, turning
-// signs into positions in the negated copy of the table (NEG); the caller's
-// first barrier publishes it.
-template <bool UNIT, bool LDSI, bool NEG>
-__device__ __forceinline__ Image<UNIT, LDSI> setup_image(const AdjArgs& a, const Ctx& x,
-                                                         uint32_t* lds) {
-    const int lane = threadIdx.x & 63;
-    const int2 span = a.rows.span[x.b];  // first row of 64 words, rows
-    const uint32_t* src = a.rows.idx + (size_t)span.x * 64;
-    Image<UNIT, LDSI> im;
-    if constexpr (LDSI) {
-        for (int e = threadIdx.x; e < span.y * 64; e += blockDim.x) {
-            uint32_t v = src[e];
-            if constexpr (NEG) {
-                const uint32_t lo = v & 0xffffu, hi = v >> 16;
-                v = ((lo & 0x7fffu) + (lo >> 15) * (a.tabN + 1)) |
-                    (((hi & 0x7fffu) + (hi >> 15) * (a.tabN + 1)) << 16);
+// Dynamic LDS of a kernel: two tables of tabN + 1 entries (NEG: each followed
+// by its negated copy), the noise buffers [2 or 1][quads], the image (LDSI).
+// The constructor zeroes the zero entries and copies the instance's image;
+// the caller's first barrier publishes them.
+template <bool UNIT, bool LDSI, bool WIDE>
+struct Lds {
+    using Im = Image<UNIT, LDSI, WIDE>;
+    using T = typename Im::T;
+    T* tabs;
+    int stride, neg;   // entries per table, and to the negated copy
+    float4* noise;
+    Im im;
+    __device__ __forceinline__ Lds(const AdjArgs& a, const Ctx& x, unsigned char* smem) {
+        neg = a.tabN + 1;
+        stride = neg * (Im::NEG ? 2 : 1);
+        tabs = reinterpret_cast<T*>(smem);
+        noise = reinterpret_cast<float4*>(smem + (((size_t)2 * stride * sizeof(T) + 15) & ~(size_t)15));
+        uint32_t* img = reinterpret_cast<uint32_t*>(noise + (a.noise2 ? 2 : 1) * a.quads);
+        if (threadIdx.x < (Im::NEG ? 4 : 2))
+            tabs[(threadIdx.x & 1) * stride + (threadIdx.x >> 1) * neg + a.tabN] = T{};
+        const int lane = threadIdx.x & 63;
+        const int2 span = a.rows.span[x.b];  // first row of 64 words, rows
+        const uint32_t* src = a.rows.idx + (size_t)span.x * 64;
+        if constexpr (LDSI) {
+            for (int e = threadIdx.x; e < span.y * 64; e += blockDim.x) {
+                uint32_t v = src[e];
+                if constexpr (Im::BYTES) {
+                    uint32_t lo = v & 0xffffu, hi = v >> 16;
+                    if constexpr (Im::NEG) {
+                        lo = (lo & 0x7fffu) + (lo >> 15) * neg;
+                        hi = (hi & 0x7fffu) + (hi >> 15) * neg;
+                    }
+                    v = lo * 8 | (hi * 8) << 16;
+                }
+                img[e] = v;
             }
-            lds[e] = v;
+            im.idx = img + lane;
+        } else {
+            im.idx = src + lane;
         }
-        im.idx = lds + lane;
-    } else {
-        im.idx = src + lane;
+        im.w = UNIT ? nullptr : a.rows.w + (size_t)span.x * 64 + lane;
     }
-    im.w = UNIT ? nullptr : a.rows.w + (size_t)span.x * 64 + lane;
-    return im;
-}
+    __device__ __forceinline__ T* tab(int p) const { return tabs + p * stride; }
+    __device__ __forceinline__ void put(int p, int slot, float2 v) const {
+        tab(p)[slot] = v;
+        if constexpr (Im::NEG) tab(p)[slot + neg] = make_float2(-v.x, -v.y);
+    }
+};
 
 // The normals of step t of every quad, four per quad in oscillator order.
 __device__ __forceinline__ void draw_noise(const AdjArgs& a, const Ctx& x, uint32_t t, float4* noise) {
@@ -286,86 +323,61 @@ struct Sched {
     }
 };
 
-// The forward steps t0 .. t1 - 1 from the words u: body(s) sees the state
-// before step s, in registers and in tab(parity).  Leaves the state at t1 in
-// u, sc and tab(returned parity).
-template <int QM, bool UNIT, bool LDSI, class Body>
+// The forward steps t0 .. t1 - 1 from the words u: before(s) sees the state
+// before step s in u and sc, sums(s, k, S) the row sums S of round k at it.
+// Leaves the state at t1 in u, sc and the table of the returned parity.
+template <int QM, bool UNIT, bool LDSI, class Before, class Sums>
 __device__ __forceinline__ int forward_steps(const AdjArgs& a, const Ctx& x,
-                                             const Image<UNIT, LDSI>& im, float2* tabs, int stride,
-                                             float4* noise, int t0, int t1, uint32_t (&u)[kMaxRounds],
-                                             float2 (&sc)[kMaxRounds], Body body) {
-    constexpr bool NEG = UNIT && LDSI;
+                                             const Lds<UNIT, LDSI, false>& l, int t0, int t1,
+                                             uint32_t (&u)[kMaxRounds], float2 (&sc)[kMaxRounds],
+                                             Before before, Sums sums) {
     const int q = QM ? QM : a.q;
     const float sqrt_dt = __builtin_sqrtf(a.dt);
-    auto put = [&](int p, int k) __attribute__((always_inline)) {
-        float2* t = tabs + p * stride;
-        t[x.slot[k]] = sc[k];
-        if constexpr (NEG) t[x.slot[k] + a.tabN + 1] = make_float2(-sc[k].x, -sc[k].y);
-    };
 #pragma unroll
     for (int k = 0; k < kMaxRounds; ++k)
         if (x.grp[k] < x.ng) {
             sc[k] = make_float2(sin_turn(u[k]), cos_turn(u[k]));
-            put(0, k);
+            l.put(0, x.slot[k], sc[k]);
         }
-    if (t0 < t1) draw_noise(a, x, (uint32_t)(a.step0 + t0), noise);
+    if (t0 < t1) draw_noise(a, x, (uint32_t)(a.step0 + t0), l.noise);
     Sched sch;
     sch.load(a, t0 >> 6);
     __syncthreads();
     int p = 0;
     for (int s = t0; s < t1; ++s) {
         if ((s >> 6) != sch.chunk) sch.load(a, s >> 6);
-        body(s);
+        before(s);
         const float kc = -a.dt * Sched::pick(sch.K, s) * kTurnScale;
         const float ks = -a.dt * Sched::pick(sch.Ks, s) * kTurnScale;
         const float ns = Sched::pick(sch.sg, s) * sqrt_dt * kTurnScale;
-        const float* z = reinterpret_cast<const float*>(noise + p * a.quads);
+        const float* z = reinterpret_cast<const float*>(l.noise + p * a.quads);
 #pragma unroll
         for (int k = 0; k < kMaxRounds; ++k) {
             if (x.grp[k] >= x.ng) break;
             const float zk = z[x.osc[k] < x.nb ? x.osc[k] : 0];
             float S[4];
-            row_sums<2, NEG>(im, tabs + p * stride, x.first[k], x.pairs[k], S);
+            row_sums(l.im, l.tab(p), x.first[k], x.pairs[k], S);
+            sums(s, k, S);
             const float si = sc[k].x, ci = sc[k].y;
             const float coup = __builtin_fmaf(si, S[0], -(ci * S[1]));
             const float drift = __builtin_fmaf(kc, coup, ks * sin_q<QM>(si, ci, u[k], q));
             u[k] = advance(u[k], __builtin_fmaf(ns, zk, drift));
             sc[k] = make_float2(sin_turn(u[k]), cos_turn(u[k]));
-            put(p ^ 1, k);
+            l.put(p ^ 1, x.slot[k], sc[k]);
         }
-        if (s + 1 < t1) draw_noise(a, x, (uint32_t)(a.step0 + s + 1), noise + (p ^ 1) * a.quads);
+        if (s + 1 < t1) draw_noise(a, x, (uint32_t)(a.step0 + s + 1), l.noise + (p ^ 1) * a.quads);
         p ^= 1;
         __syncthreads();
     }
     return p;
 }
 
-// LDS of the forward kernels: the tables [2][stride] of (s, c), stride =
-// tabN + 1 entries, twice that with the negated copies; then noise, image.
-template <bool UNIT, bool LDSI>
-struct ForwardLds {
-    float2* tabs;
-    int stride;
-    float4* noise;
-    uint32_t* img;
-    __device__ __forceinline__ ForwardLds(const AdjArgs& a, unsigned char* smem) {
-        stride = (a.tabN + 1) * (UNIT && LDSI ? 2 : 1);
-        tabs = reinterpret_cast<float2*>(smem);
-        noise = reinterpret_cast<float4*>(smem + (((size_t)2 * stride * sizeof(float2) + 15) & ~(size_t)15));
-        img = reinterpret_cast<uint32_t*>(noise + 2 * a.quads);
-        if (threadIdx.x < 4 && (UNIT && LDSI || threadIdx.x < 2))  // the zero entries
-            tabs[(threadIdx.x & 1) * stride + (threadIdx.x >> 1) * (a.tabN + 1) + a.tabN] =
-                make_float2(0.f, 0.f);
-    }
-};
-
 template <int QM, bool UNIT, bool LDSI>
 __global__ __launch_bounds__(kMaxTB) void adjoint_forward_kernel(AdjArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[kMaxWaves];
     const Ctx x = make_ctx(a);
-    const ForwardLds<UNIT, LDSI> l(a, smem);
-    const Image<UNIT, LDSI> im = setup_image<UNIT, LDSI, UNIT && LDSI>(a, x, l.img);
+    const Lds<UNIT, LDSI, false> l(a, x, smem);
     uint32_t u[kMaxRounds];
     float2 sc[kMaxRounds];
 #pragma unroll
@@ -373,20 +385,22 @@ __global__ __launch_bounds__(kMaxTB) void adjoint_forward_kernel(AdjArgs a) {
         u[k] = x.osc[k] < x.nb
                    ? phase_from_theta(a.theta0[(size_t)x.r * a.n_total + x.off + x.osc[k]])
                    : 0u;
-    const int p = forward_steps<QM>(a, x, im, l.tabs, l.stride, l.noise, 0, a.steps, u, sc, [&](int s) {
-        if (s % a.C) return;
+    const int p = forward_steps<QM>(
+        a, x, l, 0, a.steps, u, sc,
+        [&](int s) {
+            if (s % a.C) return;
 #pragma unroll
-        for (int k = 0; k < kMaxRounds; ++k)
-            if (x.osc[k] < x.nb) a.ckpt[at(a, x, s / a.C, x.osc[k])] = u[k];
-    });
+            for (int k = 0; k < kMaxRounds; ++k)
+                if (x.osc[k] < x.nb) a.ckpt[at(a, x, s / a.C, x.osc[k])] = u[k];
+        },
+        [](int, int, const float (&)[4]) {});
     // relaxed cut of the final phases: sum_i (c_i A_i + s_i B_i - sum_j J_ij) / 4
-    const float2* fin = l.tabs + p * l.stride;
     double part = 0.0;
 #pragma unroll
     for (int k = 0; k < kMaxRounds; ++k) {
         if (x.grp[k] >= x.ng) break;
         float S[4];
-        row_sums<2, UNIT && LDSI>(im, fin, x.first[k], x.pairs[k], S);
+        row_sums(l.im, l.tab(p), x.first[k], x.pairs[k], S);
         if (x.osc[k] < x.nb) {
             const double rs = a.rows.row_sum[x.off + x.osc[k]];
             part += 0.25 * ((double)sc[k].y * S[0] + (double)sc[k].x * S[1] - rs);
@@ -413,17 +427,19 @@ __global__ __launch_bounds__(kMaxTB) void adjoint_forward_kernel(AdjArgs a) {
 // its final step and stores the state at t1 in step slot t1 - t0).  The
 // Philox noise is a pure function of (seed, oscillator, step, instance) and
 // every placement of the rows gives the same bits, so these are the forward
-// pass's states.
+// pass's states.  With a.sums it also hands over what the adjoint needs of
+// the row sums it has formed anyway: csin = s A - c B and ccos0 = c A + s B
+// per step, so that the adjoint gathers two values per neighbour instead of
+// four.
 template <int QM, bool UNIT, bool LDSI>
 __global__ __launch_bounds__(kMaxTB) void adjoint_recompute_kernel(AdjArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Ctx x = make_ctx(a);
-    const ForwardLds<UNIT, LDSI> l(a, smem);
-    const Image<UNIT, LDSI> im = setup_image<UNIT, LDSI, UNIT && LDSI>(a, x, l.img);
+    const Lds<UNIT, LDSI, false> l(a, x, smem);
     const int sg = a.cur_seg;
     const int t0 = sg * a.C;
     const int t1 = t0 + a.C < a.steps ? t0 + a.C : a.steps;
-    const bool last = sg == a.nseg - 1;
+    const int tend = sg == a.nseg - 1 ? t1 : t1 - 1;  // the last state stored
     uint32_t u[kMaxRounds];
     float2 sc[kMaxRounds];
 #pragma unroll
@@ -434,9 +450,23 @@ __global__ __launch_bounds__(kMaxTB) void adjoint_recompute_kernel(AdjArgs a) {
         for (int k = 0; k < kMaxRounds; ++k)
             if (x.grp[k] < x.ng) a.seg[at(a, x, s - t0, x.slot[k])] = u[k];
     };
-    // the state at t1 - 1 needs t1 - 1 steps, the last segment's end one more
-    forward_steps<QM>(a, x, im, l.tabs, l.stride, l.noise, t0, last ? t1 : t1 - 1, u, sc, store);
-    store(last ? t1 : t1 - 1);
+    auto store_sums = [&](int s, int k, const float (&S)[4]) __attribute__((always_inline)) {
+        const float si = sc[k].x, ci = sc[k].y;
+        if (a.sums)
+            a.sums[at(a, x, s - t0, x.slot[k])] =
+                make_float2(si * S[0] - ci * S[1], ci * S[0] + si * S[1]);
+    };
+    const int p = forward_steps<QM>(a, x, l, t0, tend, u, sc, store, store_sums);
+    store(tend);
+    if (a.sums && tend < t1) {
+#pragma unroll
+        for (int k = 0; k < kMaxRounds; ++k) {
+            if (x.grp[k] >= x.ng) break;
+            float S[4];
+            row_sums(l.im, l.tab(p), x.first[k], x.pairs[k], S);
+            store_sums(tend, k, S);
+        }
+    }
 }
 
 // v plus the value a DPP move brings (0 where it brings none).
@@ -460,17 +490,14 @@ __device__ __forceinline__ float wave_sum63(float v) {
 // adjoint state left by the later segment in a.lam (or, for the last
 // segment, lam_T from the final phases); the adjoint state at t0 goes back
 // to a.lam.  Per-step gradient partials of the workgroup go to a.gpart.
-template <int QM, bool UNIT, bool LDSI>
+// WIDE: the sums over (s, c) are formed here, from a table of (s, c, s lam,
+// c lam); else they come from a.sums and the table holds (s lam, c lam).
+template <int QM, bool UNIT, bool LDSI, bool WIDE>
 __global__ __launch_bounds__(kMaxTB) void adjoint_segment_kernel(AdjArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float red[2][3][kMaxWaves];
     const Ctx x = make_ctx(a);
-    float4* const tabs = reinterpret_cast<float4*>(smem);
-    float4* const noise = tabs + 2 * (a.tabN + 1);
-    const Image<UNIT, LDSI> im = setup_image<UNIT, LDSI, false>(
-        a, x, reinterpret_cast<uint32_t*>(noise + (a.noise2 ? 2 : 1) * a.quads));
-    if (threadIdx.x < 2) tabs[threadIdx.x * (a.tabN + 1) + a.tabN] = make_float4(0.f, 0.f, 0.f, 0.f);
-    auto tab = [&](int p) { return tabs + (size_t)p * (a.tabN + 1); };
+    const Lds<UNIT, LDSI, WIDE> lds(a, x, smem);
     const int q = QM ? QM : a.q;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
     const int nwg = a.R * a.I;
@@ -479,27 +506,36 @@ __global__ __launch_bounds__(kMaxTB) void adjoint_segment_kernel(AdjArgs a) {
     const int t0 = sg * a.C;
     const int t1 = t0 + a.C < a.steps ? t0 + a.C : a.steps;
     uint32_t u[kMaxRounds], un[kMaxRounds];
+    float2 cs[kMaxRounds], csn[kMaxRounds];  // (csin, ccos0) of the step, !WIDE
     float lam[kMaxRounds];
-    auto load_words = [&](int step) __attribute__((always_inline)) {
+    auto load = [&](int step, bool sums) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < kMaxRounds; ++k)
-            un[k] = x.grp[k] < x.ng ? a.seg[at(a, x, step, x.slot[k])] : 0u;
+        for (int k = 0; k < kMaxRounds; ++k) {
+            un[k] = 0u;
+            csn[k] = make_float2(0.f, 0.f);
+            if (x.grp[k] >= x.ng) continue;
+            un[k] = a.seg[at(a, x, step, x.slot[k])];
+            if (!WIDE && sums) csn[k] = a.sums[at(a, x, step, x.slot[k])];
+        }
     };
     int p = 0;  // table written next
     if (sg == a.nseg - 1) {
         // lam_T from the final phases
-        load_words(t1 - t0);
+        load(t1 - t0, false);
 #pragma unroll
-        for (int k = 0; k < kMaxRounds; ++k)
-            if (x.grp[k] < x.ng)
-                tab(0)[x.slot[k]] = make_float4(sin_turn(un[k]), cos_turn(un[k]), 0.f, 0.f);
+        for (int k = 0; k < kMaxRounds; ++k) {
+            if (x.grp[k] >= x.ng) continue;
+            const float si = sin_turn(un[k]), ci = cos_turn(un[k]);
+            if constexpr (WIDE) lds.tab(0)[x.slot[k]] = make_float4(si, ci, 0.f, 0.f);
+            else lds.put(0, x.slot[k], make_float2(si, ci));
+        }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kMaxRounds; ++k) {
             lam[k] = 0.f;
             if (x.grp[k] >= x.ng) continue;
             float S[4];
-            row_sums<4, false>(im, tab(0), x.first[k], x.pairs[k], S);
+            row_sums(lds.im, lds.tab(0), x.first[k], x.pairs[k], S);
             const float si = sin_turn(un[k]), ci = cos_turn(un[k]);
             if (x.osc[k] < x.nb) lam[k] = -0.5f * (si * S[0] - ci * S[1]);
         }
@@ -509,31 +545,34 @@ __global__ __launch_bounds__(kMaxTB) void adjoint_segment_kernel(AdjArgs a) {
         for (int k = 0; k < kMaxRounds; ++k)
             lam[k] = x.grp[k] < x.ng ? a.lam[at(a, x, 0, x.slot[k])] : 0.f;
     }
-    load_words(t1 - 1 - t0);
+    load(t1 - 1 - t0, true);
     Sched sch;
     sch.load(a, (t1 - 1) >> 6);
+    // a step's wave partials, after the barrier that follows it: FP64, waves in order
+    auto flush = [&](int step, int buf) __attribute__((always_inline)) {
+        if (threadIdx.x < 3) {
+            double g = 0.0;
+            for (int w = 0; w < W; ++w) g += (double)red[buf][threadIdx.x][w];
+            a.gpart[((size_t)step * 3 + threadIdx.x) * nwg + x.wg] = g;
+        }
+    };
     for (int s = t1 - 1; s >= t0; --s) {
         if ((s >> 6) != sch.chunk) sch.load(a, s >> 6);
         float2 sc[kMaxRounds];
 #pragma unroll
         for (int k = 0; k < kMaxRounds; ++k) {
             u[k] = un[k];
+            cs[k] = csn[k];
             if (x.grp[k] >= x.ng) continue;
             sc[k] = make_float2(sin_turn(u[k]), cos_turn(u[k]));
-            tab(p)[x.slot[k]] = make_float4(sc[k].x, sc[k].y, sc[k].x * lam[k], sc[k].y * lam[k]);
+            const float sl = sc[k].x * lam[k], cl = sc[k].y * lam[k];
+            if constexpr (WIDE) lds.tab(p)[x.slot[k]] = make_float4(sc[k].x, sc[k].y, sl, cl);
+            else lds.put(p, x.slot[k], make_float2(sl, cl));
         }
-        if (s > t0) load_words(s - 1 - t0);  // their latency under this step
-        float4* nz = noise + (a.noise2 ? p * a.quads : 0);
+        if (s > t0) load(s - 1 - t0, true);  // their latency under this step
+        float4* nz = lds.noise + (a.noise2 ? p * a.quads : 0);
         draw_noise(a, x, (uint32_t)(a.step0 + s), nz);
         __syncthreads();
-        // the previous step's wave partials: FP64, waves in order
-        auto flush = [&](int step, int buf) __attribute__((always_inline)) {
-            if (threadIdx.x < 3) {
-                double g = 0.0;
-                for (int w = 0; w < W; ++w) g += (double)red[buf][threadIdx.x][w];
-                a.gpart[((size_t)step * 3 + threadIdx.x) * nwg + x.wg] = g;
-            }
-        };
         if (s + 1 < t1) flush(s + 1, p ^ 1);
         const float Kt = Sched::pick(sch.K, s), Kst = Sched::pick(sch.Ks, s);
         float gk = 0.f, gks = 0.f, gs = 0.f;
@@ -543,11 +582,13 @@ __global__ __launch_bounds__(kMaxTB) void adjoint_segment_kernel(AdjArgs a) {
             if (x.grp[k] >= x.ng) break;
             const float zk = z[x.osc[k] < x.nb ? x.osc[k] : 0];
             float S[4];
-            row_sums<4, false>(im, tab(p), x.first[k], x.pairs[k], S);
+            row_sums(lds.im, lds.tab(p), x.first[k], x.pairs[k], S);
             const float si = sc[k].x, ci = sc[k].y;
             const float l = lam[k];  // 0 past the instance's rows, and stays 0
-            const float csin = si * S[0] - ci * S[1];
-            const float ccos = ci * S[2] + si * S[3] - l * (ci * S[0] + si * S[1]);
+            const float Cl = WIDE ? S[2] : S[0], Dl = WIDE ? S[3] : S[1];
+            const float csin = WIDE ? si * S[0] - ci * S[1] : cs[k].x;
+            const float ccos0 = WIDE ? ci * S[0] + si * S[1] : cs[k].y;
+            const float ccos = ci * Cl + si * Dl - l * ccos0;
             gk = __builtin_fmaf(l, csin, gk);
             gks = __builtin_fmaf(l, sin_q<QM>(si, ci, u[k], q), gks);
             gs = __builtin_fmaf(l, zk, gs);
@@ -637,46 +678,53 @@ using AdjFn = void (*)(AdjArgs);
 constexpr size_t kAdjLdsLimit = 160 * 1024 - 1024;  // dynamic LDS next to the static reduction slots
 
 // Placement of the rows' words and the LDS a kernel needs with it: in LDS
-// when they fit next to the tables and noise buffers, else streamed from
-// global memory (OIM_ADJ_ROWS=global streams them at any size; any other
-// value leaves the choice).  The segment kernel of instances near 4096
-// oscillators has room for one noise buffer only, at one more barrier per
-// step.
+// when they fit next to the tables and noise buffers (which byte offsets of 16
+// bits then reach), else streamed from global memory (OIM_ADJ_ROWS=global
+// streams them at any size; any other value leaves the choice).  The wide
+// segment kernel of instances near 4096 oscillators has room for one noise
+// buffer only, at one more barrier per step.
 struct Placement {
     bool ldsi;
     int noise2;
     size_t lds;
 };
 
-Placement place(const Problem* p, const AdjArgs& a, bool segment) {
+Placement place(const Problem* p, const AdjArgs& a, bool wide) {
     const char* env = getenv("OIM_ADJ_ROWS");
     const bool stream = env && !strcmp(env, "global");
     const size_t noise = (size_t)a.quads * 16, img = (size_t)a.img_words * 4;
     auto tables = [&](bool ldsi) -> size_t {
-        if (segment) return (size_t)2 * (a.tabN + 1) * 16;
+        if (wide) return (size_t)2 * (a.tabN + 1) * 16;
         return ((size_t)2 * (a.tabN + 1) * 8 * (p->unit_weights && ldsi ? 2 : 1) + 15) & ~(size_t)15;
     };
-    if (!stream && tables(true) + 2 * noise + img <= kAdjLdsLimit)
+    if (!stream && tables(true) + 2 * noise + img <= kAdjLdsLimit && (wide || tables(true) <= 131072))
         return {true, 1, tables(true) + 2 * noise + img};
     if (tables(false) + 2 * noise <= kAdjLdsLimit) return {false, 1, tables(false) + 2 * noise};
     return {false, 0, tables(false) + noise};
 }
 
-#define OIM_ADJ_FNS(NAME)                                                                   \
-    AdjFn NAME##_fn(int q, bool unit, bool ldsi) {                                          \
-        static const AdjFn f[3][2][2] = {                                                   \
-            {{adjoint_##NAME##_kernel<0, false, false>, adjoint_##NAME##_kernel<0, false, true>}, \
-             {adjoint_##NAME##_kernel<0, true, false>, adjoint_##NAME##_kernel<0, true, true>}},  \
-            {{adjoint_##NAME##_kernel<2, false, false>, adjoint_##NAME##_kernel<2, false, true>}, \
-             {adjoint_##NAME##_kernel<2, true, false>, adjoint_##NAME##_kernel<2, true, true>}},  \
-            {{adjoint_##NAME##_kernel<3, false, false>, adjoint_##NAME##_kernel<3, false, true>}, \
-             {adjoint_##NAME##_kernel<3, true, false>, adjoint_##NAME##_kernel<3, true, true>}}}; \
-        return f[q == 2 ? 1 : q == 3 ? 2 : 0][unit][ldsi];                                  \
-    }
-OIM_ADJ_FNS(forward)
-OIM_ADJ_FNS(recompute)
-OIM_ADJ_FNS(segment)
+#define OIM_ADJ_FNS(NAME, ...)                                                               \
+    {{{adjoint_##NAME##_kernel<0, false, false __VA_ARGS__>,                                 \
+       adjoint_##NAME##_kernel<0, false, true __VA_ARGS__>},                                 \
+      {adjoint_##NAME##_kernel<0, true, false __VA_ARGS__>,                                  \
+       adjoint_##NAME##_kernel<0, true, true __VA_ARGS__>}},                                 \
+     {{adjoint_##NAME##_kernel<2, false, false __VA_ARGS__>,                                 \
+       adjoint_##NAME##_kernel<2, false, true __VA_ARGS__>},                                 \
+      {adjoint_##NAME##_kernel<2, true, false __VA_ARGS__>,                                  \
+       adjoint_##NAME##_kernel<2, true, true __VA_ARGS__>}},                                 \
+     {{adjoint_##NAME##_kernel<3, false, false __VA_ARGS__>,                                 \
+       adjoint_##NAME##_kernel<3, false, true __VA_ARGS__>},                                 \
+      {adjoint_##NAME##_kernel<3, true, false __VA_ARGS__>,                                  \
+       adjoint_##NAME##_kernel<3, true, true __VA_ARGS__>}}}
+const AdjFn kForward[3][2][2] = OIM_ADJ_FNS(forward);
+const AdjFn kRecompute[3][2][2] = OIM_ADJ_FNS(recompute);
+const AdjFn kSegment[3][2][2] = OIM_ADJ_FNS(segment, , false);
+const AdjFn kSegmentWide[3][2][2] = OIM_ADJ_FNS(segment, , true);
 #undef OIM_ADJ_FNS
+
+AdjFn pick_fn(const AdjFn (&f)[3][2][2], const Problem* p, int q, bool ldsi) {
+    return f[q == 2 ? 1 : q == 3 ? 2 : 0][p->unit_weights][ldsi];
+}
 
 int launch_adj(AdjFn fn, size_t lds, int grid, int threads, hipStream_t stream, const AdjArgs& a,
                const char* what) {
@@ -801,7 +849,8 @@ int launch_adjoint_forward(Problem* p, const oim_adjoint_cfg* cfg, const float* 
     a.thetaT = thetaT;
     a.loss = loss;
     const Placement pl = place(p, a, false);
-    return launch_adj(forward_fn(cfg->q, p->unit_weights, pl.ldsi), pl.lds, cfg->R * p->n_inst,
+    a.noise2 = 1;
+    return launch_adj(pick_fn(kForward, p, cfg->q, pl.ldsi), pl.lds, cfg->R * p->n_inst,
                       block_threads(a), stream, a, "adjoint_forward_kernel");
 }
 
@@ -856,19 +905,33 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     const size_t seg_bytes = up((size_t)(cfg->checkpoint_every + 1) * cfg->R * a.P * sizeof(uint32_t));
     const size_t lam_bytes = up((size_t)cfg->R * a.P * sizeof(float));
     const size_t part_bytes = (size_t)cfg->steps * nwg * 3 * sizeof(double);
-    const size_t need = 2 * seg_bytes + lam_bytes + part_bytes + 256;
-    if (p->adj_bytes < need) {
+    const size_t sums_bytes = up((size_t)cfg->checkpoint_every * cfg->R * a.P * sizeof(float2));
+    // The recomputation's row sums are kept where they take a small part of
+    // the card, else (or when they cannot be had) the adjoint forms them
+    // again: 128 x G(2000, 10/1999), C = 64 (0.27 GB): a segment of the adjoint
+    // 182 us with them, 221 without; its recomputation 158 and 150.
+    const size_t base = 2 * seg_bytes + lam_bytes + part_bytes + 256;
+    bool keep = 2 * sums_bytes <= ((size_t)8 << 30);
+    for (;;) {
+        const size_t need = base + (keep ? 2 * sums_bytes : 0);
+        if (p->adj_bytes >= need) break;
         (void)hipFree(p->d_adj);
         p->d_adj = nullptr;
         p->adj_bytes = 0;
         const hipError_t e = hipMalloc(&p->d_adj, need);
-        if (e != hipSuccess) {
-            p->d_adj = nullptr;
-            return e == hipErrorOutOfMemory
-                       ? set_error(OIM_E_NOMEM, "adjoint workspace: out of device memory")
-                       : hip_error(e, "adjoint workspace");
+        if (e == hipSuccess) {
+            p->adj_bytes = need;
+            break;
         }
-        p->adj_bytes = need;
+        p->d_adj = nullptr;
+        if (e == hipErrorOutOfMemory && keep) {
+            (void)hipGetLastError();
+            keep = false;
+            continue;
+        }
+        return e == hipErrorOutOfMemory
+                   ? set_error(OIM_E_NOMEM, "adjoint workspace: out of device memory")
+                   : hip_error(e, "adjoint workspace");
     }
     int st = adjoint_streams(p);
     if (st) return st;
@@ -877,10 +940,10 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     a.ckpt = const_cast<uint32_t*>(ckpt);
     a.lam = reinterpret_cast<float*>(w + 2 * seg_bytes);
     a.gpart = reinterpret_cast<double*>(w + 2 * seg_bytes + lam_bytes);
-    const Placement prec = place(p, a, false), padj = place(p, a, true);
-    const AdjFn frec = recompute_fn(cfg->q, p->unit_weights, prec.ldsi);
-    const AdjFn fadj = segment_fn(cfg->q, p->unit_weights, padj.ldsi);
-    a.noise2 = padj.noise2;
+    unsigned char* sums = w + base;
+    const Placement prec = place(p, a, false), padj = place(p, a, !keep);
+    const AdjFn frec = pick_fn(kRecompute, p, cfg->q, prec.ldsi);
+    const AdjFn fadj = pick_fn(keep ? kSegment : kSegmentWide, p, cfg->q, padj.ldsi);
     const int tb = block_threads(a);
     hipStream_t side = p->adj_stream;
     hipEvent_t* start = &p->adj_ev[0];
@@ -893,12 +956,15 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
         const int buf = sg & 1;
         a.cur_seg = sg;
         a.seg = segbuf[buf];
+        a.sums = keep ? reinterpret_cast<float2*>(sums + buf * sums_bytes) : nullptr;
+        a.noise2 = 1;
         if (sg + 2 <= a.nseg - 1 && (e = hipStreamWaitEvent(side, adj[buf], 0)) != hipSuccess)
             return hip_error(e, "adjoint buffer wait");
         if ((st = launch_adj(frec, prec.lds, nwg, tb, side, a, "adjoint_recompute_kernel"))) break;
         if ((e = hipEventRecord(rec[buf], side)) != hipSuccess ||
             (e = hipStreamWaitEvent(stream, rec[buf], 0)) != hipSuccess)
             return hip_error(e, "adjoint segment order");
+        a.noise2 = padj.noise2;
         if ((st = launch_adj(fadj, padj.lds, nwg, tb, stream, a, "adjoint_segment_kernel"))) break;
         if ((e = hipEventRecord(adj[buf], stream)) != hipSuccess)
             return hip_error(e, "adjoint segment order");

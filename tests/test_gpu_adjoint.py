@@ -303,3 +303,62 @@ def test_adjoint_row_placements_give_identical_bits(oim, dev, monkeypatch):
     for mode in ("csr", "global"):
         for a, b in zip(outs[""], outs[mode]):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("weights", ["unit", "real"])
+@pytest.mark.parametrize("sizes", [[1, 63, 64, 65], [1100, 1024, 2050]])
+def test_adjoint_sorted_rows_match_oracle(oim, orc, dev, monkeypatch, weights, sizes):
+    # rows sorted by length in groups of 64 dealt to up to sixteen waves, one to
+    # three per wave here: ragged groups, isolated oscillators, rows of very
+    # different length; in LDS and streamed from global memory, bit for bit
+    rng = np.random.default_rng(len(sizes))
+    graphs = []
+    for n in sizes:
+        m = 3 * n
+        a = np.minimum(rng.integers(0, n, m), rng.integers(0, n, m))  # long rows at low indices
+        b = rng.integers(0, n, m)
+        pairs = np.unique(np.stack([np.minimum(a, b), np.maximum(a, b)], 1)[a != b], axis=0)
+        w = np.ones(len(pairs)) if weights == "unit" else rng.standard_normal(len(pairs))
+        w *= rng.choice([-1.0, 1.0], len(pairs))
+        graphs.append(synth.csr_from_edges(n, pairs[:, 0], pairs[:, 1], w))
+    big, off = synth.block_diagonal(graphs)
+    J = -big.w
+    steps, R, C = 30, 2, 11
+    K, Ks, sg = _schedules(steps)
+    K = (K / 4.0).astype(np.float32)
+    th0 = synth.theta0(R, big.n, seed=8)
+    sd = synth.seeds(R, 2)
+    with oim.Problem.from_csr_blocks(big.n, big.row_ptr, big.col, J.astype(np.float32),
+                                     off) as prob:
+        monkeypatch.delenv("OIM_ADJ_ROWS", raising=False)
+        got = _gpu_adjoint(oim, prob, th0, K, Ks, sg, sd, 2, C)
+        monkeypatch.setenv("OIM_ADJ_ROWS", "global")
+        for a, b in zip(_gpu_adjoint(oim, prob, th0, K, Ks, sg, sd, 2, C), got):
+            np.testing.assert_array_equal(a, b)
+    loss, thT, gK, gKs, gS = got
+    L, oK, oKs, oS = orc.adjoint_csr(big.row_ptr, big.col, J.astype(np.float64),
+                                     th0.astype(np.float64), q=2, dt=DT, K=K, Ks=Ks, sigma=sg,
+                                     seeds=sd, inst_off=off)
+    assert loss.sum() == pytest.approx(L, rel=1e-5)
+    for g, ref, name in ((gK, oK, "K"), (gKs, oKs, "Ks"), (gS, oS, "sigma")):
+        ok, rel = _close_vec(g, ref, 1e-4)
+        print(f"{weights} {sizes} d/d{name}: max rel err {rel:.2e}")
+        assert ok, (name, rel)
+
+
+@pytest.mark.parametrize("n,R", [(40, 4096), (4096, 256)])
+def test_adjoint_long_segments_same_bits(oim, dev, n, R):
+    # row sums of a segment above 8 GiB are formed again instead of kept
+    # (n = 4096: with one noise buffer); shorter segments keep them, and every
+    # interval gives the same bits
+    g = synth.torus(n // 8, 8, seed=3)
+    steps = 520
+    K, Ks, sg = _schedules(steps)
+    th0 = synth.theta0(R, n, seed=2)
+    sd = synth.seeds(R, 1)
+    with oim.Problem.from_csr(n, g.row_ptr, g.col, (-g.w).astype(np.float32)) as prob:
+        ref = _gpu_adjoint(oim, prob, th0, K, Ks, sg, sd, 2, 130)
+        out = _gpu_adjoint(oim, prob, th0, K, Ks, sg, sd, 2, 520)
+    for a, b in zip(out, ref):
+        assert np.all(np.isfinite(a))
+        np.testing.assert_array_equal(a, b)
