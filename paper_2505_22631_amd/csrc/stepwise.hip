@@ -2,9 +2,10 @@
 // kernel per Euler-Maruyama step, for replicas too large for the
 // LDS-resident kernel.
 //
-// Layout: replica index fastest, [n][Rp] (Rp = R rounded up to 64), two
-// buffers of phase words (ping-pong: step s reads buffer s % 2 and writes
-// buffer (s + 1) % 2, which keeps the synchronous update of Algorithm 1).
+// Layout: replica index fastest, [n][Rp] (Rp = R rounded up to 64, below 64 to
+// a power of two, 4 at least), two buffers of phase words (ping-pong: step s
+// reads buffer s % 2 and writes buffer (s + 1) % 2, which keeps the
+// synchronous update of Algorithm 1).
 // The state is the phase word alone (4 bytes per oscillator and replica):
 // the (sin, cos) of a neighbour is recomputed from its word where it is
 // gathered, the same function of the same word as anywhere else, so the
@@ -12,7 +13,8 @@
 // (4 consecutive oscillators) and 64 replicas: CSR entries are wave-uniform
 // (scalar loads) and each neighbour gather is one coalesced 256-byte load.
 // Lane r draws the quad's four normals with one Philox call keyed by replica
-// r's seed.
+// r's seed.  With fewer than 33 replicas a wave takes 64 / Rp quads, the lanes
+// of a quad reading the same entries (stepwise_packed_kernel).
 //
 // The step loop is a hipGraph of `chunk` step kernels plus a node that
 // advances a device-resident step base; the executable graph is replayed
@@ -71,6 +73,7 @@ struct StepArgs {
     const CallArgs* call;
     int k;                // position of this node in the chunk
     int n, R, Rp, q;
+    int lr_shift;         // Rp = 1 << lr_shift (packed kernel)
     int gx;               // quad blocks (workgroups per replica block)
 };
 
@@ -95,6 +98,20 @@ __device__ __forceinline__ void step_block(int b, int nb, int gx, int& qb, int& 
 template <typename T>
 __device__ __forceinline__ const __attribute__((address_space(1))) T* global_ptr(const T* p) {
     return (const __attribute__((address_space(1))) T*)p;
+}
+
+// The new phase word of one oscillator from its own word u, its sums A = sum J
+// c_j and B = sum J s_j, the step's coefficients and its normal z.  The
+// multiply-adds are written out, so both step kernels round alike.
+template <int QM>
+__device__ __forceinline__ uint32_t step_word(uint32_t u, float A, float B, float kc, float ks,
+                                              float ns, float z, int q) {
+#pragma clang fp contract(off)
+    const float os = sin_turn(u), oc = cos_turn(u);
+    const float coup = __builtin_fmaf(os, A, -(oc * B));
+    const float sq = QM == 3 ? os * __builtin_fmaf(-4.0f * os, os, 3.0f) : sin_q<QM>(os, oc, u, q);
+    const float drift = __builtin_fmaf(ks, sq, kc * coup);
+    return advance(u, __builtin_fmaf(ns, z, drift));
 }
 
 // One Euler-Maruyama step of one quad for 64 replicas per wave.  ELL: the
@@ -334,11 +351,118 @@ __global__ __launch_bounds__(256) void stepwise_step_kernel(StepArgs a) {
     for (int j = 0; j < 4; ++j) {
         const int i = 4 * m + j;
         if (i >= a.n) break;
-        const float os = sin_turn(u0[j]), oc = cos_turn(u0[j]);
-        const float A = A0[j] + A1[j], B = B0[j] + B1[j];
-        const float coup = os * A - oc * B;
-        const float drift = kc * coup + ks * sin_q<QM>(os, oc, u0[j], q);
-        store_word(i, advance(u0[j], __builtin_fmaf(ns, z[j], drift)));
+        store_word(i, step_word<QM>(u0[j], A0[j] + A1[j], B0[j] + B1[j], kc, ks, ns, z[j], q));
+    }
+}
+
+// Four consecutive entries from any entry on, one 16-byte load.
+template <typename T>
+struct __attribute__((packed, aligned(4))) Four {
+    T v[4];
+};
+
+// The same step with fewer than 33 replicas: a wave holds 64 / Rp quads (Rp a
+// power of two), lane l replica l % Rp of quad l / Rp, so that no lane is left
+// without a replica (at 64 lanes per quad one replica used one lane in 64).
+// The lanes of a quad load the same entries; the sums and the update are
+// those of the kernel above, operation for operation.  A quad gets four lanes
+// at least: with one, a wave's 64 quads scatter its entry loads (n = 50000 of
+// degree 6, real weights, one replica: 64 steps 934 us, with four 757).  Whole
+// solves of 100 steps with two readouts on a 200 x 300 torus, 64 lanes per
+// quad before and now: 1936 -> 474 us (one replica), 1979 -> 632 (8), 1970 ->
+// 854 (16), 1976 -> 1101 (32); n = 50000 of degree 6, 64 steps, 2377 -> 757 (4
+// replicas), 2346 -> 1239 (32).  Bound by the latency of two dependent batches
+// of loads (words and entries, then neighbours' words) and by the launches.
+template <int QM, bool ELL>
+__global__ __launch_bounds__(256) void stepwise_packed_kernel(StepArgs a) {
+    const int Rp = a.Rp, shift = a.lr_shift, q = QM ? QM : a.q;
+    const int t0 = blockIdx.x * 256 + threadIdx.x;
+    const int m = t0 >> shift, r = t0 & (Rp - 1);
+    if (4 * (int64_t)m >= a.n) return;
+    const int rs = r < a.R ? r : a.R - 1;  // padding lanes borrow a replica's entries
+    const CallArgs& c = *a.call;
+    const int s_node = c.base + a.k;
+    if (s_node >= c.steps) return;
+    auto word = [&](int row) -> uint32_t { return a.Uin[((uint32_t)row << shift) + r]; };
+    uint32_t u0[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u0[j] = word(4 * m + j);
+    int64_t eb[4];
+    int len[4], lmax = a.ell_D;
+    if constexpr (!ELL) {
+        int64_t rp[5];  // row_ptr carries 4 entries of padding (empty rows)
+        lmax = 0;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) rp[j] = a.row_ptr[4 * m + j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            eb[j] = rp[j];
+            len[j] = (int)(rp[j + 1] - rp[j]);
+            lmax = len[j] > lmax ? len[j] : lmax;
+        }
+    }
+    const uint32_t t = (uint32_t)(c.step0 + s_node);
+    const int64_t so = (int64_t)rs * c.sched_stride + s_node;
+    const float Kv = global_ptr(c.K)[so], Ksv = global_ptr(c.Ks)[so], sgv = global_ptr(c.sigma)[so];
+    const uint64_t seed = global_ptr(c.seeds)[rs];
+    float A0[4], B0[4], A1[4], B1[4], z[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) A0[j] = B0[j] = A1[j] = B1[j] = 0.f;
+    for (int g = 0; g < lmax || g == 0; g += 4) {
+        // group g of the quad's four rows (past a row's end: weight 0)
+        int ci[4][4];
+        float w[4][4];
+        if constexpr (ELL) {
+            const size_t at = (size_t)m * a.ell_D + g;  // 16-byte units
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int4 cv = reinterpret_cast<const int4*>(a.col)[at + j];
+                const float4 wv = reinterpret_cast<const float4*>(a.J)[at + j];
+                ci[j][0] = cv.x; ci[j][1] = cv.y; ci[j][2] = cv.z; ci[j][3] = cv.w;
+                w[j][0] = wv.x; w[j][1] = wv.y; w[j][2] = wv.z; w[j][3] = wv.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int64_t base = eb[j] + g < a.nnz ? eb[j] + g : a.nnz;
+                const Four<int32_t> cv = *reinterpret_cast<const Four<int32_t>*>(a.col + base);
+                const Four<float> wv = *reinterpret_cast<const Four<float>*>(a.J + base);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    ci[j][h] = cv.v[h];
+                    w[j][h] = g + h < len[j] ? wv.v[h] : 0.f;
+                }
+            }
+        }
+        uint32_t p[4][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) p[j][h] = word(ci[j][h]);
+        if (g == 0) {
+            // the quad's normals while the neighbours' words are in flight
+            normals4((uint32_t)m, t, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), z);
+            asm volatile("" ::"v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]) : "memory");
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int h = 0; h < 4; h += 2) {
+                A0[j] = __builtin_fmaf(w[j][h], cos_turn(p[j][h]), A0[j]);
+                B0[j] = __builtin_fmaf(w[j][h], sin_turn(p[j][h]), B0[j]);
+                A1[j] = __builtin_fmaf(w[j][h + 1], cos_turn(p[j][h + 1]), A1[j]);
+                B1[j] = __builtin_fmaf(w[j][h + 1], sin_turn(p[j][h + 1]), B1[j]);
+            }
+    }
+    const float kc = -c.dt * Kv * kTurnScale;
+    const float ks = -c.dt * Ksv * kTurnScale;
+    const float ns = sgv * __builtin_sqrtf(c.dt) * kTurnScale;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int i = 4 * m + j;
+        if (i >= a.n) break;
+        a.Uout[((uint32_t)i << shift) + r] =
+            step_word<QM>(u0[j], A0[j] + A1[j], B0[j] + B1[j], kc, ks, ns, z[j], q);
     }
 }
 
@@ -346,34 +470,67 @@ __global__ void advance_base_kernel(CallArgs* call, int chunk) { call->base += c
 
 __global__ void set_call_kernel(CallArgs* call, CallArgs v) { *call = v; }
 
-// [R][n] theta or phase words -> [np][Rp] phase words (both buffers, so the
-// padding rows and replicas hold defined words everywhere).
+// [R][n] theta or phase words <-> [np][Rp] phase words, through LDS in tiles of
+// 64 rows x 64 (or Rp) replicas so that both sides are read and written in
+// runs (a thread per element, with one side at a stride, took 25 us in and 53
+// out for 60000 x 64).
+constexpr int kTile = 64;
+
+// Tile of a workgroup: first row and first replica (a one-dimensional grid,
+// row tiles first; the other grid dimensions are too short for many replicas).
+__device__ __forceinline__ void tile_of(int np, int& i0, int& r0) {
+    const int tiles = (np + kTile - 1) / kTile;
+    i0 = (int)(blockIdx.x % tiles) * kTile;
+    r0 = (int)(blockIdx.x / tiles) * kTile;
+}
+
+// Fills buffer 0 and, in buffer 1, the padding rows alone: the first step
+// writes the others.  Padding rows and replicas hold 0.
 __global__ __launch_bounds__(256) void stepwise_init_kernel(const float* theta, const uint32_t* phase,
                                                             uint32_t* U0, uint32_t* U1,
                                                             int n, int R, int np, int Rp) {
-    const size_t total = (size_t)np * Rp;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (size_t)gridDim.x * blockDim.x) {
-        const int i = (int)(e / Rp), r = (int)(e % Rp);
+    __shared__ uint32_t tile[kTile][kTile + 1];
+    int i0, r0;
+    tile_of(np, i0, r0);
+    const int lr = Rp < kTile ? Rp : kTile;
+    const int lane = threadIdx.x & 63;
+    for (int r = threadIdx.x >> 6; r < lr; r += 4) {
+        const int i = i0 + lane;
         uint32_t u = 0;
-        if (i < n && r < R) {
-            const size_t src = (size_t)r * n + i;
+        if (i < n && r0 + r < R) {
+            const size_t src = (size_t)(r0 + r) * n + i;
             u = phase ? phase[src] : phase_from_theta(theta[src]);
         }
-        U0[e] = u;
-        U1[e] = u;
+        tile[lane][r] = u;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < kTile * lr; e += 256) {
+        const int row = e / lr, r = e % lr, i = i0 + row;
+        if (i >= np) break;
+        const size_t o = (size_t)i * Rp + r0 + r;
+        U0[o] = tile[row][r];
+        if (i >= n) U1[o] = 0;
     }
 }
 
 __global__ __launch_bounds__(256) void stepwise_final_kernel(const uint32_t* U, float* theta,
                                                              uint32_t* phase, int n, int R, int Rp) {
-    const size_t total = (size_t)R * n;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (size_t)gridDim.x * blockDim.x) {
-        const int r = (int)(e / n), i = (int)(e % n);
-        const uint32_t u = U[(size_t)i * Rp + r];
-        theta[e] = theta_from_phase(u);
-        if (phase) phase[e] = u;
+    __shared__ uint32_t tile[kTile][kTile + 1];
+    int i0, r0;
+    tile_of(n, i0, r0);
+    const int lr = Rp < kTile ? Rp : kTile;
+    const int lane = threadIdx.x & 63;
+    for (int e = threadIdx.x; e < kTile * lr; e += 256) {
+        const int row = e / lr, r = e % lr;
+        if (i0 + row < n) tile[row][r] = U[(size_t)(i0 + row) * Rp + r0 + r];
+    }
+    __syncthreads();
+    const int i = i0 + lane;
+    if (i >= n) return;
+    for (int r = threadIdx.x >> 6; r < lr && r0 + r < R; r += 4) {
+        const size_t dst = (size_t)(r0 + r) * n + i;
+        theta[dst] = theta_from_phase(tile[lane][r]);
+        if (phase) phase[dst] = tile[lane][r];
     }
 }
 
@@ -382,45 +539,77 @@ struct ReadArgs {
     const int32_t* col;
     const float* J;
     const uint32_t* U;
-    double* part;  // [gridDim.x][Rp]
+    double* part;  // [gridDim.x][Rp] sums of a block of rows
     const CallArgs* call;
     int k;         // node position in the chunk, or -1: after the last step
     int n, Rp, q;
 };
 
-// Partial sums of sum_{i<j} J_ij term(k_i, k_j) per block of 16 rows (four
-// quads, one per wave) and replica (term = s_i s_j for q = 2, delta(k_i, k_j)
-// for q >= 3), in the library's fixed FP64 order: each row over j > i in
-// column order, a quad's rows as (r0 + r1) + (r2 + r3), the block's quads as
-// (w0 + w1) + (w2 + w3) -- the pairwise tree over the block's rows.
+// Partial sums of sum_{i<j} J_ij term(k_i, k_j) per block of rows and replica
+// (term = s_i s_j for q = 2, delta(k_i, k_j) for q >= 3), in the library's
+// fixed FP64 order: each row over j > i in column order, a quad's rows as (r0
+// + r1) + (r2 + r3), a thread's kReadQuads consecutive quads and then the
+// block's threads pairwise -- the pairwise tree over the block's rows.  A
+// thread is one replica of its quads: 64 replicas make blocks of 64 rows, one
+// replica of 4096.
+constexpr int kReadQuads = 4;
+
+// Blocks of rows of a readout.
+int read_blocks(int quads, int Rp) {
+    const int per = kReadQuads * (256 / (Rp < 64 ? Rp : 64));
+    return (quads + per - 1) / per;
+}
+
 __global__ __launch_bounds__(256) void stepwise_readout_kernel(ReadArgs a) {
-    __shared__ double red[kQuadsPerBlock][64];
+    __shared__ double red[256];
     const int steps = a.call->steps;
     const int s = a.k < 0 ? steps - 1 : a.call->base + a.k;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r = blockIdx.y * 64 + lane;
-    double rs[4] = {0.0, 0.0, 0.0, 0.0};
-    if (s < steps) {
-        const int m = blockIdx.x * kQuadsPerBlock + wave;
+    if (s >= steps) return;
+    const int lr = a.Rp < 64 ? a.Rp : 64, slots = 256 / lr;
+    const int slot = threadIdx.x / lr, r = blockIdx.y * 64 + threadIdx.x % lr;
+    auto state = [&](int row) { return nearest_state(a.U[(size_t)row * a.Rp + r], a.q); };
+    double v[kReadQuads];
+#pragma unroll
+    for (int x = 0; x < kReadQuads; ++x) {
+        const int m = (blockIdx.x * slots + slot) * kReadQuads + x;
+        double rs[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = 4 * m + j;
-            if (i >= a.n) break;
-            const int ci = nearest_state(a.U[(size_t)i * a.Rp + r], a.q);
+            if (i >= a.n) continue;
+            const int ci = state(i);
+            const int64_t e1 = a.row_ptr[i + 1];
             double acc = 0.0;
-            for (int64_t e = a.row_ptr[i]; e < a.row_ptr[i + 1]; ++e) {
-                const int c = a.col[e];
-                if (c <= i) continue;
-                const int cj = nearest_state(a.U[(size_t)c * a.Rp + r], a.q);
-                const double w = (double)a.J[e];
-                acc += (a.q == 2) ? (ci == cj ? w : -w) : (ci == cj ? w : 0.0);
+            // four entries at a time, their words in flight together
+            for (int64_t e = a.row_ptr[i]; e < e1; e += 4) {
+                int c[4], k[4];
+                float w[4];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const int64_t ee = e + h < e1 ? e + h : e1 - 1;
+                    c[h] = a.col[ee];
+                    w[h] = a.J[ee];
+                }
+#pragma unroll
+                for (int h = 0; h < 4; ++h) k[h] = state(c[h]);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const double wd = (double)w[h];
+                    const double term = a.q == 2 ? (ci == k[h] ? wd : -wd) : (ci == k[h] ? wd : 0.0);
+                    acc += e + h < e1 && c[h] > i ? term : 0.0;
+                }
             }
             rs[j] = acc;
         }
+        v[x] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
     }
-    red[wave][lane] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
+    red[threadIdx.x] = (v[0] + v[1]) + (v[2] + v[3]);
     __syncthreads();
-    if (wave == 0 && s < steps)
-        a.part[(size_t)blockIdx.x * a.Rp + r] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    for (int d = 1; d < slots; d <<= 1) {
+        if ((slot & (2 * d - 1)) == 0) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + d * lr];
+        __syncthreads();
+    }
+    if (slot == 0) a.part[(size_t)blockIdx.x * a.Rp + r] = red[threadIdx.x];
 }
 
 struct BestArgs {
@@ -435,7 +624,7 @@ struct BestArgs {
 };
 
 // One workgroup per replica: H = -(the pairwise tree over the blocks'
-// partials), trace entry, best-so-far and the colours of a new best.  The
+// partials), trace entry and best-so-far.  The
 // partials, zero-padded to a power of two P, are taken in rounds of
 // CH = min(P, 4096) values; in a round each of the 256 threads folds an
 // aligned chunk of CH / 256 (at most 16) values by the pairwise tree in
@@ -443,7 +632,6 @@ struct BestArgs {
 // pushes the round's sum into a tree over rounds.  This is the pairwise tree
 // over the padded sequence (padding zeros add exactly).
 __global__ __launch_bounds__(256) void stepwise_best_kernel(BestArgs a) {
-    __shared__ int improved;
     __shared__ double sums[256];
     __shared__ double stack[TreeAcc::kLevels];
     const CallArgs& c = *a.call;
@@ -481,16 +669,43 @@ __global__ __launch_bounds__(256) void stepwise_best_kernel(BestArgs a) {
         const double H = -outer.finish();
         const int kread = (s + a.M) / a.M - 1;
         if (c.trace) c.trace[(size_t)kread * a.R + r] = H;
-        improved = (kread == 0 || H < a.best[r]) ? 1 : 0;
-        if (improved) {
+        if (kread == 0 || H < a.best[r]) {
             a.best[r] = H;
             a.best_at[r] = (int32_t)(c.step0 + s + 1);
         }
     }
+}
+
+// The colours of the replicas whose best is this readout's (best_at names its
+// step), in tiles through LDS as the kernels above; tiles without one end at
+// once.  (One workgroup per replica reading its words at a stride of Rp took
+// most of a 98 us readout of 60000 x 64.)
+__global__ __launch_bounds__(256) void stepwise_colour_kernel(BestArgs a) {
+    __shared__ int8_t tile[kTile][kTile + 1];
+    __shared__ int any;
+    const CallArgs& c = *a.call;
+    const int s = a.k < 0 ? c.steps - 1 : c.base + a.k;
+    if (s >= c.steps || !c.best_colour) return;
+    const int32_t now = (int32_t)(c.step0 + s + 1);
+    int i0, r0;
+    tile_of(a.n, i0, r0);
+    const int lr = a.Rp < kTile ? a.Rp : kTile;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) any = 0;
     __syncthreads();
-    if (improved && c.best_colour)
-        for (int i = threadIdx.x; i < a.n; i += blockDim.x)
-            c.best_colour[(size_t)r * a.n + i] = (int8_t)nearest_state(a.U[(size_t)i * a.Rp + r], a.q);
+    if (threadIdx.x < lr && r0 + threadIdx.x < a.R && a.best_at[r0 + threadIdx.x] == now) any = 1;
+    __syncthreads();
+    if (!any) return;
+    for (int e = threadIdx.x; e < kTile * lr; e += 256) {
+        const int row = e / lr, r = e % lr;
+        if (i0 + row < a.n)
+            tile[row][r] = (int8_t)nearest_state(a.U[(size_t)(i0 + row) * a.Rp + r0 + r], a.q);
+    }
+    __syncthreads();
+    const int i = i0 + lane;
+    if (i >= a.n) return;
+    for (int r = threadIdx.x >> 6; r < lr && r0 + r < a.R; r += 4)
+        if (a.best_at[r0 + r] == now) c.best_colour[(size_t)(r0 + r) * a.n + i] = tile[lane][r];
 }
 
 int check_launch(const char* what) {
@@ -548,7 +763,7 @@ void stepwise_release(Problem* p) {
 namespace {
 
 struct Shape {
-    int n, R, steps, M, Rp, quads, np, gx, chunk;
+    int n, R, steps, M, Rp, quads, np, gx, rblocks, chunk;
     size_t cells, args_off, bytes;
 };
 
@@ -559,17 +774,24 @@ Shape shape_of(const Problem* p, const oim_run_cfg* cfg) {
     sh.steps = cfg->steps;
     sh.M = cfg->readout_every;
     sh.Rp = (sh.R + 63) / 64 * 64;
+    if (sh.R < 64)
+        for (sh.Rp = 4; sh.Rp < sh.R;) sh.Rp *= 2;
     sh.quads = (sh.n + 3) / 4;
     sh.np = sh.quads * 4;
     sh.gx = (sh.quads + kQuadsPerBlock - 1) / kQuadsPerBlock;
+    sh.rblocks = read_blocks(sh.quads, sh.Rp);
     sh.cells = (size_t)sh.np * sh.Rp;
     // chunk: a multiple of the readout period, about 64 steps
     int chunk = std::min(sh.steps, 64);
     if (sh.M > 0) chunk = std::max(1, (std::min(sh.steps, std::max(64, sh.M)) / sh.M)) * sh.M;
     sh.chunk = std::max(1, std::min(chunk, sh.steps));
-    sh.args_off = (sh.cells * (4 + 4) + (size_t)sh.gx * sh.Rp * 8 + (size_t)sh.R * 12 + 255) &
+    sh.args_off = (sh.cells * (4 + 4) + (size_t)sh.rblocks * sh.Rp * 8 + (size_t)sh.R * 12 + 255) &
                   ~(size_t)255;
-    sh.bytes = sh.args_off + 256;
+    // the workspace is sized for whole waves of replicas at any R, as the
+    // allocation-free entry point's limit is stated
+    const size_t rp64 = (size_t)(sh.R + 63) / 64 * 64;
+    sh.bytes = (((size_t)sh.np * rp64 * (4 + 4) + (size_t)sh.gx * rp64 * 8 + (size_t)sh.R * 12 + 255) &
+                ~(size_t)255) + 256;
     return sh;
 }
 
@@ -583,7 +805,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
                  bool graph) {
     const Shape sh = shape_of(p, cfg);
     const int n = sh.n, R = sh.R, steps = sh.steps, M = sh.M, Rp = sh.Rp, np = sh.np, gx = sh.gx;
-    const int chunk = sh.chunk;
+    const int chunk = sh.chunk, rblocks = sh.rblocks;
     const size_t cells = sh.cells, args_off = sh.args_off;
     if (graph && !p->step_plans) {
         p->step_plans = new (std::nothrow) PlanCache();
@@ -593,7 +815,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     uint32_t* U0 = reinterpret_cast<uint32_t*>(w);
     uint32_t* U1 = U0 + cells;
     double* part = reinterpret_cast<double*>(U1 + cells);
-    double* best = part + (size_t)gx * Rp;
+    double* best = part + (size_t)rblocks * Rp;
     int32_t* best_at = reinterpret_cast<int32_t*>(best + R);
     CallArgs* call = reinterpret_cast<CallArgs*>(w + args_off);
 
@@ -613,8 +835,9 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     hipLaunchKernelGGL(set_call_kernel, dim3(1), dim3(1), 0, stream, call, ca);
     int st = check_launch("set_call_kernel");
     if (st) return st;
-    hipLaunchKernelGGL(stepwise_init_kernel, dim3(2048), dim3(256), 0, stream, theta, phase, U0, U1,
-                       n, R, np, Rp);
+    const dim3 tiles((unsigned)(((np + kTile - 1) / kTile) * ((Rp + kTile - 1) / kTile)));
+    hipLaunchKernelGGL(stepwise_init_kernel, tiles, dim3(256), 0, stream, theta, phase, U0, U1, n, R,
+                       np, Rp);
     if ((st = check_launch("stepwise_init_kernel"))) return st;
 
     using StepFn = void (*)(StepArgs);
@@ -633,7 +856,17 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
           stepwise_step_kernel<3, true, false>},
          {stepwise_step_kernel<0, true, true>, stepwise_step_kernel<2, true, true>,
           stepwise_step_kernel<3, true, true>}}};
-    StepFn fn = kStep[ell][buf][cfg->q == 2 ? 1 : cfg->q == 3 ? 2 : 0];
+    static const StepFn kPacked[2][3] = {
+        {stepwise_packed_kernel<0, false>, stepwise_packed_kernel<2, false>,
+         stepwise_packed_kernel<3, false>},
+        {stepwise_packed_kernel<0, true>, stepwise_packed_kernel<2, true>,
+         stepwise_packed_kernel<3, true>}};
+    const int qi = cfg->q == 2 ? 1 : cfg->q == 3 ? 2 : 0;
+    const bool packed = Rp < 64;
+    StepFn fn = packed ? kPacked[ell][qi] : kStep[ell][buf][qi];
+    const int64_t lanes = (int64_t)sh.quads * Rp;  // packed: a lane per quad and replica
+    const dim3 step_grid(packed ? (unsigned)((lanes + 255) / 256) : (unsigned)(gx * (Rp / 64)));
+    const dim3 read_grid(rblocks, (Rp + 63) / 64);
     StepArgs sa{};
     sa.row_ptr = p->d_row_ptr;
     sa.col = ell ? p->d_ell_col : p->d_col;
@@ -646,6 +879,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     sa.R = R;
     sa.Rp = Rp;
     sa.q = cfg->q;
+    for (sa.lr_shift = 0; packed && (1 << sa.lr_shift) < Rp;) ++sa.lr_shift;
     sa.gx = gx;
     // the state after local step s is in buffer (s + 1) % 2; after the run,
     // in buffer steps % 2
@@ -653,7 +887,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     ReadArgs ra{p->d_row_ptr, p->d_col, p->d_J, Ufinal, part, call, 0, n, Rp, cfg->q};
     BestArgs ba{};
     ba.part = part;
-    ba.nblocks = gx;
+    ba.nblocks = rblocks;
     ba.U = Ufinal;
     ba.best = best;
     ba.best_at = best_at;
@@ -676,16 +910,18 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
             ra.U = sa.Uout;
             ba.U = sa.Uout;
             sa.k = k;
-            hipLaunchKernelGGL(fn, dim3(gx * (Rp / 64)), dim3(256), 0, s, sa);
+            hipLaunchKernelGGL(fn, step_grid, dim3(256), 0, s, sa);
             int rc = check_launch("stepwise_step_kernel");
             if (rc) return rc;
             if (M > 0 && (k + 1) % M == 0) {
                 ra.k = k;
-                hipLaunchKernelGGL(stepwise_readout_kernel, dim3(gx, Rp / 64), dim3(256), 0, s, ra);
+                hipLaunchKernelGGL(stepwise_readout_kernel, read_grid, dim3(256), 0, s, ra);
                 if ((rc = check_launch("stepwise_readout_kernel"))) return rc;
                 ba.k = k;
                 hipLaunchKernelGGL(stepwise_best_kernel, dim3(R), dim3(256), 0, s, ba);
                 if ((rc = check_launch("stepwise_best_kernel"))) return rc;
+                hipLaunchKernelGGL(stepwise_colour_kernel, tiles, dim3(256), 0, s, ba);
+                if ((rc = check_launch("stepwise_colour_kernel"))) return rc;
             }
         }
         hipLaunchKernelGGL(advance_base_kernel, dim3(1), dim3(1), 0, s, call, chunk);
@@ -772,10 +1008,12 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
         BestArgs bl = ba;
         bl.k = -1;
         bl.U = Ufinal;
-        hipLaunchKernelGGL(stepwise_readout_kernel, dim3(gx, Rp / 64), dim3(256), 0, stream, rl);
+        hipLaunchKernelGGL(stepwise_readout_kernel, read_grid, dim3(256), 0, stream, rl);
         if ((st = check_launch("stepwise_readout_kernel"))) return st;
         hipLaunchKernelGGL(stepwise_best_kernel, dim3(R), dim3(256), 0, stream, bl);
         if ((st = check_launch("stepwise_best_kernel"))) return st;
+        hipLaunchKernelGGL(stepwise_colour_kernel, tiles, dim3(256), 0, stream, bl);
+        if ((st = check_launch("stepwise_colour_kernel"))) return st;
     }
     if (ro && M > 0 && steps > 0) {
         if (ro->best_h) {
@@ -787,8 +1025,8 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
             if (e != hipSuccess) return hip_error(e, "best_step copy");
         }
     }
-    hipLaunchKernelGGL(stepwise_final_kernel, dim3(2048), dim3(256), 0, stream, Ufinal, theta, phase,
-                       n, R, Rp);
+    hipLaunchKernelGGL(stepwise_final_kernel, tiles, dim3(256), 0, stream, Ufinal, theta, phase, n, R,
+                       Rp);
     return check_launch("stepwise_final_kernel");
 }
 

@@ -515,3 +515,47 @@ def test_batch_instance_zero_matches_standalone(dev, oim, orc):
         a, _ = _gpu_run(oim, pb, th0, K, Ks, sg, sd, 3)
         b, _ = _gpu_run(oim, p0, np.ascontiguousarray(th0[:, :g0.n]), K, Ks, sg, sd, 3)
     np.testing.assert_array_equal(a[:, :g0.n], b)
+
+
+@pytest.mark.parametrize("graph", ["torus", "hub", "tiny"])
+@pytest.mark.parametrize("q", [2, 3, 5])
+def test_stepwise_packed_replicas_same_bits(dev, oim, orc, graph, q):
+    # below 33 replicas a wave holds several quads: runs of 1 .. 100 replicas
+    # (every power of two a quad's lanes can be rounded to, and more than one
+    # wave of replicas) agree bit for bit on the replicas they share, readouts
+    # and best colours included
+    import torch
+    if graph == "torus":  # padded row image
+        g = synth.torus(37, 11, seed=4)
+    elif graph == "hub":  # CSR: rows of very different length, n not a multiple of 4
+        ei = np.concatenate([np.zeros(150, np.int64), np.arange(1, 301)])
+        ej = np.concatenate([np.arange(2, 302, 2), np.arange(2, 302)])
+        keep = ei != ej
+        pairs = np.unique(np.stack([np.minimum(ei, ej), np.maximum(ei, ej)], 1)[keep], axis=0)
+        g = synth.csr_from_edges(302, pairs[:, 0], pairs[:, 1],
+                                 np.random.default_rng(1).standard_normal(len(pairs)))
+    else:
+        g = synth.csr_from_edges(3, [0], [2], [1.0])
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    steps = 9
+    K, Ks, sg = ramp_schedule(max(float(np.abs(g.w).max()) * 4, 1.0), q, steps)
+    th0 = synth.theta0(100, g.n, seed=7)
+    sd = synth.seeds(100, 3)
+    ref = None
+    prob = _problem(oim, g, -g.w)
+    for R in (100, 64, 33, 32, 17, 8, 3, 2, 1):
+        th = t(th0[:R].copy())
+        ph = oim.oim_phase_from_theta(th)
+        out = oim.run(prob, th, t(K), t(Ks), t(sg), t(sd[:R].copy()), q=q, dt=DT, readout_every=4,
+                      flags=oim.OIM_LOOP_STEPWISE, want_best=True, phase=ph)
+        got = [ph.cpu().numpy(), th.cpu().numpy(), out["best_colour"].cpu().numpy(),
+               out["trace"].cpu().numpy().T, out["best_h"].cpu().numpy(),
+               out["best_step"].cpu().numpy()]
+        if ref is None:
+            ref = got
+            for r in (0, 99):
+                assert got[4][r] == orc.h_model_fixed(g.row_ptr, g.col, (-g.w).astype(np.float32), q,
+                                                      got[2][r])
+        for a, b in zip(got, ref):
+            np.testing.assert_array_equal(a, b[:R], err_msg=f"R={R}")
+    prob.close()
