@@ -130,6 +130,22 @@ __device__ __forceinline__ float increment(float2 own, float A, float B, uint32_
 // groups one by one split the reads into blocks that each waited: slower than
 // before; now whole batches are read, padded where a row ends.)
 __host__ __device__ constexpr bool resident_rows(int ms) { return ms == 1; }
+
+// Split-row shapes among them can draw each quad's noise once, a step ahead,
+// and hand it to the rows' owners through LDS (two buffers), where otherwise
+// every wave of a slice repeats the quad's Philox call inside its chain of
+// latencies: it is drawn by the waves that hold no rows, idle ones or launched
+// for it, or, where there are none, by one wave of each slice (on another SIMD
+// for the next slice).  us per step before and now, one replica: n = 200 of
+// degree 10 unit weights 0.85 -> 0.61, real 0.93 -> 0.77; n = 500 of degree 10
+// 1.02 -> 0.85, real 1.05 -> 0.93; 32 colouring graphs of up to 600
+// oscillators x 8 replicas 1.00 -> 0.73.
+__host__ __device__ constexpr bool can_share_noise(int ms, int rpl) { return resident_rows(ms) && rpl < 4; }
+// Waves added for it: one per slice where the workgroup stays within sixteen.
+__host__ __device__ constexpr int noise_waves(int tb, int rpl) {
+    const int groups = tb / 64 * rpl / 4;
+    return tb / 64 + groups <= 16 ? groups : 0;
+}
 // LDS byte offset of the second table of a shape of `groups` slices: past the
 // first table, the colours and the zero entry of its largest instance, a
 // constant so that a read's table is part of its instruction.
@@ -149,8 +165,11 @@ __device__ __forceinline__ uint64_t sc_word(int byte_off) {
 // wave busy.  Every oscillator's arithmetic -- its row's multiply-adds in
 // entry order, its Philox normal, its update -- is the same in all shapes,
 // so they give identical results.
-template <int TB, int MS, int QM, int RPL, bool UWT>
-__global__ __launch_bounds__(TB, resident_rows(MS) ? 4 : (TB / 64 + 3) / 4)
+// XN: the noise is shared as above, whatever waves are launched past TB
+// drawing it.
+template <int TB, int MS, int QM, int RPL, bool UWT, bool XN = false>
+__global__ __launch_bounds__(TB + (XN ? 64 * noise_waves(TB, RPL) : 0),
+                             resident_rows(MS) ? 4 : (TB / 64 + 3) / 4)
 void persistent_sparse_kernel(PersistArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     // workgroup -> (instance, replica).  Consecutive workgroup ids go to the
@@ -195,7 +214,9 @@ void persistent_sparse_kernel(PersistArgs a) {
     // readout state of thread 0: [0] improved flag, [1] best step, [2..3] best H
     int* flag = reinterpret_cast<int*>(tstack + kSliceTreeLevels);
     double* best_lds = reinterpret_cast<double*>(flag + 2);
-    double* part = reinterpret_cast<double*>(flag + 8);             // [WS][G][64], RPL < 4
+    static_assert(!XN || can_share_noise(MS, RPL), "split resident rows only");
+    float* nz = reinterpret_cast<float*>(flag + 8);                 // [2][4 * plane], XN
+    double* part = reinterpret_cast<double*>(nz + (XN ? 8 * plane : 0));  // [WS][G][64], RPL < 4
     double* ssum = part + (RPL < 4 ? TB : 0);                        // [MS * WS], slice_sums
 
     const int lane = threadIdx.x & 63;
@@ -257,6 +278,31 @@ void persistent_sparse_kernel(PersistArgs a) {
         const int off = UWT ? 36 * plane : 8 * ((j0 + jj) * plane + ws * 64 + lane);
         return UWT ? make_int4(off, off, off, off) : make_int4(off, 0, off, 0);
     };
+    // XN: the slices whose noise this wave draws: duty, duty + duty_step, ...
+    // below S
+    int duty = S, duty_step = S;
+    if constexpr (XN) {
+        const int first = S * G, spare = (int)(blockDim.x >> 6) - first;
+        if (spare > 0) {
+            duty = wave >= first ? wave - first : S;
+            duty_step = spare;
+        } else if (g == ws % G) {
+            duty = ws;
+        }
+    }
+    // the normals of step t of their quads, into buffer `buf`
+    auto draw = [&](uint32_t t, int buf) __attribute__((always_inline)) {
+        for (int sl = duty; sl < S; sl += duty_step) {
+            // (re-materialised every step, as in the two-phase step below)
+            uint32_t mm = (uint32_t)(sl * 64 + lane), kk0 = k0, kk1 = k1;
+            asm volatile("" : "+v"(mm), "+s"(kk0), "+s"(kk1));
+            float z4[4];
+            normals4(mm, t, (uint32_t)inst_id, kk0, kk1, z4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) nz[buf * 4 * plane + j * plane + sl * 64 + lane] = z4[j];
+        }
+    };
+    if constexpr (XN) draw((uint32_t)a.step0, 0);
     if constexpr (RES) {
 #pragma unroll
         for (int jj = 0; jj < RPL; ++jj)
@@ -286,8 +332,9 @@ void persistent_sparse_kernel(PersistArgs a) {
 
     // One step of resident rows (see resident_rows): the first NV groups of
     // every row's entries come from registers, their LDS reads go out at
-    // once, and the Philox noise is computed while they are in flight; the
-    // rest of a long row is streamed, its first loads issued before the
+    // once, and noise is computed while they are in flight (the quad's own, or
+    // with XN, on the wave whose duty it is, the next step's); the rest of a
+    // long row is streamed, its first loads issued before the
     // resident groups are used.  Groups are read G16 at a time, those past a
     // row's end being padding that adds +-0.  Sums, increment and update are
     // those of the two-phase step below, operation for operation; step s
@@ -351,7 +398,12 @@ void persistent_sparse_kernel(PersistArgs a) {
             for (int jj = 0; jj < RPL; ++jj)
 #pragma unroll
                 for (int h = 0; h < G16; ++h) read(jj, h, res[jj][c + h]);
-            if (c == 0) {
+            if (c == 0 && XN) {
+#pragma unroll
+                for (int jj = 0; jj < RPL; ++jj)
+                    z[jj] = nz[(decltype(odd)::value ? 4 * plane : 0) + (j0 + jj) * plane + m];
+                draw(t + 1u, decltype(odd)::value ? 0 : 1);
+            } else if (c == 0) {
                 // (re-materialised and pinned as in the two-phase step)
                 uint32_t mm = (uint32_t)m, kk0 = k0, kk1 = k1;
                 asm volatile("" : "+v"(mm), "+s"(kk0), "+s"(kk1));
@@ -423,6 +475,8 @@ void persistent_sparse_kernel(PersistArgs a) {
             if (ws < S) {
                 if (s & 1) resident_step(std::true_type{}, t, kc, ks, ns);
                 else resident_step(std::false_type{}, t, kc, ks, ns);
+            } else if constexpr (XN) {
+                draw(t + 1u, (s + 1) & 1);
             }
             __syncthreads();
         } else {
@@ -811,7 +865,7 @@ void persistent_sparse_kernel(PersistArgs a) {
                 }
                 if constexpr (RPL < 4) {
                     // the quad's partial sums meet in LDS; wave g = 0 folds them
-                    part[(ws * G + g) * 64 + lane] = v;
+                    if (wave < W) part[(ws * G + g) * 64 + lane] = v;
                     __syncthreads();
                     if (g == 0 && slice < S) {
                         const double* pp = part + ws * G * 64 + lane;
@@ -926,6 +980,17 @@ constexpr int kVariantCount = 0 OIM_PERSIST_VARIANTS(OIM_PERSIST_COUNT_ONE);
 // The unit-weight instantiations (q classes generic, 2, 3) of every variant,
 // in list order; defined in sparse_persistent_uw.hip.
 extern const KernelFn kUniformKernels[kVariantCount][3];
+
+// The shapes that can share their noise (can_share_noise), and their
+// instantiations that do.
+#define OIM_NOISE_VARIANTS(X)                                                            \
+    X(256, 1, 1) X(256, 1, 2) X(512, 1, 1) X(512, 1, 2) X(1024, 1, 1) X(1024, 1, 2)
+struct NoiseKernels {
+    int tb, ms, rpl;
+    KernelFn fn[3];
+};
+constexpr int kNoiseCount = 0 OIM_NOISE_VARIANTS(OIM_PERSIST_COUNT_ONE);
+extern const NoiseKernels kUniformNoiseKernels[kNoiseCount];
 
 }  // namespace persist
 }  // namespace oim

@@ -18,6 +18,14 @@ struct Variant {
     int covers() const { return (tb / 64) / (4 / rpl) * ms; }
 };
 
+#define OIM_NOISE_ENTRY(TB, MS, RPL)                                                     \
+    {TB, MS, RPL,                                                                        \
+     {persistent_sparse_kernel<TB, MS, 0, RPL, false, true>,                             \
+      persistent_sparse_kernel<TB, MS, 2, RPL, false, true>,                             \
+      persistent_sparse_kernel<TB, MS, 3, RPL, false, true>}},
+
+const NoiseKernels kNoiseKernels[kNoiseCount] = {OIM_NOISE_VARIANTS(OIM_NOISE_ENTRY)};
+
 #define OIM_VARIANT_ENTRY(TB, MS, RPL)                                                   \
     Variant{TB, MS, RPL,                                                                 \
             {persistent_sparse_kernel<TB, MS, 0, RPL, false>,                            \
@@ -29,12 +37,13 @@ const Variant kVariants[kVariantCount] = {OIM_PERSIST_VARIANTS(OIM_VARIANT_ENTRY
 constexpr size_t kLdsLimit = 160 * 1024;
 
 // LDS of a launch; with slice_sums, room for the readout's per-slice sums
-// (slices covered by the variant) too.
-size_t lds_bytes(int plane, int tb, int ms, int rpl, int covered = 0) {
+// (slices covered by the variant) too, and with `noise` the two noise buffers.
+size_t lds_bytes(int plane, int tb, int ms, int rpl, int covered = 0, bool noise = false) {
     size_t b = (size_t)8 * 4 * plane;                 // (sin, cos) table
     if (resident_rows(ms)) b += second_table(tb / 64 * rpl / 4);  // and the second one
     b += (size_t)4 * plane + 16;                      // colours for readout, zero entry
     b += sizeof(double) * (tb / 64 + kSliceTreeLevels) + 32;  // reduction, tree levels, readout state
+    if (noise) b += (size_t)32 * plane;
     if (rpl < 4) b += sizeof(double) * (size_t)tb;    // quads' partial row sums (readout)
     b += sizeof(double) * (size_t)covered;            // per-slice sums (readout), if used
     return b;
@@ -99,7 +108,7 @@ const Variant* default_variant(const Problem* p, int R) {
     const bool uw = p->d_sell_uw != nullptr;
     const bool long_rows = p->nnz / p->n >= 24;
     const Variant* v = nullptr;
-    if (4 * S <= waves) {
+    if (4 * S <= waves && !(uw && !long_rows && (S == 4 || g > 2))) {
         v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
     } else if (2 * S <= waves) {
         v = long_rows && S > 4 ? covering(1024, 1, S) : covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
@@ -210,16 +219,43 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
         a.w0 = p->uniform_w;
         fn = kUniformKernels[v - kVariants][qi];
     }
+    // Noise shared within the workgroup, where it has waves to draw it: idle
+    // ones, or while a CU has one or two workgroups one more per slice, within
+    // the sixteen waves of this kernel's registers.  With unit weights also
+    // where every wave holds rows and the CU one workgroup (us per step, G(800,
+    // 0.06) 3.05 -> 2.98, n = 2000 of degree 10 2.19 -> 2.12); not with general
+    // weights (n = 800 of degree 10, 1.37 -> 1.47) and not where more busy
+    // workgroups share a CU, which hide each other's Philox calls (n = 200 of
+    // degree 42, 600 replicas: 2.24 -> 2.70, real weights 2.94 -> 4.45).
+    const int64_t per_cu = ((int64_t)cfg->R * p->n_inst + 255) / 256;
+    int threads = v->tb;
+    bool noise = false;
+    if (can_share_noise(v->ms, v->rpl) &&
+        lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers(), true) <= kLdsLimit) {
+        const int extra = noise_waves(v->tb, v->rpl);
+        if (v->covers() > S) {
+            noise = true;
+        } else if (extra && per_cu <= 2 && per_cu * (v->tb / 64 + extra) <= 16) {
+            threads += 64 * extra;
+            noise = true;
+        } else {
+            noise = per_cu <= 1 && p->d_sell_uw;
+        }
+    }
+    for (int k = 0; noise && k < kNoiseCount; ++k) {
+        const NoiseKernels& nk = (p->d_sell_uw ? kUniformNoiseKernels : kNoiseKernels)[k];
+        if (nk.tb == v->tb && nk.ms == v->ms && nk.rpl == v->rpl) fn = nk.fn[qi];
+    }
     // the readout keeps per-slice sums in LDS when there is room for them
-    const size_t lds_fast = lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers());
+    const size_t lds_fast = lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers(), noise);
     a.slice_sums = (a.M > 0 && lds_fast <= kLdsLimit) ? 1 : 0;
-    const size_t lds = a.slice_sums ? lds_fast : lds_bytes(plane, v->tb, v->ms, v->rpl);
+    const size_t lds = a.slice_sums ? lds_fast : lds_bytes(plane, v->tb, v->ms, v->rpl, 0, noise);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, "hipFuncSetAttribute");
     if ((int64_t)cfg->R * p->n_inst > 0x7fffffff)
         return set_error(OIM_E_ARG, "R * instances too large");
-    hipLaunchKernelGGL(fn, dim3(cfg->R * p->n_inst), dim3(v->tb), lds, stream, a);
+    hipLaunchKernelGGL(fn, dim3(cfg->R * p->n_inst), dim3(threads), lds, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "persistent_sparse_kernel launch");
     return OIM_OK;

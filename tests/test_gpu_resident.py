@@ -61,3 +61,41 @@ def test_resident_rows_same_bits(oim, degree, weights, n, q, steps):
                 ref = got
             for a, b in zip(got, ref):
                 np.testing.assert_array_equal(a, b, err_msg=f"shape {shape}")
+
+
+@pytest.mark.parametrize("weights", ["unit", "real"])
+@pytest.mark.parametrize("sizes,R,shapes", [
+    ([1000], 2, ((1024, 1, 1), (512, 1, 2))),          # every wave holds rows
+    ([770, 30, 255, 256, 257, 1], 2, ((1024, 1, 1), (512, 1, 2), (1024, 1, 2))),
+    ([1700], 2, ((1024, 1, 2),)),                      # two idle waves for seven slices
+    ([2048], 1, ((1024, 1, 2),)),
+    ([510], 300, ((512, 1, 1), (256, 1, 2))),          # two workgroups per CU
+    ([250], 600, ((256, 1, 1), (256, 1, 2), (512, 1, 1))),
+])
+def test_shared_noise_same_bits(oim, sizes, R, weights, shapes):
+    """Split-row shapes whose noise is drawn by idle or added waves, or by one
+    wave of each slice, against whole quads, which draw their own."""
+    import torch
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    gs = [_circulant(n, 6 if n > 6 else 0, weights) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    ptr = np.concatenate([[0]] + [g.row_ptr[1:] + sum(h.row_ptr[-1] for h in gs[:k])
+                                  for k, g in enumerate(gs)]).astype(np.int64)
+    col = np.concatenate([g.col + off[k] for k, g in enumerate(gs)]).astype(np.int32)
+    w = np.concatenate([g.w for g in gs])
+    q, steps, n = 3, 6, int(off[-1])
+    with oim.Problem.from_csr_blocks(n, ptr, col, (-w).astype(np.float32), off) as prob:
+        K, Ks, sg = ramp_schedule(max(prob.info["max_abs_row_sum"], 1.0), q, steps)
+        th0 = synth.theta0(R, n, seed=2)
+        ref = None
+        for shape in ((512, 4, 4),) + shapes:
+            oim.oim_set_tuning(prob.handle, q, *shape)
+            th = t(th0)
+            ph = oim.oim_phase_from_theta(th)
+            out = oim.run(prob, th, t(K), t(Ks), t(sg), t(synth.seeds(R, 5)), q=q, dt=DT,
+                          readout_every=2, phase=ph, want_best=True)
+            got = [ph.cpu().numpy()] + [v.cpu().numpy() for v in out.values()]
+            if ref is None:
+                ref = got
+            for a, b in zip(got, ref):
+                np.testing.assert_array_equal(a, b, err_msg=f"shape {shape}")
