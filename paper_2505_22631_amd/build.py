@@ -13,7 +13,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liboim.so")
 OBJ = os.path.join(HERE, "_build")
 SOURCES = ["api.cpp", "validate.cpp", "readout.hip", "sparse_persistent.hip",
-           "sparse_persistent_uw.hip", "stepwise.hip",
+           "sparse_persistent_uw.hip", "sparse_sorted.hip", "sparse_sorted_uw.hip", "stepwise.hip",
            "dense.hip", "adjoint.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -48,6 +48,10 @@ void release(Problem* p) {
     hipFree(p->d_sell);
     hipFree(p->d_sell_uw);
     hipFree(p->d_row_split);
+    hipFree(p->d_sorted_run);
+    hipFree(p->d_sorted_row);
+    hipFree(p->d_sorted_run0);
+    hipFree(p->d_sorted);
     hipFree(p->d_inst);
     hipFree(p->d_order);
     stepwise_release(p);
@@ -186,6 +190,21 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
         p->ell_D = ell.D;
         if ((st = dev_upload(&p->d_ell_col, ell.col.data(), ell.col.size(), "upload ell col")) ||
             (st = dev_upload(&p->d_ell_J, ell.J.data(), ell.J.size(), "upload ell J"))) {
+            release(p);
+            return st;
+        }
+    }
+    // the sorted rows of the LDS-resident loop's small shapes
+    SortedRows sorted;
+    if (p->max_inst_n <= kSortedMaxN &&
+        build_sorted(n, row_ptr, col_idx, J, n_inst, n_inst > 1 ? inst_off : nullptr, w0,
+                     INT32_MAX, sorted)) {
+        p->sorted_bytes = (uint32_t)(sorted.entries.size() * sizeof(int4));
+        if ((st = dev_upload(&p->d_sorted_run, sorted.run.data(), sorted.run.size(), "upload runs")) ||
+            (st = dev_upload(&p->d_sorted_row, sorted.row.data(), sorted.row.size(), "upload sorted rows")) ||
+            (st = dev_upload(&p->d_sorted_run0, sorted.run0.data(), sorted.run0.size(), "upload runs")) ||
+            (st = dev_upload(&p->d_sorted, sorted.entries.data(), sorted.entries.size(),
+                             "upload sorted entries"))) {
             release(p);
             return st;
         }

@@ -48,6 +48,25 @@ struct SellImage {
     int32_t max_slices = 0;
 };
 
+// The rows of a sparse problem of small instances as the sorted-rows kernel
+// walks them.  Within an instance of n oscillators, 64 * ceil(n / 64) rows
+// (those past n empty) are sorted by their 16-byte groups of entries, most
+// first, equal ones by table slot, those past n last; 64 consecutive ones
+// are a run, padded to its first row's groups and one group of padding more:
+// group h of lane l at (base + h) * 64 + l.  Entries are those of SellImage in
+// the same order: LDS byte offsets, four to a group, with one weight of +-1 on
+// every entry, else (offset, weight) pairs, two to a group.  Padding points at
+// the zero entry, with weight 0.
+struct SortedRows {
+    std::vector<int2> run;       // per run: (base, groups per row)
+    std::vector<int2> row;       // per run and lane: (oscillator, upper start | length << 16)
+    std::vector<int32_t> run0;   // per instance: its first run
+    std::vector<int4> entries;
+};
+
+// Largest instance of that image.
+constexpr int kSortedMaxN = 4096;
+
 constexpr size_t kCsrPad = 4;
 
 // The rows of a sparse problem as the adjoint kernels walk them.  Within an
@@ -119,6 +138,13 @@ struct Problem {
     int2* d_sell = nullptr;
     uint32_t* d_sell_uw = nullptr;  // unit-weight image, or null
     int2* d_row_split = nullptr;    // SellImage::row_split
+
+    // device: SortedRows (instances of at most kSortedMaxN oscillators), else null
+    int2* d_sorted_run = nullptr;
+    int2* d_sorted_row = nullptr;
+    int32_t* d_sorted_run0 = nullptr;
+    int4* d_sorted = nullptr;
+    uint32_t sorted_bytes = 0;
     float uniform_w = 0.f;          // the weight every entry shares (+1 or -1), or 0
 
     // device: dense coupling (dense problems), FP32 and the BF16 split
@@ -175,6 +201,10 @@ int validate_blocks(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, i
 // unit-weight image too, or 0.
 void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
                 int32_t n_inst, const int32_t* inst_off, SellImage& out, float uniform_w = 0.f);
+// False, leaving `out` empty, if the image's bytes pass `max_bytes`.
+bool build_sorted(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
+                  int32_t n_inst, const int32_t* inst_off, float uniform_w, uint64_t max_bytes,
+                  SortedRows& out);
 
 // Every row padded to the same length D (the longest row rounded up to 4,
 // at least 4), quads of rows padded to 4 rows, stored quad by quad in

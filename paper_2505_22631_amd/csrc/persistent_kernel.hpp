@@ -28,8 +28,6 @@
 #pragma once
 #include <float.h>
 
-#include <type_traits>
-
 #include "internal.hpp"
 #include "noise.hpp"
 #include "phase.hpp"
@@ -116,47 +114,6 @@ __device__ __forceinline__ float increment(float2 own, float A, float B, uint32_
     return __builtin_fmaf(ns, z, det);
 }
 
-// Shapes of one slice per wave group keep the first 8 / RPL groups of 16
-// bytes of every row's entries and their own (sin, cos) in registers and
-// read and write two tables in turn, one barrier per step.  Such instances are
-// small, so a step is a chain of latencies -- the entries' L2 round trip, two
-// barriers, an own-entry read -- rather than a stream of work; what is left
-// of the chain is LDS reads, Philox beside them, the sums and the update.  us
-// per step before and now, one replica: n = 200 of degree 10 unit weights
-// 1.03 -> 0.85, real weights 1.31 -> 0.93; n = 800 of degree 10 1.49 -> 1.24,
-// real 1.93 -> 1.37; n = 800 of degree 47, bound by its LDS reads, 3.13 ->
-// 3.05, real 4.72 -> 3.94; n = 2000 of degree 10 2.41 -> 2.19, real 3.00 ->
-// 2.46; n = 3500 of degree 10 3.56 -> 3.08, real 4.87 -> 4.36.  (Guarding the
-// groups one by one split the reads into blocks that each waited: slower than
-// before; now whole batches are read, padded where a row ends.)
-__host__ __device__ constexpr bool resident_rows(int ms) { return ms == 1; }
-
-// Split-row shapes among them can draw each quad's noise once, a step ahead,
-// and hand it to the rows' owners through LDS (two buffers), where otherwise
-// every wave of a slice repeats the quad's Philox call inside its chain of
-// latencies: it is drawn by the waves that hold no rows, idle ones or launched
-// for it, or, where there are none, by one wave of each slice (on another SIMD
-// for the next slice).  us per step before and now, one replica: n = 200 of
-// degree 10 unit weights 0.85 -> 0.61, real 0.93 -> 0.77; n = 500 of degree 10
-// 1.02 -> 0.85, real 1.05 -> 0.93; 32 colouring graphs of up to 600
-// oscillators x 8 replicas 1.00 -> 0.73.
-__host__ __device__ constexpr bool can_share_noise(int ms, int rpl) { return resident_rows(ms) && rpl < 4; }
-// Waves added for it: one per slice where the workgroup stays within sixteen.
-__host__ __device__ constexpr int noise_waves(int tb, int rpl) {
-    const int groups = tb / 64 * rpl / 4;
-    return tb / 64 + groups <= 16 ? groups : 0;
-}
-// LDS byte offset of the second table of a shape of `groups` slices: past the
-// first table, the colours and the zero entry of its largest instance, a
-// constant so that a read's table is part of its instruction.
-__host__ __device__ constexpr int second_table(int groups) { return 36 * 64 * groups + 16; }
-
-// The same entry as one 64-bit word (sine below).
-__device__ __forceinline__ uint64_t sc_word(int byte_off) {
-    typedef __attribute__((address_space(3))) const uint64_t lds_u64;
-    return *reinterpret_cast<lds_u64*>((uint32_t)byte_off);
-}
-
 // Launch shape: TB threads (W = TB / 64 waves), MS slices per wave group,
 // RPL rows of every quad per lane.  RPL = 4: a lane owns whole quads (one
 // wave per slice).  RPL = 2 or 1 (rows split): G = 4 / RPL waves share a
@@ -165,12 +122,8 @@ __device__ __forceinline__ uint64_t sc_word(int byte_off) {
 // wave busy.  Every oscillator's arithmetic -- its row's multiply-adds in
 // entry order, its Philox normal, its update -- is the same in all shapes,
 // so they give identical results.
-// XN: the noise is shared as above, whatever waves are launched past TB
-// drawing it.
-template <int TB, int MS, int QM, int RPL, bool UWT, bool XN = false>
-__global__ __launch_bounds__(TB + (XN ? 64 * noise_waves(TB, RPL) : 0),
-                             resident_rows(MS) ? 4 : (TB / 64 + 3) / 4)
-void persistent_sparse_kernel(PersistArgs a) {
+template <int TB, int MS, int QM, int RPL, bool UWT>
+__global__ __launch_bounds__(TB) void persistent_sparse_kernel(PersistArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     // workgroup -> (instance, replica).  Consecutive workgroup ids go to the
     // 8 XCDs in turn, each with its own L2; the replicas of one instance are
@@ -201,22 +154,16 @@ void persistent_sparse_kernel(PersistArgs a) {
     constexpr int G = 4 / RPL;     // waves per slice
     constexpr int WS = W / G;      // wave groups (slices in flight)
     constexpr int U = 8 / RPL;     // 16-byte entry loads per row per iteration
-    constexpr bool RES = resident_rows(MS);
-    constexpr int T1 = RES ? second_table(WS) : 0;  // byte offset of the second table
-    constexpr int U4 = U / 2;      // 16-byte loads (4 edges) per row per iteration, unit weights
     float2* sc = reinterpret_cast<float2*>(smem);                   // [4 * plane]
     unsigned char* col8 = smem + (size_t)8 * 4 * plane;            // [4 * plane] (readout)
-    // (0, 0) at byte 36 * plane of each table, what padding entries of the
-    // unit-weight image read
+    // (0, 0) at byte 36 * plane, what padding entries of the unit-weight image read
     float2* zero_entry = reinterpret_cast<float2*>(col8 + 4 * plane);
-    double* red = reinterpret_cast<double*>(col8 + 4 * plane + 16 + T1);  // [W]
+    double* red = reinterpret_cast<double*>(col8 + 4 * plane + 16);  // [W]
     double* tstack = red + W;                                                   // tree levels
     // readout state of thread 0: [0] improved flag, [1] best step, [2..3] best H
     int* flag = reinterpret_cast<int*>(tstack + kSliceTreeLevels);
     double* best_lds = reinterpret_cast<double*>(flag + 2);
-    static_assert(!XN || can_share_noise(MS, RPL), "split resident rows only");
-    float* nz = reinterpret_cast<float*>(flag + 8);                 // [2][4 * plane], XN
-    double* part = reinterpret_cast<double*>(nz + (XN ? 8 * plane : 0));  // [WS][G][64], RPL < 4
+    double* part = reinterpret_cast<double*>(flag + 8);             // [WS][G][64], RPL < 4
     double* ssum = part + (RPL < 4 ? TB : 0);                        // [MS * WS], slice_sums
 
     const int lane = threadIdx.x & 63;
@@ -238,13 +185,6 @@ void persistent_sparse_kernel(PersistArgs a) {
     uint32_t ph[MS][RPL];
     float drift[MS][RPL];
     int sbase[MS], sdeg[MS];
-    // resident rows: the first groups of each row's entries and the lane's own
-    // (sin, cos), held in registers for the whole run
-    constexpr int G16 = 4 / RPL;            // 16-byte groups per row read together
-    constexpr int E = UWT ? 4 : 2;          // edges per group
-    constexpr int NV = RES ? 2 * G16 : 1;   // resident groups per row
-    int4 res[RPL][NV];
-    float2 own_sc[RPL];
 
 #pragma unroll
     for (int k = 0; k < MS; ++k) {
@@ -261,57 +201,12 @@ void persistent_sparse_kernel(PersistArgs a) {
             const uint32_t u = valid ? (pw ? pw[i] : phase_from_theta(th[i])) : 0u;
             ph[k][jj] = u;
             drift[k][jj] = 0.0f;
-            const float2 v = make_float2(sin_turn(u), cos_turn(u));
-            if (slice < S) sc[j * plane + m] = v;
-            if constexpr (RES) own_sc[jj] = v;
+            if (slice < S) sc[j * plane + m] = make_float2(sin_turn(u), cos_turn(u));
         }
-    }
-    const int D16 = UWT ? sdeg[0] >> 2 : sdeg[0] >> 1;  // resident rows: 16-byte groups per row
-    // group h of row jj of the wave's slice
-    auto load_group = [&](int jj, int h) __attribute__((always_inline)) {
-        const int base = UWT ? sbase[0] >> 1 : sbase[0];
-        return load_pair(UWT ? rsrc_uw : rsrc, voff, (base + (j0 + jj) * D16 + h) * 1024);
-    };
-    // what a group past the row's end holds: the zero entry, or with general
-    // weights the row itself at weight 0
-    auto pad_group = [&](int jj) __attribute__((always_inline)) {
-        const int off = UWT ? 36 * plane : 8 * ((j0 + jj) * plane + ws * 64 + lane);
-        return UWT ? make_int4(off, off, off, off) : make_int4(off, 0, off, 0);
-    };
-    // XN: the slices whose noise this wave draws: duty, duty + duty_step, ...
-    // below S
-    int duty = S, duty_step = S;
-    if constexpr (XN) {
-        const int first = S * G, spare = (int)(blockDim.x >> 6) - first;
-        if (spare > 0) {
-            duty = wave >= first ? wave - first : S;
-            duty_step = spare;
-        } else if (g == ws % G) {
-            duty = ws;
-        }
-    }
-    // the normals of step t of their quads, into buffer `buf`
-    auto draw = [&](uint32_t t, int buf) __attribute__((always_inline)) {
-        for (int sl = duty; sl < S; sl += duty_step) {
-            // (re-materialised every step, as in the two-phase step below)
-            uint32_t mm = (uint32_t)(sl * 64 + lane), kk0 = k0, kk1 = k1;
-            asm volatile("" : "+v"(mm), "+s"(kk0), "+s"(kk1));
-            float z4[4];
-            normals4(mm, t, (uint32_t)inst_id, kk0, kk1, z4);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) nz[buf * 4 * plane + j * plane + sl * 64 + lane] = z4[j];
-        }
-    };
-    if constexpr (XN) draw((uint32_t)a.step0, 0);
-    if constexpr (RES) {
-#pragma unroll
-        for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-            for (int h = 0; h < NV; ++h) res[jj][h] = h < D16 ? load_group(jj, h) : pad_group(jj);
     }
     if (threadIdx.x == 0) {
         *best_lds = DBL_MAX;
-        zero_entry[0] = zero_entry[T1 / 8] = make_float2(0.f, 0.f);
+        *zero_entry = make_float2(0.f, 0.f);
         flag[1] = -1;
     }
     __syncthreads();
@@ -329,128 +224,6 @@ void persistent_sparse_kernel(PersistArgs a) {
     };
     float cK = sched(a.K, 0), cKs = sched(a.Ks, 0), cS = sched(a.sigma, 0);
     float nK = sched(a.K, 1), nKs = sched(a.Ks, 1), nS = sched(a.sigma, 1);
-
-    // One step of resident rows (see resident_rows): the first NV groups of
-    // every row's entries come from registers, their LDS reads go out at
-    // once, and noise is computed while they are in flight (the quad's own, or
-    // with XN, on the wave whose duty it is, the next step's); the rest of a
-    // long row is streamed, its first loads issued before the
-    // resident groups are used.  Groups are read G16 at a time, those past a
-    // row's end being padding that adds +-0.  Sums, increment and update are
-    // those of the two-phase step below, operation for operation; step s
-    // reads table s % 2 and writes the other, so one barrier per step is
-    // enough.
-    auto resident_step = [&](auto odd, uint32_t t, float kc, float ks, float ns)
-        __attribute__((always_inline)) {
-        constexpr int rd = decltype(odd)::value ? T1 : 0, wr = decltype(odd)::value ? 0 : T1;
-        const int m = ws * 64 + lane;
-        float A[RPL], B[RPL], z[RPL];
-#pragma unroll
-        for (int jj = 0; jj < RPL; ++jj) A[jj] = B[jj] = 0.f;
-        int4 str[RPL][G16];
-        auto stream = [&](int h0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-                for (int h = 0; h < G16; ++h)
-                    str[jj][h] = h == 0 || h0 + h < D16 ? load_group(jj, h0 + h) : pad_group(jj);
-        };
-        uint64_t p[RPL][G16][E];
-        auto read = [&](int jj, int h, const int4& v) __attribute__((always_inline)) {
-            p[jj][h][0] = sc_word(v.x + rd);
-            if constexpr (UWT) {
-                p[jj][h][1] = sc_word(v.y + rd);
-                p[jj][h][2] = sc_word(v.z + rd);
-                p[jj][h][3] = sc_word(v.w + rd);
-            } else {
-                p[jj][h][1] = sc_word(v.z + rd);
-            }
-        };
-        // the reads' results arrive here, not before
-        auto arrive = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-                for (int h = 0; h < G16; ++h)
-#pragma unroll
-                    for (int x = 0; x < E; ++x) asm volatile("" : "+v"(p[jj][h][x]));
-        };
-        auto add = [&](int jj, int h, const int4& v) __attribute__((always_inline)) {
-#pragma unroll
-            for (int x = 0; x < E; ++x) {
-                const float ps = __uint_as_float((uint32_t)p[jj][h][x]);
-                const float pc = __uint_as_float((uint32_t)(p[jj][h][x] >> 32));
-                if constexpr (UWT) {
-                    A[jj] = A[jj] + pc;
-                    B[jj] = B[jj] + ps;
-                } else {
-                    const float w = __int_as_float(x == 0 ? v.y : v.w);
-                    A[jj] = __builtin_fmaf(w, pc, A[jj]);
-                    B[jj] = __builtin_fmaf(w, ps, B[jj]);
-                }
-            }
-        };
-        if (D16 > NV) stream(NV);
-#pragma unroll
-        for (int c = 0; c < NV; c += G16) {
-            if (c > 0 && c >= D16) break;
-#pragma unroll
-            for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-                for (int h = 0; h < G16; ++h) read(jj, h, res[jj][c + h]);
-            if (c == 0 && XN) {
-#pragma unroll
-                for (int jj = 0; jj < RPL; ++jj)
-                    z[jj] = nz[(decltype(odd)::value ? 4 * plane : 0) + (j0 + jj) * plane + m];
-                draw(t + 1u, decltype(odd)::value ? 0 : 1);
-            } else if (c == 0) {
-                // (re-materialised and pinned as in the two-phase step)
-                uint32_t mm = (uint32_t)m, kk0 = k0, kk1 = k1;
-                asm volatile("" : "+v"(mm), "+s"(kk0), "+s"(kk1));
-                float zz[4];
-                if constexpr (RPL == 4) normals4(mm, t, (uint32_t)inst_id, kk0, kk1, zz);
-                else normals2(mm, t, (uint32_t)inst_id, kk0, kk1, RPL == 2 ? g : g >> 1, zz);
-#pragma unroll
-                for (int jj = 0; jj < RPL; ++jj) {
-                    z[jj] = RPL > 1 ? zz[jj] : (g & 1) ? zz[1] : zz[0];
-                    asm volatile("" : "+v"(z[jj]));
-                }
-            }
-            arrive();
-#pragma unroll
-            for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-                for (int h = 0; h < G16; ++h) add(jj, h, res[jj][c + h]);
-        }
-        for (int h0 = NV; h0 < D16; h0 += G16) {
-            int4 cur[RPL][G16];
-#pragma unroll
-            for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-                for (int h = 0; h < G16; ++h) {
-                    cur[jj][h] = str[jj][h];
-                    read(jj, h, cur[jj][h]);
-                }
-            if (h0 + G16 < D16) stream(h0 + G16);
-            arrive();
-#pragma unroll
-            for (int jj = 0; jj < RPL; ++jj)
-#pragma unroll
-                for (int h = 0; h < G16; ++h) add(jj, h, cur[jj][h]);
-        }
-#pragma unroll
-        for (int jj = 0; jj < RPL; ++jj) {
-            if constexpr (UWT) {
-                A[jj] = a.w0 * A[jj];
-                B[jj] = a.w0 * B[jj];
-            }
-            const float inc = increment<QM>(own_sc[jj], A[jj], B[jj], ph[0][jj], q, kc, ks, ns, z[jj]);
-            const uint32_t u = advance(ph[0][jj], inc);
-            ph[0][jj] = u;
-            own_sc[jj] = make_float2(sin_turn(u), cos_turn(u));
-            sc[wr / 8 + (j0 + jj) * plane + m] = own_sc[jj];
-        }
-    };
 
     for (int s = 0; s < a.steps; ++s) {
         const uint32_t t = (uint32_t)(a.step0 + s);
@@ -471,15 +244,6 @@ void persistent_sparse_kernel(PersistArgs a) {
         const float ks = -a.dt * Kst * kTurnScale;
         const float ns = St * sqrt_dt * kTurnScale;
 
-        if constexpr (RES) {
-            if (ws < S) {
-                if (s & 1) resident_step(std::true_type{}, t, kc, ks, ns);
-                else resident_step(std::false_type{}, t, kc, ks, ns);
-            } else if constexpr (XN) {
-                draw(t + 1u, (s + 1) & 1);
-            }
-            __syncthreads();
-        } else {
         // ---- phase A: noise, and coupling sums over the sliced-ELL rows ----
         // The first edge loads of a slice are issued, then its Philox noise
         // is computed while they are in flight (the noise depends only on
@@ -525,6 +289,7 @@ void persistent_sparse_kernel(PersistArgs a) {
                     // equals the chain of roundings of the negated terms, so
                     // the result is the multiply-add chain's up to the sign
                     // of a zero sum, which no phase update can tell apart.
+                    constexpr int U4 = U / 2;  // 16-byte loads (4 edges) per row per iteration
                     const int D4 = sdeg[k] >> 2;
                     int4 v[RPL][U4];
                     auto load_iter = [&](int e4) __attribute__((always_inline)) {
@@ -652,7 +417,6 @@ void persistent_sparse_kernel(PersistArgs a) {
             }
         }
         __syncthreads();
-        }
 
         // ---- optional readout: threshold, Eq. 1 / Eq. 2, best-so-far ----
         if (a.M > 0 && ((s + 1) % a.M == 0 || s + 1 == a.steps)) {
@@ -865,7 +629,7 @@ void persistent_sparse_kernel(PersistArgs a) {
                 }
                 if constexpr (RPL < 4) {
                     // the quad's partial sums meet in LDS; wave g = 0 folds them
-                    if (wave < W) part[(ws * G + g) * 64 + lane] = v;
+                    part[(ws * G + g) * 64 + lane] = v;
                     __syncthreads();
                     if (g == 0 && slice < S) {
                         const double* pp = part + ws * G * 64 + lane;
@@ -961,7 +725,8 @@ using KernelFn = void (*)(PersistArgs);
 // quad per lane), in the order the autotuner tries them: block sizes from
 // one wave up -- the small ones suit batches of small instances (fewer idle
 // lanes, cheap barriers) -- then the split-row shapes, which suit instances
-// of a few slices with long rows.
+// of a few slices with long rows.  Shapes of one slice per wave group run
+// sorted_kernel.hpp's kernel where the problem has its image.
 #define OIM_PERSIST_VARIANTS(X)                                                          \
     X(64, 1, 4) X(64, 2, 4) X(64, 3, 4) X(64, 4, 4) X(64, 6, 4) X(64, 8, 4)               \
     X(128, 1, 4) X(128, 2, 4) X(128, 3, 4) X(128, 4, 4) X(128, 6, 4) X(128, 8, 4)         \
@@ -980,17 +745,6 @@ constexpr int kVariantCount = 0 OIM_PERSIST_VARIANTS(OIM_PERSIST_COUNT_ONE);
 // The unit-weight instantiations (q classes generic, 2, 3) of every variant,
 // in list order; defined in sparse_persistent_uw.hip.
 extern const KernelFn kUniformKernels[kVariantCount][3];
-
-// The shapes that can share their noise (can_share_noise), and their
-// instantiations that do.
-#define OIM_NOISE_VARIANTS(X)                                                            \
-    X(256, 1, 1) X(256, 1, 2) X(512, 1, 1) X(512, 1, 2) X(1024, 1, 1) X(1024, 1, 2)
-struct NoiseKernels {
-    int tb, ms, rpl;
-    KernelFn fn[3];
-};
-constexpr int kNoiseCount = 0 OIM_NOISE_VARIANTS(OIM_PERSIST_COUNT_ONE);
-extern const NoiseKernels kUniformNoiseKernels[kNoiseCount];
 
 }  // namespace persist
 }  // namespace oim

@@ -2,7 +2,9 @@
 // (persistent_kernel.hpp), the default choice, the launch and the autotuner.
 #include <float.h>
 
-#include "persistent_kernel.hpp"
+#include <algorithm>
+
+#include "sorted_kernel.hpp"
 
 namespace oim {
 
@@ -18,14 +20,6 @@ struct Variant {
     int covers() const { return (tb / 64) / (4 / rpl) * ms; }
 };
 
-#define OIM_NOISE_ENTRY(TB, MS, RPL)                                                     \
-    {TB, MS, RPL,                                                                        \
-     {persistent_sparse_kernel<TB, MS, 0, RPL, false, true>,                             \
-      persistent_sparse_kernel<TB, MS, 2, RPL, false, true>,                             \
-      persistent_sparse_kernel<TB, MS, 3, RPL, false, true>}},
-
-const NoiseKernels kNoiseKernels[kNoiseCount] = {OIM_NOISE_VARIANTS(OIM_NOISE_ENTRY)};
-
 #define OIM_VARIANT_ENTRY(TB, MS, RPL)                                                   \
     Variant{TB, MS, RPL,                                                                 \
             {persistent_sparse_kernel<TB, MS, 0, RPL, false>,                            \
@@ -37,13 +31,11 @@ const Variant kVariants[kVariantCount] = {OIM_PERSIST_VARIANTS(OIM_VARIANT_ENTRY
 constexpr size_t kLdsLimit = 160 * 1024;
 
 // LDS of a launch; with slice_sums, room for the readout's per-slice sums
-// (slices covered by the variant) too, and with `noise` the two noise buffers.
-size_t lds_bytes(int plane, int tb, int ms, int rpl, int covered = 0, bool noise = false) {
+// (slices covered by the variant) too.
+size_t lds_bytes(int plane, int tb, int ms, int rpl, int covered = 0) {
     size_t b = (size_t)8 * 4 * plane;                 // (sin, cos) table
-    if (resident_rows(ms)) b += second_table(tb / 64 * rpl / 4);  // and the second one
     b += (size_t)4 * plane + 16;                      // colours for readout, zero entry
     b += sizeof(double) * (tb / 64 + kSliceTreeLevels) + 32;  // reduction, tree levels, readout state
-    if (noise) b += (size_t)32 * plane;
     if (rpl < 4) b += sizeof(double) * (size_t)tb;    // quads' partial row sums (readout)
     b += sizeof(double) * (size_t)covered;            // per-slice sums (readout), if used
     return b;
@@ -79,17 +71,31 @@ const Variant* fewest_waves(int S, int tb_hint) {
     return best;
 }
 
+// Whether a CU holds `groups` workgroups of `waves` waves at once at this
+// kernel's registers, four waves per SIMD: a workgroup's waves go to the SIMDs
+// in turn (three of five waves do not fit: n = 200 real weights, 600 replicas,
+// 0.87 us per step with four waves each, 1.25 with five).
+bool cu_holds(int64_t groups, int64_t waves) {
+    return waves > 4 ? groups * ((waves + 3) / 4) <= 4 : groups * waves <= 16;
+}
+
 // Default choice without tuning, from the slices of the largest instance (S),
 // the workgroups a CU holds at once and the rows' mean length: about sixteen
 // working waves per CU, four per SIMD.
-//  - A step's latency is shared by the waves of a workgroup, so while a CU has
-//    few workgroups the rows of a quad are split over waves until sixteen
-//    work: us per step with whole quads on 256 threads and now, one replica,
-//    G(200, 0.05) 1.57 -> 0.85 (256 x 1 with 1 row per lane), G(800, 0.06)
-//    4.5 -> 3.0 (1024 x 1 x 1), n = 2000 of degree 10 2.4 -> 2.2 (1024 x 1 x 2;
-//    real weights 3.0 -> 2.5), n = 1500 of degree 46 5.4 -> 4.7 (1024 x 2 x 1:
-//    long rows take one more split).  A split repeats the quad's Philox call in
-//    each of its waves, so it ends there.
+//  - A step's latency is shared by the waves of a workgroup, so the rows are
+//    split over as many waves as the CU holds with its other workgroups
+//    (cu_holds), unit weights with room for the noise's waves: us per step with
+//    4, 2 and 1 rows per lane, n = 800 of degree 10 one replica 2.0, 1.01, 1.01
+//    (real weights 2.1, 1.31, 0.94), 500 replicas 2.4, 1.82, 2.3 (real 3.0,
+//    1.65, 2.3); n = 500, 500 replicas 1.85, 1.13, 1.28 (real 2.0, 1.23, 1.17).
+//    Longer rows weigh more than the noise: G(800, 0.06) one replica 4.0, 2.5,
+//    2.2, 500 replicas 5.4, 4.2, 4.8 (real 8.3, 5.2, 5.0), 600 replicas 7.1,
+//    6.5, 7.4 (real 9.7, 9.0, 7.7).  Past that unit weights take whole quads
+//    (n = 2000, 500 replicas 3.7, against 3.9 with 2 rows per lane), real ones 2
+//    rows (4.0 against 3.7).
+//  - Nine to sixteen slices of real weights or long rows keep sixteen waves of
+//    sorted rows however many replicas there are (n = 4000 of degree 30, 600
+//    replicas: 22.4 us, real 26, against 23.7 and 34 on 256 threads).
 //  - Instances of more slices take sixteen waves of whole quads: n = 3500 of
 //    degree 10 4.1 -> 3.1 us (1024 x 1), n = 10000 of degree 5 8.6 -> 6.0
 //    (1024 x 3); the general image, which holds more registers, twelve waves of
@@ -108,12 +114,15 @@ const Variant* default_variant(const Problem* p, int R) {
     const bool uw = p->d_sell_uw != nullptr;
     const bool long_rows = p->nnz / p->n >= 24;
     const Variant* v = nullptr;
-    if (4 * S <= waves && !(uw && !long_rows && (S == 4 || g > 2))) {
+    // waves of the split shapes with 1 and 2 rows per lane
+    const int64_t w1 = (p->max_inst_n + 63) / 64, w2 = (w1 + 1) / 2;
+    if (w1 <= 16 && (long_rows ? !uw || cu_holds(per_cu, w1)
+                               : cu_holds(per_cu, uw && S > 1 ? w1 + S : w1))) {
         v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
-    } else if (2 * S <= waves) {
-        v = long_rows && S > 4 ? covering(1024, 1, S) : covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
-    } else if (uw && long_rows && waves == 16 && S <= 16) {
-        v = covering(1024, 2, S);
+    } else if (w2 <= 16 && (!uw || long_rows || S <= 2 || cu_holds(per_cu, w2))) {
+        v = covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
+    } else if (S > 8 && S <= 16 && (!uw || long_rows)) {
+        v = covering(1024, 4, S);
     } else if (!uw && waves == 16 && S > 32 && S <= 48) {
         v = covering(768, 4, S);
     } else {
@@ -174,6 +183,37 @@ bool persistent_sparse_fits(const Problem* p) {
 }
 
 namespace {
+// A shape of one slice per wave group on the sorted rows: the waves that hold
+// rows of the largest instance and, while a CU has one or two workgroups,
+// one more per slice to draw its noise, as far as the sixteen waves of this
+// kernel's registers go.
+int launch_sorted(const Problem* p, const Variant& v, const PersistArgs& a, int qi,
+                  hipStream_t stream) {
+    SortedArgs sa{};
+    sa.p = a;
+    sa.entries = p->d_sorted;
+    sa.run = p->d_sorted_run;
+    sa.row = p->d_sorted_row;
+    sa.run0 = p->d_sorted_run0;
+    sa.bytes = p->sorted_bytes;
+    const int S = p->max_slices;
+    const SortedShape* shape = nullptr;
+    for (const SortedShape& k : p->d_sell_uw ? kSortedUniform : kSorted)
+        if (k.C == v.covers() && k.rpl == v.rpl) shape = &k;
+    if (!shape) return set_error(OIM_E_UNSUPPORTED, "no sorted-rows shape");
+    const int64_t per_cu = ((int64_t)a.R * p->n_inst + 255) / 256;
+    int waves = ((p->max_inst_n + 63) / 64 + v.rpl - 1) / v.rpl;
+    for (int k = 0; k < S && cu_holds(per_cu, waves + 1); ++k) ++waves;
+    const size_t lds = sorted_lds(shape->C, S * 64);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(shape->fn[qi]),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_error(e, "hipFuncSetAttribute");
+    hipLaunchKernelGGL(shape->fn[qi], dim3(a.R * p->n_inst), dim3(64 * waves), lds, stream, sa);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "sorted_kernel launch");
+    return OIM_OK;
+}
+
 // sched_stride: the row length of per-replica schedules ([R][sched_stride]),
 // or 0 for one schedule shared by every replica.
 int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, const float* Ks,
@@ -212,50 +252,24 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
     a.R = cfg->R;
     a.sched_stride = sched_stride;
     const int qi = cfg->q == 2 ? 1 : cfg->q == 3 ? 2 : 0;
+    if ((int64_t)cfg->R * p->n_inst > 0x7fffffff)
+        return set_error(OIM_E_ARG, "R * instances too large");
+    a.w0 = p->uniform_w;
+    if (v->ms == 1 && p->d_sorted) return launch_sorted(p, *v, a, qi, stream);
     KernelFn fn = v->fn[qi];
     if (p->d_sell_uw) {
         a.sell_uw = reinterpret_cast<const int4*>(p->d_sell_uw);
         a.sell_uw_bytes = (uint32_t)(p->sell_entries * 4);
-        a.w0 = p->uniform_w;
         fn = kUniformKernels[v - kVariants][qi];
     }
-    // Noise shared within the workgroup, where it has waves to draw it: idle
-    // ones, or while a CU has one or two workgroups one more per slice, within
-    // the sixteen waves of this kernel's registers.  With unit weights also
-    // where every wave holds rows and the CU one workgroup (us per step, G(800,
-    // 0.06) 3.05 -> 2.98, n = 2000 of degree 10 2.19 -> 2.12); not with general
-    // weights (n = 800 of degree 10, 1.37 -> 1.47) and not where more busy
-    // workgroups share a CU, which hide each other's Philox calls (n = 200 of
-    // degree 42, 600 replicas: 2.24 -> 2.70, real weights 2.94 -> 4.45).
-    const int64_t per_cu = ((int64_t)cfg->R * p->n_inst + 255) / 256;
-    int threads = v->tb;
-    bool noise = false;
-    if (can_share_noise(v->ms, v->rpl) &&
-        lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers(), true) <= kLdsLimit) {
-        const int extra = noise_waves(v->tb, v->rpl);
-        if (v->covers() > S) {
-            noise = true;
-        } else if (extra && per_cu <= 2 && per_cu * (v->tb / 64 + extra) <= 16) {
-            threads += 64 * extra;
-            noise = true;
-        } else {
-            noise = per_cu <= 1 && p->d_sell_uw;
-        }
-    }
-    for (int k = 0; noise && k < kNoiseCount; ++k) {
-        const NoiseKernels& nk = (p->d_sell_uw ? kUniformNoiseKernels : kNoiseKernels)[k];
-        if (nk.tb == v->tb && nk.ms == v->ms && nk.rpl == v->rpl) fn = nk.fn[qi];
-    }
     // the readout keeps per-slice sums in LDS when there is room for them
-    const size_t lds_fast = lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers(), noise);
+    const size_t lds_fast = lds_bytes(plane, v->tb, v->ms, v->rpl, v->covers());
     a.slice_sums = (a.M > 0 && lds_fast <= kLdsLimit) ? 1 : 0;
-    const size_t lds = a.slice_sums ? lds_fast : lds_bytes(plane, v->tb, v->ms, v->rpl, 0, noise);
+    const size_t lds = a.slice_sums ? lds_fast : lds_bytes(plane, v->tb, v->ms, v->rpl);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, "hipFuncSetAttribute");
-    if ((int64_t)cfg->R * p->n_inst > 0x7fffffff)
-        return set_error(OIM_E_ARG, "R * instances too large");
-    hipLaunchKernelGGL(fn, dim3(cfg->R * p->n_inst), dim3(threads), lds, stream, a);
+    hipLaunchKernelGGL(fn, dim3(cfg->R * p->n_inst), dim3(v->tb), lds, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "persistent_sparse_kernel launch");
     return OIM_OK;

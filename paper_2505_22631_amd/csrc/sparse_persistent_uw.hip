@@ -16,13 +16,5 @@ namespace persist {
 
 const KernelFn kUniformKernels[kVariantCount][3] = {OIM_PERSIST_VARIANTS(OIM_UNIFORM_ENTRY)};
 
-#define OIM_UNIFORM_NOISE_ENTRY(TB, MS, RPL)                                             \
-    {TB, MS, RPL,                                                                        \
-     {persistent_sparse_kernel<TB, MS, 0, RPL, true, true>,                              \
-      persistent_sparse_kernel<TB, MS, 2, RPL, true, true>,                              \
-      persistent_sparse_kernel<TB, MS, 3, RPL, true, true>}},
-
-const NoiseKernels kUniformNoiseKernels[kNoiseCount] = {OIM_NOISE_VARIANTS(OIM_UNIFORM_NOISE_ENTRY)};
-
 }  // namespace persist
 }  // namespace oim

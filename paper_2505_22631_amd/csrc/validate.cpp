@@ -252,6 +252,69 @@ void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const
     });
 }
 
+bool build_sorted(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
+                  int32_t n_inst, const int32_t* inst_off, float uniform_w, uint64_t max_bytes,
+                  SortedRows& out) {
+    out = SortedRows{};
+    const bool uw = uniform_w == 1.0f || uniform_w == -1.0f;
+    const int64_t per = uw ? 4 : 2;  // entries per group
+    std::vector<int32_t> count, order;
+    uint64_t groups64 = 0;
+    for (int32_t b = 0; b < n_inst; ++b) {
+        const int32_t o = inst_off ? inst_off[b] : 0;
+        const int32_t nb = inst_off ? inst_off[b + 1] - o : n;
+        const int64_t plane = ((int64_t)nb + 255) / 256 * 64;
+        const int32_t runs = (nb + 63) / 64;
+        auto groups = [&](int32_t i) {
+            return i < nb ? (int32_t)((row_ptr[o + i + 1] - row_ptr[o + i] + per - 1) / per) : -1;
+        };
+        // counting sort by groups, most first, over the table slots in order
+        int32_t gmax = 0;
+        for (int32_t i = 0; i < nb; ++i) gmax = std::max(gmax, groups(i));
+        count.assign((size_t)gmax + 3, 0);
+        for (int32_t i = 0; i < runs * 64; ++i) ++count[(size_t)(gmax - groups(i)) + 1];
+        for (size_t d = 1; d < count.size(); ++d) count[d] += count[d - 1];
+        order.resize((size_t)runs * 64);
+        for (int32_t j = 0; j < 4; ++j)
+            for (int32_t i = j; i < runs * 64; i += 4)
+                order[(size_t)count[(size_t)(gmax - groups(i))]++] = i;
+        out.run0.push_back((int32_t)out.run.size());
+        for (int32_t k = 0; k < runs; ++k) {
+            const int32_t D = std::max(0, groups(order[(size_t)k * 64]));
+            const uint64_t base = groups64;
+            groups64 += (uint64_t)D + 1;
+            if (groups64 * 1024 > max_bytes) {
+                out = SortedRows{};
+                return false;
+            }
+            out.run.push_back(int2{(int32_t)base, D});
+            const int32_t zero = (int32_t)(36 * plane);
+            out.entries.resize((size_t)groups64 * 64, uw ? int4{zero, zero, zero, zero} : int4{zero, 0, zero, 0});
+            for (int32_t l = 0; l < 64; ++l) {
+                const int32_t i = order[(size_t)k * 64 + l];
+                const int64_t rb = i < nb ? row_ptr[o + i] : 0;
+                const int32_t len = i < nb ? (int32_t)(row_ptr[o + i + 1] - rb) : 0;
+                int32_t up = 0;  // columns ascend along a row
+                while (up < len && col_idx[rb + up] - o <= i) ++up;
+                out.row.push_back(int2{i, up | len << 16});
+                for (int32_t e = 0; e < len; ++e) {
+                    int4& g = out.entries[((size_t)base + (size_t)(e / per)) * 64 + l];
+                    int32_t* word = &g.x;
+                    const int32_t c = col_idx[rb + e] - o;
+                    const int32_t at = (int32_t)(8 * ((c & 3) * plane + (c >> 2)));
+                    if (uw) {
+                        word[e & 3] = at;
+                    } else {
+                        word[2 * (e & 1)] = at;
+                        std::memcpy(&word[2 * (e & 1) + 1], &J[rb + e], 4);
+                    }
+                }
+            }
+        }
+    }
+    return true;
+}
+
 bool ell_wanted(int32_t n, const int64_t* row_ptr, int mode) {
     if (mode == 0 || n <= 0) return false;
     int64_t dmax = 0, csr_groups = 0;

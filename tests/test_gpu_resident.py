@@ -70,6 +70,8 @@ def test_resident_rows_same_bits(oim, degree, weights, n, q, steps):
     ([1700], 2, ((1024, 1, 2),)),                      # two idle waves for seven slices
     ([2048], 1, ((1024, 1, 2),)),
     ([510], 300, ((512, 1, 1), (256, 1, 2))),          # two workgroups per CU
+    ([4095], 2, ((1024, 1, 4),)),
+    ([3, 900, 64, 65], 2, ((256, 1, 4), (512, 1, 4), (512, 1, 2))),
     ([250], 600, ((256, 1, 1), (256, 1, 2), (512, 1, 1))),
 ])
 def test_shared_noise_same_bits(oim, sizes, R, weights, shapes):
