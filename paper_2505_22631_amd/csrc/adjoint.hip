@@ -769,69 +769,49 @@ AdjArgs base_args(const Problem* p, const oim_adjoint_cfg* cfg, const float* K, 
 // A wave per group of 64 rows of the largest instance, sixteen at most.
 int block_threads(const AdjArgs& a) { return a.tabN < kMaxTB ? a.tabN : kMaxTB; }
 
-template <typename T>
-int alloc_and_copy(T** dst, const T* src, size_t count, const char* what) {
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(dst), count * sizeof(T) + 16);
-    if (e != hipSuccess) {
-        *dst = nullptr;
-        return e == hipErrorOutOfMemory ? set_error(OIM_E_NOMEM, std::string(what) + ": out of device memory")
-                                        : hip_error(e, what);
-    }
-    if (src) e = hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice);
-    return e == hipSuccess ? OIM_OK : hip_error(e, what);
-}
-
 }  // namespace
 
-int adjoint_prepare(Problem* p, const AdjRowsHost& h) {
-    // one upload: group spans, groups, first groups, oscillators, slots, instances of groups
+void adjoint_layout(const Problem* p, const AdjRowsHost& h, AdjLayout& out) {
+    // group spans, groups, first groups, oscillators, slots, instances of groups
     const size_t I = h.span.size(), G = h.group.size(), n = h.slot_of.size();
-    std::vector<unsigned char> blob;
     auto append = [&](const void* src, size_t bytes) {
-        const size_t o = blob.size();
-        blob.resize(o + (bytes + 15) / 16 * 16);
-        if (bytes) std::memcpy(blob.data() + o, src, bytes);
+        const size_t o = out.blob.size();
+        out.blob.resize(o + (bytes + 15) / 16 * 16);
+        if (bytes) std::memcpy(out.blob.data() + o, src, bytes);
         return o;
     };
-    const size_t o_span = append(h.span.data(), I * sizeof(int2));
-    const size_t o_group = append(h.group.data(), G * sizeof(int2));
-    const size_t o_group0 = append(h.group0.data(), I * sizeof(int32_t));
-    const size_t o_osc = append(h.osc.data(), G * 64 * sizeof(int16_t));
-    const size_t o_slot = append(h.slot_of.data(), n * sizeof(uint16_t));
-    const size_t o_inst = append(h.inst_of.data(), G * sizeof(int32_t));
-    unsigned char* d = nullptr;
-    int st = alloc_and_copy(&d, blob.data(), blob.size(), "adjoint rows");
-    p->d_adj_rows = d;
-    if (st) return st;
+    out.span = append(h.span.data(), I * sizeof(int2));
+    out.group = append(h.group.data(), G * sizeof(int2));
+    out.group0 = append(h.group0.data(), I * sizeof(int32_t));
+    out.osc = append(h.osc.data(), G * 64 * sizeof(int16_t));
+    out.slot = append(h.slot_of.data(), n * sizeof(uint16_t));
+    out.inst = append(h.inst_of.data(), G * sizeof(int32_t));
     const size_t words = (size_t)h.rows64 * 64;
-    const size_t idx_bytes = (words * 4 + 255) / 256 * 256;
-    const size_t w_bytes = p->unit_weights ? 0 : (words * 8 + 255) / 256 * 256;
-    unsigned char* img = nullptr;
-    st = alloc_and_copy(&img, static_cast<const unsigned char*>(nullptr), idx_bytes + w_bytes + n * 8,
-                        "adjoint row image");
-    p->d_adj_img = img;
-    if (st) return st;
+    out.idx_bytes = (words * 4 + 255) / 256 * 256;
+    out.w_bytes = p->unit_weights ? 0 : (words * 8 + 255) / 256 * 256;
+    out.image_bytes = out.idx_bytes + out.w_bytes + n * 8 + 16;
+}
+
+int adjoint_build(Problem* p, const AdjRowsHost& h, const AdjLayout& l) {
+    const unsigned char* d = static_cast<const unsigned char*>(p->d_adj_rows);
+    unsigned char* img = static_cast<unsigned char*>(p->d_adj_img);
     uint32_t* idx = reinterpret_cast<uint32_t*>(img);
-    float2* w = w_bytes ? reinterpret_cast<float2*>(img + idx_bytes) : nullptr;
-    double* row_sum = reinterpret_cast<double*>(img + idx_bytes + w_bytes);
+    float2* w = l.w_bytes ? reinterpret_cast<float2*>(img + l.idx_bytes) : nullptr;
+    double* row_sum = reinterpret_cast<double*>(img + l.idx_bytes + l.w_bytes);
     AdjRows& r = p->adj_rows;
-    r.span = reinterpret_cast<const int2*>(d + o_span);
-    r.group = reinterpret_cast<const int2*>(d + o_group);
-    r.group0 = reinterpret_cast<const int32_t*>(d + o_group0);
-    r.osc = reinterpret_cast<const int16_t*>(d + o_osc);
+    r.span = reinterpret_cast<const int2*>(d + l.span);
+    r.group = reinterpret_cast<const int2*>(d + l.group);
+    r.group0 = reinterpret_cast<const int32_t*>(d + l.group0);
+    r.osc = reinterpret_cast<const int16_t*>(d + l.osc);
     r.idx = idx;
     r.w = w;
     r.row_sum = row_sum;
     p->adj_max_words = h.max_words;
-    hipLaunchKernelGGL(adjoint_rows_kernel, dim3((unsigned)G), dim3(64), 0, 0, r, p->d_row_ptr, p->d_col,
-                       p->d_J, p->d_inst, reinterpret_cast<const int32_t*>(d + o_inst),
-                       reinterpret_cast<const uint16_t*>(d + o_slot), idx, w, row_sum,
+    hipLaunchKernelGGL(adjoint_rows_kernel, dim3((unsigned)h.group.size()), dim3(64), 0, 0, r, p->d_row_ptr, p->d_col,
+                       p->d_J, p->d_inst, reinterpret_cast<const int32_t*>(d + l.inst),
+                       reinterpret_cast<const uint16_t*>(d + l.slot), idx, w, row_sum,
                        (p->max_inst_n + 63) & ~63, p->unit_weights ? 1 : 0);
-    st = check_launch("adjoint_rows_kernel");
-    if (st) return st;
-    // callers may run on any stream next
-    const hipError_t e = hipStreamSynchronize(0);
-    return e == hipSuccess ? OIM_OK : hip_error(e, "adjoint row image");
+    return check_launch("adjoint_rows_kernel");
 }
 
 int64_t adjoint_checkpoint_words(const Problem* p, const oim_adjoint_cfg* cfg) {

@@ -58,10 +58,11 @@ struct SellImage {
 // every entry, else (offset, weight) pairs, two to a group.  Padding points at
 // the zero entry, with weight 0.
 struct SortedRows {
-    std::vector<int2> run;       // per run: (base, groups per row)
-    std::vector<int2> row;       // per run and lane: (oscillator, upper start | length << 16)
-    std::vector<int32_t> run0;   // per instance: its first run
-    std::vector<int4> entries;
+    std::vector<int2> run;        // per run: (base, groups per row)
+    std::vector<int32_t> osc;     // per run and lane: oscillator of the instance
+    std::vector<int32_t> run0;    // per instance: its first run
+    std::vector<int32_t> inst_of; // per run: its instance
+    int64_t groups = 0;           // of 64 lanes, in all
 };
 
 // Largest instance of that image.
@@ -135,16 +136,22 @@ struct Problem {
     int32_t sell_slices = 0;
     int64_t sell_entries = 0;
     int2* d_sell_desc = nullptr;
-    int2* d_sell = nullptr;
+    int2* d_sell = nullptr;         // null where the unit-weight image takes its place
     uint32_t* d_sell_uw = nullptr;  // unit-weight image, or null
     int2* d_row_split = nullptr;    // SellImage::row_split
 
-    // device: SortedRows (instances of at most kSortedMaxN oscillators), else null
+    // device: SortedRows (instances of at most kSortedMaxN oscillators), else null;
+    // per run and lane (oscillator, upper start | length << 16)
     int2* d_sorted_run = nullptr;
     int2* d_sorted_row = nullptr;
     int32_t* d_sorted_run0 = nullptr;
+    int32_t* d_sorted_osc = nullptr;
+    int32_t* d_sorted_inst = nullptr;
     int4* d_sorted = nullptr;
     uint32_t sorted_bytes = 0;
+
+    // one allocation that holds every image made at creation (sparse problems)
+    void* d_images = nullptr;
     float uniform_w = 0.f;          // the weight every entry shares (+1 or -1), or 0
 
     // device: dense coupling (dense problems), FP32 and the BF16 split
@@ -202,9 +209,8 @@ int validate_blocks(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, i
 void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
                 int32_t n_inst, const int32_t* inst_off, SellImage& out, float uniform_w = 0.f);
 // False, leaving `out` empty, if the image's bytes pass `max_bytes`.
-bool build_sorted(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
-                  int32_t n_inst, const int32_t* inst_off, float uniform_w, uint64_t max_bytes,
-                  SortedRows& out);
+bool build_sorted(int32_t n, const int64_t* row_ptr, int32_t n_inst, const int32_t* inst_off,
+                  float uniform_w, uint64_t max_bytes, SortedRows& out);
 
 // Every row padded to the same length D (the longest row rounded up to 4,
 // at least 4), quads of rows padded to 4 rows, stored quad by quad in
@@ -270,7 +276,17 @@ int tune_persistent(Problem* p, const oim_run_cfg* cfg, const float* K, const fl
                     int32_t trial_steps, oim_tune_report* rep, hipStream_t stream);
 int validate_adjoint_cfg(const Problem* p, const oim_adjoint_cfg* cfg);
 int64_t adjoint_checkpoint_words(const Problem* p, const oim_adjoint_cfg* cfg);
-int adjoint_prepare(Problem* p, const AdjRowsHost& rows);
+// The adjoint's rows: what creation uploads (`blob`, to d_adj_rows) and
+// reserves (image_bytes, at d_adj_img), and the launch that fills the image.
+struct AdjLayout {
+    std::vector<unsigned char> blob;
+    size_t span = 0, group = 0, group0 = 0, osc = 0, slot = 0, inst = 0;
+    size_t idx_bytes = 0, w_bytes = 0, image_bytes = 0;
+};
+void adjoint_layout(const Problem* p, const AdjRowsHost& rows, AdjLayout& out);
+int adjoint_build(Problem* p, const AdjRowsHost& rows, const AdjLayout& layout);
+// Fills the sorted rows' image from the CSR (`runs` runs).
+int sorted_build(const Problem* p, int32_t runs);
 constexpr int kAdjEvents = 5;
 void adjoint_release(Problem* p);
 int launch_adjoint_forward(Problem* p, const oim_adjoint_cfg* cfg, const float* K, const float* Ks,

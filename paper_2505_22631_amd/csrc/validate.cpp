@@ -187,6 +187,25 @@ void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const
     const bool uw = uniform_w == 1.0f || uniform_w == -1.0f;
     out.inst.clear();
     out.max_slices = 0;
+    // a slice's rows are padded to its longest one, rounded up to 4
+    auto slice_degree = [&](int32_t o, int32_t nb, int32_t s) {
+        int32_t mx = 0;
+        const int64_t lo = 4LL * s * kSliceQuads, hi = std::min<int64_t>(nb, lo + 4 * kSliceQuads);
+        for (int64_t i = lo; i < hi; ++i)
+            mx = std::max<int32_t>(mx, (int32_t)(row_ptr[o + i + 1] - row_ptr[o + i]));
+        return (mx + 3) & ~3;
+    };
+    size_t total = 0, slices = 0;
+    for (int32_t b = 0; b < n_inst; ++b) {
+        const int32_t o = inst_off ? inst_off[b] : 0;
+        const int32_t nb = inst_off ? inst_off[b + 1] - inst_off[b] : n;
+        for (int32_t s = 0; 4LL * s * kSliceQuads < nb; ++s, ++slices)
+            total += (size_t)4 * slice_degree(o, nb, s) * kSliceQuads;
+    }
+    out.desc.reserve(slices);
+    out.row_split.reserve(slices * 4 * kSliceQuads);
+    out.entries.reserve(total);
+    if (uw) out.entries_uw.reserve(total);
     int64_t rows4 = 0;  // running offset in int4 rows (64 int4 per row)
     int32_t slice_base = 0;
     for (int32_t b = 0; b < n_inst; ++b) {
@@ -200,11 +219,7 @@ void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const
         const int64_t plane = (int64_t)S * kSliceQuads;
         auto lds_off = [plane](int64_t i) { return (int32_t)(8 * ((i & 3) * plane + (i >> 2))); };
         for (int32_t s = 0; s < S; ++s) {
-            int32_t mx = 0;
-            const int64_t lo = 4LL * s * kSliceQuads, hi = std::min<int64_t>(nb, 4LL * (s + 1) * kSliceQuads);
-            for (int64_t i = lo; i < hi; ++i)
-                mx = std::max<int32_t>(mx, (int32_t)(row_ptr[o + i + 1] - row_ptr[o + i]));
-            const int32_t deg = (mx + 3) & ~3;
+            const int32_t deg = slice_degree(o, nb, s);
             out.desc.push_back(int2{(int32_t)rows4, deg});
             const size_t first = out.entries.size();
             out.entries.resize(first + (size_t)4 * deg / 2 * kSliceQuads * 2, int2{0, 0});
@@ -212,32 +227,35 @@ void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const
             if (uw) out.entries_uw.resize(first_uw + (size_t)4 * deg * kSliceQuads, 0u);
             const uint32_t zero_off = (uint32_t)(36 * plane);  // after table and colours
             for (int j = 0; j < 4; ++j) {
+                int64_t rb[kSliceQuads];
+                int32_t rl[kSliceQuads], self[kSliceQuads];
                 for (int l = 0; l < kSliceQuads; ++l) {
                     const int64_t i = 4LL * (s * kSliceQuads + l) + j;  // local index
-                    const int32_t self = (int32_t)std::min<int64_t>(i, nb - 1);
-                    const int64_t rb = i < nb ? row_ptr[o + i] : 0;
-                    const int64_t rl = i < nb ? row_ptr[o + i + 1] - row_ptr[o + i] : 0;
-                    int32_t first_up = 0;  // columns ascend along a row
-                    while (first_up < rl && col_idx[rb + first_up] - o <= i) ++first_up;
-                    out.row_split.push_back(int2{first_up, (int32_t)rl});
-                    for (int32_t e = 0; e < deg; ++e) {
-                        int2 v;
-                        if (e < rl) {
-                            v.x = lds_off(col_idx[rb + e] - o);
-                            float w = J[rb + e];
-                            std::memcpy(&v.y, &w, 4);
-                        } else {
-                            v.x = lds_off(self);
-                            v.y = 0;
+                    self[l] = lds_off(std::min<int64_t>(i, nb - 1));
+                    rb[l] = i < nb ? row_ptr[o + i] : 0;
+                    rl[l] = i < nb ? (int32_t)(row_ptr[o + i + 1] - rb[l]) : 0;
+                    // columns ascend along a row
+                    const int32_t* c = col_idx + rb[l];
+                    const int32_t first_up =
+                        (int32_t)(std::upper_bound(c, c + rl[l], (int32_t)(o + i)) - c);
+                    out.row_split.push_back(int2{first_up, rl[l]});
+                }
+                // an entry of every lane at a time, so that the image is
+                // written in order
+                for (int32_t e = 0; e < deg; ++e) {
+                    int2* to = &out.entries[first + (((size_t)j * (deg / 2) + e / 2) * kSliceQuads) * 2 + (e & 1)];
+                    for (int l = 0; l < kSliceQuads; ++l) {
+                        int2 v{self[l], 0};
+                        if (e < rl[l]) {
+                            v.x = lds_off(col_idx[rb[l] + e] - o);
+                            std::memcpy(&v.y, &J[rb[l] + e], 4);
                         }
-                        const int64_t q4 = ((int64_t)j * (deg / 2) + e / 2) * kSliceQuads + l;
-                        out.entries[first + (size_t)(q4 * 2 + (e & 1))] = v;
-                        if (uw) {
-                            const int64_t u4 = ((int64_t)j * (deg / 4) + e / 4) * kSliceQuads + l;
-                            out.entries_uw[first_uw + (size_t)(u4 * 4 + (e & 3))] =
-                                e < rl ? (uint32_t)v.x : zero_off;
-                        }
+                        to[2 * l] = v;
                     }
+                    if (!uw) continue;
+                    uint32_t* tu = &out.entries_uw[first_uw + (((size_t)j * (deg / 4) + e / 4) * kSliceQuads) * 4 + (e & 3)];
+                    for (int l = 0; l < kSliceQuads; ++l)
+                        tu[4 * l] = e < rl[l] ? (uint32_t)to[2 * l].x : zero_off;
                 }
             }
             rows4 += 4LL * deg / 2;
@@ -252,21 +270,19 @@ void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const
     });
 }
 
-bool build_sorted(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
-                  int32_t n_inst, const int32_t* inst_off, float uniform_w, uint64_t max_bytes,
-                  SortedRows& out) {
+bool build_sorted(int32_t n, const int64_t* row_ptr, int32_t n_inst, const int32_t* inst_off,
+                  float uniform_w, uint64_t max_bytes, SortedRows& out) {
     out = SortedRows{};
     const bool uw = uniform_w == 1.0f || uniform_w == -1.0f;
-    const int64_t per = uw ? 4 : 2;  // entries per group
+    const int shift = uw ? 2 : 1;
+    const int64_t per = 1 << shift;  // entries per group
     std::vector<int32_t> count, order;
-    uint64_t groups64 = 0;
     for (int32_t b = 0; b < n_inst; ++b) {
         const int32_t o = inst_off ? inst_off[b] : 0;
         const int32_t nb = inst_off ? inst_off[b + 1] - o : n;
-        const int64_t plane = ((int64_t)nb + 255) / 256 * 64;
         const int32_t runs = (nb + 63) / 64;
         auto groups = [&](int32_t i) {
-            return i < nb ? (int32_t)((row_ptr[o + i + 1] - row_ptr[o + i] + per - 1) / per) : -1;
+            return i < nb ? (int32_t)((row_ptr[o + i + 1] - row_ptr[o + i] + per - 1) >> shift) : -1;
         };
         // counting sort by groups, most first, over the table slots in order
         int32_t gmax = 0;
@@ -281,36 +297,15 @@ bool build_sorted(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, con
         out.run0.push_back((int32_t)out.run.size());
         for (int32_t k = 0; k < runs; ++k) {
             const int32_t D = std::max(0, groups(order[(size_t)k * 64]));
-            const uint64_t base = groups64;
-            groups64 += (uint64_t)D + 1;
-            if (groups64 * 1024 > max_bytes) {
+            out.run.push_back(int2{(int32_t)out.groups, D});
+            out.inst_of.push_back(b);
+            out.groups += D + 1;
+            if ((uint64_t)out.groups * 1024 > max_bytes) {
                 out = SortedRows{};
                 return false;
             }
-            out.run.push_back(int2{(int32_t)base, D});
-            const int32_t zero = (int32_t)(36 * plane);
-            out.entries.resize((size_t)groups64 * 64, uw ? int4{zero, zero, zero, zero} : int4{zero, 0, zero, 0});
-            for (int32_t l = 0; l < 64; ++l) {
-                const int32_t i = order[(size_t)k * 64 + l];
-                const int64_t rb = i < nb ? row_ptr[o + i] : 0;
-                const int32_t len = i < nb ? (int32_t)(row_ptr[o + i + 1] - rb) : 0;
-                int32_t up = 0;  // columns ascend along a row
-                while (up < len && col_idx[rb + up] - o <= i) ++up;
-                out.row.push_back(int2{i, up | len << 16});
-                for (int32_t e = 0; e < len; ++e) {
-                    int4& g = out.entries[((size_t)base + (size_t)(e / per)) * 64 + l];
-                    int32_t* word = &g.x;
-                    const int32_t c = col_idx[rb + e] - o;
-                    const int32_t at = (int32_t)(8 * ((c & 3) * plane + (c >> 2)));
-                    if (uw) {
-                        word[e & 3] = at;
-                    } else {
-                        word[2 * (e & 1)] = at;
-                        std::memcpy(&word[2 * (e & 1) + 1], &J[rb + e], 4);
-                    }
-                }
-            }
         }
+        out.osc.insert(out.osc.end(), order.begin(), order.end());
     }
     return true;
 }
