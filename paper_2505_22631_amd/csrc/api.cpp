@@ -240,6 +240,7 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
         p->sorted_bytes = (uint32_t)((size_t)sorted.groups * 1024);
         images.reserve(&p->d_sorted_row, sorted.osc.size());
         images.reserve(&p->d_sorted, (size_t)sorted.groups * 64);
+        if (p->max_inst_n <= kSortedSplitN) images.reserve(&p->d_sorted2, (size_t)sorted.groups * 64);
     }
     if (adj_ok)
         images.reserve(reinterpret_cast<unsigned char**>(&p->d_adj_img), adj_layout.image_bytes);

@@ -54,7 +54,7 @@ struct SellImage {
 // first, equal ones by table slot, those past n last; 64 consecutive ones
 // are a run, padded to its first row's groups and one group of padding more:
 // group h of lane l at (base + h) * 64 + l.  Entries are those of SellImage in
-// the same order: LDS byte offsets, four to a group, with one weight of +-1 on
+// the same order: LDS byte offsets (of either copy in the second image), four to a group, with one weight of +-1 on
 // every entry, else (offset, weight) pairs, two to a group.  Padding points at
 // the zero entry, with weight 0.
 struct SortedRows {
@@ -67,6 +67,8 @@ struct SortedRows {
 
 // Largest instance of that image.
 constexpr int kSortedMaxN = 4096;
+// Largest instance that its split-row shapes hold.
+constexpr int kSortedSplitN = 2048;
 
 constexpr size_t kCsrPad = 4;
 
@@ -148,6 +150,7 @@ struct Problem {
     int32_t* d_sorted_osc = nullptr;
     int32_t* d_sorted_inst = nullptr;
     int4* d_sorted = nullptr;
+    int4* d_sorted2 = nullptr;  // for two copies of the tables (at most kSortedSplitN), or null
     uint32_t sorted_bytes = 0;
 
     // one allocation that holds every image made at creation (sparse problems)

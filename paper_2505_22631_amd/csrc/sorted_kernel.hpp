@@ -19,15 +19,17 @@
 //
 // What bounds it: with one workgroup per CU and short rows the chain LDS
 // reads -> sums -> update -> barrier, with long ones the LDS reads (8 bytes per
-// entry from random banks).  us per step of the shapes that walked each
-// slice's longest row with two barriers, and now, one replica: n = 200 of
-// degree 10 unit weights 1.03 -> 0.58, real weights 1.31 -> 0.60; n = 500 of
-// degree 10 1.25 -> 0.68, real 1.60 -> 0.66; G(800, 0.06) 3.13 -> 2.20, real
-// 4.72 -> 2.32; n = 2000 of degree 10 2.41 -> 1.95, real 3.00 -> 1.81; n = 4000
-// of degree 6 real weights 4.5 -> 2.9.  Of that, 0.85 -> 0.60 us (n = 200, unit
-// weights) is the noise drawn once by waves of their own, 2.97 -> 2.20 (real
-// 3.97 -> 2.32) on G(800, 0.06) the sorting, whose runs' longest rows sum to
-// 1.05 times the entries where whole slices' took 1.4.
+// entry from random banks; G(800, 0.06) 13 waves x 48 reads of 6 to 9 cycles).
+// us per step of the shapes that walked each slice's longest row with two
+// barriers, and now, one replica: n = 200 of degree 10 unit weights 1.03 ->
+// 0.61, real weights 1.31 -> 0.60; n = 500 of degree 10 1.25 -> 0.64, real 1.60
+// -> 0.63; G(800, 0.06) 3.13 -> 1.78, real 4.72 -> 2.12; n = 2000 of degree 10
+// 2.41 -> 1.73, real 3.00 -> 1.52; n = 4000 of degree 6 real weights 4.5 ->
+// 2.9.  Of that the noise drawn once by waves of their own gave 0.85 -> 0.60 us
+// (n = 200, unit weights), the sorting 2.97 -> 2.20 (real 3.97 -> 2.32) on
+// G(800, 0.06), whose runs' longest rows sum to 1.05 times the entries where
+// whole slices' took 1.4, and the second copy of the table 2.20 -> 1.78 (real
+// 2.32 -> 2.12; n = 2000 1.95 -> 1.73, real 1.81 -> 1.52).
 #pragma once
 #include <type_traits>
 
@@ -54,14 +56,27 @@ __device__ __forceinline__ uint64_t sc_word(int byte_off) {
     return *reinterpret_cast<lds_u64*>((uint32_t)byte_off);
 }
 
-// LDS byte offset of the second table of a shape of C slices: past the first
-// table, the colours and the zero entry of its largest instance, a constant
-// so that a read's table is part of its instruction.
-__host__ __device__ constexpr int sorted_table1(int C) { return 36 * 64 * C + 16; }
+// Split-row shapes keep every (sin, cos) twice, the second time in an order of
+// its own, and each entry points at the copy that leaves the LDS banks less
+// contended (see sorted_rows_kernel).
+__host__ __device__ constexpr int copies(int rpl) { return rpl < 4 ? 2 : 1; }
+// Where the second copy holds slot s: the same 32 slots, permuted by their
+// number, so that its bank says nothing about the first copy's.
+__host__ __device__ constexpr int second_slot(int s, int plane) {
+    return 4 * plane + (s ^ ((s >> 5) & 31));
+}
+
+// Layout of a table: the copies of (sin, cos), of the colours, the zero entry
+// at byte 36 * copies * plane.  The second table of a shape of C slices starts
+// past the first one of its largest instance, a constant so that a read's
+// table is part of its instruction.
+__host__ __device__ constexpr int sorted_table1(int C, int cp) { return 36 * cp * 64 * C + 16; }
 
 // LDS of a launch: the tables, the noise buffers, the readout's sums.
-inline size_t sorted_lds(int C, int plane) {
-    return (size_t)sorted_table1(C) + 36 * (size_t)plane + 16 + 32 * (size_t)plane + 16 * sizeof(double);
+inline size_t sorted_lds(int C, int rpl, int plane) {
+    const int cp = copies(rpl);
+    return (size_t)sorted_table1(C, cp) + 36 * (size_t)cp * plane + 16 + 32 * (size_t)plane +
+           16 * sizeof(double);
 }
 
 // C slices of capacity, RPL rows per lane: wave w holds runs w * RPL ..
@@ -91,15 +106,16 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
     const int plane = S * 64;
     const int runs = (n + 63) >> 6;
     const int run0 = sa.run0[inst_id];
-    constexpr int T1 = sorted_table1(C);
+    constexpr int CP = copies(RPL);
+    constexpr int T1 = sorted_table1(C, CP);
     constexpr int E = UWT ? 4 : 2;      // entries per 16-byte group
     constexpr int GB = 4 / RPL;         // groups of a row read together
     constexpr int NV = 2 * GB;          // resident groups per row
     float2* sc = reinterpret_cast<float2*>(smem);
-    unsigned char* col8 = smem + (size_t)32 * plane;
-    // (0, 0) at byte 36 * plane of each table, what padding entries read
-    float2* zero_entry = reinterpret_cast<float2*>(smem + (size_t)36 * plane);
-    float* nz = reinterpret_cast<float*>(smem + T1 + 36 * plane + 16);  // [2][4 * plane]
+    unsigned char* col8 = smem + (size_t)32 * CP * plane;
+    // (0, 0) in each table, what padding entries read
+    float2* zero_entry = reinterpret_cast<float2*>(smem + (size_t)36 * CP * plane);
+    float* nz = reinterpret_cast<float*>(smem + T1 + 36 * CP * plane + 16);  // [2][4 * plane]
     double* red = reinterpret_cast<double*>(nz + 8 * plane);            // [16]
 
     const int lane = threadIdx.x & 63;
@@ -118,7 +134,7 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
 
     // the lane's rows: oscillator (past n: none), table slot, (first group,
     // groups), phase, (sin, cos)
-    int osc[RPL], slot[RPL], base[RPL], D[RPL];
+    int osc[RPL], slot[RPL], slot2[RPL], base[RPL], D[RPL];
     uint32_t ph[RPL];
     float2 own_sc[RPL];
     int4 res[RPL][NV];
@@ -138,10 +154,14 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
         const int i = sa.row[(run0 + run) * 64 + lane].x;
         osc[jj] = have(jj) ? i : n;
         slot[jj] = (i & 3) * plane + (i >> 2);
+        slot2[jj] = CP > 1 ? second_slot(slot[jj], plane) : 0;
         const uint32_t u = osc[jj] < n ? (pw ? pw[osc[jj]] : phase_from_theta(th[osc[jj]])) : 0u;
         ph[jj] = u;
         own_sc[jj] = make_float2(sin_turn(u), cos_turn(u));
-        if (have(jj)) sc[slot[jj]] = own_sc[jj];
+        if (have(jj)) {
+            sc[slot[jj]] = own_sc[jj];
+            if constexpr (CP > 1) sc[slot2[jj]] = own_sc[jj];
+        }
 #pragma unroll
         for (int h = 0; h < NV; ++h) res[jj][h] = load_group(jj, h);
     }
@@ -281,7 +301,10 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
             const uint32_t u = advance(ph[jj], inc);
             ph[jj] = u;
             own_sc[jj] = make_float2(sin_turn(u), cos_turn(u));
-            if (have(jj)) sc[wr / 8 + slot[jj]] = own_sc[jj];
+            if (have(jj)) {
+                sc[wr / 8 + slot[jj]] = own_sc[jj];
+                if constexpr (CP > 1) sc[wr / 8 + slot2[jj]] = own_sc[jj];
+            }
         }
     };
 
@@ -319,7 +342,10 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
 #pragma unroll
             for (int jj = 0; jj < RPL; ++jj) {
                 own_c[jj] = nearest_state(ph[jj], q);
-                if (have(jj)) col8[slot[jj]] = (unsigned char)own_c[jj];
+                if (have(jj)) {
+                    col8[slot[jj]] = (unsigned char)own_c[jj];
+                    if constexpr (CP > 1) col8[slot2[jj]] = (unsigned char)own_c[jj];
+                }
                 ul[jj] = have(jj) ? sa.row[(run0 + wave * RPL + jj) * 64 + lane].y : 0;
             }
             __syncthreads();

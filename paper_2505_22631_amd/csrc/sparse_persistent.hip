@@ -85,14 +85,14 @@ bool cu_holds(int64_t groups, int64_t waves) {
 //  - A step's latency is shared by the waves of a workgroup, so the rows are
 //    split over as many waves as the CU holds with its other workgroups
 //    (cu_holds), unit weights with room for the noise's waves: us per step with
-//    4, 2 and 1 rows per lane, n = 800 of degree 10 one replica 2.0, 1.01, 1.01
-//    (real weights 2.1, 1.31, 0.94), 500 replicas 2.4, 1.82, 2.3 (real 3.0,
-//    1.65, 2.3); n = 500, 500 replicas 1.85, 1.13, 1.28 (real 2.0, 1.23, 1.17).
-//    Longer rows weigh more than the noise: G(800, 0.06) one replica 4.0, 2.5,
-//    2.2, 500 replicas 5.4, 4.2, 4.8 (real 8.3, 5.2, 5.0), 600 replicas 7.1,
-//    6.5, 7.4 (real 9.7, 9.0, 7.7).  Past that unit weights take whole quads
-//    (n = 2000, 500 replicas 3.7, against 3.9 with 2 rows per lane), real ones 2
-//    rows (4.0 against 3.7).
+//    4, 2 and 1 rows per lane, n = 800 of degree 10 one replica 2.0, 0.93, 1.04
+//    (real weights 2.1, 1.26, 0.96), 500 replicas 2.4, 1.63, 2.2 (real 3.0,
+//    1.54, 2.2); n = 500, 500 replicas 1.85, 1.09, 1.15 (real 2.0, 1.21, 1.09).
+//    Longer rows weigh more than the noise: G(800, 0.06) one replica 4.0, 2.2,
+//    1.8, 500 replicas 5.4, 3.4, 4.0 (real 8.2, 5.0, 4.5).  Past that unit
+//    weights take whole quads (n = 1500, 500 replicas 2.90, against 2.98 with 2
+//    rows per lane; 600 replicas 4.5 against 5.1), real ones 2 rows (3.3 against
+//    2.7).
 //  - Nine to sixteen slices of real weights or long rows keep sixteen waves of
 //    sorted rows however many replicas there are (n = 4000 of degree 30, 600
 //    replicas: 22.4 us, real 26, against 23.7 and 34 on 256 threads).
@@ -191,7 +191,7 @@ int launch_sorted(const Problem* p, const Variant& v, const PersistArgs& a, int 
                   hipStream_t stream) {
     SortedArgs sa{};
     sa.p = a;
-    sa.entries = p->d_sorted;
+    sa.entries = copies(v.rpl) > 1 ? p->d_sorted2 : p->d_sorted;
     sa.run = p->d_sorted_run;
     sa.row = p->d_sorted_row;
     sa.run0 = p->d_sorted_run0;
@@ -204,7 +204,7 @@ int launch_sorted(const Problem* p, const Variant& v, const PersistArgs& a, int 
     const int64_t per_cu = ((int64_t)a.R * p->n_inst + 255) / 256;
     int waves = ((p->max_inst_n + 63) / 64 + v.rpl - 1) / v.rpl;
     for (int k = 0; k < S && cu_holds(per_cu, waves + 1); ++k) ++waves;
-    const size_t lds = sorted_lds(shape->C, S * 64);
+    const size_t lds = sorted_lds(shape->C, v.rpl, S * 64);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(shape->fn[qi]),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, "hipFuncSetAttribute");
