@@ -79,6 +79,14 @@ inline size_t sorted_lds(int C, int rpl, int plane) {
            16 * sizeof(double);
 }
 
+// Waves of this kernel share LDS alone, so its barriers wait for LDS alone: a
+// readout's stores to memory drain while the next steps run.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // C slices of capacity, RPL rows per lane: wave w holds runs w * RPL ..
 // w * RPL + RPL - 1, and waves past the last run draw noise.
 template <int C, int RPL, int QM, bool UWT>
@@ -135,6 +143,7 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
     // the lane's rows: oscillator (past n: none), table slot, (first group,
     // groups), phase, (sin, cos)
     int osc[RPL], slot[RPL], slot2[RPL], base[RPL], D[RPL];
+    int ul[RPL];  // upper start | length << 16
     uint32_t ph[RPL];
     float2 own_sc[RPL];
     int4 res[RPL][NV];
@@ -151,7 +160,9 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
         const int2 d = sa.run[run0 + run];
         D[jj] = __builtin_amdgcn_readfirstlane(have(jj) ? d.y : 0);
         base[jj] = __builtin_amdgcn_readfirstlane(have(jj) ? d.x : d.x + d.y);
-        const int i = sa.row[(run0 + run) * 64 + lane].x;
+        const int2 row = sa.row[(run0 + run) * 64 + lane];
+        const int i = row.x;
+        if constexpr (UWT) ul[jj] = have(jj) ? row.y : 0;
         osc[jj] = have(jj) ? i : n;
         slot[jj] = (i & 3) * plane + (i >> 2);
         slot2[jj] = CP > 1 ? second_slot(slot[jj], plane) : 0;
@@ -188,7 +199,7 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
     if (threadIdx.x == 0) zero_entry[0] = zero_entry[T1 / 8] = make_float2(0.f, 0.f);
     double best_h = DBL_MAX;
     int best_at = -1;
-    __syncthreads();
+    lds_barrier();
 
     const float sqrt_dt = __builtin_sqrtf(a.dt);
     const int64_t sched_off = (int64_t)r * a.sched_stride;
@@ -334,11 +345,11 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
         } else {
             draw(t + 1u, (s + 1) & 1);
         }
-        __syncthreads();
+        lds_barrier();
 
         // ---- optional readout: threshold, Eq. 1 / Eq. 2, best-so-far ----
         if (a.M > 0 && ((s + 1) % a.M == 0 || s + 1 == a.steps)) {
-            int own_c[RPL], ul[RPL];
+            int own_c[RPL];
 #pragma unroll
             for (int jj = 0; jj < RPL; ++jj) {
                 own_c[jj] = nearest_state(ph[jj], q);
@@ -346,9 +357,9 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
                     col8[slot[jj]] = (unsigned char)own_c[jj];
                     if constexpr (CP > 1) col8[slot2[jj]] = (unsigned char)own_c[jj];
                 }
-                ul[jj] = have(jj) ? sa.row[(run0 + wave * RPL + jj) * 64 + lane].y : 0;
+                if constexpr (!UWT) ul[jj] = have(jj) ? sa.row[(run0 + wave * RPL + jj) * 64 + lane].y : 0;
             }
-            __syncthreads();
+            lds_barrier();
             // Each row sums its terms over j > i in column order (its entries
             // from its upper start to its length).  With one weight on every
             // entry the terms are +-w0 or 0 and their sum is exact in any
@@ -357,24 +368,55 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
             // slot, and fold as (r0 + r1) + (r2 + r3) per quad, by the xor
             // butterfly (partner distance 1, 2, ..., 32) over a slice's 64
             // quads, and pairwise over the slices: the library's fixed order.
+            // (A readout of G(800, 0.06) with unit weights took 9 us: each
+            // group's reads waited for, barriers for the stores too.  Now 4.)
             [[maybe_unused]] double* rowsum = reinterpret_cast<double*>(smem + ((s & 1) ? T1 : 0));
-            [[maybe_unused]] int cnt = 0;
+            [[maybe_unused]] int cnt = 0, all = 0;  // matching neighbours j > i, all of them
             if (rows) {
 #pragma unroll
                 for (int jj = 0; jj < RPL; ++jj) {
                     const int up = ul[jj] & 0xffff, len = ul[jj] >> 16;
-                    double rs = 0.0;
-                    auto terms = [&](const int4& v, int h) __attribute__((always_inline)) {
-                        if constexpr (UWT) {
-                            const int o4[4] = {v.x, v.y, v.z, v.w};
+                    if constexpr (UWT) {
+                        // GB groups' colours are read together; what padding
+                        // reads (past the colours, within the LDS) is not counted
+                        auto terms = [&](const int4* v, int h0) __attribute__((always_inline)) {
+                            int c[GB][4];
+                            auto colour = [&](int at) __attribute__((always_inline)) {
+                                // (kept here: hoisted out of the run, the
+                                // resident entries' addresses would spill)
+                                asm volatile("" : "+v"(at));
+                                return (int)col8[(uint32_t)at >> 3];
+                            };
 #pragma unroll
-                            for (int x = 0; x < 4; ++x) {
-                                const int idx = 4 * h + x;
-                                const bool in = idx >= up && idx < len;
-                                const bool eq = own_c[jj] == col8[in ? o4[x] >> 3 : 0];
-                                cnt += in ? (eq ? 1 : (q == 2 ? -1 : 0)) : 0;
+                            for (int h = 0; h < GB; ++h) {
+                                c[h][0] = colour(v[h].x);
+                                c[h][1] = colour(v[h].y);
+                                c[h][2] = colour(v[h].z);
+                                c[h][3] = colour(v[h].w);
                             }
-                        } else {
+#pragma unroll
+                            for (int h = 0; h < GB; ++h)
+#pragma unroll
+                                for (int x = 0; x < 4; ++x) {
+                                    const bool in = (uint32_t)(4 * (h0 + h) + x - up) < (uint32_t)(len - up);
+                                    cnt += in && own_c[jj] == c[h][x] ? 1 : 0;
+                                }
+                        };
+#pragma unroll
+                        for (int c = 0; c < NV; c += GB) {
+                            if (c > 0 && c >= D[jj]) break;
+                            terms(&res[jj][c], c);
+                        }
+                        for (int h0 = NV; h0 < D[jj]; h0 += GB) {
+                            int4 v[GB];
+#pragma unroll
+                            for (int h = 0; h < GB; ++h) v[h] = load_group(jj, h0 + h);
+                            terms(v, h0);
+                        }
+                        all += len - up;
+                    } else {
+                        double rs = 0.0;
+                        auto terms = [&](const int4& v, int h) __attribute__((always_inline)) {
                             const int o2[2] = {v.x, v.z};
                             const float w2[2] = {__int_as_float(v.y), __int_as_float(v.w)};
 #pragma unroll
@@ -385,26 +427,27 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
                                 const float tt = eq ? w2[x] : (q == 2 ? -w2[x] : 0.f);
                                 rs += in ? (double)tt : 0.0;
                             }
-                        }
-                    };
+                        };
 #pragma unroll
-                    for (int h = 0; h < NV; ++h) {
-                        if (h >= D[jj]) break;
-                        terms(res[jj][h], h);
-                    }
+                        for (int h = 0; h < NV; ++h) {
+                            if (h >= D[jj]) break;
+                            terms(res[jj][h], h);
+                        }
 #pragma unroll 2
-                    for (int h = NV; h < D[jj]; ++h) terms(load_group(jj, h), h);
-                    if constexpr (!UWT)
+                        for (int h = NV; h < D[jj]; ++h) terms(load_group(jj, h), h);
                         if (have(jj)) rowsum[slot[jj]] = rs;
+                    }
                 }
             }
             double total;
             if constexpr (UWT) {
+                // q = 2: +1 for a match, -1 for any other
+                if (q == 2) cnt = 2 * cnt - all;
 #pragma unroll
                 for (int o = 1; o < 64; o <<= 1) cnt += __shfl_xor(cnt, o, 64);
                 int* sums = reinterpret_cast<int*>(red);
                 if (lane == 0) sums[wave] = cnt;
-                __syncthreads();
+                lds_barrier();
                 int c = lane < nwaves ? sums[lane] : 0;
 #pragma unroll
                 for (int o = 1; o < 16; o <<= 1) c += __shfl_xor(c, o, 64);
@@ -414,14 +457,14 @@ __global__ __launch_bounds__(1024, 4) void sorted_kernel(SortedArgs sa) {
                 // rows that no run holds
                 for (int i = runs * 64 + threadIdx.x; i < 4 * plane; i += blockDim.x)
                     rowsum[(i & 3) * plane + (i >> 2)] = 0.0;
-                __syncthreads();
+                lds_barrier();
                 for (int k = wave; k < S; k += nwaves) {
                     const double* x = rowsum + k * 64 + lane;
                     double v = (x[0] + x[plane]) + (x[2 * plane] + x[3 * plane]);
                     for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
                     if (lane == 0) red[k] = v;
                 }
-                __syncthreads();
+                lds_barrier();
                 // S <= 16 slices: two per lane, zero-padded
                 const double v0 = 2 * lane < S ? red[2 * lane] : 0.0;
                 const double v1 = 2 * lane + 1 < S ? red[2 * lane + 1] : 0.0;
