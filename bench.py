@@ -46,9 +46,13 @@ DT = float(np.float32(0.01))
 SPARSE_SOURCES = ["paper_2505_22631_amd/csrc/sparse_persistent.hip",
                   "paper_2505_22631_amd/csrc/sparse_persistent_uw.hip",
                   "paper_2505_22631_amd/csrc/persistent_kernel.hpp",
+                  "paper_2505_22631_amd/csrc/sorted_kernel.hpp",
+                  "paper_2505_22631_amd/csrc/sparse_sorted.hip",
+                  "paper_2505_22631_amd/csrc/sparse_sorted_uw.hip",
                   "paper_2505_22631_amd/csrc/noise.hpp", "paper_2505_22631_amd/csrc/phase.hpp",
                   "paper_2505_22631_amd/csrc/tree.hpp"]
-DENSE_SOURCES = ["paper_2505_22631_amd/csrc/dense.hip", "paper_2505_22631_amd/csrc/noise.hpp",
+DENSE_SOURCES = ["paper_2505_22631_amd/csrc/dense.hip", "paper_2505_22631_amd/csrc/dense_pairs.hpp",
+                 "paper_2505_22631_amd/csrc/noise.hpp",
                  "paper_2505_22631_amd/csrc/phase.hpp"]
 ADJOINT_SOURCES = ["paper_2505_22631_amd/csrc/adjoint.hip", "paper_2505_22631_amd/csrc/noise.hpp",
                    "paper_2505_22631_amd/csrc/phase.hpp"]
