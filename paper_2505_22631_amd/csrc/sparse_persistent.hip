@@ -102,8 +102,9 @@ bool cu_holds(int64_t groups, int64_t waves) {
 //    four slices for 33 to 48 (10.8 -> 9.3, against 9.75 with sixteen).
 //  - Where a CU holds several workgroups each takes its share of the sixteen
 //    waves: 256 colouring graphs of up to 600 oscillators x 8 replicas 3.6 ->
-//    2.9 us (256 -> 128 threads), of up to 250 3.1 -> 1.8 (64); n = 2000, 600
-//    replicas 6.0 -> 5.4 (512 -> 256).  Beyond 16 slices the sixteen waves stay
+//    2.9 us (256 -> 128 threads); n = 2000, 600 replicas 6.0 -> 5.4 (512 ->
+//    256).  Up to two slices keep 2 rows per lane (graphs of up to 250: 1.7 us
+//    whole on 64 threads, 1.25 split).  Beyond 16 slices the sixteen waves stay
 //    (n = 6000, 600 replicas: 11.8 us with 1024 x 2, 15.6 with 512 x 5).
 const Variant* default_variant(const Problem* p, int R) {
     const int S = p->max_slices;
