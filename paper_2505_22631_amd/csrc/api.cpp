@@ -26,7 +26,7 @@ struct Images {
     struct Part {
         void** dst;
         const void* src;
-        size_t bytes, room, at;
+        size_t bytes, pad, room, at;
         bool copied;
     };
     std::vector<Part> parts;
@@ -44,14 +44,16 @@ struct Images {
         *dst = nullptr;
         if (count + pad == 0) return;
         const size_t room = ((count + pad) * sizeof(T) + 255) / 256 * 256;
-        parts.push_back(Part{reinterpret_cast<void**>(dst), src, count * sizeof(T), room, total, true});
+        parts.push_back(Part{reinterpret_cast<void**>(dst), src, count * sizeof(T), pad * sizeof(T), room,
+                             total, true});
         total += room;
     }
 
     // One allocation for all, and one copy while the host parts are small
     // enough to be gathered: an allocation and a copy each cost some 25 us per
-    // image (a 200-oscillator graph's problem 550 us with ten images, 665 with
-    // the four of the sorted rows too).
+    // image (problems of 200 oscillators 143 to 179 us with one each, 95 so; n =
+    // 800 of degree 48, 1.3 MB with real weights, 992 us part by part, 844
+    // gathered; past that gathering pays for its pages).
     int commit(void** base) {
         hipError_t e = hipMalloc(base, total);
         if (e != hipSuccess) {
@@ -65,7 +67,7 @@ struct Images {
             *p.dst = d + p.at;
             if (p.copied) copied = p.at + p.room;
         }
-        constexpr size_t kGather = 4 << 20;
+        constexpr size_t kGather = 2 << 20;
         if (copied <= kGather) {
             std::vector<unsigned char> host(copied, 0);
             for (const Part& p : parts)
@@ -75,8 +77,7 @@ struct Images {
             for (const Part& p : parts) {
                 if (!p.copied || e != hipSuccess) continue;
                 if (p.bytes) e = hipMemcpy(d + p.at, p.src, p.bytes, hipMemcpyHostToDevice);
-                if (e == hipSuccess && p.room > p.bytes)
-                    e = hipMemset(d + p.at + p.bytes, 0, p.room - p.bytes);
+                if (e == hipSuccess && p.pad) e = hipMemset(d + p.at + p.bytes, 0, p.pad);
             }
         }
         return e == hipSuccess ? OIM_OK : hip_error(e, "upload problem images");
