@@ -244,18 +244,17 @@ void build_sell(int32_t n, const int64_t* row_ptr, const int32_t* col_idx, const
                 // written in order
                 for (int32_t e = 0; e < deg; ++e) {
                     int2* to = &out.entries[first + (((size_t)j * (deg / 2) + e / 2) * kSliceQuads) * 2 + (e & 1)];
+                    uint32_t* tu = uw ? &out.entries_uw[first_uw + (((size_t)j * (deg / 4) + e / 4) * kSliceQuads) * 4 + (e & 3)] : nullptr;
                     for (int l = 0; l < kSliceQuads; ++l) {
                         int2 v{self[l], 0};
-                        if (e < rl[l]) {
+                        const bool in = e < rl[l];
+                        if (in) {
                             v.x = lds_off(col_idx[rb[l] + e] - o);
                             std::memcpy(&v.y, &J[rb[l] + e], 4);
                         }
                         to[2 * l] = v;
+                        if (tu) tu[4 * l] = in ? (uint32_t)v.x : zero_off;
                     }
-                    if (!uw) continue;
-                    uint32_t* tu = &out.entries_uw[first_uw + (((size_t)j * (deg / 4) + e / 4) * kSliceQuads) * 4 + (e & 3)];
-                    for (int l = 0; l < kSliceQuads; ++l)
-                        tu[4 * l] = e < rl[l] ? (uint32_t)to[2 * l].x : zero_off;
                 }
             }
             rows4 += 4LL * deg / 2;
