@@ -328,9 +328,10 @@ int launched(const char* what) {
     return e == hipSuccess ? OIM_OK : hip_error(e, what);
 }
 
-// More than 64 KiB of dynamic LDS has to be asked for.
-int allow_lds(const void* fn, size_t bytes) {
-    if (bytes <= 64 * 1024) return OIM_OK;
+// More than 64 KiB of LDS has to be asked for: the dynamic part, which with
+// the kernel's static arrays may not pass the CU's 160 KiB.
+int allow_lds(const void* fn, size_t bytes, size_t fixed = 0) {
+    if (bytes + fixed <= 64 * 1024) return OIM_OK;
     const hipError_t e =
         hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     return e == hipSuccess ? OIM_OK : hip_error(e, "hipFuncSetAttribute");
@@ -388,11 +389,12 @@ template <int MODE>
 int launch_sparse_sum(const Problem* p, int R, const int8_t* colour, const float* theta, int q,
                       int64_t* oi, double* oa, double* ob, hipStream_t s) {
     // the staged copies next to the static arrays (16.5 KiB), where they fit
+    constexpr size_t kFixed = 20 * 1024;
     size_t lds = (size_t)p->n * ((theta ? 4 : 0) + (colour ? 1 : 0));
-    const bool stage = lds + 20 * 1024 <= dpair::kLdsLimit;
+    const bool stage = lds + kFixed <= dpair::kLdsLimit;
     if (!stage) lds = 0;
     auto fn = stage ? sparse_sum_kernel<MODE, true> : sparse_sum_kernel<MODE, false>;
-    if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds + 20 * 1024)) return st;
+    if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds, kFixed)) return st;
     hipLaunchKernelGGL(fn, dim3(R), dim3(kSumTB), lds, s, p->n, p->d_row_ptr, p->d_col, p->d_J,
                        colour, theta, q, oi, oa, ob);
     return launched("readout launch");

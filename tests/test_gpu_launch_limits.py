@@ -1,0 +1,55 @@
+"""Calls at the edges of what one kernel launch takes: scoring where the staged
+copies come near the LDS of a CU."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oim():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_22631_amd as m
+    m.lib()
+    return m
+
+
+def _t(x):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def _ring(n, weights, seed=0):
+    """Rings of step 1 and 7 on n oscillators."""
+    i = np.arange(n)
+    ei, ej = np.concatenate([i, i]), np.concatenate([(i + 1) % n, (i + 7) % n])
+    rng = np.random.default_rng(seed + n)
+    w = np.ones(ei.size) if weights == "unit" else rng.standard_normal(ei.size) * np.exp(
+        rng.uniform(-4, 2, ei.size))
+    return synth.csr_from_edges(n, ei, ej, w.astype(np.float32))
+
+
+# phases and colours, phases alone, colours alone: the smallest and largest
+# sizes whose copies sit in more than 124 KiB of LDS, and the first beyond
+@pytest.mark.parametrize("n,what", [(25293, "both"), (28672, "both"), (28673, "both"),
+                                    (31617, "phases"), (35840, "phases"), (35841, "phases"),
+                                    (126465, "cut"), (143360, "cut"), (143361, "cut")])
+def test_scoring_near_the_lds_limit(oim, orc, n, what):
+    g = _ring(n, "real")
+    J = (-g.w).astype(np.float32)
+    th = synth.theta0(1, n, seed=n)
+    col = np.random.default_rng(n).integers(0, 2, (1, n)).astype(np.int8)
+    with oim.Problem.from_csr(n, g.row_ptr, g.col, J) as prob:
+        if what == "cut":
+            cut = oim.oim_cut(prob.handle, _t(col), exact=False)
+            assert cut[0].item() == orc.cut_fixed(g.row_ptr, g.col, J, col[0])
+            return
+        hm, h6 = oim.oim_energy(prob.handle, 2, _t(th), _t(col) if what == "both" else None)
+        if hm is not None:
+            assert hm[0].item() == orc.h_model_fixed(g.row_ptr, g.col, J, 2, col[0])
+        want = orc.h_eq6_fixed(g.row_ptr, g.col, J, th[0].astype(np.float64))
+        assert abs(h6[0].item() - want) <= 2.0**-51 * np.abs(J).astype(np.float64).sum() / 2
