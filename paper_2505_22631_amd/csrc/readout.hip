@@ -337,6 +337,16 @@ int allow_lds(const void* fn, size_t bytes, size_t fixed = 0) {
     return e == hipSuccess ? OIM_OK : hip_error(e, "hipFuncSetAttribute");
 }
 
+// Workgroups of 1024 threads in one launch: a grid dimension ends at 2^32
+// threads, past which the launch wraps without an error, so more replicas go
+// in several launches.
+constexpr int64_t kMaxGroups = (int64_t)1 << 21;
+
+template <typename T>
+T* offset(T* p, int64_t k) {
+    return p ? p + k : nullptr;
+}
+
 template <int KIND, bool INTS>
 int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* oi, double* of,
                        hipStream_t s) {
@@ -346,8 +356,11 @@ int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* o
               : nr == 2 ? dense_pair_kernel<2, KIND, INTS>
                         : dense_pair_kernel<1, KIND, INTS>;
     if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
-    hipLaunchKernelGGL(fn, dim3((R + nr - 1) / nr), dim3(dpair::kTB), lds, s, p->n, R, p->d_Jdense,
-                       colour, oi, of);
+    for (int64_t r0 = 0; r0 < R; r0 += nr * kMaxGroups) {
+        const int count = (int)(R - r0 < nr * kMaxGroups ? R - r0 : nr * kMaxGroups);
+        hipLaunchKernelGGL(fn, dim3((count + nr - 1) / nr), dim3(dpair::kTB), lds, s, p->n, count,
+                           p->d_Jdense, colour + r0 * p->n, offset(oi, r0), offset(of, r0));
+    }
     return launched("readout launch");
 }
 
@@ -375,12 +388,12 @@ int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* ou
     } else if ((int64_t)p->n * lpr <= 256) {
         tb = 256;
     }
-    for (int r0 = 0; r0 < R; r0 += 65535) {  // grid.y limit
-        const int nr = R - r0 < 65535 ? R - r0 : 65535;
+    for (int64_t r0 = 0; r0 < R; r0 += 65535) {  // grid.y limit
+        const int nr = (int)(R - r0 < 65535 ? R - r0 : 65535);
         if (chunks > 1)
             hipLaunchKernelGGL(zero_kernel, dim3((nr + 255) / 256), dim3(256), 0, s, nr, out + r0);
         hipLaunchKernelGGL(fn, dim3(chunks, nr), dim3(tb), 0, s, p->n, (int)rows, p->d_row_ptr,
-                           p->d_col, p->d_J, colour + (int64_t)r0 * p->n, out + r0);
+                           p->d_col, p->d_J, colour + r0 * p->n, out + r0);
     }
     return launched("readout launch");
 }
@@ -395,8 +408,12 @@ int launch_sparse_sum(const Problem* p, int R, const int8_t* colour, const float
     if (!stage) lds = 0;
     auto fn = stage ? sparse_sum_kernel<MODE, true> : sparse_sum_kernel<MODE, false>;
     if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds, kFixed)) return st;
-    hipLaunchKernelGGL(fn, dim3(R), dim3(kSumTB), lds, s, p->n, p->d_row_ptr, p->d_col, p->d_J,
-                       colour, theta, q, oi, oa, ob);
+    for (int64_t r0 = 0; r0 < R; r0 += kMaxGroups) {
+        const int count = (int)(R - r0 < kMaxGroups ? R - r0 : kMaxGroups);
+        hipLaunchKernelGGL(fn, dim3(count), dim3(kSumTB), lds, s, p->n, p->d_row_ptr, p->d_col, p->d_J,
+                           offset(colour, r0 * p->n), offset(theta, r0 * p->n), q, offset(oi, r0),
+                           offset(oa, r0), offset(ob, r0));
+    }
     return launched("readout launch");
 }
 
@@ -453,8 +470,12 @@ int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
         if (st) return st;
     }
     if (h_eq6) {
-        hipLaunchKernelGGL(dense_cos_kernel, dim3(R), dim3(dpair::kTB),
-                           sizeof(double) * dpair::row_blocks(p->n), s, p->n, p->d_Jdense, theta, h_eq6);
+        for (int64_t r0 = 0; r0 < R; r0 += kMaxGroups) {
+            const int count = (int)(R - r0 < kMaxGroups ? R - r0 : kMaxGroups);
+            hipLaunchKernelGGL(dense_cos_kernel, dim3(count), dim3(dpair::kTB),
+                               sizeof(double) * dpair::row_blocks(p->n), s, p->n, p->d_Jdense,
+                               theta + r0 * p->n, h_eq6 + r0);
+        }
         return launched("readout launch");
     }
     return OIM_OK;

@@ -1,5 +1,6 @@
 """Calls at the edges of what one kernel launch takes: scoring where the staged
-copies come near the LDS of a CU."""
+copies come near the LDS of a CU, and more workgroups than a launch of
+1024-thread ones holds (a grid dimension ends at 2^32 threads)."""
 import numpy as np
 import pytest
 
@@ -21,6 +22,22 @@ def oim():
 def _t(x):
     import torch
     return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def _repeat(x, R):
+    """[P][..] tiled to R rows on the GPU: row r is x[r % P]."""
+    t = _t(x)
+    P = x.shape[0]
+    return t.repeat(*([-(-R // P)] + [1] * (x.ndim - 1)))[:R].contiguous()
+
+
+def _same_period(out, P):
+    """Every row r of out equals row r % P."""
+    R = out.shape[0]
+    head = R // P * P
+    ref = out[:P].unsqueeze(0)
+    assert bool((out[:head].view(-1, P, *out.shape[1:]) == ref).all())
+    assert bool((out[head:] == out[:R - head]).all())
 
 
 def _ring(n, weights, seed=0):
@@ -53,3 +70,35 @@ def test_scoring_near_the_lds_limit(oim, orc, n, what):
             assert hm[0].item() == orc.h_model_fixed(g.row_ptr, g.col, J, 2, col[0])
         want = orc.h_eq6_fixed(g.row_ptr, g.col, J, th[0].astype(np.float64))
         assert abs(h6[0].item() - want) <= 2.0**-51 * np.abs(J).astype(np.float64).sum() / 2
+
+
+@pytest.mark.parametrize("form", ["sparse", "dense"])
+def test_scoring_of_many_replicas(oim, orc, form):
+    # 2^22 workgroups of 1024 threads and more
+    n, P = 9, 50
+    R = (1 << 22) + 3 if form == "sparse" else (1 << 24) + 5
+    g = _ring(n, "real")
+    J = (-g.w).astype(np.float32)
+    rng = np.random.default_rng(3)
+    col = rng.integers(0, 2, (P, n)).astype(np.int8)
+    th = synth.theta0(P, n, seed=4)
+    if form == "sparse":
+        prob = oim.Problem.from_csr(n, g.row_ptr, g.col, J)
+    else:
+        Jd = np.zeros((n, n), np.float32)
+        Jd[np.repeat(np.arange(n), np.diff(g.row_ptr)), g.col] = J
+        prob = oim.Problem.from_dense(Jd)
+    with prob:
+        dcol, dth = _repeat(col, R), _repeat(th, R)
+        hm, h6 = oim.oim_energy(prob.handle, 2, dth, dcol)
+        cut = oim.oim_cut(prob.handle, dcol, exact=False)
+        conf = oim.oim_conflicts(prob.handle, dcol)
+        for out in (hm, h6, cut, conf):
+            _same_period(out, P)
+        bound = 2.0**-51 * np.abs(J).astype(np.float64).sum() / 2
+        for r in range(P):
+            assert hm[r].item() == orc.h_model_fixed(g.row_ptr, g.col, J, 2, col[r])
+            assert cut[r].item() == orc.cut_fixed(g.row_ptr, g.col, J, col[r])
+            assert conf[r].item() == orc.conflicts(g.row_ptr, g.col, J, col[r])
+            want = orc.h_eq6_fixed(g.row_ptr, g.col, J, th[r].astype(np.float64))
+            assert abs(h6[r].item() - want) <= bound
