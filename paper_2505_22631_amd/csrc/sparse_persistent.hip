@@ -154,19 +154,32 @@ bool variant_ok(const Problem* p, const Variant& v) {
            lds_bytes(p->max_slices * 64, v.tb, v.ms, v.rpl) <= kLdsLimit;
 }
 
+// Whether one launch holds a workgroup of v.tb threads for every replica and
+// instance: a grid dimension ends at 2^32 threads, past which a launch wraps
+// without an error.
+bool launch_holds(const Problem* p, int R, const Variant& v) {
+    return (int64_t)R * p->n_inst < ((int64_t)1 << 32) / v.tb;
+}
+
 int q_class(int q) { return q == 2 ? 1 : q == 3 ? 2 : 0; }
 
 // The variant a run uses: the tuned one for this SHIL order if set, else an
-// OIM_PERSIST_TB block-size hint, else the default choice.
+// OIM_PERSIST_TB block-size hint, else the default choice -- unless that one's
+// launch would not hold the workgroups: then the one of the fewest threads.
 const Variant* run_variant(const Problem* p, int q, int R) {
     const int qc = q_class(q);
+    const Variant* v = nullptr;
     if (p->tuned_tb[qc]) {
-        const Variant* v = find_variant(p->tuned_tb[qc], p->tuned_ms[qc], p->tuned_rpl[qc]);
-        if (v && variant_ok(p, *v)) return v;
+        v = find_variant(p->tuned_tb[qc], p->tuned_ms[qc], p->tuned_rpl[qc]);
+        if (v && !variant_ok(p, *v)) v = nullptr;
     }
     const int hint = env_int("OIM_PERSIST_TB", 0);
-    const Variant* v = hint ? fewest_waves(p->max_slices, hint) : nullptr;
-    return v ? v : default_variant(p, R);
+    if (!v && hint) v = fewest_waves(p->max_slices, hint);
+    if (!v) v = default_variant(p, R);
+    if (!v || launch_holds(p, R, *v)) return v;
+    for (const Variant& k : kVariants)
+        if (variant_ok(p, k) && k.tb < v->tb) v = &k;
+    return v;
 }
 
 }  // namespace
@@ -253,8 +266,7 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
     a.R = cfg->R;
     a.sched_stride = sched_stride;
     const int qi = cfg->q == 2 ? 1 : cfg->q == 3 ? 2 : 0;
-    if ((int64_t)cfg->R * p->n_inst > 0x7fffffff)
-        return set_error(OIM_E_ARG, "R * instances too large");
+    if (!launch_holds(p, cfg->R, *v)) return set_error(OIM_E_ARG, "R * instances too large");
     a.w0 = p->uniform_w;
     if (v->ms == 1 && p->d_sorted) return launch_sorted(p, *v, a, qi, stream);
     KernelFn fn = v->fn[qi];
@@ -342,7 +354,7 @@ int tune_persistent(Problem* p, const oim_run_cfg* cfg, const float* K, const fl
     int tried = 0;
     for (const Variant& v : kVariants) {
         if (st) break;
-        if (!variant_ok(p, v)) continue;
+        if (!variant_ok(p, v) || !launch_holds(p, cfg->R, v)) continue;
         float t[2] = {0.f, 0.f};
         time_variant(v, trial_steps, 2, t);
         if (st) break;

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import synth
+from _util import DT
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +103,35 @@ def test_scoring_of_many_replicas(oim, orc, form):
             assert conf[r].item() == orc.conflicts(g.row_ptr, g.col, J, col[r])
             want = orc.h_eq6_fixed(g.row_ptr, g.col, J, th[r].astype(np.float64))
             assert abs(h6[r].item() - want) <= bound
+
+
+def _many_instances(big, count):
+    """`count` single oscillators and one ring of `big`, as a batch."""
+    g = _ring(big, "real")
+    n = count + big
+    ptr = np.concatenate([np.zeros(count, np.int64), g.row_ptr])
+    off = np.concatenate([np.arange(count + 1), [n]]).astype(np.int32)
+    return n, ptr, (g.col + count).astype(np.int32), (-g.w).astype(np.float32), off
+
+
+def test_run_of_many_workgroups(oim):
+    # 1028 replicas of 4097 instances: more than 2^22 workgroups, a default
+    # or tuned shape of 1024 threads would not hold
+    import torch
+    n, ptr, col, J, off = _many_instances(2000, 4096)
+    P, R, steps = 4, 1028, 3
+    th0, sd = synth.theta0(P, n, seed=5), synth.seeds(P, 6)
+    K, Ks, sg = (_t(x) for x in (synth.ramp(0, 2, steps), synth.ramp(0, 3, steps),
+                                 synth.const(0.1, steps)))
+    with oim.Problem.from_csr_blocks(n, ptr, col, J, off) as prob:
+        ref = _t(th0)
+        oim.run(prob, ref, K, Ks, sg, _t(sd), q=2, dt=DT)
+        for tuned in (None, (1024, 1, 2)):
+            if tuned:
+                oim.oim_set_tuning(prob.handle, 2, *tuned)
+            th = _repeat(th0, R)
+            out = oim.run(prob, th, K, Ks, sg, _repeat(sd.view(np.int64), R).view(torch.uint64),
+                          q=2, dt=DT, readout_every=2)
+            assert torch.equal(th[:P], ref)
+            _same_period(th, P)
+            _same_period(out["best_h"].view(R, -1), P)
