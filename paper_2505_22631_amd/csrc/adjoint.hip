@@ -89,6 +89,7 @@ struct AdjArgs {
     double* gpart;         // [steps][3][R * I] (backward)
     float* lam;            // [R][P] adjoint state between segments, slot order (backward)
     int cur_seg;           // segment of this launch (backward)
+    int wg0;               // the launch's first workgroup
 };
 
 template <int QM>
@@ -116,7 +117,7 @@ struct Ctx {
 
 __device__ __forceinline__ Ctx make_ctx(const AdjArgs& a) {
     Ctx x;
-    x.wg = blockIdx.x;
+    x.wg = a.wg0 + (int)blockIdx.x;
     x.b = x.wg % a.I;
     x.r = x.wg / a.I;
     const int4 in = a.inst[x.b];
@@ -726,12 +727,19 @@ AdjFn pick_fn(const AdjFn (&f)[3][2][2], const Problem* p, int q, bool ldsi) {
     return f[q == 2 ? 1 : q == 3 ? 2 : 0][p->unit_weights][ldsi];
 }
 
-int launch_adj(AdjFn fn, size_t lds, int grid, int threads, hipStream_t stream, const AdjArgs& a,
+// A grid dimension ends at 2^32 threads, past which a launch wraps without an
+// error, so more than 2^31 go in several launches.
+int launch_adj(AdjFn fn, size_t lds, int grid, int threads, hipStream_t stream, AdjArgs a,
                const char* what) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, what);
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), lds, stream, a);
+    const int most = (int)(((int64_t)1 << 31) / threads);
+    for (int64_t g = 0; g < grid; g += most) {
+        a.wg0 = (int)g;
+        hipLaunchKernelGGL(fn, dim3((unsigned)(grid - g < most ? grid - g : most)), dim3(threads), lds,
+                           stream, a);
+    }
     e = hipGetLastError();
     return e == hipSuccess ? OIM_OK : hip_error(e, what);
 }
@@ -950,8 +958,11 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
             return hip_error(e, "adjoint segment order");
     }
     if (st) return st;
-    hipLaunchKernelGGL(adjoint_reduce_kernel, dim3(cfg->steps), dim3(256), 0, stream, a.gpart, nwg, gK,
-                       gKs, gS);
+    constexpr int64_t kSteps = (int64_t)1 << 23;  // of one launch, as in launch_adj
+    for (int64_t s = 0; s < cfg->steps; s += kSteps)
+        hipLaunchKernelGGL(adjoint_reduce_kernel,
+                           dim3((unsigned)(cfg->steps - s < kSteps ? cfg->steps - s : kSteps)), dim3(256), 0,
+                           stream, a.gpart + 3 * s * nwg, nwg, gK + s, gKs + s, gS + s);
     return check_launch("adjoint_reduce_kernel");
 }
 

@@ -135,3 +135,38 @@ def test_run_of_many_workgroups(oim):
             assert torch.equal(th[:P], ref)
             _same_period(th, P)
             _same_period(out["best_h"].view(R, -1), P)
+
+
+def test_adjoint_of_many_workgroups(oim):
+    # the same number of workgroups of 1024 threads
+    import torch
+    n, ptr, col, J, off = _many_instances(1000, 4096)
+    P, R, steps = 4, 1028, 2
+    th0, sd = synth.theta0(P, n, seed=7), synth.seeds(P, 8)
+    K, Ks, sg = (_t(x) for x in (synth.const(1.0, steps), synth.const(2.0, steps),
+                                 synth.const(0.1, steps)))
+
+    def adjoint(prob, th, seeds):
+        reps = th.shape[0]
+        words = oim.oim_adjoint_checkpoint_words(prob.handle, q=2, R=reps, steps=steps, dt=DT,
+                                                 checkpoint_every=steps)
+        ckpt = torch.empty(words, dtype=torch.uint32, device="cuda")
+        thT = torch.empty_like(th)
+        loss = torch.empty(reps * len(off[1:]), dtype=torch.float64, device="cuda")
+        oim.oim_adjoint_forward(prob.handle, n, th, K, Ks, sg, seeds, ckpt, q=2, dt=DT,
+                                checkpoint_every=steps, theta_T=thT, loss=loss)
+        grad = [torch.full((steps,), float("nan"), dtype=torch.float64, device="cuda")
+                for _ in range(3)]
+        oim.oim_adjoint_backward(prob.handle, reps, K, Ks, sg, seeds, ckpt, *grad, q=2, dt=DT,
+                                 checkpoint_every=steps)
+        return thT, loss.view(reps, -1), [g.cpu().numpy() for g in grad]
+
+    with oim.Problem.from_csr_blocks(n, ptr, col, J, off) as prob:
+        thT1, loss1, g1 = adjoint(prob, _t(th0), _t(sd))
+        thT, loss, g = adjoint(prob, _repeat(th0, R),
+                               _repeat(sd.view(np.int64), R).view(torch.uint64))
+    assert torch.equal(thT[:P], thT1) and torch.equal(loss[:P], loss1)
+    _same_period(thT, P)
+    _same_period(loss, P)
+    for a, b in zip(g, g1):  # R / P times the same partials, summed in FP64
+        np.testing.assert_allclose(a, (R // P) * b, rtol=1e-9)
