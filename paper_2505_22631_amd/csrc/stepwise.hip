@@ -718,7 +718,7 @@ int check_launch(const char* what) {
 // workspace they were captured on, and an event recorded after their last
 // use so they can be destroyed safely.
 struct Plan {
-    int q = 0, R = 0, M = 0, chunk = 0;
+    int q = 0, R = 0, M = 0, chunk = 0, global_addr = 0;
     const void* work = nullptr;
     hipGraph_t g[2] = {nullptr, nullptr};
     hipGraphExec_t x[2] = {nullptr, nullptr};
@@ -764,6 +764,7 @@ namespace {
 
 struct Shape {
     int n, R, steps, M, Rp, quads, np, gx, rblocks, chunk;
+    int global_addr;  // 64-bit global addressing asked for
     size_t cells, args_off, bytes;
 };
 
@@ -773,8 +774,12 @@ Shape shape_of(const Problem* p, const oim_run_cfg* cfg) {
     sh.R = cfg->R;
     sh.steps = cfg->steps;
     sh.M = cfg->readout_every;
+    // OIM_STEPWISE_GLOBAL_ADDR=1 takes the 64-lane kernel and the 64-bit global
+    // addressing of states of 4 GiB and more for any size
+    const char* env = getenv("OIM_STEPWISE_GLOBAL_ADDR");
+    sh.global_addr = env && atoi(env) != 0;
     sh.Rp = (sh.R + 63) / 64 * 64;
-    if (sh.R < 64)
+    if (sh.R < 64 && !sh.global_addr)
         for (sh.Rp = 4; sh.Rp < sh.R;) sh.Rp *= 2;
     sh.quads = (sh.n + 3) / 4;
     sh.np = sh.quads * 4;
@@ -842,11 +847,8 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
 
     using StepFn = void (*)(StepArgs);
     const bool ell = p->d_ell_col != nullptr;
-    // buffer addressing for states below 4 GiB (OIM_STEPWISE_GLOBAL_ADDR=1
-    // takes the 64-bit global addressing of larger states for any size)
-    bool buf = cells * 4 < ((size_t)1 << 32);
-    if (const char* env = getenv("OIM_STEPWISE_GLOBAL_ADDR"))
-        if (atoi(env) != 0) buf = false;
+    // buffer addressing for states below 4 GiB
+    const bool buf = cells * 4 < ((size_t)1 << 32) && !sh.global_addr;
     static const StepFn kStep[2][2][3] = {
         {{stepwise_step_kernel<0, false, false>, stepwise_step_kernel<2, false, false>,
           stepwise_step_kernel<3, false, false>},
@@ -939,7 +941,8 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
         Plan* plan = nullptr;
         for (int i = 0; i < cache.count; ++i) {
             Plan& c = cache.plans[i];
-            if (c.q == cfg->q && c.R == R && c.M == M && c.chunk == chunk && c.work == work) {
+            if (c.q == cfg->q && c.R == R && c.M == M && c.chunk == chunk &&
+                c.global_addr == sh.global_addr && c.work == work) {
                 plan = &c;
                 break;
             }
@@ -989,6 +992,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
             pl.R = R;
             pl.M = M;
             pl.chunk = chunk;
+            pl.global_addr = sh.global_addr;
             pl.work = work;
             plan = &pl;
         }
