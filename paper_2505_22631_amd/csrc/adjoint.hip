@@ -899,31 +899,22 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     // again: 128 x G(2000, 10/1999), C = 64 (0.27 GB): a segment of the adjoint
     // 182 us with them, 221 without; its recomputation 158 and 150.
     const size_t base = 2 * seg_bytes + lam_bytes + part_bytes + 256;
-    bool keep = 2 * sums_bytes <= ((size_t)8 << 30);
-    for (;;) {
-        const size_t need = base + (keep ? 2 * sums_bytes : 0);
-        if (p->adj_bytes >= need) break;
-        (void)hipFree(p->d_adj);
-        p->d_adj = nullptr;
-        p->adj_bytes = 0;
-        const hipError_t e = hipMalloc(&p->d_adj, need);
-        if (e == hipSuccess) {
-            p->adj_bytes = need;
-            break;
-        }
-        p->d_adj = nullptr;
-        if (e == hipErrorOutOfMemory && keep) {
-            (void)hipGetLastError();
-            keep = false;
-            continue;
-        }
-        return e == hipErrorOutOfMemory
-                   ? set_error(OIM_E_NOMEM, "adjoint workspace: out of device memory")
-                   : hip_error(e, "adjoint workspace");
-    }
-    int st = adjoint_streams(p);
+    const size_t extra = 2 * sums_bytes <= ((size_t)8 << 30) ? 2 * sums_bytes : 0;
+    bool keep = false;
+    hipError_t e = hipSuccess;
+    int st = grow_workspace(
+        p->adj_work, base, extra, keep,
+        [&](size_t bytes, void** ptr) {
+            e = hipMalloc(ptr, bytes);
+            if (e == hipErrorOutOfMemory) (void)hipGetLastError();  // not the next launch's error
+            return e == hipSuccess ? 0 : e == hipErrorOutOfMemory ? kRefused : -1;
+        },
+        [](void* ptr) { (void)hipFree(ptr); });
+    if (st == kRefused) return set_error(OIM_E_NOMEM, "adjoint workspace: out of device memory");
+    if (st) return hip_error(e, "adjoint workspace");
+    st = adjoint_streams(p);
     if (st) return st;
-    unsigned char* w = static_cast<unsigned char*>(p->d_adj);
+    unsigned char* w = static_cast<unsigned char*>(p->adj_work.ptr);
     uint32_t* segbuf[2] = {reinterpret_cast<uint32_t*>(w), reinterpret_cast<uint32_t*>(w + seg_bytes)};
     a.ckpt = const_cast<uint32_t*>(ckpt);
     a.lam = reinterpret_cast<float*>(w + 2 * seg_bytes);
@@ -937,7 +928,7 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     hipEvent_t* start = &p->adj_ev[0];
     hipEvent_t* rec = &p->adj_ev[1];   // [2]
     hipEvent_t* adj = &p->adj_ev[3];   // [2]
-    hipError_t e = hipEventRecord(*start, stream);
+    e = hipEventRecord(*start, stream);
     if (e == hipSuccess) e = hipStreamWaitEvent(side, *start, 0);
     if (e != hipSuccess) return hip_error(e, "adjoint stream fork");
     for (int sg = a.nseg - 1; sg >= 0 && !st; --sg) {

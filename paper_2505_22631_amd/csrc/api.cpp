@@ -90,7 +90,7 @@ void release(Problem* p) {
     stepwise_release(p);
     hipFree(p->d_work);
     adjoint_release(p);
-    hipFree(p->d_adj);
+    hipFree(p->adj_work.ptr);
     dense_release(p);
     unregister_problem(p);
     delete p;

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "oim.h"
+#include "workspace.hpp"
 
 namespace oim {
 
@@ -182,8 +183,7 @@ struct Problem {
 
     // cached scratch of the adjoint backward pass, and its second stream and
     // events (start, recomputed[2], adjoint done[2])
-    void* d_adj = nullptr;
-    size_t adj_bytes = 0;
+    Workspace adj_work;
     hipStream_t adj_stream = nullptr;
     hipEvent_t adj_ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
 };
