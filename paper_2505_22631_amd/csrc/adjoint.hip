@@ -898,8 +898,11 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
     // the card, else (or when they cannot be had) the adjoint forms them
     // again: 128 x G(2000, 10/1999), C = 64 (0.27 GB): a segment of the adjoint
     // 182 us with them, 221 without; its recomputation 158 and 150.
+    // (OIM_ADJ_SUMS=0 forms them again at any size.)
     const size_t base = 2 * seg_bytes + lam_bytes + part_bytes + 256;
-    const size_t extra = 2 * sums_bytes <= ((size_t)8 << 30) ? 2 * sums_bytes : 0;
+    const char* env = getenv("OIM_ADJ_SUMS");
+    const bool hand_over = !(env && !strcmp(env, "0")) && 2 * sums_bytes <= ((size_t)8 << 30);
+    const size_t extra = hand_over ? 2 * sums_bytes : 0;
     bool keep = false;
     hipError_t e = hipSuccess;
     int st = grow_workspace(
