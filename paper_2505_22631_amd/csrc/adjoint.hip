@@ -46,6 +46,7 @@
 
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <type_traits>
 #include <vector>
 
@@ -822,6 +823,49 @@ int adjoint_build(Problem* p, const AdjRowsHost& h, const AdjLayout& l) {
     return check_launch("adjoint_rows_kernel");
 }
 
+namespace {
+
+// The adjoint's rows of a problem whose creation found no room for them.
+int adjoint_make_rows(Problem* p) {
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lock(mu);
+    if (p->adj_rows.row_sum) return OIM_OK;
+    std::vector<int64_t> row_ptr((size_t)p->n + 1);
+    std::vector<int4> inst((size_t)p->n_inst);
+    hipError_t e = hipMemcpy(row_ptr.data(), p->d_row_ptr, row_ptr.size() * 8, hipMemcpyDeviceToHost);
+    if (e == hipSuccess)
+        e = hipMemcpy(inst.data(), p->d_inst, inst.size() * sizeof(int4), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_error(e, "adjoint rows");
+    std::vector<int32_t> off;
+    for (const int4& in : inst) off.push_back(in.z);
+    off.push_back(p->n);
+    AdjRowsHost rows;
+    build_adj_rows(p->n, row_ptr.data(), p->n_inst, off.data(), rows);
+    AdjLayout layout;
+    adjoint_layout(p, rows, layout);
+    const size_t blob = (layout.blob.size() + 255) / 256 * 256;
+    if (!p->d_adj_own) {
+        e = hipMalloc(&p->d_adj_own, blob + layout.image_bytes);
+        if (e != hipSuccess) {
+            p->d_adj_own = nullptr;
+            (void)hipGetLastError();
+            return e == hipErrorOutOfMemory ? set_error(OIM_E_NOMEM, "adjoint rows: out of device memory")
+                                            : hip_error(e, "adjoint rows");
+        }
+    }
+    p->d_adj_rows = p->d_adj_own;
+    p->d_adj_img = static_cast<unsigned char*>(p->d_adj_own) + blob;
+    e = hipMemcpy(p->d_adj_rows, layout.blob.data(), layout.blob.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_error(e, "adjoint rows");
+    int st = adjoint_build(p, rows, layout);
+    // the caller's stream runs next
+    if (!st && (e = hipStreamSynchronize(0)) != hipSuccess) st = hip_error(e, "adjoint rows");
+    if (st) p->adj_rows = AdjRows{};
+    return st;
+}
+
+}  // namespace
+
 int64_t adjoint_checkpoint_words(const Problem* p, const oim_adjoint_cfg* cfg) {
     const int64_t nseg = (cfg->steps + cfg->checkpoint_every - 1) / cfg->checkpoint_every;
     return nseg * cfg->R * (int64_t)p->sell_slices * 4 * kSliceQuads;
@@ -831,6 +875,7 @@ int launch_adjoint_forward(Problem* p, const oim_adjoint_cfg* cfg, const float* 
                            const float* sigma, const uint64_t* seeds, int64_t step0,
                            const float* theta0, uint32_t* ckpt, float* thetaT, double* loss,
                            hipStream_t stream) {
+    if (int st = adjoint_make_rows(p)) return st;
     AdjArgs a = base_args(p, cfg, K, Ks, sigma, seeds, step0);
     a.theta0 = theta0;
     a.ckpt = ckpt;
@@ -886,8 +931,9 @@ int launch_adjoint_backward(Problem* p, const oim_adjoint_cfg* cfg, const float*
                             const float* sigma, const uint64_t* seeds, int64_t step0,
                             const uint32_t* ckpt, double* gK, double* gKs, double* gS,
                             hipStream_t stream) {
-    AdjArgs a = base_args(p, cfg, K, Ks, sigma, seeds, step0);
     if (cfg->steps == 0) return OIM_OK;
+    if (int st = adjoint_make_rows(p)) return st;
+    AdjArgs a = base_args(p, cfg, K, Ks, sigma, seeds, step0);
     const int nwg = cfg->R * p->n_inst;
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t seg_bytes = up((size_t)(cfg->checkpoint_every + 1) * cfg->R * a.P * sizeof(uint32_t));

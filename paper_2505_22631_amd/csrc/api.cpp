@@ -55,9 +55,13 @@ struct Images {
     // 800 of degree 48, 1.3 MB with real weights, 992 us part by part, 844
     // gathered; past that gathering pays for its pages).
     int commit(void** base) {
-        hipError_t e = hipMalloc(base, total);
+        // (OIM_IMAGE_LIMIT: bytes above which an allocation counts as refused)
+        const char* env = getenv("OIM_IMAGE_LIMIT");
+        hipError_t e = env && total > strtoull(env, nullptr, 10) ? hipErrorOutOfMemory
+                                                                 : hipMalloc(base, total);
         if (e != hipSuccess) {
             *base = nullptr;
+            (void)hipGetLastError();  // not the next launch's error
             return e == hipErrorOutOfMemory ? set_error(OIM_E_NOMEM, "problem images: out of device memory")
                                             : hip_error(e, "problem images");
         }
@@ -87,6 +91,7 @@ struct Images {
 void release(Problem* p) {
     if (!p) return;
     hipFree(p->d_images);
+    hipFree(p->d_adj_own);
     stepwise_release(p);
     hipFree(p->d_work);
     adjoint_release(p);
@@ -195,58 +200,76 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
     // row_ptr with kCsrPad more copies of nnz: rows past n are empty
     std::vector<int64_t> row_ptr_padded(row_ptr, row_ptr + (size_t)n + 1);
     row_ptr_padded.resize((size_t)n + 1 + kCsrPad, nnz);
-    Images images;
-    images.add(&p->d_row_ptr, row_ptr_padded.data(), row_ptr_padded.size());
-    images.add(&p->d_col, col_idx, (size_t)nnz, kCsrPad);
-    images.add(&p->d_J, J, (size_t)nnz, kCsrPad);
-    images.add(&p->d_sell_desc, img.desc.data(), img.desc.size());
-    if (img.entries_uw.empty()) images.add(&p->d_sell, img.entries.data(), img.entries.size());
-    images.add(&p->d_sell_uw, img.entries_uw.data(), img.entries_uw.size());
-    images.add(&p->d_row_split, img.row_split.data(), img.row_split.size());
-    images.add(&p->d_inst, img.inst.data(), img.inst.size());
-    images.add(&p->d_order, img.order.data(), img.order.size());
     // the padded row image of the stepwise loop (OIM_STEPWISE_ELL=0 never
     // builds it, =1 builds it for any single graph)
     int ell_mode = 2;
     if (const char* env = getenv("OIM_STEPWISE_ELL")) ell_mode = atoi(env) == 0 ? 0 : 1;
     EllImage ell;
-    if (n_inst == 1 && ell_wanted(n, row_ptr, ell_mode)) {
+    const bool ell_ok = n_inst == 1 && ell_wanted(n, row_ptr, ell_mode);
+    if (ell_ok) {
         build_ell(n, row_ptr, col_idx, J, ell);
         p->ell_D = ell.D;
-        images.add(&p->d_ell_col, ell.col.data(), ell.col.size());
-        images.add(&p->d_ell_J, ell.J.data(), ell.J.size());
     }
     // the sorted rows of the LDS-resident loop's small shapes
     SortedRows sorted;
-    const bool sorted_ok =
+    bool sorted_ok =
         p->max_inst_n <= kSortedMaxN &&
         build_sorted(n, row_ptr, n_inst, n_inst > 1 ? inst_off : nullptr, w0, INT32_MAX, sorted);
-    if (sorted_ok) {
-        images.add(&p->d_sorted_run, sorted.run.data(), sorted.run.size());
-        images.add(&p->d_sorted_run0, sorted.run0.data(), sorted.run0.size());
-        images.add(&p->d_sorted_osc, sorted.osc.data(), sorted.osc.size());
-        images.add(&p->d_sorted_inst, sorted.inst_of.data(), sorted.inst_of.size());
-    }
-    const bool adj_ok = p->max_inst_n <= kAdjMaxN;
+    bool adj_ok = p->max_inst_n <= kAdjMaxN;
     AdjRowsHost adj;
     AdjLayout adj_layout;
     if (adj_ok) {
         build_adj_rows(n, row_ptr, n_inst, n_inst > 1 ? inst_off : nullptr, adj);
         adjoint_layout(p, adj, adj_layout);
-        images.add(reinterpret_cast<unsigned char**>(&p->d_adj_rows), adj_layout.blob.data(),
-                   adj_layout.blob.size());
     }
-    // and what kernels fill
-    if (sorted_ok) {
-        p->sorted_bytes = (uint32_t)((size_t)sorted.groups * 1024);
-        images.reserve(&p->d_sorted_row, sorted.osc.size());
-        images.reserve(&p->d_sorted, (size_t)sorted.groups * 64);
-        if (p->max_inst_n <= kSortedSplitN) images.reserve(&p->d_sorted2, (size_t)sorted.groups * 64);
+    auto commit = [&]() {
+        Images images;
+        images.add(&p->d_row_ptr, row_ptr_padded.data(), row_ptr_padded.size());
+        images.add(&p->d_col, col_idx, (size_t)nnz, kCsrPad);
+        images.add(&p->d_J, J, (size_t)nnz, kCsrPad);
+        images.add(&p->d_sell_desc, img.desc.data(), img.desc.size());
+        if (img.entries_uw.empty()) images.add(&p->d_sell, img.entries.data(), img.entries.size());
+        images.add(&p->d_sell_uw, img.entries_uw.data(), img.entries_uw.size());
+        images.add(&p->d_row_split, img.row_split.data(), img.row_split.size());
+        images.add(&p->d_inst, img.inst.data(), img.inst.size());
+        images.add(&p->d_order, img.order.data(), img.order.size());
+        if (ell_ok) {
+            images.add(&p->d_ell_col, ell.col.data(), ell.col.size());
+            images.add(&p->d_ell_J, ell.J.data(), ell.J.size());
+        }
+        if (sorted_ok) {
+            images.add(&p->d_sorted_run, sorted.run.data(), sorted.run.size());
+            images.add(&p->d_sorted_run0, sorted.run0.data(), sorted.run0.size());
+            images.add(&p->d_sorted_osc, sorted.osc.data(), sorted.osc.size());
+            images.add(&p->d_sorted_inst, sorted.inst_of.data(), sorted.inst_of.size());
+        }
+        if (adj_ok)
+            images.add(reinterpret_cast<unsigned char**>(&p->d_adj_rows), adj_layout.blob.data(),
+                       adj_layout.blob.size());
+        // and what kernels fill
+        if (sorted_ok) {
+            p->sorted_bytes = (uint32_t)((size_t)sorted.groups * 1024);
+            images.reserve(&p->d_sorted_row, sorted.osc.size());
+            images.reserve(&p->d_sorted, (size_t)sorted.groups * 64);
+            if (p->max_inst_n <= kSortedSplitN) images.reserve(&p->d_sorted2, (size_t)sorted.groups * 64);
+        }
+        if (adj_ok)
+            images.reserve(reinterpret_cast<unsigned char**>(&p->d_adj_img), adj_layout.image_bytes);
+        return images.commit(&p->d_images);
+    };
+    if ((st = current_device(&p->device)) == OIM_OK) st = commit();
+    // What runs can do without is left out where memory is short: first the
+    // sorted rows (the general kernel's shapes take their place), then the
+    // adjoint's rows (made by the first adjoint call).
+    if (st == OIM_E_NOMEM && sorted_ok) {
+        sorted_ok = false;
+        st = commit();
     }
-    if (adj_ok)
-        images.reserve(reinterpret_cast<unsigned char**>(&p->d_adj_img), adj_layout.image_bytes);
-    if ((st = current_device(&p->device)) || (st = images.commit(&p->d_images)) ||
-        (sorted_ok && (st = sorted_build(p, (int32_t)sorted.run.size()))) ||
+    if (st == OIM_E_NOMEM && adj_ok) {
+        adj_ok = false;
+        st = commit();
+    }
+    if (st || (sorted_ok && (st = sorted_build(p, (int32_t)sorted.run.size()))) ||
         (adj_ok && (st = adjoint_build(p, adj, adj_layout)))) {
         release(p);
         return st;
@@ -259,6 +282,7 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
             return hip_error(e, "problem images");
         }
     }
+    clear_error();
     *out = register_problem(p);
     return OIM_OK;
 }

@@ -143,7 +143,8 @@ struct Problem {
     uint32_t* d_sell_uw = nullptr;  // unit-weight image, or null
     int2* d_row_split = nullptr;    // SellImage::row_split
 
-    // device: SortedRows (instances of at most kSortedMaxN oscillators), else null;
+    // device: SortedRows (instances of at most kSortedMaxN oscillators, at most
+    // 2 GiB, memory to spare), else null;
     // per run and lane (oscillator, upper start | length << 16)
     int2* d_sorted_run = nullptr;
     int2* d_sorted_row = nullptr;
@@ -175,10 +176,12 @@ struct Problem {
     int16_t tuned_ms[3] = {0, 0, 0};
     int16_t tuned_rpl[3] = {4, 4, 4};
 
-    // the adjoint's rows (instances of at most kAdjMaxN oscillators), else null
+    // the adjoint's rows (instances of at most kAdjMaxN oscillators), else null;
+    // an allocation of their own where creation left them out
     AdjRows adj_rows;
     void* d_adj_rows = nullptr;
     void* d_adj_img = nullptr;
+    void* d_adj_own = nullptr;
     int32_t adj_max_words = 0;
 
     // cached scratch of the adjoint backward pass, and its second stream and
