@@ -23,6 +23,8 @@
 #include <float.h>
 
 #include <cmath>
+#include <cstdio>
+#include <cstdlib>
 
 #include "dense_pairs.hpp"
 #include "internal.hpp"
@@ -921,6 +923,12 @@ TileChoice choose_tile(int n, int R, int q) {
         tile_of<F32, 1, 1, 4, 1, 1, 6>(q),                     // 64 x 16
         tile_of<F32, 1, 1, 2, 1, F32 ? 2 : 1, F32 ? 4 : 6>(q)  // 32 x 16
     };
+    // (OIM_DENSE_TILE=<rows>x<replicas> takes that tile at any size)
+    const char* env = getenv("OIM_DENSE_TILE");
+    int rows = 0, reps = 0;
+    if (env && sscanf(env, "%dx%d", &rows, &reps) == 2)
+        for (const TileChoice& t : tiles)
+            if (t.rows == rows && t.reps == reps) return t;
     const TileChoice* best = nullptr;
     int64_t best_cost = 0;
     for (const TileChoice& t : tiles) {
