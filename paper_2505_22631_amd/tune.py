@@ -6,7 +6,8 @@ problem's shape bucket up in a JSON cache (path from OIM_TUNE_CACHE, else
 oim_set_tuning, otherwise it runs oim_autotune on a prefix of the schedule and
 stores the winner.  The bucket is (device architecture, instances, largest
 instance in 64-quad slices, mean degree rounded, replicas, SHIL order class),
-so problems of the same shape share one measurement.
+so problems of the same shape share one measurement.  An entry measured on
+kernels of another revision is measured again.
 """
 from __future__ import annotations
 
@@ -16,6 +17,13 @@ import os
 import torch
 
 from . import oim_autotune, oim_set_tuning
+
+
+# Revision of the kernels that the launch variants run: one higher whenever a
+# change moves their times against each other.  2: shapes of one slice per wave
+# group on sorted rows (entries without a revision are older: G(800, 0.06)
+# pinned to 1024 x 2 slices x 1 row takes 3.2 us per step, the default 1.8).
+KERNELS = 2
 
 
 def cache_path() -> str:
@@ -48,8 +56,8 @@ def tuned(problem, theta, K, Ks, sigma, seeds, *, q, dt, trial_steps=None, retun
     key = bucket(problem, R, q)
     path = cache_path()
     cache = _load(path)
-    if not retune and key in cache:
-        e = cache[key]
+    e = cache.get(key)
+    if not retune and e is not None and e.get("kernels") == KERNELS:
         oim_set_tuning(problem.handle, q, e["block"], e["slices_per_wave"],
                        e.get("rows_per_lane", 4))
         return e, False
@@ -59,7 +67,7 @@ def tuned(problem, theta, K, Ks, sigma, seeds, *, q, dt, trial_steps=None, retun
                        trial_steps=ts)
     e = {"block": rep["block"], "slices_per_wave": rep["slices_per_wave"],
          "rows_per_lane": rep["rows_per_lane"], "trial_ms": rep["ms"],
-         "trial_steps": ts, "tried": rep["tried"]}
+         "trial_steps": ts, "tried": rep["tried"], "kernels": KERNELS}
     cache[key] = e
     try:
         os.makedirs(os.path.dirname(path), exist_ok=True)
