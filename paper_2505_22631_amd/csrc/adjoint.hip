@@ -47,6 +47,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <type_traits>
 #include <vector>
 
@@ -825,11 +826,7 @@ int adjoint_build(Problem* p, const AdjRowsHost& h, const AdjLayout& l) {
 
 namespace {
 
-// The adjoint's rows of a problem whose creation found no room for them.
-int adjoint_make_rows(Problem* p) {
-    static std::mutex mu;
-    std::lock_guard<std::mutex> lock(mu);
-    if (p->adj_rows.row_sum) return OIM_OK;
+int make_rows(Problem* p) {
     std::vector<int64_t> row_ptr((size_t)p->n + 1);
     std::vector<int4> inst((size_t)p->n_inst);
     hipError_t e = hipMemcpy(row_ptr.data(), p->d_row_ptr, row_ptr.size() * 8, hipMemcpyDeviceToHost);
@@ -862,6 +859,18 @@ int adjoint_make_rows(Problem* p) {
     if (!st && (e = hipStreamSynchronize(0)) != hipSuccess) st = hip_error(e, "adjoint rows");
     if (st) p->adj_rows = AdjRows{};
     return st;
+}
+
+// The adjoint's rows of a problem whose creation found no room for them.
+int adjoint_make_rows(Problem* p) {
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lock(mu);
+    if (p->adj_rows.row_sum) return OIM_OK;
+    try {
+        return make_rows(p);
+    } catch (const std::bad_alloc&) {
+        return set_error(OIM_E_NOMEM, "adjoint rows: host allocation failed");
+    }
 }
 
 }  // namespace

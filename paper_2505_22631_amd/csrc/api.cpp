@@ -133,43 +133,10 @@ int check_device(const Problem* p) {
     return OIM_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-__attribute__((visibility("default"))) int oim_abi_version(void) { return OIM_ABI_VERSION; }
-
-__attribute__((visibility("default"))) const char* oim_status_str(int s) {
-    switch (s) {
-        case OIM_OK: return "OIM_OK";
-        case OIM_E_ARG: return "OIM_E_ARG";
-        case OIM_E_CSR: return "OIM_E_CSR";
-        case OIM_E_ASYM: return "OIM_E_ASYM";
-        case OIM_E_NONFINITE: return "OIM_E_NONFINITE";
-        case OIM_E_UNSUPPORTED: return "OIM_E_UNSUPPORTED";
-        case OIM_E_NOMEM: return "OIM_E_NOMEM";
-        case OIM_E_HIP: return "OIM_E_HIP";
-        case OIM_E_STATE: return "OIM_E_STATE";
-        default: return "OIM_E_UNKNOWN";
-    }
-}
-
-__attribute__((visibility("default"))) const char* oim_last_error(void) {
-    return last_error_cstr();
-}
-
-__attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
-    int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
-    int32_t n_inst, const int32_t* inst_off, uint32_t flags, oim_problem* out) {
-    clear_error();
-    if (!out) return set_error(OIM_E_ARG, "out is NULL");
-    *out = nullptr;
-    if (flags != 0) return set_error(OIM_E_ARG, "flags must be 0");
-    int st = validate_csr(n, nnz, row_ptr, col_idx, J);
-    if (st) return st;
-    if ((st = validate_blocks(n, row_ptr, col_idx, n_inst, inst_off))) return st;
-    Problem* p = new (std::nothrow) Problem();
-    if (!p) return set_error(OIM_E_NOMEM, "host allocation failed");
+// The images of a sparse problem, from checked arrays.
+int build_problem(Problem* p, int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx,
+                  const float* J, int32_t n_inst, const int32_t* inst_off) {
+    int st = OIM_OK;
     p->n = n;
     p->nnz = nnz;
     p->n_inst = n_inst;
@@ -270,21 +237,62 @@ __attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
         st = commit();
     }
     if (st || (sorted_ok && (st = sorted_build(p, (int32_t)sorted.run.size()))) ||
-        (adj_ok && (st = adjoint_build(p, adj, adj_layout)))) {
-        release(p);
+        (adj_ok && (st = adjoint_build(p, adj, adj_layout))))
         return st;
-    }
     if (sorted_ok || adj_ok) {
         // callers may run on any stream next
         const hipError_t e = hipStreamSynchronize(0);
-        if (e != hipSuccess) {
-            release(p);
-            return hip_error(e, "problem images");
-        }
+        if (e != hipSuccess) return hip_error(e, "problem images");
     }
     clear_error();
-    *out = register_problem(p);
     return OIM_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+__attribute__((visibility("default"))) int oim_abi_version(void) { return OIM_ABI_VERSION; }
+
+__attribute__((visibility("default"))) const char* oim_status_str(int s) {
+    switch (s) {
+        case OIM_OK: return "OIM_OK";
+        case OIM_E_ARG: return "OIM_E_ARG";
+        case OIM_E_CSR: return "OIM_E_CSR";
+        case OIM_E_ASYM: return "OIM_E_ASYM";
+        case OIM_E_NONFINITE: return "OIM_E_NONFINITE";
+        case OIM_E_UNSUPPORTED: return "OIM_E_UNSUPPORTED";
+        case OIM_E_NOMEM: return "OIM_E_NOMEM";
+        case OIM_E_HIP: return "OIM_E_HIP";
+        case OIM_E_STATE: return "OIM_E_STATE";
+        default: return "OIM_E_UNKNOWN";
+    }
+}
+
+__attribute__((visibility("default"))) const char* oim_last_error(void) {
+    return last_error_cstr();
+}
+
+__attribute__((visibility("default"))) int oim_problem_from_csr_blocks(
+    int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx, const float* J,
+    int32_t n_inst, const int32_t* inst_off, uint32_t flags, oim_problem* out) {
+    clear_error();
+    if (!out) return set_error(OIM_E_ARG, "out is NULL");
+    *out = nullptr;
+    if (flags != 0) return set_error(OIM_E_ARG, "flags must be 0");
+    int st = validate_csr(n, nnz, row_ptr, col_idx, J);
+    if (st) return st;
+    if ((st = validate_blocks(n, row_ptr, col_idx, n_inst, inst_off))) return st;
+    Problem* p = new (std::nothrow) Problem();
+    if (!p) return set_error(OIM_E_NOMEM, "host allocation failed");
+    try {
+        st = build_problem(p, n, nnz, row_ptr, col_idx, J, n_inst, inst_off);
+        if (!st) *out = register_problem(p);
+    } catch (const std::bad_alloc&) {
+        st = set_error(OIM_E_NOMEM, "host allocation failed");
+    }
+    if (st) release(p);
+    return st;
 }
 
 __attribute__((visibility("default"))) int oim_problem_from_csr(
