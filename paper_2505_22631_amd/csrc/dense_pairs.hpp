@@ -7,7 +7,7 @@
 // two).  A term that does not count adds +0, which leaves a partial sum as it
 // is (no partial sum is -0).
 //
-// One workgroup of 16 waves takes NR replicas.  A wave owns a block of 64
+// One workgroup of up to 16 waves takes NR replicas.  A wave owns a block of 64
 // rows, one per lane, and walks the columns upwards: J is symmetric bit for
 // bit (checked at upload), so the 64 rows' entries of column j are the 256
 // contiguous bytes J[j][i0 .. i0 + 63], one coalesced load shared by the NR
@@ -53,12 +53,17 @@ inline size_t lds_bytes(int n, int nr, bool ints) {
     return (size_t)nr * code_stride(n) + (size_t)nr * row_blocks(n) * (ints ? 16 : 8);
 }
 
-// Replicas per workgroup: sharing a column load and its conversion among
-// replicas pays once the chip is full without it (two workgroups of 1024
-// threads on each of 256 CUs) and the colours of two workgroups fit the LDS.
-inline int replicas_per_group(int n, int R, bool ints) {
-    if (R > 1024 && 2 * lds_bytes(n, 4, ints) <= kLdsLimit) return 4;
-    if (R > 256 && 2 * lds_bytes(n, 2, ints) <= kLdsLimit) return 2;
+// Waves of a workgroup: as many as there are row blocks, sixteen at most.
+inline int group_waves(int n) { return row_blocks(n) < kWaves ? row_blocks(n) : kWaves; }
+
+// Replicas per workgroup of `waves` waves: sharing a column load and its
+// conversion among replicas pays once the chip is full without it (64 waves per
+// CU for four: n = 100, 1500 replicas 12.5, 10.7 and 16.5 us with 1, 2 and 4;
+// 20000 replicas 87, 53, 45) and the colours of two workgroups fit the LDS.
+inline int replicas_per_group(int n, int R, bool ints, int waves = kWaves) {
+    const int64_t total = (int64_t)R * waves;
+    if (total > 16384 && 2 * lds_bytes(n, 4, ints) <= kLdsLimit) return 4;
+    if (R > 256 && total > 2048 && 2 * lds_bytes(n, 2, ints) <= kLdsLimit) return 2;
     return 1;
 }
 
@@ -89,9 +94,9 @@ __device__ __forceinline__ void block_sums(const float* __restrict__ J, int n,
                                            const unsigned char* code, double* bs, int64_t* bi) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nblk = row_blocks(n), ld = code_stride(n);
-    for (int t = 0; t * kWaves < nblk; ++t) {
-        const int blk = t * kWaves + ((t & 1) ? kWaves - 1 - wave : wave);
+    const int nblk = row_blocks(n), ld = code_stride(n), waves = blockDim.x >> 6;
+    for (int t = 0; t * waves < nblk; ++t) {
+        const int blk = t * waves + ((t & 1) ? waves - 1 - wave : wave);
         if (blk >= nblk) continue;
         const int i = blk * 64 + lane;
         const float* col = J + (i < n ? i : n - 1);

@@ -76,53 +76,80 @@ __global__ __launch_bounds__(dpair::kTB) void dense_pair_kernel(int n, int R, co
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         const int8_t* k = colour + (int64_t)(r0 + r < R ? r0 + r : R - 1) * n;
-        for (int j = threadIdx.x; j < ld; j += dpair::kTB)
+        for (int j = threadIdx.x; j < ld; j += blockDim.x)
             smem[r * ld + j] = j < n ? (unsigned char)k[j] : 0;
     }
     __syncthreads();
     dpair::block_sums<NR, KIND, true, INTS>(J, n, smem, bs, bi);
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (wave < NR && r0 + wave < R) {
-        const double v = dpair::fold_blocks(bs + wave * nblk, nblk);
-        if (lane == 0 && out_f64) out_f64[r0 + wave] = v;
+    const int lane = threadIdx.x & 63;
+    for (int r = threadIdx.x >> 6; r < NR && r0 + r < R; r += blockDim.x >> 6) {
+        const double v = dpair::fold_blocks(bs + r * nblk, nblk);
+        if (lane == 0 && out_f64) out_f64[r0 + r] = v;
         if constexpr (INTS) {
-            const int64_t vi = dpair::fold_blocks_int(bi + wave * nblk, nblk);
-            if (lane == 0 && out_i64) out_i64[r0 + wave] = vi;
+            const int64_t vi = dpair::fold_blocks_int(bi + r * nblk, nblk);
+            if (lane == 0 && out_i64) out_i64[r0 + r] = vi;
         }
     }
 }
 
 // Eq. 6 at the continuous phases [R][n]: the same walk with one FP64 cosine
-// per pair, which bounds it; one replica per workgroup.
-__global__ __launch_bounds__(dpair::kTB) void dense_cos_kernel(int n, const float* __restrict__ J,
-                                                               const float* __restrict__ theta,
-                                                               double* out) {
+// per pair, which bounds it; one replica per workgroup.  KIND: Eq. 1 or Eq. 2 at
+// the colours too, in the same walk (n = 10, 32 replicas 14.4 us in two
+// launches, 11.2 in one; n = 500, 32 replicas 161 and 146), or kNone.
+constexpr int kNone = -1;
+
+template <int KIND>
+__global__ __launch_bounds__(dpair::kTB) void dense_energy_kernel(int n, const float* __restrict__ J,
+                                                                  const float* __restrict__ theta,
+                                                                  const int8_t* __restrict__ colour,
+                                                                  double* h_eq6, double* h_model) {
     extern __shared__ __align__(16) unsigned char smem[];
+    const int nblk = dpair::row_blocks(n), waves = blockDim.x >> 6;
     double* bs = reinterpret_cast<double*>(smem);
-    const int nblk = dpair::row_blocks(n);
+    [[maybe_unused]] double* bk = bs + nblk;
+    [[maybe_unused]] int8_t* code = reinterpret_cast<int8_t*>(bk + nblk);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float* th = theta + (int64_t)blockIdx.x * n;
-    for (int t = 0; t * dpair::kWaves < nblk; ++t) {
-        const int blk = t * dpair::kWaves + ((t & 1) ? dpair::kWaves - 1 - wave : wave);
+    if constexpr (KIND != kNone) {
+        const int8_t* k = colour + (int64_t)blockIdx.x * n;
+        for (int j = threadIdx.x; j < n; j += blockDim.x) code[j] = k[j];
+        __syncthreads();
+    }
+    for (int t = 0; t * waves < nblk; ++t) {
+        const int blk = t * waves + ((t & 1) ? waves - 1 - wave : wave);
         if (blk >= nblk) continue;
         const int i = blk * 64 + lane, ic = i < n ? i : n - 1;
         const double ti = (double)th[ic];
         double acc = 0.0;
+        [[maybe_unused]] double acc_k = 0.0;
+        [[maybe_unused]] int ci = 0;
+        if constexpr (KIND != kNone) ci = code[ic];
         for (int j = blk * 64 + 1; j < n; ++j) {
             const double c = cos(ti - (double)th[j]);
-            const double term = -(double)J[(size_t)j * n + ic] * c;
+            const double w = -(double)J[(size_t)j * n + ic];
+            const double term = w * c;
             acc += j > i ? term : 0.0;
+            if constexpr (KIND != kNone) acc_k += j > i ? dpair::term<KIND>(ci == code[j], w) : 0.0;
         }
         double v = i < n ? acc : 0.0;
         for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
         if (lane == 0) bs[blk] = v;
+        if constexpr (KIND != kNone) {
+            v = i < n ? acc_k : 0.0;
+            for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+            if (lane == 0) bk[blk] = v;
+        }
     }
     __syncthreads();
     if (threadIdx.x < 64) {
         const double v = dpair::fold_blocks(bs, nblk);
-        if (threadIdx.x == 0) out[blockIdx.x] = v;
+        if (threadIdx.x == 0) h_eq6[blockIdx.x] = v;
+        if constexpr (KIND != kNone) {
+            const double vk = dpair::fold_blocks(bk, nblk);
+            if (threadIdx.x == 0) h_model[blockIdx.x] = vk;
+        }
     }
 }
 
@@ -350,7 +377,7 @@ T* offset(T* p, int64_t k) {
 template <int KIND, bool INTS>
 int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* oi, double* of,
                        hipStream_t s) {
-    const int nr = dpair::replicas_per_group(p->n, R, INTS);
+    const int nr = dpair::replicas_per_group(p->n, R, INTS, dpair::group_waves(p->n));
     const size_t lds = dpair::lds_bytes(p->n, nr, INTS);
     auto fn = nr == 4   ? dense_pair_kernel<4, KIND, INTS>
               : nr == 2 ? dense_pair_kernel<2, KIND, INTS>
@@ -358,7 +385,7 @@ int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* o
     if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
     for (int64_t r0 = 0; r0 < R; r0 += nr * kMaxGroups) {
         const int count = (int)(R - r0 < nr * kMaxGroups ? R - r0 : nr * kMaxGroups);
-        hipLaunchKernelGGL(fn, dim3((count + nr - 1) / nr), dim3(dpair::kTB), lds, s, p->n, count,
+        hipLaunchKernelGGL(fn, dim3((count + nr - 1) / nr), dim3(64 * dpair::group_waves(p->n)), lds, s, p->n, count,
                            p->d_Jdense, colour + r0 * p->n, offset(oi, r0), offset(of, r0));
     }
     return launched("readout launch");
@@ -463,21 +490,24 @@ int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
     if (!p->dense)
         return launch_sparse_sum<2>(p, R, h_model ? colour : nullptr, h_eq6 ? theta : nullptr, q,
                                     nullptr, h_model, h_eq6, s);
-    if (h_model) {
-        const int st = q == 2
-                           ? launch_dense_pairs<dpair::kIsing, false>(p, R, colour, nullptr, h_model, s)
-                           : launch_dense_pairs<dpair::kSame, false>(p, R, colour, nullptr, h_model, s);
-        if (st) return st;
-    }
     if (h_eq6) {
+        auto fn = !h_model ? dense_energy_kernel<kNone>
+                  : q == 2 ? dense_energy_kernel<dpair::kIsing>
+                           : dense_energy_kernel<dpair::kSame>;
+        const size_t sums = sizeof(double) * dpair::row_blocks(p->n);
+        const size_t lds = h_model ? 2 * sums + p->n : sums;
+        if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
         for (int64_t r0 = 0; r0 < R; r0 += kMaxGroups) {
             const int count = (int)(R - r0 < kMaxGroups ? R - r0 : kMaxGroups);
-            hipLaunchKernelGGL(dense_cos_kernel, dim3(count), dim3(dpair::kTB),
-                               sizeof(double) * dpair::row_blocks(p->n), s, p->n, p->d_Jdense,
-                               theta + r0 * p->n, h_eq6 + r0);
+            hipLaunchKernelGGL(fn, dim3(count), dim3(64 * dpair::group_waves(p->n)), lds, s, p->n,
+                               p->d_Jdense, theta + r0 * p->n, offset(colour, r0 * p->n), h_eq6 + r0,
+                               offset(h_model, r0));
         }
         return launched("readout launch");
     }
+    if (h_model)
+        return q == 2 ? launch_dense_pairs<dpair::kIsing, false>(p, R, colour, nullptr, h_model, s)
+                      : launch_dense_pairs<dpair::kSame, false>(p, R, colour, nullptr, h_model, s);
     return OIM_OK;
 }
 
