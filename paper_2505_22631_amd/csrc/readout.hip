@@ -155,17 +155,25 @@ __global__ __launch_bounds__(dpair::kTB) void dense_energy_kernel(int n, const f
 
 // ---- sparse coupling ----
 
-// Upper-triangle entries of row i, four at a time so that their columns and
-// weights, then what the caller gathers at those columns, are in flight
-// together: fn(valid, gathered, w) for each, in column order.  With LPR lanes
-// per row (whole-number sums only), lane `sub` of them takes every LPR-th
-// group of four.
-template <int LPR, class Gather, class Fn>
+// Upper-triangle entries of row i: fn(valid, gathered, w) for each, in column
+// order.  BATCH 4: four at a time, so that their columns and weights, then what
+// the caller gathers at those columns, are in flight together, for launches
+// that leave the chip idle; with LPR lanes per row (whole-number sums only),
+// lane `sub` of them takes every LPR-th group of four.  BATCH 1: one at a time,
+// gathering for the upper entries alone, for launches that fill it.
+template <int LPR, int BATCH, class Gather, class Fn>
 __device__ __forceinline__ void upper_entries(const int64_t* __restrict__ row_ptr,
                                               const int32_t* __restrict__ col,
                                               const float* __restrict__ J, int i, int sub,
                                               Gather gather, Fn fn) {
     const int64_t e1 = row_ptr[i + 1];
+    if constexpr (BATCH == 1) {
+        for (int64_t e = row_ptr[i]; e < e1; ++e) {
+            const int j = col[e];
+            if (j > i) fn(true, gather(j), J[e]);
+        }
+        return;
+    }
     for (int64_t e = row_ptr[i] + 4 * sub; e < e1; e += 4 * LPR) {
         int j[4];
         float w[4];
@@ -196,7 +204,7 @@ __global__ void zero_kernel(int R, int64_t* out) {
     if (r < R) out[r] = 0;
 }
 
-template <bool CUT, int LPR>
+template <bool CUT, int LPR, int BATCH>
 __global__ __launch_bounds__(1024) void sparse_int_kernel(
     int n, int rows, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
     const float* __restrict__ J, const int8_t* __restrict__ colour, int64_t* out) {
@@ -208,7 +216,7 @@ __global__ __launch_bounds__(1024) void sparse_int_kernel(
     const int64_t i1 = i0 + rows < n ? i0 + rows : n;
     for (int64_t i = i0 + threadIdx.x / LPR; i < i1; i += blockDim.x / LPR) {
         const int ki = k[i];
-        upper_entries<LPR>(row_ptr, col, J, (int)i, threadIdx.x % LPR,
+        upper_entries<LPR, BATCH>(row_ptr, col, J, (int)i, threadIdx.x % LPR,
                            [&](int j) { return (int)k[j]; },
                            [&](bool on, int kj, float w) {
                                if (CUT) acc += on && ki != kj ? (int64_t)(-w) : 0;
@@ -226,15 +234,19 @@ __global__ __launch_bounds__(1024) void sparse_int_kernel(
     }
 }
 
-// FP64 results: one workgroup of 16 waves per replica.  A wave takes every
-// 16th block of 64 rows, one row per lane, without a barrier; the block sums
+// FP64 results: one workgroup of 1 to 16 waves per replica.  A wave takes every
+// so manieth block of 64 rows, one row per lane, without a barrier; the block sums
 // of a round of kRoundBlocks blocks meet in LDS, where a wave folds each
 // result's by the pairwise tree, and the rounds (a power of two of rows
 // each) are folded in order.  STAGE: the replica's colours and phases are
 // copied to LDS first, so a neighbour's value is an LDS read.  Bound by the
 // latency of the row bounds and entries (and, for Eq. 6, the FP64 cosines).
 // 100 x 100 torus, real weights, 64 replicas: cut 73 -> 25 us, both energies
-// 130 -> 42 us against four waves with two to four barriers per 256 rows.
+// 130 -> 42 us against four waves with two to four barriers per 256 rows.  For
+// many replicas a workgroup of sixteen waves was far too much (n = 10, 20000
+// replicas, both energies 64 -> 288 us; n = 800 of degree 48, 1000 replicas,
+// Eq. 1 123 -> 281): their waves follow from the replicas and the rows, and
+// full chips take the entries one by one (41 and 110 us).
 constexpr int kSumTB = 1024;
 constexpr int kSumWaves = kSumTB / 64;
 constexpr int kRoundBlocks = 1024;
@@ -245,14 +257,17 @@ struct Gathered {
 };
 
 // MODE 0: cut (FP64 and, when out_i64, int64), 2: energies.
-template <int MODE, bool STAGE>
+template <int MODE, bool STAGE, int BATCH>
 __global__ __launch_bounds__(kSumTB) void sparse_sum_kernel(
     int n, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
     const float* __restrict__ J, const int8_t* __restrict__ colour,
     const float* __restrict__ theta, int q, int64_t* out_i64, double* out_a, double* out_b) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double bs[2][kRoundBlocks];
     __shared__ double stack[2][TreeAcc::kLevels];
+    const int nblk = (n + 63) / 64;
+    const int room = nblk < kRoundBlocks ? nblk : kRoundBlocks;
+    double* const bs[2] = {reinterpret_cast<double*>(smem), reinterpret_cast<double*>(smem) + room};
+    const int waves = blockDim.x >> 6;  // at most nblk
     const int r = blockIdx.x;
     const int8_t* k = colour ? colour + (int64_t)r * n : nullptr;
     const float* th = theta ? theta + (int64_t)r * n : nullptr;
@@ -260,10 +275,10 @@ __global__ __launch_bounds__(kSumTB) void sparse_sum_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool want_a = out_a != nullptr, want_b = MODE == 2 && out_b != nullptr;
     const bool want_i = MODE == 0 && out_i64 != nullptr;
-    float* th_lds = reinterpret_cast<float*>(smem);
+    float* th_lds = reinterpret_cast<float*>(bs[1] + (MODE == 2 ? room : 0));
     int8_t* k_lds = reinterpret_cast<int8_t*>(th_lds + (th ? n : 0));
     if constexpr (STAGE) {
-        for (int i = threadIdx.x; i < n; i += kSumTB) {
+        for (int i = threadIdx.x; i < n; i += blockDim.x) {
             if (th) th_lds[i] = th[i];
             if (k) k_lds[i] = k[i];
         }
@@ -280,19 +295,19 @@ __global__ __launch_bounds__(kSumTB) void sparse_sum_kernel(
         }
         return g;
     };
-    const int nblk = (n + 63) / 64;
     TreeAcc tree_a(stack[0]), tree_b(stack[1]);
+    const int wave_b = waves > 1 ? 1 : 0;  // the one that folds the second result
     int64_t tot_i = 0;
     for (int b0 = 0; b0 < nblk; b0 += kRoundBlocks) {
         const int nb = nblk - b0 < kRoundBlocks ? nblk - b0 : kRoundBlocks;
-        for (int b = wave; b < nb; b += kSumWaves) {
+        for (int b = wave; b < nb; b += waves) {
             const int i = (b0 + b) * 64 + lane;
             int64_t acc_i = 0;
             double acc_a = 0.0, acc_b = 0.0;
             if (i < n) {
                 const Gathered own = gather(i);
                 const double ti = (double)own.th;
-                upper_entries<1>(row_ptr, col, J, i, 0, gather, [&](bool on, Gathered g, float w) {
+                upper_entries<1, BATCH>(row_ptr, col, J, i, 0, gather, [&](bool on, Gathered g, float w) {
                     if (!on) return;
                     if (MODE == 0) {
                         if (own.k != g.k) {
@@ -330,21 +345,21 @@ __global__ __launch_bounds__(kSumTB) void sparse_sum_kernel(
             const double v = dpair::fold_blocks(bs[0], nb);
             if (lane == 0) tree_a.push(v);
         }
-        if (wave == 1 && want_b) {
+        if (wave == wave_b && want_b) {
             const double v = dpair::fold_blocks(bs[1], nb);
             if (lane == 0) tree_b.push(v);
         }
         __syncthreads();
     }
     if (wave == 0 && lane == 0 && want_a) out_a[r] = tree_a.finish();
-    if (wave == 1 && lane == 0 && want_b) out_b[r] = tree_b.finish();
+    if (wave == wave_b && lane == 0 && want_b) out_b[r] = tree_b.finish();
     if (MODE == 0 && want_i) {
         int64_t* ti = reinterpret_cast<int64_t*>(bs[0]);
         if (lane == 0) ti[wave] = tot_i;
         __syncthreads();
         if (threadIdx.x == 0) {
             int64_t t = 0;
-            for (int w = 0; w < kSumWaves; ++w) t += ti[w];
+            for (int w = 0; w < waves; ++w) t += ti[w];
             out_i64[r] = t;
         }
     }
@@ -391,30 +406,51 @@ int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* o
     return launched("readout launch");
 }
 
+// The smallest power of two from `lo` on that is at least x, at most 1024.
+int pow2_from(int lo, int64_t x) {
+    while (lo < x && lo < 1024) lo *= 2;
+    return lo;
+}
+
 template <bool CUT>
 int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* out, hipStream_t s) {
     // lanes per row: about one group of four entries each at the mean degree
-    const int64_t deg = p->nnz / p->n;
-    const int lpr = deg > 32 ? 16 : deg > 8 ? 4 : 1;
-    auto fn = lpr == 16  ? sparse_int_kernel<CUT, 16>
-              : lpr == 4 ? sparse_int_kernel<CUT, 4>
-                         : sparse_int_kernel<CUT, 1>;
+    const int64_t n = p->n, deg = p->nnz / n;
+    int lpr = deg > 32 ? 16 : deg > 8 ? 4 : 1;
     // A replica of at most 6 passes of 1024 threads stays in one workgroup,
     // which saves the zeroing launch (about 5 us; a pass is latency, 1 to 2
     // us).  Beyond, workgroups of 256 threads take one pass each while that
     // gives at most 2048 of them (eight per CU), else more.
-    int tb = 1024, chunks = 1;
-    int64_t rows = p->n;
-    if ((int64_t)p->n * lpr > 6 * 1024) {
+    int tb = 1024, chunks = 1, batch = 4;
+    int64_t rows = n;
+    if (R >= (deg > 8 ? 512 : 256) && deg <= 32 && n * R >= (256 << 10)) {
+        // Replicas that fill the chip: a workgroup each, a lane per row, upper
+        // entries alone, threads enough for 1024 per CU and 20 passes (us in
+        // groups of four split over workgroups, and so: n = 200 of degree 10,
+        // 4000 replicas 29 and 21; n = 3000 of degree 8, 300 replicas 39 and 28,
+        // 4000 284 and 203; n = 60000 of degree 4, 2000 replicas 6630 and 1630);
+        // groups of four where 1024 rows' entries pass the L1 (n = 25000 of
+        // degree 12, 2000 replicas 2290 one by one, 1720).
+        tb = pow2_from(64, (256 << 10) / R);
+        tb = pow2_from(tb, n / 20);
+        if (n < tb) tb = pow2_from(64, n);
+        if (tb < 1024 || n <= 8192 || deg <= 8) lpr = batch = 1;
+    } else if (R >= 512 && deg > 32) {
+        tb = 512;  // n = 800 of degree 48, 2000 replicas: 434 us split, 227 so
+    } else if (n * lpr > 6 * 1024) {
         tb = 256;
         const int64_t per_pass = tb / lpr;
-        const int64_t passes = (p->n + per_pass - 1) / per_pass;
+        const int64_t passes = (n + per_pass - 1) / per_pass;
         const int64_t per_group = passes * R / 2048 > 1 ? passes * R / 2048 : 1;
         chunks = (int)((passes + per_group - 1) / per_group);
         rows = per_group * per_pass;
-    } else if ((int64_t)p->n * lpr <= 256) {
+    } else if (n * lpr <= 256) {
         tb = 256;
     }
+    auto fn = batch == 1  ? sparse_int_kernel<CUT, 1, 1>
+              : lpr == 16 ? sparse_int_kernel<CUT, 16, 4>
+              : lpr == 4  ? sparse_int_kernel<CUT, 4, 4>
+                          : sparse_int_kernel<CUT, 1, 4>;
     for (int64_t r0 = 0; r0 < R; r0 += 65535) {  // grid.y limit
         const int nr = (int)(R - r0 < 65535 ? R - r0 : 65535);
         if (chunks > 1)
@@ -428,16 +464,35 @@ int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* ou
 template <int MODE>
 int launch_sparse_sum(const Problem* p, int R, const int8_t* colour, const float* theta, int q,
                       int64_t* oi, double* oa, double* ob, hipStream_t s) {
-    // the staged copies next to the static arrays (16.5 KiB), where they fit
-    constexpr size_t kFixed = 20 * 1024;
-    size_t lds = (size_t)p->n * ((theta ? 4 : 0) + (colour ? 1 : 0));
-    const bool stage = lds + kFixed <= dpair::kLdsLimit;
-    if (!stage) lds = 0;
-    auto fn = stage ? sparse_sum_kernel<MODE, true> : sparse_sum_kernel<MODE, false>;
+    // block sums and, where they fit beside them, the staged copies
+    constexpr size_t kFixed = 2 * 1024;
+    const int nblk = (p->n + 63) / 64;
+    const size_t sums = (size_t)(nblk < kRoundBlocks ? nblk : kRoundBlocks) * 8 * (MODE == 2 ? 2 : 1);
+    const size_t copies = (size_t)p->n * ((theta ? 4 : 0) + (colour ? 1 : 0));
+    const bool stage = copies + sums + kFixed <= dpair::kLdsLimit;
+    const size_t lds = sums + (stage ? copies : 0);
+    // Waves per replica: about 12288 in all (16384 with cosines; 2048 and 4096
+    // where rows are long, whose lines the waves of a CU take from each other's
+    // L1), enough for 32 per CU beside the copies, sixteen at most.
+    const int64_t deg = p->nnz / p->n;
+    const bool long_rows = deg >= 24;
+    const int heavy = theta ? 2 : 1;
+    const int most = long_rows ? 8 * heavy : kSumWaves;
+    const int64_t share = (long_rows ? 2048 * heavy : theta && R >= 2048 ? 16384 : 12288) / R;
+    int waves = 1;
+    while (waves < most && (2 * waves <= share || waves * 5120 < (int64_t)(copies + sums))) waves *= 2;
+    if (waves > nblk) waves = nblk;
+    // Entries one by one once the waves fill the chip (not with short rows
+    // whose lines then pass the L1, nor for colours alone with short rows).
+    const int64_t total = (int64_t)R * waves;
+    const bool one = long_rows ? total >= 1536
+                               : (MODE == 0 || theta) && total >= 4000 && waves * deg <= 60;
+    auto fn = stage ? (one ? sparse_sum_kernel<MODE, true, 1> : sparse_sum_kernel<MODE, true, 4>)
+                    : (one ? sparse_sum_kernel<MODE, false, 1> : sparse_sum_kernel<MODE, false, 4>);
     if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds, kFixed)) return st;
     for (int64_t r0 = 0; r0 < R; r0 += kMaxGroups) {
         const int count = (int)(R - r0 < kMaxGroups ? R - r0 : kMaxGroups);
-        hipLaunchKernelGGL(fn, dim3(count), dim3(kSumTB), lds, s, p->n, p->d_row_ptr, p->d_col, p->d_J,
+        hipLaunchKernelGGL(fn, dim3(count), dim3(64 * waves), lds, s, p->n, p->d_row_ptr, p->d_col, p->d_J,
                            offset(colour, r0 * p->n), offset(theta, r0 * p->n), q, offset(oi, r0),
                            offset(oa, r0), offset(ob, r0));
     }

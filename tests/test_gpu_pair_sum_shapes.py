@@ -1,6 +1,7 @@
-"""Every shape of the scoring kernels (waves and replicas per workgroup) where it
-can go wrong: one wave for several replicas, ragged replica groups, rows around
-a block of 64, the first and last replica of a launch that fills the chip."""
+"""Every shape of the scoring kernels (waves and replicas per workgroup, entries
+one by one or in groups, lanes per row) where it can go wrong: one wave for
+several replicas, ragged replica groups, rows around a block of 64, the first
+and last replica of a launch that fills the chip."""
 import numpy as np
 import pytest
 
@@ -69,3 +70,23 @@ def test_dense_shapes(oim, orc, n, R, q, integer):
     J = J + J.T
     with oim.Problem.from_dense(J) as prob:
         _check(oim, orc, prob, orc.dense_to_csr(J), R, q, True)
+
+
+# (n, mean degree, replicas): 1 to 16 waves, entries one by one and in fours,
+# long rows; whole-number sums of 64 to 1024 threads, 1, 4 and 16 lanes per row
+@pytest.mark.parametrize("n,degree,R", [
+    (9, 3, 5), (64, 6, 5000), (65, 6, 5000), (63, 4, 20001), (129, 5, 300), (200, 10, 1400),
+    (300, 10, 4100), (600, 6, 601), (1100, 5, 300), (1025, 12, 700), (2100, 4, 12300),
+    (4200, 12, 600), (9000, 12, 520), (9000, 4, 520), (130, 40, 600), (500, 60, 3), (500, 60, 200),
+    (500, 40, 2100), (700, 30, 600)])
+@pytest.mark.parametrize("weights", ["pm1", "real"])
+def test_sparse_shapes(oim, orc, n, degree, R, weights):
+    g = synth.gnp_avg_degree(n, min(degree, n - 1), seed=n + degree)
+    if weights == "real":
+        ei, ej, _ = g.upper_edges()
+        rng = np.random.default_rng(n)
+        w = rng.standard_normal(ei.size) * np.exp(rng.uniform(-4, 2, ei.size))
+        g = synth.csr_from_edges(n, ei, ej, w.astype(np.float32))
+    J = (-g.w).astype(np.float32)
+    with oim.Problem.from_csr(n, g.row_ptr, g.col, J) as prob:
+        _check(oim, orc, prob, (g.row_ptr, g.col, J), R, 2 if R % 2 else 3, n * R < 1e7)
