@@ -88,13 +88,14 @@ __device__ __forceinline__ double term(bool same, double w) {
 // Block sums of the workgroup's NR replicas into LDS: bs[r][block], and with
 // INTS the same as int64 (every row sum is then an exact integer).  NEG: the
 // pair's weight is -J instead of J.  `code` as staged by the caller (and
-// published by a barrier); ends without one.
-template <int NR, int KIND, bool NEG, bool INTS>
+// published by a barrier); ends without one.  WAVES 0: as many as were launched.
+template <int NR, int KIND, bool NEG, bool INTS, int WAVES = kWaves>
 __device__ __forceinline__ void block_sums(const float* __restrict__ J, int n,
                                            const unsigned char* code, double* bs, int64_t* bi) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nblk = row_blocks(n), ld = code_stride(n), waves = blockDim.x >> 6;
+    const int nblk = row_blocks(n), ld = code_stride(n);
+    const int waves = WAVES ? WAVES : (int)blockDim.x >> 6;
     for (int t = 0; t * waves < nblk; ++t) {
         const int blk = t * waves + ((t & 1) ? waves - 1 - wave : wave);
         if (blk >= nblk) continue;

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void phase_convert_kernel(int64_t count, const
 
 // Cut (kDiffer), conflicts (kCount) or Eq. 1 / Eq. 2 (kIsing / kSame) of
 // colours [R][n] with the pair's weight -J; NR replicas per workgroup.
-template <int NR, int KIND, bool INTS>
+template <int NR, int KIND, bool INTS, int WAVES>
 __global__ __launch_bounds__(dpair::kTB) void dense_pair_kernel(int n, int R, const float* J,
                                                                 const int8_t* colour,
                                                                 int64_t* out_i64, double* out_f64) {
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(dpair::kTB) void dense_pair_kernel(int n, int R, co
             smem[r * ld + j] = j < n ? (unsigned char)k[j] : 0;
     }
     __syncthreads();
-    dpair::block_sums<NR, KIND, true, INTS>(J, n, smem, bs, bi);
+    dpair::block_sums<NR, KIND, true, INTS, WAVES>(J, n, smem, bs, bi);
     __syncthreads();
     const int lane = threadIdx.x & 63;
     for (int r = threadIdx.x >> 6; r < NR && r0 + r < R; r += blockDim.x >> 6) {
@@ -95,8 +95,7 @@ __global__ __launch_bounds__(dpair::kTB) void dense_pair_kernel(int n, int R, co
 
 // Eq. 6 at the continuous phases [R][n]: the same walk with one FP64 cosine
 // per pair, which bounds it; one replica per workgroup.  KIND: Eq. 1 or Eq. 2 at
-// the colours too, in the same walk (n = 10, 32 replicas 14.4 us in two
-// launches, 11.2 in one; n = 500, 32 replicas 161 and 146), or kNone.
+// the colours too, after it (in the cosines' own loop it cost more), or kNone.
 constexpr int kNone = -1;
 
 template <int KIND>
@@ -105,16 +104,14 @@ __global__ __launch_bounds__(dpair::kTB) void dense_energy_kernel(int n, const f
                                                                   const int8_t* __restrict__ colour,
                                                                   double* h_eq6, double* h_model) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int nblk = dpair::row_blocks(n), waves = blockDim.x >> 6;
-    double* bs = reinterpret_cast<double*>(smem);
-    [[maybe_unused]] double* bk = bs + nblk;
-    [[maybe_unused]] int8_t* code = reinterpret_cast<int8_t*>(bk + nblk);
+    const int nblk = dpair::row_blocks(n), ld = dpair::code_stride(n), waves = blockDim.x >> 6;
+    double* bs = reinterpret_cast<double*>(KIND != kNone ? smem + ld : smem);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float* th = theta + (int64_t)blockIdx.x * n;
     if constexpr (KIND != kNone) {
         const int8_t* k = colour + (int64_t)blockIdx.x * n;
-        for (int j = threadIdx.x; j < n; j += blockDim.x) code[j] = k[j];
+        for (int j = threadIdx.x; j < ld; j += blockDim.x) smem[j] = j < n ? (unsigned char)k[j] : 0;
         __syncthreads();
     }
     for (int t = 0; t * waves < nblk; ++t) {
@@ -123,31 +120,22 @@ __global__ __launch_bounds__(dpair::kTB) void dense_energy_kernel(int n, const f
         const int i = blk * 64 + lane, ic = i < n ? i : n - 1;
         const double ti = (double)th[ic];
         double acc = 0.0;
-        [[maybe_unused]] double acc_k = 0.0;
-        [[maybe_unused]] int ci = 0;
-        if constexpr (KIND != kNone) ci = code[ic];
         for (int j = blk * 64 + 1; j < n; ++j) {
             const double c = cos(ti - (double)th[j]);
-            const double w = -(double)J[(size_t)j * n + ic];
-            const double term = w * c;
+            const double term = -(double)J[(size_t)j * n + ic] * c;
             acc += j > i ? term : 0.0;
-            if constexpr (KIND != kNone) acc_k += j > i ? dpair::term<KIND>(ci == code[j], w) : 0.0;
         }
         double v = i < n ? acc : 0.0;
         for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
         if (lane == 0) bs[blk] = v;
-        if constexpr (KIND != kNone) {
-            v = i < n ? acc_k : 0.0;
-            for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) bk[blk] = v;
-        }
     }
+    if constexpr (KIND != kNone) dpair::block_sums<1, KIND, true, false, 0>(J, n, smem, bs + nblk, nullptr);
     __syncthreads();
     if (threadIdx.x < 64) {
         const double v = dpair::fold_blocks(bs, nblk);
         if (threadIdx.x == 0) h_eq6[blockIdx.x] = v;
         if constexpr (KIND != kNone) {
-            const double vk = dpair::fold_blocks(bk, nblk);
+            const double vk = dpair::fold_blocks(bs + nblk, nblk);
             if (threadIdx.x == 0) h_model[blockIdx.x] = vk;
         }
     }
@@ -392,15 +380,23 @@ T* offset(T* p, int64_t k) {
 template <int KIND, bool INTS>
 int launch_dense_pairs(const Problem* p, int R, const int8_t* colour, int64_t* oi, double* of,
                        hipStream_t s) {
-    const int nr = dpair::replicas_per_group(p->n, R, INTS, dpair::group_waves(p->n));
+    // (sixteen waves as a constant: the cut of n = 6000 took 1550 us with their
+    // number read, 1390 so)
+    const int waves = dpair::group_waves(p->n);
+    const int nr = dpair::replicas_per_group(p->n, R, INTS, waves);
     const size_t lds = dpair::lds_bytes(p->n, nr, INTS);
-    auto fn = nr == 4   ? dense_pair_kernel<4, KIND, INTS>
-              : nr == 2 ? dense_pair_kernel<2, KIND, INTS>
-                        : dense_pair_kernel<1, KIND, INTS>;
+    auto pick = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        return nr == 4   ? dense_pair_kernel<4, KIND, INTS, W>
+               : nr == 2 ? dense_pair_kernel<2, KIND, INTS, W>
+                         : dense_pair_kernel<1, KIND, INTS, W>;
+    };
+    auto fn = waves == dpair::kWaves ? pick(std::integral_constant<int, dpair::kWaves>{})
+                                     : pick(std::integral_constant<int, 0>{});
     if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
     for (int64_t r0 = 0; r0 < R; r0 += nr * kMaxGroups) {
         const int count = (int)(R - r0 < nr * kMaxGroups ? R - r0 : nr * kMaxGroups);
-        hipLaunchKernelGGL(fn, dim3((count + nr - 1) / nr), dim3(64 * dpair::group_waves(p->n)), lds, s, p->n, count,
+        hipLaunchKernelGGL(fn, dim3((count + nr - 1) / nr), dim3(64 * waves), lds, s, p->n, count,
                            p->d_Jdense, colour + r0 * p->n, offset(oi, r0), offset(of, r0));
     }
     return launched("readout launch");
@@ -545,12 +541,23 @@ int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
     if (!p->dense)
         return launch_sparse_sum<2>(p, R, h_model ? colour : nullptr, h_eq6 ? theta : nullptr, q,
                                     nullptr, h_model, h_eq6, s);
+    // Both in one launch (us in two and in one: n = 10, 32 replicas 14.2 and
+    // 11.5; n = 500 161 and 156), not where sixteen waves per replica fill the
+    // chip: the pair sums then share columns among replicas, and the cosines
+    // alone take fewer registers (n = 2000, 1500 replicas 6840 and 8400).
+    const bool both = h_model && h_eq6 && (R <= 256 || dpair::group_waves(p->n) < dpair::kWaves);
+    if (h_model && !both) {
+        const int st = q == 2
+                           ? launch_dense_pairs<dpair::kIsing, false>(p, R, colour, nullptr, h_model, s)
+                           : launch_dense_pairs<dpair::kSame, false>(p, R, colour, nullptr, h_model, s);
+        if (st) return st;
+    }
     if (h_eq6) {
-        auto fn = !h_model ? dense_energy_kernel<kNone>
+        auto fn = !both    ? dense_energy_kernel<kNone>
                   : q == 2 ? dense_energy_kernel<dpair::kIsing>
                            : dense_energy_kernel<dpair::kSame>;
         const size_t sums = sizeof(double) * dpair::row_blocks(p->n);
-        const size_t lds = h_model ? 2 * sums + p->n : sums;
+        const size_t lds = both ? dpair::code_stride(p->n) + 2 * sums : sums;
         if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
         for (int64_t r0 = 0; r0 < R; r0 += kMaxGroups) {
             const int count = (int)(R - r0 < kMaxGroups ? R - r0 : kMaxGroups);
@@ -560,9 +567,6 @@ int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
         }
         return launched("readout launch");
     }
-    if (h_model)
-        return q == 2 ? launch_dense_pairs<dpair::kIsing, false>(p, R, colour, nullptr, h_model, s)
-                      : launch_dense_pairs<dpair::kSame, false>(p, R, colour, nullptr, h_model, s);
     return OIM_OK;
 }
 

@@ -61,7 +61,8 @@ def _check(oim, orc, prob, csr, R, q, theta):
 
 # one, two and four replicas per workgroup of one, two and three waves
 @pytest.mark.parametrize("n,R,q", [(1, 3, 2), (10, 2051, 2), (10, 16387, 3), (64, 2049, 3),
-                                   (65, 1027, 2), (66, 8195, 2), (130, 703, 3), (130, 5463, 2)])
+                                   (65, 1027, 2), (66, 8195, 2), (130, 703, 3), (130, 5463, 2),
+                                   (1000, 2, 2), (1000, 257, 3)])
 @pytest.mark.parametrize("integer", [True, False])
 def test_dense_shapes(oim, orc, n, R, q, integer):
     rng = np.random.default_rng(n)
