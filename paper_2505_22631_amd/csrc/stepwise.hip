@@ -486,7 +486,7 @@ __device__ __forceinline__ void tile_of(int np, int& i0, int& r0) {
 
 // Fills buffer 0 and, in buffer 1, the padding rows alone: the first step
 // writes the others.  Padding rows and replicas hold 0.
-__global__ __launch_bounds__(256) void stepwise_init_kernel(const float* theta, const uint32_t* phase,
+__global__ __launch_bounds__(1024) void stepwise_init_kernel(const float* theta, const uint32_t* phase,
                                                             uint32_t* U0, uint32_t* U1,
                                                             int n, int R, int np, int Rp) {
     __shared__ uint32_t tile[kTile][kTile + 1];
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256) void stepwise_init_kernel(const float* theta, 
     tile_of(np, i0, r0);
     const int lr = Rp < kTile ? Rp : kTile;
     const int lane = threadIdx.x & 63;
-    for (int r = threadIdx.x >> 6; r < lr; r += 4) {
+    for (int r = threadIdx.x >> 6; r < lr; r += blockDim.x >> 6) {
         const int i = i0 + lane;
         uint32_t u = 0;
         if (i < n && r0 + r < R) {
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void stepwise_init_kernel(const float* theta, 
         tile[lane][r] = u;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < kTile * lr; e += 256) {
+    for (int e = threadIdx.x; e < kTile * lr; e += blockDim.x) {
         const int row = e / lr, r = e % lr, i = i0 + row;
         if (i >= np) break;
         const size_t o = (size_t)i * Rp + r0 + r;
@@ -513,21 +513,21 @@ __global__ __launch_bounds__(256) void stepwise_init_kernel(const float* theta, 
     }
 }
 
-__global__ __launch_bounds__(256) void stepwise_final_kernel(const uint32_t* U, float* theta,
+__global__ __launch_bounds__(1024) void stepwise_final_kernel(const uint32_t* U, float* theta,
                                                              uint32_t* phase, int n, int R, int Rp) {
     __shared__ uint32_t tile[kTile][kTile + 1];
     int i0, r0;
     tile_of(n, i0, r0);
     const int lr = Rp < kTile ? Rp : kTile;
     const int lane = threadIdx.x & 63;
-    for (int e = threadIdx.x; e < kTile * lr; e += 256) {
+    for (int e = threadIdx.x; e < kTile * lr; e += blockDim.x) {
         const int row = e / lr, r = e % lr;
         if (i0 + row < n) tile[row][r] = U[(size_t)(i0 + row) * Rp + r0 + r];
     }
     __syncthreads();
     const int i = i0 + lane;
     if (i >= n) return;
-    for (int r = threadIdx.x >> 6; r < lr && r0 + r < R; r += 4) {
+    for (int r = threadIdx.x >> 6; r < lr && r0 + r < R; r += blockDim.x >> 6) {
         const size_t dst = (size_t)(r0 + r) * n + i;
         theta[dst] = theta_from_phase(tile[lane][r]);
         if (phase) phase[dst] = tile[lane][r];
@@ -548,15 +548,15 @@ struct ReadArgs {
 // Partial sums of sum_{i<j} J_ij term(k_i, k_j) per block of rows and replica
 // (term = s_i s_j for q = 2, delta(k_i, k_j) for q >= 3), in the library's
 // fixed FP64 order: each row over j > i in column order, a quad's rows as (r0
-// + r1) + (r2 + r3), a thread's kReadQuads consecutive quads and then the
-// block's threads pairwise -- the pairwise tree over the block's rows.  A
-// thread is one replica of its quads: 64 replicas make blocks of 64 rows, one
-// replica of 4096.
-constexpr int kReadQuads = 4;
+// + r1) + (r2 + r3), then the block's threads pairwise -- the pairwise tree over
+// the block's rows.  A thread is one replica of its quad: 64 replicas make
+// blocks of 16 rows, four of 256.  (Four quads per thread, for fewer partials,
+// were a longer chain: 64 steps with 8 readouts of n = 3000 of degree 20, 64
+// replicas 1210 us, 830 so; of a 200 x 300 torus, 64 replicas 1060 and 1050.)
 
 // Blocks of rows of a readout.
 int read_blocks(int quads, int Rp) {
-    const int per = kReadQuads * (256 / (Rp < 64 ? Rp : 64));
+    const int per = 256 / (Rp < 64 ? Rp : 64);
     return (quads + per - 1) / per;
 }
 
@@ -568,42 +568,37 @@ __global__ __launch_bounds__(256) void stepwise_readout_kernel(ReadArgs a) {
     const int lr = a.Rp < 64 ? a.Rp : 64, slots = 256 / lr;
     const int slot = threadIdx.x / lr, r = blockIdx.y * 64 + threadIdx.x % lr;
     auto state = [&](int row) { return nearest_state(a.U[(size_t)row * a.Rp + r], a.q); };
-    double v[kReadQuads];
+    const int m = blockIdx.x * slots + slot;
+    double rs[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int x = 0; x < kReadQuads; ++x) {
-        const int m = (blockIdx.x * slots + slot) * kReadQuads + x;
-        double rs[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < 4; ++j) {
+        const int i = 4 * m + j;
+        if (i >= a.n) continue;
+        const int ci = state(i);
+        const int64_t e1 = a.row_ptr[i + 1];
+        double acc = 0.0;
+        // four entries at a time, their words in flight together
+        for (int64_t e = a.row_ptr[i]; e < e1; e += 4) {
+            int c[4], k[4];
+            float w[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = 4 * m + j;
-            if (i >= a.n) continue;
-            const int ci = state(i);
-            const int64_t e1 = a.row_ptr[i + 1];
-            double acc = 0.0;
-            // four entries at a time, their words in flight together
-            for (int64_t e = a.row_ptr[i]; e < e1; e += 4) {
-                int c[4], k[4];
-                float w[4];
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    const int64_t ee = e + h < e1 ? e + h : e1 - 1;
-                    c[h] = a.col[ee];
-                    w[h] = a.J[ee];
-                }
-#pragma unroll
-                for (int h = 0; h < 4; ++h) k[h] = state(c[h]);
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    const double wd = (double)w[h];
-                    const double term = a.q == 2 ? (ci == k[h] ? wd : -wd) : (ci == k[h] ? wd : 0.0);
-                    acc += e + h < e1 && c[h] > i ? term : 0.0;
-                }
+            for (int h = 0; h < 4; ++h) {
+                const int64_t ee = e + h < e1 ? e + h : e1 - 1;
+                c[h] = a.col[ee];
+                w[h] = a.J[ee];
             }
-            rs[j] = acc;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) k[h] = state(c[h]);
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const double wd = (double)w[h];
+                const double term = a.q == 2 ? (ci == k[h] ? wd : -wd) : (ci == k[h] ? wd : 0.0);
+                acc += e + h < e1 && c[h] > i ? term : 0.0;
+            }
         }
-        v[x] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
+        rs[j] = acc;
     }
-    red[threadIdx.x] = (v[0] + v[1]) + (v[2] + v[3]);
+    red[threadIdx.x] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
     __syncthreads();
     for (int d = 1; d < slots; d <<= 1) {
         if ((slot & (2 * d - 1)) == 0) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + d * lr];
@@ -621,10 +616,11 @@ struct BestArgs {
     const CallArgs* call;
     int k;            // node position in the chunk, or -1: after the last step
     int M, n, R, Rp, q;
+    int colours;      // 1: the best kernel writes the colours of a new best
 };
 
 // One workgroup per replica: H = -(the pairwise tree over the blocks'
-// partials), trace entry and best-so-far.  The
+// partials), trace entry, best-so-far and (a.colours) the colours of a new best.  The
 // partials, zero-padded to a power of two P, are taken in rounds of
 // CH = min(P, 4096) values; in a round each of the 256 threads folds an
 // aligned chunk of CH / 256 (at most 16) values by the pairwise tree in
@@ -632,6 +628,7 @@ struct BestArgs {
 // pushes the round's sum into a tree over rounds.  This is the pairwise tree
 // over the padded sequence (padding zeros add exactly).
 __global__ __launch_bounds__(256) void stepwise_best_kernel(BestArgs a) {
+    __shared__ int improved;
     __shared__ double sums[256];
     __shared__ double stack[TreeAcc::kLevels];
     const CallArgs& c = *a.call;
@@ -669,11 +666,17 @@ __global__ __launch_bounds__(256) void stepwise_best_kernel(BestArgs a) {
         const double H = -outer.finish();
         const int kread = (s + a.M) / a.M - 1;
         if (c.trace) c.trace[(size_t)kread * a.R + r] = H;
-        if (kread == 0 || H < a.best[r]) {
+        improved = kread == 0 || H < a.best[r] ? 1 : 0;
+        if (improved) {
             a.best[r] = H;
             a.best_at[r] = (int32_t)(c.step0 + s + 1);
         }
     }
+    if (!a.colours || !c.best_colour) return;
+    __syncthreads();
+    if (improved)
+        for (int i = threadIdx.x; i < a.n; i += blockDim.x)
+            c.best_colour[(size_t)r * a.n + i] = (int8_t)nearest_state(a.U[(size_t)i * a.Rp + r], a.q);
 }
 
 // The colours of the replicas whose best is this readout's (best_at names its
@@ -696,7 +699,7 @@ __global__ __launch_bounds__(256) void stepwise_colour_kernel(BestArgs a) {
     if (threadIdx.x < lr && r0 + threadIdx.x < a.R && a.best_at[r0 + threadIdx.x] == now) any = 1;
     __syncthreads();
     if (!any) return;
-    for (int e = threadIdx.x; e < kTile * lr; e += 256) {
+    for (int e = threadIdx.x; e < kTile * lr; e += blockDim.x) {
         const int row = e / lr, r = e % lr;
         if (i0 + row < a.n)
             tile[row][r] = (int8_t)nearest_state(a.U[(size_t)(i0 + row) * a.Rp + r0 + r], a.q);
@@ -704,7 +707,7 @@ __global__ __launch_bounds__(256) void stepwise_colour_kernel(BestArgs a) {
     __syncthreads();
     const int i = i0 + lane;
     if (i >= a.n) return;
-    for (int r = threadIdx.x >> 6; r < lr && r0 + r < a.R; r += 4)
+    for (int r = threadIdx.x >> 6; r < lr && r0 + r < a.R; r += blockDim.x >> 6)
         if (a.best_at[r0 + r] == now) c.best_colour[(size_t)(r0 + r) * a.n + i] = tile[lane][r];
 }
 
@@ -765,6 +768,7 @@ namespace {
 struct Shape {
     int n, R, steps, M, Rp, quads, np, gx, rblocks, chunk;
     int global_addr;  // 64-bit global addressing asked for
+    int packed;       // several quads per wave
     size_t cells, args_off, bytes;
 };
 
@@ -779,8 +783,10 @@ Shape shape_of(const Problem* p, const oim_run_cfg* cfg) {
     const char* env = getenv("OIM_STEPWISE_GLOBAL_ADDR");
     sh.global_addr = env && atoi(env) != 0;
     sh.Rp = (sh.R + 63) / 64 * 64;
-    if (sh.R < 64 && !sh.global_addr)
-        for (sh.Rp = 4; sh.Rp < sh.R;) sh.Rp *= 2;
+    int pow2 = 4;
+    while (pow2 < sh.R && pow2 < 64) pow2 *= 2;
+    sh.packed = !sh.global_addr && pow2 < 64;
+    if (sh.packed) sh.Rp = pow2;
     sh.quads = (sh.n + 3) / 4;
     sh.np = sh.quads * 4;
     sh.gx = (sh.quads + kQuadsPerBlock - 1) / kQuadsPerBlock;
@@ -841,7 +847,8 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     int st = check_launch("set_call_kernel");
     if (st) return st;
     const dim3 tiles((unsigned)(((np + kTile - 1) / kTile) * ((Rp + kTile - 1) / kTile)));
-    hipLaunchKernelGGL(stepwise_init_kernel, tiles, dim3(256), 0, stream, theta, phase, U0, U1, n, R,
+    const dim3 tile_tb(256);
+    hipLaunchKernelGGL(stepwise_init_kernel, tiles, tile_tb, 0, stream, theta, phase, U0, U1, n, R,
                        np, Rp);
     if ((st = check_launch("stepwise_init_kernel"))) return st;
 
@@ -864,7 +871,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
         {stepwise_packed_kernel<0, true>, stepwise_packed_kernel<2, true>,
          stepwise_packed_kernel<3, true>}};
     const int qi = cfg->q == 2 ? 1 : cfg->q == 3 ? 2 : 0;
-    const bool packed = Rp < 64;
+    const bool packed = sh.packed;
     StepFn fn = packed ? kPacked[ell][qi] : kStep[ell][buf][qi];
     const int64_t lanes = (int64_t)sh.quads * Rp;  // packed: a lane per quad and replica
     const dim3 step_grid(packed ? (unsigned)((lanes + 255) / 256) : (unsigned)(gx * (Rp / 64)));
@@ -899,6 +906,10 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     ba.R = R;
     ba.Rp = Rp;
     ba.q = cfg->q;
+    // colours by the best kernel: at a stride, but without a launch more
+    // (64 steps with 8 readouts, 64 replicas, n = 1000 308 and 291 us, n = 6000
+    // 371 and 363, n = 15000 497 and 513)
+    ba.colours = n <= 8192;
 
     // Record one chunk: step kernels (with readouts where due) and the base
     // advance.  Buffer parity alternates per step (step s reads buffer s % 2);
@@ -922,7 +933,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
                 ba.k = k;
                 hipLaunchKernelGGL(stepwise_best_kernel, dim3(R), dim3(256), 0, s, ba);
                 if ((rc = check_launch("stepwise_best_kernel"))) return rc;
-                hipLaunchKernelGGL(stepwise_colour_kernel, tiles, dim3(256), 0, s, ba);
+                if (!ba.colours) hipLaunchKernelGGL(stepwise_colour_kernel, tiles, dim3(256), 0, s, ba);
                 if ((rc = check_launch("stepwise_colour_kernel"))) return rc;
             }
         }
@@ -1016,7 +1027,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
         if ((st = check_launch("stepwise_readout_kernel"))) return st;
         hipLaunchKernelGGL(stepwise_best_kernel, dim3(R), dim3(256), 0, stream, bl);
         if ((st = check_launch("stepwise_best_kernel"))) return st;
-        hipLaunchKernelGGL(stepwise_colour_kernel, tiles, dim3(256), 0, stream, bl);
+        if (!bl.colours) hipLaunchKernelGGL(stepwise_colour_kernel, tiles, dim3(256), 0, stream, bl);
         if ((st = check_launch("stepwise_colour_kernel"))) return st;
     }
     if (ro && M > 0 && steps > 0) {
@@ -1029,7 +1040,7 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
             if (e != hipSuccess) return hip_error(e, "best_step copy");
         }
     }
-    hipLaunchKernelGGL(stepwise_final_kernel, tiles, dim3(256), 0, stream, Ufinal, theta, phase, n, R,
+    hipLaunchKernelGGL(stepwise_final_kernel, tiles, tile_tb, 0, stream, Ufinal, theta, phase, n, R,
                        Rp);
     return check_launch("stepwise_final_kernel");
 }

@@ -75,3 +75,36 @@ def test_stepwise_global_addressing_at_any_size(oim, R, monkeypatch):
             steps = {k for e in prof.events()
                      for k in ("stepwise_packed_kernel", "stepwise_step_kernel") if k in e.name}
             assert steps == {kernel}
+
+
+def _ring_of(n, degree):
+    """n oscillators with `degree` neighbours each."""
+    i = np.arange(n)
+    ei, ej = zip(*[(i, (i + k) % n) for k in range(1, degree // 2 + 1)])
+    return synth.csr_from_edges(n, np.concatenate(ei), np.concatenate(ej), np.ones(n * degree // 2))
+
+
+@pytest.mark.parametrize("R", [1, 2, 16, 32, 40, 64, 200])
+@pytest.mark.parametrize("n,degree", [(9, 2), (64, 4), (301, 6), (1003, 4), (5001, 4), (8192, 2),
+                                      (8193, 2)])
+def test_stepwise_readouts(oim, orc, n, degree, R):
+    # in-run readouts with blocks of 16 to 256 rows, the colours of a best by
+    # either kernel (up to 8192 oscillators, and above)
+    q = 2 if R % 2 == 0 else 3
+    g = _ring_of(n, degree)
+    J = (-g.w).astype(np.float32)
+    with oim.Problem.from_csr(n, g.row_ptr, g.col, J) as prob:
+        K, Ks, sg = (_t(x) for x in ramp_schedule(prob.info["max_abs_row_sum"], q, 11))
+        th = _t(synth.theta0(R, n, seed=R))
+        ph = oim.oim_phase_from_theta(th)
+        out = oim.run(prob, th, K, Ks, sg, _t(synth.seeds(R, 3)), q=q, dt=DT, readout_every=4,
+                      want_best=True, flags=oim.OIM_LOOP_STEPWISE, phase=ph)
+        out = {k: v.cpu().numpy() for k, v in out.items()}
+        words = ph.cpu().numpy()
+    np.testing.assert_array_equal(out["best_h"], out["trace"].min(axis=0))
+    np.testing.assert_array_equal(out["best_step"],
+                                  np.array([4, 8, 11])[out["trace"].argmin(axis=0)])
+    for r in sorted({0, R // 2, R - 1}):
+        assert out["best_h"][r] == orc.h_model_fixed(g.row_ptr, g.col, J, q, out["best_colour"][r])
+        last = (((q * words[r].astype(np.uint64) + (1 << 31)) >> 32) % q).astype(np.int8)
+        assert out["trace"][-1, r] == orc.h_model_fixed(g.row_ptr, g.col, J, q, last)
