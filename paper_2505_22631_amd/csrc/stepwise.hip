@@ -2,8 +2,8 @@
 // kernel per Euler-Maruyama step, for replicas too large for the
 // LDS-resident kernel.
 //
-// Layout: replica index fastest, [n][Rp] (Rp = R rounded up to 64, below 64 to
-// a power of two, 4 at least), two buffers of phase words (ping-pong: step s
+// Layout: replica index fastest, [n][Rp] (Rp = R rounded up to 64; below 33
+// replicas, where the packed kernel runs, to a power of two, 4 at least), two buffers of phase words (ping-pong: step s
 // reads buffer s % 2 and writes buffer (s + 1) % 2, which keeps the
 // synchronous update of Algorithm 1).
 // The state is the phase word alone (4 bytes per oscillator and replica):
@@ -13,7 +13,7 @@
 // (4 consecutive oscillators) and 64 replicas: CSR entries are wave-uniform
 // (scalar loads) and each neighbour gather is one coalesced 256-byte load.
 // Lane r draws the quad's four normals with one Philox call keyed by replica
-// r's seed.  With fewer than 33 replicas a wave takes 64 / Rp quads, the lanes
+// r's seed.  With fewer than 33 replicas a wave can take 64 / Rp quads, the lanes
 // of a quad reading the same entries (stepwise_packed_kernel).
 //
 // The step loop is a hipGraph of `chunk` step kernels plus a node that
@@ -772,6 +772,21 @@ struct Shape {
     size_t cells, args_off, bytes;
 };
 
+// Whether a run with fewer than 33 replicas (a power of two, Rp) takes the
+// packed kernel: where the waves of 64 lanes per quad would be many, where the
+// entries come from the padded image and few lanes need them, or where rows are
+// longer than the image's first group.  Its entry loads are vector loads with
+// a longer latency, which a small graph pays on every step: 64 steps with 64
+// lanes per quad and packed (us): n = 2000 of degree 6, CSR, one replica 374
+// and 416, n = 5000, 8 replicas 455 and 454, n = 10000 569 and 472; 50 x 20 and
+// 300 x 20 tori, 16 replicas 198 and 217, 242 and 223; n = 60 of degree 4, one
+// replica 196 and 161; n = 300 of degree 6 (image rows of 8) 309 and 244.
+bool packs(const Problem* p, int quads, int Rp) {
+    if (Rp >= 64) return false;
+    if (!p->d_ell_col) return quads >= (Rp <= 4 ? 2000 : 1250) || quads * Rp <= 128;
+    return p->ell_D > 4 || Rp <= 8 || quads >= 1024;
+}
+
 Shape shape_of(const Problem* p, const oim_run_cfg* cfg) {
     Shape sh{};
     sh.n = p->n;
@@ -785,7 +800,7 @@ Shape shape_of(const Problem* p, const oim_run_cfg* cfg) {
     sh.Rp = (sh.R + 63) / 64 * 64;
     int pow2 = 4;
     while (pow2 < sh.R && pow2 < 64) pow2 *= 2;
-    sh.packed = !sh.global_addr && pow2 < 64;
+    sh.packed = !sh.global_addr && packs(p, (sh.n + 3) / 4, pow2);
     if (sh.packed) sh.Rp = pow2;
     sh.quads = (sh.n + 3) / 4;
     sh.np = sh.quads * 4;
@@ -847,7 +862,8 @@ int run_stepwise(Problem* p, const oim_run_cfg* cfg, const float* K, const float
     int st = check_launch("set_call_kernel");
     if (st) return st;
     const dim3 tiles((unsigned)(((np + kTile - 1) / kTile) * ((Rp + kTile - 1) / kTile)));
-    const dim3 tile_tb(256);
+    // a tile of few replicas is small work
+    const dim3 tile_tb(Rp >= 64 ? 1024 : Rp >= 32 ? 512 : 256);
     hipLaunchKernelGGL(stepwise_init_kernel, tiles, tile_tb, 0, stream, theta, phase, U0, U1, n, R,
                        np, Rp);
     if ((st = check_launch("stepwise_init_kernel"))) return st;

@@ -34,12 +34,22 @@ def _run(oim, prob, R, q, run):
     return [th.cpu().numpy(), ph.cpu().numpy()] + [v.cpu().numpy() for v in out.values()]
 
 
+# several quads per wave: the padded image at any size here, the CSR below 33
+# quads and from 1250 (4 replicas: 2000) on
 @pytest.mark.parametrize("weights", ["pm1", "real"])
-@pytest.mark.parametrize("R,q", [(1, 2), (5, 3), (32, 5), (33, 2), (70, 3), (70, 5)])
-def test_stepwise_addressing_same_bits(oim, R, q, weights, monkeypatch):
+@pytest.mark.parametrize("n,R,q", [(203, 1, 2), (203, 5, 3), (203, 32, 5), (203, 33, 2), (203, 70, 3),
+                                   (203, 70, 5), (97, 2, 5), (97, 4, 2), (97, 3, 3), (5003, 5, 5),
+                                   (5003, 32, 3), (5003, 17, 2), (8003, 1, 3), (8003, 4, 5)])
+def test_stepwise_addressing_same_bits(oim, n, R, q, weights, monkeypatch):
     # one problem for both ways of addressing, so that a graph captured for one
     # may not serve the other; the CSR and the padded row image
-    g = synth.random_small(203, 0.05, seed=7, weights=weights)
+    if n < 1000:
+        g = synth.random_small(n, 10 / n, seed=7, weights=weights)
+    else:
+        g = synth.gnp_avg_degree(n, 5, seed=7)
+        if weights == "real":
+            ei, ej, _ = g.upper_edges()
+            g = synth.csr_from_edges(n, ei, ej, np.random.default_rng(3).standard_normal(ei.size))
     ref = None
     for image in ("0", "1"):
         monkeypatch.setenv("OIM_STEPWISE_ELL", image)
@@ -56,11 +66,11 @@ def test_stepwise_addressing_same_bits(oim, R, q, weights, monkeypatch):
                     np.testing.assert_array_equal(a, b, err_msg=f"image {image} addr {addr}")
 
 
-@pytest.mark.parametrize("R", [3, 32])
-def test_stepwise_global_addressing_at_any_size(oim, R, monkeypatch):
+@pytest.mark.parametrize("rows,R", [(10, 3), (400, 32)])
+def test_stepwise_global_addressing_at_any_size(oim, rows, R, monkeypatch):
     # the kernel that ran, by name
     import torch
-    g = synth.torus(10, 12, seed=3)
+    g = synth.torus(rows, 12, seed=3)
     with oim.Problem.from_csr(g.n, g.row_ptr, g.col, (-g.w).astype(np.float32)) as prob:
         for addr, kernel in (("0", "stepwise_packed_kernel"), ("1", "stepwise_step_kernel")):
             monkeypatch.setenv("OIM_STEPWISE_GLOBAL_ADDR", addr)
