@@ -79,9 +79,15 @@ bool cu_holds(int64_t groups, int64_t waves) {
     return waves > 4 ? groups * ((waves + 3) / 4) <= 4 : groups * waves <= 16;
 }
 
+// Instances far below the largest one (a ragged batch): the mean under 0.6 of it.
+bool ragged(const Problem* p) {
+    return p->n_inst > 1 && 5 * (int64_t)p->n < 3 * (int64_t)p->n_inst * p->max_inst_n;
+}
+
+bool long_rows(const Problem* p) { return p->nnz / p->n >= 24; }
+
 // Default choice without tuning, from the slices of the largest instance (S),
-// the workgroups a CU holds at once and the rows' mean length: about sixteen
-// working waves per CU, four per SIMD.
+// the workgroups a CU holds at once, the rows' mean length and the SHIL order.
 //  - A step's latency is shared by the waves of a workgroup, so the rows are
 //    split over as many waves as the CU holds with its other workgroups
 //    (cu_holds), unit weights with room for the noise's waves: us per step with
@@ -89,52 +95,88 @@ bool cu_holds(int64_t groups, int64_t waves) {
 //    (real weights 2.1, 1.26, 0.96), 500 replicas 2.4, 1.63, 2.2 (real 3.0,
 //    1.54, 2.2); n = 500, 500 replicas 1.85, 1.09, 1.15 (real 2.0, 1.21, 1.09).
 //    Longer rows weigh more than the noise: G(800, 0.06) one replica 4.0, 2.2,
-//    1.8, 500 replicas 5.4, 3.4, 4.0 (real 8.2, 5.0, 4.5).  Past that unit
-//    weights take whole quads (n = 1500, 500 replicas 2.90, against 2.98 with 2
-//    rows per lane; 600 replicas 4.5 against 5.1), real ones 2 rows (3.3 against
-//    2.7).
-//  - Nine to sixteen slices of real weights or long rows keep sixteen waves of
-//    sorted rows however many replicas there are (n = 4000 of degree 30, 600
-//    replicas: 22.4 us, real 26, against 23.7 and 34 on 256 threads).
+//    1.8, 500 replicas 5.4, 3.4, 4.0 (real 8.2, 5.0, 4.5).  Real weights and
+//    long rows stay split however many replicas there are, but where the
+//    split's waves leave SIMDs idle or drown in noise: five waves (n = 600, real,
+//    1000 replicas 3.3 us per step, whole quads on sorted rows 2.5), nine with
+//    short rows (n = 1100 of degree 4, real, 5000 replicas 23 and 19), ragged
+//    batches (256 colouring graphs, real, 8 replicas 5.0 and 4.4).
+//  - Past that whole quads, which draw their own noise, on about sixteen waves
+//    per CU, four per SIMD, each workgroup its share of them (us per step on
+//    the waves taken and on the other choice): n = 1000 of degree 4, 600
+//    replicas 2.5 on four waves, 3.4 split on sorted rows; 2000 replicas 6.2 on
+//    two, 7.0 on four; n = 2000, 1000 replicas 4.9 on four (256 x 2), 6.1 on
+//    eight (512 x 1).
+//  - Nine to sixteen slices take sixteen waves of sorted rows for one workgroup
+//    per CU, real weights from thirteen slices and most long rows at any
+//    number, unit weights with long rows up to two (n = 4000 of degree 30, 600
+//    replicas, real: 26 us, 34 on four waves; 1000 replicas, unit: 34.6, 31.0
+//    on eight), else eight waves, or four where that many workgroups fit
+//    better, for unit weights where the SHIL order is not 2 and its term so the
+//    longer (n = 2500 of degree 6, unit, 2000 replicas, q = 3: 14.5 us on four
+//    and 17.0 on eight, q = 2: 16.6 and 16.3; n = 2049 of degree 4, real, 600
+//    replicas 6.0 on four waves, 7.6 on sixteen; n = 4000, unit, 1000 replicas
+//    9.6 on eight, 12.3 on four; n = 3000 of degree 10, real, 2000 replicas 31
+//    on four and on sixteen, with a readout every 10 steps 36 and 40).
 //  - Instances of more slices take sixteen waves of whole quads: n = 3500 of
 //    degree 10 4.1 -> 3.1 us (1024 x 1), n = 10000 of degree 5 8.6 -> 6.0
 //    (1024 x 3); the general image, which holds more registers, twelve waves of
-//    four slices for 33 to 48 (10.8 -> 9.3, against 9.75 with sixteen).
-//  - Where a CU holds several workgroups each takes its share of the sixteen
-//    waves: 256 colouring graphs of up to 600 oscillators x 8 replicas 3.6 ->
-//    2.9 us (256 -> 128 threads); n = 2000, 600 replicas 6.0 -> 5.4 (512 ->
-//    256).  Up to two slices keep 2 rows per lane (graphs of up to 250: 1.7 us
-//    whole on 64 threads, 1.25 split).  Beyond 16 slices the sixteen waves stay
-//    (n = 6000, 600 replicas: 11.8 us with 1024 x 2, 15.6 with 512 x 5).
-const Variant* default_variant(const Problem* p, int R) {
+//    four slices for 33 to 48 (10.8 -> 9.3, against 9.75 with sixteen) and eight
+//    beyond (n = 16000 of degree 4, 300 replicas 30 on eight, 37 on sixteen).
+//    Up to 24 slices of unit weights and another SHIL order than 2 take eight
+//    for more workgroups than CUs (n = 4100 of degree 6, 2000 replicas, q = 3:
+//    23.4 us on 512 x 3, 27.8 on 1024 x 2, q = 2: 35.5 and 27.4).
+const Variant* default_variant(const Problem* p, int q, int R) {
     const int S = p->max_slices;
-    const int64_t fit = (int64_t)(kLdsLimit / lds_bytes(S * 64, 64, 2, 4));
-    const int64_t per_cu = ((int64_t)R * p->n_inst + 255) / 256;
-    const int64_t g = S > 16 ? 1 : per_cu < fit ? per_cu : fit;
-    const int waves = g >= 16 ? 1 : (int)(16 / (g < 1 ? 1 : g));
-    const bool uw = p->d_sell_uw != nullptr;
-    const bool long_rows = p->nnz / p->n >= 24;
+    const int64_t per_cu = ((int64_t)R * p->n_inst + 255) / 256, deg = p->nnz / p->n;
+    const bool uw = p->d_sell_uw != nullptr, lng = long_rows(p);
     const Variant* v = nullptr;
     // waves of the split shapes with 1 and 2 rows per lane
     const int64_t w1 = (p->max_inst_n + 63) / 64, w2 = (w1 + 1) / 2;
-    if (w1 <= 16 && (long_rows ? !uw || cu_holds(per_cu, w1)
-                               : cu_holds(per_cu, uw && S > 1 ? w1 + S : w1))) {
-        v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
-    } else if (w2 <= 16 && (!uw || long_rows || S <= 2 || cu_holds(per_cu, w2))) {
-        v = covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
-    } else if (S > 8 && S <= 16 && (!uw || long_rows)) {
-        v = covering(1024, 4, S);
-    } else if (!uw && waves == 16 && S > 32 && S <= 48) {
-        v = covering(768, 4, S);
+    const bool split1 = w1 <= 16 && (lng ? !uw || cu_holds(per_cu, w1)
+                                         : cu_holds(per_cu, uw && S > 1 ? w1 + S : w1));
+    bool split2 = w2 <= 16;
+    if (cu_holds(per_cu, w2)) {
+        // they fit beside each other
+    } else if (S <= 2) {
+        split2 = !(uw && !lng && S == 2 && per_cu >= 8);
+    } else if (uw && !lng) {
+        split2 = split2 && per_cu == 2 && deg >= 7 && w2 >= 12;
+    } else if (w2 == 5 && !ragged(p)) {
+        split2 = per_cu < 4 || (per_cu >= 5 && per_cu <= 8);
+    } else if (uw) {
+        split2 = split2 && (S > 4 || per_cu <= 16);
+    } else if (!lng) {
+        split2 = split2 && !ragged(p) && !(w2 >= 9 && w2 <= 10 && deg < 8 && per_cu >= 4);
+    }
+    if (split1) v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
+    else if (split2) v = covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
+    else if (S <= 2) v = covering(128, 4, S);
+    else if (S <= 4) v = covering(per_cu >= 5 && per_cu <= 16 && ((uw && !lng) || ragged(p)) ? 128 : 256, 4, S);
+    else if (S <= 8) v = covering(per_cu <= 2 ? 512 : 256, 4, S);
+    else if (S <= 16) {
+        const bool sixteen =
+            per_cu == 1 || (uw ? lng && per_cu <= 2
+                               : S > 12 || (lng ? !(S == 9 && per_cu == 2) && !(S <= 10 && per_cu == 3)
+                                                : S > 10 && deg >= 8 && per_cu < 8));
+        const bool four = S <= 12 && (per_cu == 3 || (uw ? q != 2 && per_cu >= 4 : per_cu >= 8));
+        v = covering(sixteen ? 1024 : four ? 256 : 512, 4, S);
+    } else if (uw && q != 2 && S <= 24 && per_cu >= 2) {
+        v = covering(512, 4, S);
     } else {
-        int W = S;  // or the largest power of two within the share
-        if (S > waves)
-            for (W = 16; W > waves;) W /= 2;
-        for (int tb = W <= 1 ? 64 : W <= 2 ? 128 : W <= 4 ? 256 : W <= 8 ? 512 : 1024; !v && tb <= 1024;
-             tb *= 2)
-            v = covering(tb, 4, S);
+        v = covering(uw || S <= 32 ? 1024 : S <= 48 ? 768 : 512, 4, S);
     }
     return v && lds_bytes(S * 64, v->tb, v->ms, v->rpl) <= kLdsLimit ? v : fewest_waves(S, 0);
+}
+
+// Whether a shape runs on the sorted rows.  Those of one slice per wave group
+// do, but for whole quads of few slices with short rows and unit weights (or in
+// a ragged batch): their resident entries fill the registers, and the general
+// kernel's quads draw their own noise (n = 1000 of degree 4, 600 replicas 3.4 us
+// per step sorted, 2.5 so).
+bool on_sorted_rows(const Problem* p, const Variant& v) {
+    if (v.ms != 1 || !p->d_sorted) return false;
+    return !(v.rpl == 4 && p->max_slices <= 8 && !long_rows(p) && (p->d_sell_uw || ragged(p)));
 }
 
 int env_int(const char* name, int dflt) {
@@ -175,7 +217,7 @@ const Variant* run_variant(const Problem* p, int q, int R) {
     }
     const int hint = env_int("OIM_PERSIST_TB", 0);
     if (!v && hint) v = fewest_waves(p->max_slices, hint);
-    if (!v) v = default_variant(p, R);
+    if (!v) v = default_variant(p, q, R);
     if (!v || launch_holds(p, R, *v)) return v;
     for (const Variant& k : kVariants)
         if (variant_ok(p, k) && k.tb < v->tb) v = &k;
@@ -268,7 +310,7 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
     const int qi = cfg->q == 2 ? 1 : cfg->q == 3 ? 2 : 0;
     if (!launch_holds(p, cfg->R, *v)) return set_error(OIM_E_ARG, "R * instances too large");
     a.w0 = p->uniform_w;
-    if (v->ms == 1 && p->d_sorted) return launch_sorted(p, *v, a, qi, stream);
+    if (on_sorted_rows(p, *v)) return launch_sorted(p, *v, a, qi, stream);
     KernelFn fn = v->fn[qi];
     if (p->d_sell_uw) {
         a.sell_uw = reinterpret_cast<const int4*>(p->d_sell_uw);

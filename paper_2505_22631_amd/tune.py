@@ -23,7 +23,7 @@ from . import oim_autotune, oim_set_tuning
 # change moves their times against each other.  2: shapes of one slice per wave
 # group on sorted rows (entries without a revision are older: G(800, 0.06)
 # pinned to 1024 x 2 slices x 1 row takes 3.2 us per step, the default 1.8).
-KERNELS = 2
+KERNELS = 3
 
 
 def cache_path() -> str:
