@@ -360,8 +360,10 @@ int oim_adjoint_forward(oim_problem p, const oim_adjoint_cfg* cfg, const float* 
  * `stream`, so the call stays asynchronous and later work on `stream` sees
  * the gradients.  Uses a workspace cached in p (2 (C + 1) R slots words,
  * R slots floats, 24 bytes per step, replica and instance, and 4 C R slots
- * floats more while those are at most 8 GiB and can be had); one stream at a
- * time per problem.  Errors as the forward pass, plus OIM_E_NOMEM. */
+ * floats more while those are at most 8 GiB and can be had; a size that could
+ * not is not asked for again), kept until p is destroyed, and the sorted rows,
+ * made by the first adjoint call where problem creation had no room for them;
+ * one stream at a time per problem.  Errors as the forward pass, plus OIM_E_NOMEM. */
 int oim_adjoint_backward(oim_problem p, const oim_adjoint_cfg* cfg, const float* K,
                          const float* Ks, const float* sigma, const uint64_t* seeds,
                          int64_t step0, const uint32_t* ckpt, double* gK, double* gKs,

@@ -874,8 +874,9 @@ void dense_release(Problem* p) {
 namespace {
 
 // Workspace of one run: U (4 B) + two X sets (8 B each: 4 x BF16 or 2 x FP32)
-// per (replica, row) slot, then the readout scratch H[R], best tmp [R]
-// (FP64) and best step [R].
+// per (replica, row) slot, then best value [R] (FP64) and best step [R].  8 R
+// bytes more are counted, unused: which runs fit the allocation-free call's
+// array is part of its contract.
 size_t dense_need(int n, int R) {
     const int np = (n + kTM - 1) / kTM * kTM;
     const int Rp = (R + kTR - 1) / kTR * kTR;
@@ -957,8 +958,7 @@ int run_dense(Problem* p, const oim_run_cfg* cfg, const float* K, const float* K
     uint32_t* U = reinterpret_cast<uint32_t*>(w);
     unsigned char* X0 = w + plane * 4;
     unsigned char* X1 = X0 + 4 * plane * 2;
-    double* H = reinterpret_cast<double*>(w + plane * 4 + 2 * 4 * plane * 2);
-    double* btmp = H + R;
+    double* btmp = reinterpret_cast<double*>(w + plane * 4 + 2 * 4 * plane * 2);
     int32_t* bstep = reinterpret_cast<int32_t*>(btmp + R);
 
     if (fp32)

@@ -13,9 +13,10 @@
 // the host is only a stand-in for the symbol).  Every call on a device shares
 // the array: calls that overlap on one device (concurrent streams or threads)
 // race on it.  Nothing in it needs to start at zero: each run writes every
-// part it later reads (the init kernel fills the state and both buffers, the
-// first readout of a call resets the best-so-far, the per-call argument block
-// is written by the call's first kernel).
+// part it later reads (the init kernel fills the state and whatever of the
+// second buffer no step writes, the first readout of a call resets the
+// best-so-far, the per-call argument block is written by the call's first
+// kernel).
 #include <mutex>
 
 #include "internal.hpp"

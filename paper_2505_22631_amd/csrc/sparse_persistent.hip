@@ -240,9 +240,9 @@ bool persistent_sparse_fits(const Problem* p) {
 
 namespace {
 // A shape of one slice per wave group on the sorted rows: the waves that hold
-// rows of the largest instance and, while a CU has one or two workgroups,
-// one more per slice to draw its noise, as far as the sixteen waves of this
-// kernel's registers go.
+// rows of the largest instance and up to one more per slice to draw its noise,
+// as long as the CU holds them beside its other workgroups (cu_holds: the
+// sixteen waves of this kernel's registers).
 int launch_sorted(const Problem* p, const Variant& v, const PersistArgs& a, int qi,
                   hipStream_t stream) {
     SortedArgs sa{};
