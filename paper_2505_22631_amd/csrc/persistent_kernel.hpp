@@ -726,7 +726,8 @@ using KernelFn = void (*)(PersistArgs);
 // one wave up -- the small ones suit batches of small instances (fewer idle
 // lanes, cheap barriers) -- then the split-row shapes, which suit instances
 // of a few slices with long rows.  Shapes of one slice per wave group run
-// sorted_kernel.hpp's kernel where the problem has its image.
+// sorted_kernel.hpp's kernel where the problem has its image, but for whole
+// quads with short rows and unit weights (on_sorted_rows).
 #define OIM_PERSIST_VARIANTS(X)                                                          \
     X(64, 1, 4) X(64, 2, 4) X(64, 3, 4) X(64, 4, 4) X(64, 6, 4) X(64, 8, 4)               \
     X(128, 1, 4) X(128, 2, 4) X(128, 3, 4) X(128, 4, 4) X(128, 6, 4) X(128, 8, 4)         \
