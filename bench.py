@@ -90,6 +90,16 @@ def _launch_shape(args, prob, q):
     return {"block": b, "slices_per_wave": s, "rows_per_lane": l}
 
 
+def _resident_kernel(launch):
+    """The LDS-resident kernel a launch shape runs: split rows of one slice per
+    wave group go by length (sorted_kernel); whole quads of one slice do so
+    only with long rows or other than unit weights."""
+    if launch["slices_per_wave"] > 1:
+        return "persistent_sparse_kernel"
+    return ("sorted_kernel" if launch.get("rows_per_lane", 4) < 4
+            else "sorted_kernel or persistent_sparse_kernel")
+
+
 def _shape_suffix(R, launch):
     """Profile key suffix of a launch of the LDS-resident kernel: replicas and
     launch shape (threads x slices per wave x rows per lane), since counters
@@ -431,7 +441,7 @@ def maxcut_workload(args, name, g, R, steps, M, label, timed_steps, plain_replic
             sw["roofline"]["traffic"] = per_step * sw_steps if per_step is not None else None
 
     roof = hbm_roofline(sparse_bytes_per_step(g.n, g.nnz, R), steps, kern_ms,
-                        "persistent_sparse_kernel",
+                        _resident_kernel(launch),
                         {"launch": {"block": launch["block"],
                                     "slices_per_wave": launch["slices_per_wave"],
                                     "rows_per_lane": launch.get("rows_per_lane", 4)}})
@@ -632,7 +642,7 @@ def colouring_workload(args):
     plain_t99_best = plain_t(hit_best)
     plain_t99_planted = plain_t(hit_planted)
     bps = sparse_bytes_per_step(big.n, big.nnz, R)
-    roof = hbm_roofline(bps, steps, run_ms, "persistent_sparse_kernel",
+    roof = hbm_roofline(bps, steps, run_ms, _resident_kernel(launch),
                         {"launch": {"block": launch["block"],
                                     "slices_per_wave": launch["slices_per_wave"],
                                     "rows_per_lane": launch.get("rows_per_lane", 4)}})
