@@ -24,8 +24,13 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-ta
 
 
 # Per-source code generation options: the dense kernel keeps its MFMA
-# accumulators in architectural VGPRs (stable allocation, no AGPR copies).
-EXTRA = {"dense.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# accumulators in architectural VGPRs (stable allocation, no AGPR copies); the
+# host loops of problem creation are aligned, so that their speed does not hang
+# on where the linker puts them (30000 oscillators of degree 6 4.85 ms by
+# chance, 4.56 ms so; a batch of 256 graphs of 300 10.4 and 9.8 ms).
+HOST_ALIGN = ["-falign-functions=64", "-falign-loops=32"]
+EXTRA = {"dense.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "api.cpp": HOST_ALIGN, "validate.cpp": HOST_ALIGN}
 
 
 def _compile(src: str) -> str:
