@@ -79,45 +79,90 @@ bool cu_holds(int64_t groups, int64_t waves) {
     return waves > 4 ? groups * ((waves + 3) / 4) <= 4 : groups * waves <= 16;
 }
 
-// Instances far below the largest one (a ragged batch): the mean under 0.6 of it.
+// Instances far below the largest one (a ragged batch): the mean under 0.65 of it.
 bool ragged(const Problem* p) {
-    return p->n_inst > 1 && 5 * (int64_t)p->n < 3 * (int64_t)p->n_inst * p->max_inst_n;
+    return p->n_inst > 1 && 20 * (int64_t)p->n < 13 * (int64_t)p->n_inst * p->max_inst_n;
 }
 
 bool long_rows(const Problem* p) { return p->nnz / p->n >= 24; }
 
+const Variant* find_variant(int tb, int ms, int rpl) {
+    for (const Variant& v : kVariants)
+        if (v.tb == tb && v.ms == ms && v.rpl == rpl) return &v;
+    return nullptr;
+}
+
+// Whole quads of five slices and more: see default_variant.
+int quad_threads(const Problem* p, int q, int M, int64_t per_cu) {
+    const int S = p->max_slices;
+    const int64_t deg = p->nnz / p->n;
+    const bool often = M > 0 && M <= 16;  // readouts that weigh
+    if (S <= 8) {
+        if (!p->d_sell_uw) return 256;
+        if (per_cu == 2) return 512;
+        return S <= 6 && !ragged(p) && per_cu >= 5 && (per_cu <= 7 || q != 2) ? 128 : 256;
+    }
+    if (S <= 16) {
+        if (per_cu == 1) return 1024;
+        if (p->d_sell_uw && long_rows(p) && often && per_cu <= 3) return 1024;
+        if (p->d_sell_uw)
+            return S <= 12 && (per_cu == 3 || (per_cu >= 4 && q != 2) || (per_cu >= 5 && S >= 10)) ? 256 : 512;
+        if (S > 12) return ragged(p) && per_cu >= 4 ? 512 : 1024;
+        if (S <= 10 && per_cu == 3) return 256;
+        if (S == 9 && per_cu == 2) return 512;
+        if (often && per_cu >= 5) return 256;
+        if (deg >= 12 || (S >= 11 && deg >= 6)) return 1024;
+        return per_cu >= 3 && per_cu != 4 ? 256 : 512;
+    }
+    if (p->d_sell_uw && q != 2 && S <= 24 && per_cu >= 2) return 512;
+    return p->d_sell_uw || S <= 32 ? 1024 : S <= 48 ? 768 : 512;
+}
+
 // Default choice without tuning, from the slices of the largest instance (S),
-// the workgroups a CU holds at once, the rows' mean length and the SHIL order.
+// the workgroups a CU holds at once (per_cu) and the rows' mean length (deg).
+// All figures are us per step.
 //  - A step's latency is shared by the waves of a workgroup, so the rows are
 //    split over as many waves as the CU holds with its other workgroups
-//    (cu_holds), unit weights with room for the noise's waves: us per step with
-//    4, 2 and 1 rows per lane, n = 800 of degree 10 one replica 2.0, 0.93, 1.04
+//    (cu_holds), short unit-weight rows with room for the noise's waves: 4, 2
+//    and 1 rows per lane, n = 800 of degree 10, one replica 2.0, 0.93, 1.04
 //    (real weights 2.1, 1.26, 0.96), 500 replicas 2.4, 1.63, 2.2 (real 3.0,
-//    1.54, 2.2); n = 500, 500 replicas 1.85, 1.09, 1.15 (real 2.0, 1.21, 1.09).
-//    Longer rows weigh more than the noise: G(800, 0.06) one replica 4.0, 2.2,
-//    1.8, 500 replicas 5.4, 3.4, 4.0 (real 8.2, 5.0, 4.5).  Real weights and
-//    long rows stay split however many replicas there are, but where the
-//    split's waves leave SIMDs idle or drown in noise: five waves (n = 600, real,
-//    1000 replicas 3.3 us per step, whole quads on sorted rows 2.5), nine with
-//    short rows (n = 1100 of degree 4, real, 5000 replicas 23 and 19), ragged
-//    batches (256 colouring graphs, real, 8 replicas 5.0 and 4.4).
-//  - Past that whole quads, which draw their own noise, on about sixteen waves
-//    per CU, four per SIMD, each workgroup its share of them (us per step on
-//    the waves taken and on the other choice): n = 1000 of degree 4, 600
-//    replicas 2.5 on four waves, 3.4 split on sorted rows; 2000 replicas 6.2 on
-//    two, 7.0 on four; n = 2000, 1000 replicas 4.9 on four (256 x 2), 6.1 on
-//    eight (512 x 1).
+//    1.54, 2.2); G(800, 0.06) one replica 4.0, 2.2, 1.8.
+//  - Past that two rows per lane stay the better choice for real weights and
+//    longer rows, whose entries weigh more than the noise that every wave of a
+//    split waits for, and the sorted rows keep them in registers: a batch of
+//    256 graphs of 100 to 1000, degree 8, real, 8 replicas 5.9 and 7.4 in whole
+//    quads; of 1024 graphs of 100 to 500, degree 20, unit, 2 replicas 4.6 and
+//    8.0; n = 400 of degree 14, unit, 2048 replicas 3.9 and 4.1; n = 1500 of
+//    degree 7, real, 1536 replicas 8.3 and 10.5.  Long real rows up to three and
+//    four slices even take one row per lane (n = 600 of degree 20, 2048
+//    replicas 10.5, 11.4 with two).
+//  - Whole quads draw their own noise: unit weights with short rows take them,
+//    on the general kernel (on_sorted_rows), about sixteen waves per CU: n = 400
+//    of degree 4, 2048 replicas 2.4 on two waves (3.3 split); n = 600 of degree
+//    7, 1024 replicas 2.9 on four (two 3.6, split 4.4), 2048 replicas 4.8 on two
+//    (5.1, 7.2), 8192 replicas, q = 3, readouts every 10 steps 20.0 on one (two
+//    24.0, four 21.8); n = 1500 of degree 4, 512 replicas 2.6 on eight (split
+//    3.3), 1536 replicas 5.8 on two (6.8 on four, split 9.4).  A ragged batch's
+//    workgroups are mostly small: 256 graphs of 100 to 1000, degree 4, 8
+//    replicas 3.6 on two waves, 4.0 on four.
+//  - Real weights do so with the shortest rows of three slices (64 graphs of
+//    100 to 600, degree 4.6, 16 replicas 2.5 on four waves, split 3.0; 32
+//    replicas 4.2 on two, split 5.1), unless few replicas share general images
+//    that pass the L2s (1024 such graphs, one replica 3.0 split, 5.4), and in
+//    ragged batches of five to eight (40 graphs of 300 to 1400, degree 4, 38
+//    replicas 6.0, split 7.0), and with nine or ten split waves of short rows,
+//    which leave SIMDs idle (n = 1100 of degree 4, 5000 replicas 19, split 23).
 //  - Nine to sixteen slices take sixteen waves of sorted rows for one workgroup
-//    per CU, real weights from thirteen slices and most long rows at any
-//    number, unit weights with long rows up to two (n = 4000 of degree 30, 600
-//    replicas, real: 26 us, 34 on four waves; 1000 replicas, unit: 34.6, 31.0
-//    on eight), else eight waves, or four where that many workgroups fit
-//    better, for unit weights where the SHIL order is not 2 and its term so the
-//    longer (n = 2500 of degree 6, unit, 2000 replicas, q = 3: 14.5 us on four
-//    and 17.0 on eight, q = 2: 16.6 and 16.3; n = 2049 of degree 4, real, 600
-//    replicas 6.0 on four waves, 7.6 on sixteen; n = 4000, unit, 1000 replicas
-//    9.6 on eight, 12.3 on four; n = 3000 of degree 10, real, 2000 replicas 31
-//    on four and on sixteen, with a readout every 10 steps 36 and 40).
+//    per CU. Real weights do at any number from thirteen slices and with longer
+//    rows (n = 3000 of degree 14, 1536 replicas 27, 32 on four or eight waves),
+//    unless readouts weigh (every 10 steps 35 and 36, n = 2500 33 and 30) or
+//    the batch is ragged (40 graphs of 500 to 4000, degree 4, 38 replicas 14.8,
+//    13.9 on eight); unit weights with long rows only where readouts weigh (n =
+//    2500 of degree 30, 300 replicas 14.0, 15.4 on eight; without 11.6 and
+//    11.4). The others take eight waves, or four where those fit the CU better
+//    or the SHIL order is not 2 and its term so the longer (n = 3000 of degree
+//    7, unit, 1024 replicas 9.9 on eight, 11.2 on four, q = 3 with readouts
+//    12.7 and 11.1; n = 2500 of degree 4, real, 1536 replicas 12.8 and 12.3).
 //  - Instances of more slices take sixteen waves of whole quads: n = 3500 of
 //    degree 10 4.1 -> 3.1 us (1024 x 1), n = 10000 of degree 5 8.6 -> 6.0
 //    (1024 x 3); the general image, which holds more registers, twelve waves of
@@ -126,68 +171,68 @@ bool long_rows(const Problem* p) { return p->nnz / p->n >= 24; }
 //    Up to 24 slices of unit weights and another SHIL order than 2 take eight
 //    for more workgroups than CUs (n = 4100 of degree 6, 2000 replicas, q = 3:
 //    23.4 us on 512 x 3, 27.8 on 1024 x 2, q = 2: 35.5 and 27.4).
-const Variant* default_variant(const Problem* p, int q, int R) {
+const Variant* default_variant(const Problem* p, int q, int M, int R) {
     const int S = p->max_slices;
     const int64_t per_cu = ((int64_t)R * p->n_inst + 255) / 256, deg = p->nnz / p->n;
     const bool uw = p->d_sell_uw != nullptr, lng = long_rows(p);
-    const Variant* v = nullptr;
     // waves of the split shapes with 1 and 2 rows per lane
     const int64_t w1 = (p->max_inst_n + 63) / 64, w2 = (w1 + 1) / 2;
-    const bool split1 = w1 <= 16 && (lng ? !uw || cu_holds(per_cu, w1)
-                                         : cu_holds(per_cu, uw && S > 1 ? w1 + S : w1));
-    bool split2 = w2 <= 16;
-    if (cu_holds(per_cu, w2)) {
-        // they fit beside each other
-    } else if (S <= 2) {
-        split2 = !(uw && !lng && S == 2 && per_cu >= 8);
-    } else if (uw && !lng) {
-        split2 = split2 && per_cu == 2 && deg >= 7 && w2 >= 12;
-    } else if (w2 == 5 && !ragged(p)) {
-        split2 = per_cu < 4 || (per_cu >= 5 && per_cu <= 8);
-    } else if (uw) {
-        split2 = split2 && (S > 4 || per_cu <= 16);
-    } else if (!lng) {
-        split2 = split2 && !ragged(p) && !(w2 >= 9 && w2 <= 10 && deg < 8 && per_cu >= 4);
+    // the general images pass the L2s (4 MiB on each of 8 XCDs), read by few replicas
+    const bool streams = p->n_inst > 1 && R < 4 && p->sell_entries * 8 > (28 << 20);
+    int rpl = 4, tb = 0, ms = 0;
+    if (w1 <= 16 && (cu_holds(per_cu, w1 + (uw && S > 1 && deg < 16 ? S : 0)) ||
+                     (!uw && (lng || (S == 3 && deg >= 16))))) {
+        rpl = 1;
+    } else if (w2 <= 16 && cu_holds(per_cu, w2)) {
+        rpl = 2;
+    } else if (S == 1) {
+        if (uw && !lng && per_cu >= 12) tb = 64;
+        else rpl = 2;
+    } else if (S == 2) {
+        if (uw && deg < 9 && per_cu >= 6) tb = 128;
+        else rpl = 2;
+    } else if (S == 3 && uw) {
+        if (lng && per_cu < 12 && per_cu != 4) rpl = 2;
+        else if (lng || per_cu <= 5) tb = 256;
+        else if (per_cu <= 10) tb = 128;
+        else tb = q != 2 ? 64 : ragged(p) ? 128 : 256;
+    } else if (S == 3 && deg < 5 && per_cu > 3) {
+        if (streams && per_cu <= 5) rpl = 2;
+        else if (streams) tb = 256;
+        else if (per_cu <= 5) tb = 256, ms = 2;
+        else tb = 128;
+    } else if (S == 3) {
+        if (deg >= 5 && (per_cu == 4 || per_cu >= 12)) tb = 256;
+        else rpl = 2;
+    } else if (S == 4) {
+        if (!uw || deg >= 16 || per_cu <= 2 || (deg >= 12 && per_cu <= 5)) rpl = 2;
+        else tb = ragged(p) && per_cu >= 6 ? 128 : 256;
+    } else if (w2 <= 16) {
+        if (uw ? deg >= 16 || per_cu == 1 || (deg >= 8 && per_cu <= 3 && w2 > 10)
+               : !(ragged(p) && deg < 5 && per_cu >= 3) &&
+                     !(w2 >= 9 && w2 <= 10 && deg < 8 && per_cu >= 4))
+            rpl = 2;
     }
-    if (split1) v = covering(S == 1 ? 256 : S == 2 ? 512 : 1024, 1, S);
-    else if (split2) v = covering(S <= 2 ? 256 : S <= 4 ? 512 : 1024, 2, S);
-    else if (S <= 2) v = covering(128, 4, S);
-    else if (S <= 4) v = covering(per_cu >= 5 && per_cu <= 16 && ((uw && !lng) || ragged(p)) ? 128 : 256, 4, S);
-    else if (S <= 8) v = covering(per_cu <= 2 ? 512 : 256, 4, S);
-    else if (S <= 16) {
-        const bool sixteen =
-            per_cu == 1 || (uw ? lng && per_cu <= 2
-                               : S > 12 || (lng ? !(S == 9 && per_cu == 2) && !(S <= 10 && per_cu == 3)
-                                                : S > 10 && deg >= 8 && per_cu < 8));
-        const bool four = S <= 12 && (per_cu == 3 || (uw ? q != 2 && per_cu >= 4 : per_cu >= 8));
-        v = covering(sixteen ? 1024 : four ? 256 : 512, 4, S);
-    } else if (uw && q != 2 && S <= 24 && per_cu >= 2) {
-        v = covering(512, 4, S);
-    } else {
-        v = covering(uw || S <= 32 ? 1024 : S <= 48 ? 768 : 512, 4, S);
-    }
+    if (rpl == 1) tb = S == 1 ? 256 : S == 2 ? 512 : 1024;
+    else if (rpl == 2) tb = S <= 2 ? 256 : S <= 4 ? 512 : 1024;
+    else if (!tb) tb = quad_threads(p, q, M, per_cu);
+    const Variant* v = ms ? find_variant(tb, ms, rpl) : covering(tb, rpl, S);
     return v && lds_bytes(S * 64, v->tb, v->ms, v->rpl) <= kLdsLimit ? v : fewest_waves(S, 0);
 }
 
 // Whether a shape runs on the sorted rows.  Those of one slice per wave group
-// do, but for whole quads of few slices with short rows and unit weights (or in
-// a ragged batch): their resident entries fill the registers, and the general
-// kernel's quads draw their own noise (n = 1000 of degree 4, 600 replicas 3.4 us
-// per step sorted, 2.5 so).
+// do, but for whole quads of few slices with short rows and unit weights: their
+// resident entries fill the registers, and the general kernel's quads draw
+// their own noise (n = 1000 of degree 4, 600 replicas 3.4 us per step sorted,
+// 2.5 so).
 bool on_sorted_rows(const Problem* p, const Variant& v) {
     if (v.ms != 1 || !p->d_sorted) return false;
-    return !(v.rpl == 4 && p->max_slices <= 8 && !long_rows(p) && (p->d_sell_uw || ragged(p)));
+    return !(v.rpl == 4 && p->max_slices <= 8 && !long_rows(p) && p->d_sell_uw);
 }
 
 int env_int(const char* name, int dflt) {
     const char* v = getenv(name);
     return v ? atoi(v) : dflt;
-}
-
-const Variant* find_variant(int tb, int ms, int rpl) {
-    for (const Variant& v : kVariants)
-        if (v.tb == tb && v.ms == ms && v.rpl == rpl) return &v;
-    return nullptr;
 }
 
 // The variant covers every slice of the largest instance and its LDS fits.
@@ -208,7 +253,7 @@ int q_class(int q) { return q == 2 ? 1 : q == 3 ? 2 : 0; }
 // The variant a run uses: the tuned one for this SHIL order if set, else an
 // OIM_PERSIST_TB block-size hint, else the default choice -- unless that one's
 // launch would not hold the workgroups: then the one of the fewest threads.
-const Variant* run_variant(const Problem* p, int q, int R) {
+const Variant* run_variant(const Problem* p, int q, int M, int R) {
     const int qc = q_class(q);
     const Variant* v = nullptr;
     if (p->tuned_tb[qc]) {
@@ -217,7 +262,7 @@ const Variant* run_variant(const Problem* p, int q, int R) {
     }
     const int hint = env_int("OIM_PERSIST_TB", 0);
     if (!v && hint) v = fewest_waves(p->max_slices, hint);
-    if (!v) v = default_variant(p, q, R);
+    if (!v) v = default_variant(p, q, M, R);
     if (!v || launch_holds(p, R, *v)) return v;
     for (const Variant& k : kVariants)
         if (variant_ok(p, k) && k.tb < v->tb) v = &k;
@@ -277,7 +322,7 @@ int launch_variant(const Problem* p, const oim_run_cfg* cfg, const float* K, con
                    uint32_t* phase, const oim_readout* ro, hipStream_t stream,
                    const Variant* forced, int32_t sched_stride) {
     const int S = p->max_slices;
-    const Variant* v = forced ? forced : run_variant(p, cfg->q, cfg->R);
+    const Variant* v = forced ? forced : run_variant(p, cfg->q, cfg->readout_every, cfg->R);
     if (!v || !persistent_sparse_fits(p) || !variant_ok(p, *v))
         return set_error(OIM_E_UNSUPPORTED, "replica does not fit the LDS-resident kernel");
     PersistArgs a{};
