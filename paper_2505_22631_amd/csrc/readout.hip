@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kSumTB) void sparse_sum_kernel(
     const int nblk = (n + 63) / 64;
     const int room = nblk < kRoundBlocks ? nblk : kRoundBlocks;
     double* const bs[2] = {reinterpret_cast<double*>(smem), reinterpret_cast<double*>(smem) + room};
-    const int waves = WAVES ? WAVES : blockDim.x >> 6;  // at most nblk
+    const int waves = WAVES ? WAVES : blockDim.x >> 6;  // MODE 0: at most nblk
     const int r = blockIdx.x;
     const int8_t* k = colour ? colour + (int64_t)r * n : nullptr;
     const float* th = theta ? theta + (int64_t)r * n : nullptr;
@@ -421,7 +421,31 @@ int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* ou
     // gives at most 2048 of them (eight per CU), else more.
     int tb = 1024, chunks = 1, batch = 4;
     int64_t rows = n;
-    if (R >= (deg > 8 ? 512 : 256) && deg <= 32 && n * R >= (256 << 10)) {
+    if (deg > 14 && R >= 256) {
+        // Longer rows, replicas that nearly fill the chip: four lanes per row, a
+        // workgroup each for up to two per CU and from 1000; a lane per row and its upper
+        // entries alone while 1024 threads per CU hold all replicas (us with
+        // sixteen lanes split over workgroups, four lanes, one: n = 698 of degree
+        // 71, 300 replicas 64, 46, 120; 2000 294, 243, 202; 9000 1303, 1076, 1420;
+        // n = 2031 of degree 22, 1000 replicas 161, 111, 113).
+        lpr = 4;
+        if (R >= 1536 && R <= 6144) {
+            lpr = batch = 1;
+            tb = pow2_from(64, (256 << 10) / R / 2 + 1);
+        } else if (R > 6144 && deg <= 18) {
+            lpr = batch = 1;
+            tb = 256;
+        } else if (n <= 64) {
+            tb = 256;
+        } else if (n > 256 && R < 1000 && !(R > 384 && R <= 512)) {
+            tb = 256;
+            const int64_t passes = (n + 63) / 64;
+            int64_t per_group = passes * R / 4096;
+            per_group = per_group < 1 ? 1 : per_group > 4 ? 4 : per_group;
+            chunks = (int)((passes + per_group - 1) / per_group);
+            rows = per_group * 64;
+        }
+    } else if (R >= (deg > 8 ? 512 : 256) && deg <= 14 && n * R >= (256 << 10)) {
         // Replicas that fill the chip: a workgroup each, a lane per row, upper
         // entries alone, threads enough for 1024 per CU and 20 passes (us in
         // groups of four split over workgroups, and so: n = 200 of degree 10,
@@ -433,8 +457,6 @@ int launch_sparse_int(const Problem* p, int R, const int8_t* colour, int64_t* ou
         tb = pow2_from(tb, n / 20);
         if (n < tb) tb = pow2_from(64, n);
         if (tb < 1024 || n <= 8192 || deg <= 8) lpr = batch = 1;
-    } else if (R >= 512 && deg > 32) {
-        tb = 512;  // n = 800 of degree 48, 2000 replicas: 434 us split, 227 so
     } else if (n * lpr > 6 * 1024) {
         tb = 256;
         const int64_t per_pass = tb / lpr;
@@ -469,22 +491,37 @@ int launch_sparse_sum(const Problem* p, int R, const int8_t* colour, const float
     const size_t copies = (size_t)p->n * ((theta ? 4 : 0) + (colour ? 1 : 0));
     const bool stage = copies + sums + kFixed <= dpair::kLdsLimit;
     const size_t lds = sums + (stage ? copies : 0);
-    // Waves per replica: about 12288 in all (16384 with cosines; 2048 and 4096
+    // Waves per replica: about 12288 in all (16384 with cosines), sixteen at most;
     // where rows are long, whose lines the waves of a CU take from each other's
-    // L1), enough for 32 per CU beside the copies, sixteen at most.
+    // L1, few (us: n = 1500 of degree 40, cut, 500 replicas 99 with three, 118 with
+    // four; 1500 182 with three, 226 with one; 3000 262 with two, 369 with one; n =
+    // 500, both energies, 500 replicas 59 with four, 70 with eight); enough for 32
+    // per CU beside the copies.
     const int64_t deg = p->nnz / p->n;
     const bool long_rows = deg >= 24;
-    const int heavy = theta ? 2 : 1;
-    const int most = long_rows ? 8 * heavy : kSumWaves;
-    const int64_t share = (long_rows ? 2048 * heavy : theta && R >= 2048 ? 16384 : 12288) / R;
+    auto within = [](int64_t v, int lo, int hi) { return (int)(v < lo ? lo : v > hi ? hi : v); };
     int waves = 1;
-    while (waves < most && (2 * waves <= share || waves * 5120 < (int64_t)(copies + sums))) waves *= 2;
-    if (waves > nblk) waves = nblk;
+    if (long_rows) {
+        waves = R > 6000   ? 1
+                : R > 1920 ? 2
+                : R >= 700 ? 3
+                : R < 64   ? kSumWaves
+                : theta    ? within(2048 / R, 4, nblk <= 32 ? 8 : kSumWaves)
+                           : within(800 / R, 3, 8);
+        while (waves < kSumWaves && waves * 5120 < (int64_t)(copies + sums)) ++waves;
+    } else {
+        const int64_t share = (theta && R >= 2048 ? 16384 : 12288) / R;
+        while (waves < kSumWaves && (2 * waves <= share || waves * 5120 < (int64_t)(copies + sums)))
+            waves *= 2;
+    }
+    // no more than there are blocks of rows, but one for each result (n = 25, 88
+    // replicas, both energies 14.4 us with one wave, 13.0 with two)
+    if (waves > nblk) waves = oa && ob && nblk == 1 && R <= 4096 ? 2 : nblk;
     // Entries one by one once the waves fill the chip (not with short rows
-    // whose lines then pass the L1, nor for colours alone with short rows).
+    // whose lines then pass the L1, nor for colours alone with the shortest).
     const int64_t total = (int64_t)R * waves;
-    const bool one = long_rows ? total >= 1536
-                               : (MODE == 0 || theta) && total >= 4000 && waves * deg <= 60;
+    const bool one = long_rows ? total >= 2048
+                               : (MODE == 0 || theta || deg >= 16) && total >= 4000 && waves * deg <= 60;
     auto fn = stage ? (one                  ? sparse_sum_kernel<MODE, true, 1, 0>
                        : waves == kSumWaves ? sparse_sum_kernel<MODE, true, 4, kSumWaves>
                                             : sparse_sum_kernel<MODE, true, 4, 0>)
@@ -547,11 +584,24 @@ int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
     if (!p->dense)
         return launch_sparse_sum<2>(p, R, h_model ? colour : nullptr, h_eq6 ? theta : nullptr, q,
                                     nullptr, h_model, h_eq6, s);
+    // Waves: as many for each SIMD, two where the chip is full without more (n =
+    // 621, 1330 replicas, Eq. 6: 655 us with eight, 685 with twelve, 816 with ten,
+    // one per block of rows; n = 400, 3000 replicas: 572 with eight, 670 with
+    // seven; n = 960, 3000: 2855 with twelve, 3248 with fifteen).
+    const int nblk = dpair::row_blocks(p->n);
+    const int waves = nblk <= 2                ? nblk
+                      : nblk <= 4              ? 4
+                      : nblk <= 8              ? 8
+                      : nblk <= 11 && R > 256  ? 8
+                      : nblk < dpair::kWaves   ? 12
+                                               : dpair::kWaves;
     // Both in one launch (us in two and in one: n = 10, 32 replicas 14.2 and
-    // 11.5; n = 500 161 and 156), not where sixteen waves per replica fill the
-    // chip: the pair sums then share columns among replicas, and the cosines
-    // alone take fewer registers (n = 2000, 1500 replicas 6840 and 8400).
-    const bool both = h_model && h_eq6 && (R <= 256 || dpair::group_waves(p->n) < dpair::kWaves);
+    // 11.5; n = 500 161 and 156; n = 814, 1330 replicas 1213 and 1182), not where
+    // the pair sums of many replicas share columns (n = 500, 3000 replicas 910
+    // and 952) or the cosines alone take fewer registers (sixteen waves: n = 2000,
+    // 1500 replicas 6840 and 8400).
+    const bool both = h_model && h_eq6 &&
+                      (R <= 256 || (waves < dpair::kWaves && (R <= 1000 || nblk <= 2 || nblk > 8)));
     if (h_model && !both) {
         const int st = q == 2
                            ? launch_dense_pairs<dpair::kIsing, false>(p, R, colour, nullptr, h_model, s)
@@ -567,7 +617,7 @@ int launch_energy(const Problem* p, int32_t q, int32_t R, const float* theta,
         if (int st = allow_lds(reinterpret_cast<const void*>(fn), lds)) return st;
         for (int64_t r0 = 0; r0 < R; r0 += kMaxGroups) {
             const int count = (int)(R - r0 < kMaxGroups ? R - r0 : kMaxGroups);
-            hipLaunchKernelGGL(fn, dim3(count), dim3(64 * dpair::group_waves(p->n)), lds, s, p->n,
+            hipLaunchKernelGGL(fn, dim3(count), dim3(64 * waves), lds, s, p->n,
                                p->d_Jdense, theta + r0 * p->n, offset(colour, r0 * p->n), h_eq6 + r0,
                                offset(h_model, r0));
         }

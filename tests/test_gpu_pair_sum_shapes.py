@@ -62,7 +62,8 @@ def _check(oim, orc, prob, csr, R, q, theta):
 # one, two and four replicas per workgroup of one, two and three waves
 @pytest.mark.parametrize("n,R,q", [(1, 3, 2), (10, 2051, 2), (10, 16387, 3), (64, 2049, 3),
                                    (65, 1027, 2), (66, 8195, 2), (130, 703, 3), (130, 5463, 2),
-                                   (1000, 2, 2), (1000, 257, 3)])
+                                   (1000, 2, 2), (1000, 257, 3), (150, 3, 2), (300, 1001, 3), (520, 257, 2),
+                                   (520, 1003, 3), (960, 300, 2)])
 @pytest.mark.parametrize("integer", [True, False])
 def test_dense_shapes(oim, orc, n, R, q, integer):
     rng = np.random.default_rng(n)
@@ -76,6 +77,8 @@ def test_dense_shapes(oim, orc, n, R, q, integer):
 # (n, mean degree, replicas): 1 to 16 waves, entries one by one and in fours,
 # long rows; whole-number sums of 64 to 1024 threads, 1, 4 and 16 lanes per row
 @pytest.mark.parametrize("n,degree,R", [
+    (25, 12, 88), (300, 20, 300), (300, 20, 400), (300, 20, 1001), (300, 20, 1600),
+    (300, 16, 6200), (500, 40, 701), (500, 40, 1930), (700, 30, 30), (700, 30, 270),
     (9, 3, 5), (64, 6, 5000), (65, 6, 5000), (63, 4, 20001), (129, 5, 300), (200, 10, 1400),
     (300, 10, 4100), (600, 6, 601), (1100, 5, 300), (1025, 12, 700), (2100, 4, 12300),
     (4200, 12, 600), (9000, 12, 520), (9000, 4, 520), (130, 40, 600), (500, 60, 3), (500, 60, 200),
